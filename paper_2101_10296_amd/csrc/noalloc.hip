@@ -8,6 +8,7 @@
 // that overlap on one GPU (different streams or threads) race and must be serialised by the
 // caller; calls on one stream are ordered by the stream.  Nothing in the array has to start
 // at zero: every slot a kernel reads was written earlier in the same call.
+#include <algorithm>
 #include <mutex>
 
 #include "runtime.hpp"
@@ -60,7 +61,7 @@ qaoa_status run_energy_grad_noalloc(qaoa_plan_s* P, int64_t n_points, const doub
               "qaoa_energy or qaoa_energy_grad call on this device";
         return QAOA_EINVAL;
     }
-    if (!P->hbm_groups.empty()) {
+    if (std::any_of(P->hp.cones.begin(), P->hp.cones.end(), [&](const Cone& c) { return c.k > P->opt.k_lds_max; })) {
         msg = "the plan has light cones held in device memory (more than " + std::to_string(P->opt.k_lds_max) +
               " qubits); their states need allocations";
         return QAOA_EINVAL;
@@ -105,6 +106,14 @@ qaoa_status run_energy_grad_noalloc(qaoa_plan_s* P, int64_t n_points, const doub
     } while (0)
     for (int64_t i0 = 0; i0 < n_points; i0 += chunk) {
         const int64_t pc = std::min<int64_t>(chunk, n_points - i0);
+        if (depth1_closed(P)) {
+            // rows i0 .. i0 + pc - 1 of each instance's block of n_points angles
+            D1Args da{P->d_d1, P->d_d1w, M, gamma + i0, beta + i0, n_points, P->d_inst_delta, pc, M, zz, g, 1.0};
+            NCHECK(launch_depth1_terms(da, 0, pc * M, true, stream));
+            NCHECK(launch_combine(P->d_W, zz, g, M, p, P->d_inst_orbit, P->d_inst_delta, ni, pc, n_points, i0, energy,
+                                  dgamma, dbeta, stream));
+            continue;
+        }
         // tables [instance][point of the chunk][layer]: one launch per instance (its angles
         // are rows i0 .. i0 + pc - 1 of its [n_points][p] block)
         for (int32_t j = 0; j < ni; ++j) {

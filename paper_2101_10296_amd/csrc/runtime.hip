@@ -258,7 +258,12 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     // workgroup-resident cones (k <= k_lds_max), grouped by K; larger cones go to the
     // HBM-resident passes, grouped by k
     std::vector<int64_t> ord, hord;
-    for (int64_t m = 0; m < Mall; ++m) (hp.cones[m].k <= P->opt.k_lds_max ? ord : hord).push_back(m);
+    const bool d1 = depth1_closed(P);
+    P->max_k = 0;
+    for (const Cone& c : hp.cones) P->max_k = std::max(P->max_k, c.k);
+    std::vector<int64_t> d1ord;
+    for (int64_t m = 0; m < Mall; ++m)
+        (d1 ? d1ord : hp.cones[m].k <= P->opt.k_lds_max ? ord : hord).push_back(m);
     std::stable_sort(ord.begin(), ord.end(), [&](int64_t a, int64_t b) { return hp.cones[a].k < hp.cones[b].k; });
     std::stable_sort(hord.begin(), hord.end(), [&](int64_t a, int64_t b) { return hp.cones[a].k < hp.cones[b].k; });
     const int64_t M = static_cast<int64_t>(ord.size());
@@ -299,6 +304,37 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
         if (P->lds_groups.empty() || P->lds_groups.back().K != c.k) P->lds_groups.push_back({c.k, s, 0, 1});
         P->lds_groups.back().count += 1;
         P->lds_groups.back().rowcap = std::max(P->lds_groups.back().rowcap, d.cut_range);
+    }
+    // depth-1 cones: the couplings of the edge's two ends
+    std::vector<ConeD1> dc(d1ord.size());
+    std::vector<double2> dw;
+    P->d1_groups.clear();
+    const bool d1_by_k = P->opt.profile || P->opt.one_cone_at_a_time;
+    if (d1_by_k)
+        std::stable_sort(d1ord.begin(), d1ord.end(), [&](int64_t a, int64_t b) { return hp.cones[a].k < hp.cones[b].k; });
+    for (size_t s = 0; s < d1ord.size(); ++s) {
+        const Cone& c = hp.cones[d1ord[s]];
+        ConeD1& d = dc[s];
+        if (dw.size() > static_cast<size_t>(INT32_MAX) - 32) {
+            msg = "the plan's cones hold more than 2^31 - 1 neighbours; descriptors index them with 32-bit integers";
+            return QAOA_EINVAL;
+        }
+        d = {static_cast<int32_t>(d1ord[s]), c.inst, static_cast<int32_t>(dw.size()), c.k - 2, 0.0};
+        dw.resize(dw.size() + static_cast<size_t>(c.k - 2), double2{0.0, 0.0});
+        for (size_t e = 0; e < c.ea.size(); ++e) {
+            if (c.ea[e] > 1) continue;   // couplings between neighbours have no part in the term
+            const double w = hp.realw ? c.wf[e] : static_cast<double>(c.ew[e]);
+            if (c.eb[e] == 1) {
+                d.wuv = w;
+            } else {
+                double2& x = dw[static_cast<size_t>(d.off + c.eb[e] - 2)];
+                (c.ea[e] == 0 ? x.x : x.y) = w;
+            }
+        }
+        const int kk = d1_by_k ? c.k : 0;
+        if (P->d1_groups.empty() || P->d1_groups.back().K != kk)
+            P->d1_groups.push_back({kk, static_cast<int64_t>(s), 0, 1});
+        P->d1_groups.back().count += 1;
     }
     // HBM-class descriptors; their edges follow the workgroup-resident ones
     std::vector<ConeHbm> hc(hord.size());
@@ -366,6 +402,8 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     const size_t o_id = place(hp.inst_delta.size() * sizeof(double));
     const size_t o_ones = place(ones.size() * sizeof(double));
     const size_t o_ewd = hp.realw ? place(std::max<size_t>(ewd.size(), 1) * sizeof(double)) : 0;
+    const size_t o_dc = d1 ? place(dc.size() * sizeof(ConeD1)) : 0;
+    const size_t o_dw = d1 ? place(dw.size() * sizeof(double2)) : 0;
     const size_t copied = arena;
     const size_t o_cut = place(static_cast<size_t>(std::max<int64_t>(cut_bytes, 16)));
     const size_t o_tt = place(static_cast<size_t>(std::max<int64_t>(tt_bytes, 16)));
@@ -395,6 +433,10 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
         put(o_id, hp.inst_delta.data(), hp.inst_delta.size() * sizeof(double));
         put(o_ones, ones.data(), ones.size() * sizeof(double));
         if (hp.realw) put(o_ewd, ewd.data(), ewd.size() * sizeof(double));
+        if (d1) {
+            put(o_dc, dc.data(), dc.size() * sizeof(ConeD1));
+            put(o_dw, dw.data(), dw.size() * sizeof(double2));
+        }
         if (P->d_arena) {   // an earlier first call failed after allocating: start over
             hipFree(P->d_arena);
             P->d_arena = nullptr;
@@ -413,9 +455,13 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     P->d_inst_delta = reinterpret_cast<double*>(base + o_id);
     P->d_ones = reinterpret_cast<double*>(base + o_ones);
     P->d_ewd = hp.realw ? reinterpret_cast<double*>(base + o_ewd) : nullptr;
+    P->d_d1 = d1 ? reinterpret_cast<ConeD1*>(base + o_dc) : nullptr;
+    P->d_d1w = d1 ? reinterpret_cast<double2*>(base + o_dw) : nullptr;
     P->d_cut = base + o_cut;
     P->d_tt = base + o_tt;
-    if (hp.realw) {
+    if (d1) {
+        // no tables
+    } else if (hp.realw) {
         QCHECK(launch_cut_tables_real(P->d_cones, M, P->d_ea, P->d_eb, P->d_ewd, reinterpret_cast<float*>(P->d_cut),
                                       nullptr));
         QCHECK(launch_tt_tables_real(P->d_hcones, static_cast<int64_t>(hc.size()), max_groups, P->d_ea, P->d_eb,
@@ -481,6 +527,92 @@ qaoa_status kernel_times(qaoa_plan_s* P, int32_t cap, int32_t* k_out, int64_t* i
 
 namespace {
 
+// Device bytes of one (cone, point) item held as passes over device memory: its states (psi,
+// lambda, or one state per checkpoint and lambda) and its partial sums.
+size_t hbm_item_bytes(int k, int p, bool grad, bool ckpt) {
+    const size_t state = (size_t{1} << (k - 1)) * sizeof(float2);
+    const size_t sums = (size_t{1} << (k - 1 - HT)) * static_cast<size_t>(2 * p + 1) * sizeof(double);
+    const size_t phi = p >= 2 ? (ckpt ? static_cast<size_t>(hbm_checkpoints(k, p)) : size_t{1}) * state : 0;
+    return phi + (grad && p >= 2 ? state : 0) + sums;
+}
+
+// A memory budget that does not hold one item of a class is refused, also where the class runs
+// without states of its own in device memory.
+bool budget_refuses(const qaoa_plan_s* P, int k, bool grad, std::string& msg) {
+    if (P->opt.mem_budget_bytes == 0) return false;
+    const size_t budget = static_cast<size_t>(P->opt.mem_budget_bytes);
+    const size_t need = hbm_item_bytes(k, P->hp.p, grad, grad && P->hp.p >= 2 && P->opt.checkpoint_mode == 1);
+    if (budget >= need) return false;
+    msg = "one " + std::to_string(k) + "-qubit item needs " + std::to_string(need) +
+          " bytes, more than the memory budget of " + std::to_string(budget);
+    return true;
+}
+
+// Orbit-weighted sums of the term rows zz, g (null: energies only) into E and dE.
+qaoa_status finish_sums(qaoa_plan_s* P, int64_t n_points, double* zz, double* g, double* energy, double* dgamma,
+                        double* dbeta, bool terms_read, GroupTimer& tm, hipStream_t stream, std::string& msg) {
+    const HostPlan& hp = P->hp;
+    const int32_t p = hp.p, M = static_cast<int32_t>(hp.cones.size());
+    const double* deltas = P->d_inst_delta;
+    QCHECK(tm.begin(-2, n_points));
+    if (terms_read) {
+        // the caller reads the per-term gradient: gamma derivatives in radians (the combination
+        // then scales by the unit once more, so it gets unit weights)
+        bool unit = true;
+        for (double d : hp.inst_delta) unit = unit && d == 1.0;
+        if (!unit) {
+            QCHECK(launch_scale_gamma_terms(g, n_points, p, M, P->d_inst_orbit, hp.n_inst, P->d_inst_delta, stream));
+            deltas = P->d_ones;
+        }
+    }
+    QCHECK(launch_combine(P->d_W, zz, g, M, p, P->d_inst_orbit, deltas, hp.n_inst, n_points, n_points, 0, energy,
+                          dgamma, dbeta, stream));
+    QCHECK(tm.end());
+    return QAOA_OK;
+}
+
+// The launches of a depth-1 call.  One instance of few orbits: terms and weighted sums in one
+// launch (2048 orbits are eight per thread of the point's workgroup; larger plans fill the chip
+// better with a thread per term and a separate sum).
+qaoa_status enqueue_depth1(qaoa_plan_s* P, int64_t n_points, const double* gamma, const double* beta, double* energy,
+                           double* term_zz, double* dgamma, double* dbeta, double* term_grad, hipStream_t stream,
+                           std::string& msg) {
+    const HostPlan& hp = P->hp;
+    const bool grad = dgamma != nullptr;
+    const int32_t M = static_cast<int32_t>(hp.cones.size());
+    if (P->max_k > P->opt.k_lds_max && budget_refuses(P, P->max_k, grad, msg)) return QAOA_ENOMEM;
+    D1Args a{P->d_d1, P->d_d1w, M, gamma, beta, n_points, P->d_inst_delta, n_points, M, term_zz, term_grad, 1.0};
+    if (hp.n_inst == 1 && M <= 2048 && !P->opt.profile && !P->opt.one_cone_at_a_time) {
+        a.g_scale = hp.inst_delta[0];   // the caller's per-term gradient is in radians
+        QCHECK(launch_depth1_point(a, P->d_W, energy, dgamma, dbeta, stream));
+        return QAOA_OK;
+    }
+    qaoa_status st;
+    if (!term_zz) {
+        if ((st = grow(P->d_zz, P->cap_zz, static_cast<size_t>(n_points) * M, msg)) != QAOA_OK) return st;
+        a.zz = P->d_zz;
+    }
+    if (grad && !term_grad) {
+        if ((st = grow(P->d_g, P->cap_g, static_cast<size_t>(n_points) * 2 * M, msg)) != QAOA_OK) return st;
+        a.g = P->d_g;
+    }
+    GroupTimer tm(P, stream);
+    for (const auto& grp : P->d1_groups) {
+        D1Args c = a;
+        c.cones = P->d_d1 + grp.first;
+        c.n_cones = grp.count;
+        const int64_t items = grp.count * n_points;
+        QCHECK(tm.begin(grp.K, items));
+        if (P->opt.one_cone_at_a_time) {
+            for (int64_t t = 0; t < items; ++t) QCHECK(launch_depth1_terms(c, t, t + 1, grad, stream));
+        } else {
+            QCHECK(launch_depth1_terms(c, 0, items, grad, stream));
+        }
+        QCHECK(tm.end());
+    }
+    return finish_sums(P, n_points, a.zz, a.g, energy, dgamma, dbeta, term_grad != nullptr, tm, stream, msg);
+}
+
 // The launch sequence of one energy call.  With fixed_batches the HBM groups reuse the
 // batch sizes of the previous call (and so allocate nothing): used while capturing.
 qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const double* beta, double* energy,
@@ -489,6 +621,8 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
                     std::string& msg) {
     qaoa_status st = ensure_device(P, msg);
     if (st != QAOA_OK) return st;
+    if (depth1_closed(P))
+        return enqueue_depth1(P, n_points, gamma, beta, energy, term_zz, dgamma, dbeta, term_grad, stream, msg);
     const HostPlan& hp = P->hp;
     const bool grad = (dgamma != nullptr);
     const int32_t p = hp.p;
@@ -562,12 +696,10 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         const int stride = 2 * p + 1;                // values stored per (item, tile)
         const bool need_phi = p >= 2;
         const bool need_lam = grad && p >= 2;
-        const size_t state_bytes = (size_t{1} << kh) * sizeof(float2);
-        const size_t gpart_bytes = static_cast<size_t>(tiles) * stride * sizeof(double);
         // checkpoints: every forward pass but the final one keeps its output (nck states)
         const int nck = hbm_checkpoints(k, p);
-        const size_t per_unc = (need_phi ? state_bytes : 0) + (need_lam ? state_bytes : 0) + gpart_bytes;
-        const size_t per_ck = static_cast<size_t>(nck) * state_bytes + state_bytes + gpart_bytes;
+        const size_t per_unc = hbm_item_bytes(k, p, grad, false);
+        const size_t per_ck = hbm_item_bytes(k, p, grad, true);
         size_t budget = static_cast<size_t>(P->opt.mem_budget_bytes);
         if (!fixed_batches && budget == 0) {
             size_t fr = 0, tot = 0;
@@ -698,23 +830,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         }
         QCHECK(tm.end());
     }
-    QCHECK(tm.begin(-2, n_points));
-    if (grad && term_grad) {
-        // the caller reads the per-term gradient: gamma derivatives in radians (the combination
-        // then scales by the unit once more, so it gets unit weights)
-        bool unit = true;
-        for (double d : hp.inst_delta) unit = unit && d == 1.0;
-        if (!unit) {
-            QCHECK(launch_scale_gamma_terms(g, n_points, p, M, P->d_inst_orbit, hp.n_inst, P->d_inst_delta, stream));
-        }
-        QCHECK(launch_combine(P->d_W, zz, g, M, p, P->d_inst_orbit, unit ? P->d_inst_delta : P->d_ones, hp.n_inst,
-                              n_points, n_points, 0, energy, dgamma, dbeta, stream));
-    } else {
-        QCHECK(launch_combine(P->d_W, zz, g, M, p, P->d_inst_orbit, P->d_inst_delta, hp.n_inst, n_points, n_points,
-                              0, energy, dgamma, dbeta, stream));
-    }
-    QCHECK(tm.end());
-    return QAOA_OK;
+    return finish_sums(P, n_points, zz, g, energy, dgamma, dbeta, grad && term_grad, tm, stream, msg);
 }
 
 void drop_graph(qaoa_plan_s* P) {
@@ -798,7 +914,7 @@ void release_device(qaoa_plan_s* P) {
         hipEventDestroy(t.stop);
     }
     P->timed.clear();
-    if (!P->dev_ready && !P->d_phase) return;
+    if (!P->dev_ready && !P->d_arena && !P->d_phase) return;
     hipDeviceSynchronize();
     hipFree(P->d_arena);
     hipFree(P->d_phase);
@@ -810,6 +926,8 @@ void release_device(qaoa_plan_s* P) {
     hipFree(P->d_gpart);
     P->d_arena = nullptr;
     P->d_cones = nullptr;
+    P->d_d1 = nullptr;
+    P->d_d1w = nullptr;
     P->d_cut = nullptr;
     P->d_W = nullptr;
     P->d_hcones = nullptr;

@@ -6,6 +6,7 @@
 #include <string>
 #include <vector>
 
+#include "depth1.hpp"
 #include "device.hpp"
 #include "hbm_impl.hpp"
 #include "plan.hpp"
@@ -19,6 +20,7 @@ struct qaoa_plan_s {
     void* d_arena = nullptr;
     int device = -1;
     bool dev_ready = false;
+    int32_t max_k = 0;                  // largest cone (qubits)
     struct Group {
         int K;          // cone qubits
         int64_t first;  // first slot in d_cones
@@ -28,6 +30,11 @@ struct qaoa_plan_s {
     std::vector<Group> lds_groups;      // workgroup-resident cones, grouped by K
     qaoa::ConeDev* d_cones = nullptr;
     uint8_t* d_cut = nullptr;
+    // depth-1 plans: every cone, whatever its size, in closed form (in orbit order; sorted by k
+    // where a launch covers one cone size or one item: profile, one_cone_at_a_time)
+    qaoa::ConeD1* d_d1 = nullptr;
+    double2* d_d1w = nullptr;
+    std::vector<Group> d1_groups;       // by k (sorted plans), else one group with K = 0
     // HBM-resident cones, grouped by k
     struct HGroup {
         int K;
@@ -95,6 +102,9 @@ qaoa_status run_energy(qaoa_plan_s* plan, int64_t n_points, const double* gamma,
                        double* energy, double* term_zz, double* dgamma, double* dbeta, double* term_grad,
                        hipStream_t stream,
                        std::string& msg);
+
+// Depth-1 plans evaluated in closed form; tune = 2..5 asks for a layout of the statevector kernel.
+inline bool depth1_closed(const qaoa_plan_s* P) { return P->hp.p == 1 && P->opt.tune < 2; }
 
 void release_device(qaoa_plan_s* plan);
 
