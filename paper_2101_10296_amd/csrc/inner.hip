@@ -1,0 +1,82 @@
+// Tables, chunk sums and dispatch of the inner-state kernel (inner_impl.hpp).
+#include "inner.hpp"
+
+namespace qaoa {
+
+hipError_t launch_inner_k3_6(int, bool, const InArgs&, hipStream_t);
+hipError_t launch_inner_k7_8(int, bool, const InArgs&, hipStream_t);
+hipError_t launch_inner_k9_10(int, bool, const InArgs&, hipStream_t);
+
+hipError_t launch_inner(int kin, bool grad, const InArgs& a, hipStream_t st) {
+    if (a.p < 2 || a.p > IN_PMAX || kin < IN_KMIN || kin > IN_KMAX) return hipErrorInvalidValue;
+    if (kin <= 6) return launch_inner_k3_6(kin, grad, a, st);
+    if (kin <= 8) return launch_inner_k7_8(kin, grad, a, st);
+    return launch_inner_k9_10(kin, grad, a, st);
+}
+
+namespace {
+
+__global__ void __launch_bounds__(64)
+k_inner_tables(const ConeIn* __restrict__ cones, const int32_t* __restrict__ ea, const int32_t* __restrict__ eb,
+               const int32_t* __restrict__ ew, int32_t p, int32_t cut_min, uint8_t* __restrict__ tab) {
+    const ConeIn& cd = cones[blockIdx.x];
+    const uint32_t n = 1u << cd.kin, ts = n < 16u ? 16u : n;
+    uint8_t* out = tab + static_cast<size_t>(cd.tab_off) * 16;
+    for (int l = 2; l <= p; ++l, out += ts) {
+        const int m = cd.mixed[l - 1], cmin = cd.base[l] + cut_min;
+        for (uint32_t x = threadIdx.x; x < ts; x += 64) {
+            int32_t c = 0;
+            for (int32_t e = 0; e < cd.n_edges; ++e) {
+                const int32_t i = ea[cd.edge_off + e], j = eb[cd.edge_off + e];
+                if (j < m) c += ew[cd.edge_off + e] * static_cast<int32_t>(((x >> i) ^ (x >> j)) & 1u);
+            }
+            out[x] = static_cast<uint8_t>(x < n ? c - cmin : 0);
+        }
+    }
+}
+
+// One thread per (point, cone, value): the chunks of a cone in order.
+__global__ void __launch_bounds__(256) k_inner_sum(InArgs a, int32_t n_cones, int32_t nv) {
+    const int64_t n = static_cast<int64_t>(a.P) * n_cones * nv;
+    for (int64_t t = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; t < n;
+         t += static_cast<int64_t>(gridDim.x) * blockDim.x) {
+        const int v = static_cast<int>(t % nv);
+        const int64_t pc = t / nv;
+        const int32_t c = static_cast<int32_t>(pc % n_cones);
+        const int64_t i = pc / n_cones;
+        const double* src = a.part + (i * a.units + static_cast<int64_t>(c) * a.chunks) * nv + v;
+        double x = 0.0;
+        for (int ch = 0; ch < a.chunks; ++ch) x += src[static_cast<size_t>(ch) * nv];
+        const int32_t orbit = a.cones[c].orbit;
+        const size_t pt = static_cast<size_t>(i + a.point0);
+        if (v == 0) a.zz[pt * a.M + orbit] = x;
+        else a.g[(pt * 2 * a.p + (v - 1)) * a.M + orbit] = x;
+    }
+}
+
+}  // namespace
+
+hipError_t launch_inner_sum(const InArgs& a, int32_t n_cones, bool grad, hipStream_t st) {
+    const int nv = grad ? 2 * a.p + 1 : 1;
+    const int64_t n = static_cast<int64_t>(a.P) * n_cones * nv;
+    if (n <= 0) return hipSuccess;
+    const int64_t blocks = (n + 255) / 256;
+    hipLaunchKernelGGL(k_inner_sum, dim3(static_cast<unsigned>(blocks < 65536 ? blocks : 65536)), dim3(256), 0, st, a,
+                       n_cones, nv);
+    return hipGetLastError();
+}
+
+hipError_t launch_inner_tables(const ConeIn* cones, int64_t n_cones, const int32_t* ea, const int32_t* eb,
+                               const int32_t* ew, int32_t p, int32_t cut_min, uint8_t* tab, hipStream_t st) {
+    // a grid holds fewer than 2^32 threads
+    constexpr int64_t CH = static_cast<int64_t>(UINT32_MAX) / 64;
+    for (int64_t c0 = 0; c0 < n_cones; c0 += CH) {
+        const unsigned nx = static_cast<unsigned>(n_cones - c0 < CH ? n_cones - c0 : CH);
+        hipLaunchKernelGGL(k_inner_tables, dim3(nx), dim3(64), 0, st, cones + c0, ea, eb, ew, p, cut_min, tab);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+}  // namespace qaoa

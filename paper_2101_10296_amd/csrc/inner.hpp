@@ -1,0 +1,73 @@
+// Light cones evaluated on their inner qubits: descriptors and launchers (inner.hip).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+namespace qaoa {
+
+constexpr int IN_KMIN = 3;     // inner qubits of a cone with a shell at p >= 2
+constexpr int IN_KMAX = 10;    // 2^10 amplitudes: 16 per lane of one wave
+constexpr int IN_PMAX = 9;     // every layer adds a qubit: p - 1 <= inner - 2
+constexpr int IN_ROUNDS = 8;   // rounds of configurations per unit of work
+
+// One light cone: the inner qubits 0 .. kin-1 (closer than p to the edge) carry the state, the
+// shell (at distance p) is a sum over configurations.
+struct ConeIn {
+    int32_t orbit;             // term index m (output column)
+    int32_t inst;              // instance of the cone
+    int32_t n_grp, grp_off;    // shell groups
+    uint32_t nc;               // configurations: product of (m_g + 1)
+    int32_t tab_off;           // first table in units of 16 bytes
+    int32_t kin;               // inner qubits
+    int32_t edge_off, n_edges; // cone edges (pairs of qubits, the first the smaller)
+    int32_t pad0_;
+    double shell_norm;         // 2^-(shell qubits)
+    int16_t base[IN_PMAX + 1]; // [l], l = 2..p: phase row index of table value 0 of layer l; [1] = [2]
+    float mid[IN_PMAX + 1];    // [l]: centre of layer l's cut values, relative to row index 0
+    uint8_t mixed[IN_PMAX + 3];// [l]: qubits that layer l mixes (a prefix): those closer than p - l + 1
+};
+
+// Shell qubits with the same couplings: only how many of them are 1 matters.
+struct GrpIn {
+    int32_t m;        // qubits in the group
+    int32_t wsum;     // sum of their couplings (one qubit's)
+    int32_t h[8];     // coupling to inner qubit 2 + i
+};
+
+struct InArgs {
+    const ConeIn* cones;       // cones of this class (inner qubits), from the launch's first
+    const GrpIn* grp;
+    const uint8_t* tab;
+    const double* gamma;       // [inst][gamma_P][p]
+    const double* beta;
+    int64_t gamma_P;
+    const double* deltas;
+    int32_t p, R, cut_min;     // depth; phase row length and the cut value of entry 0
+    int32_t P;                 // points of the launch
+    int32_t point0;            // first of them
+    int32_t M;
+    int32_t units;             // units of work per point: cones x chunks
+    int32_t chunks;            // units per cone
+    int32_t upw;               // units per wave
+    int32_t blocks;            // workgroups per point
+    // segments of one instance each (the workgroups of one share its phase rows); n_seg > 1:
+    // seg[0..n_seg] first unit, then n_seg + 1 first workgroups for this upw, then n_seg instances
+    const int32_t* seg;
+    int32_t n_seg;
+    int32_t inst0;             // n_seg = 1: its instance
+    double* zz;                // [P][M], rows from point 0 of the call
+    double* g;                 // [P][2p][M]
+    double* part;              // chunks > 1: [P of the launch][units][values]
+};
+
+hipError_t launch_inner(int kin, bool grad, const InArgs& a, hipStream_t st);
+// sums the chunks of every (point, cone) into zz and g
+hipError_t launch_inner_sum(const InArgs& a, int32_t n_cones, bool grad, hipStream_t st);
+// Table of layer l (2..p) of every cone: the cut of the couplings inside the qubits mixed by
+// layer l - 1, minus its smallest value, a byte per inner basis state.
+hipError_t launch_inner_tables(const ConeIn* cones, int64_t n_cones, const int32_t* ea, const int32_t* eb,
+                               const int32_t* ew, int32_t p, int32_t cut_min, uint8_t* tab, hipStream_t st);
+
+}  // namespace qaoa

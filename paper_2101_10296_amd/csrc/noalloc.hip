@@ -116,7 +116,7 @@ qaoa_status run_energy_grad_noalloc(qaoa_plan_s* P, int64_t n_points, const doub
         }
         // tables [instance][point of the chunk][layer]: one launch per instance (its angles
         // are rows i0 .. i0 + pc - 1 of its [n_points][p] block)
-        for (int32_t j = 0; j < ni; ++j) {
+        for (int32_t j = 0; j < ni && !P->lds_groups.empty(); ++j) {
             const size_t src = (static_cast<size_t>(j) * n_points + i0) * p;
             const size_t dst = static_cast<size_t>(j) * pc * p;
             NCHECK(launch_tables(gamma + src, beta + src, pc * p, R, hp.cut_min, P->d_inst_delta + j, pc * p,
@@ -126,6 +126,10 @@ qaoa_status run_energy_grad_noalloc(qaoa_plan_s* P, int64_t n_points, const doub
         // instance's block of n_points
         const EvalArgs ea{static_cast<int32_t>(pc), p, M, R, phase, mix, gamma + static_cast<size_t>(i0) * p,
                           static_cast<int32_t>(n_points), hp.realw ? 1 : 0, zz, g};
+        for (const auto& grp : P->in_groups)
+            if (P->opt.tune != 1)   // a tuned plan holds these cones in lds_groups too
+                NCHECK(launch_inner_group(P, grp, true, 0, pc, gamma + static_cast<size_t>(i0) * p,
+                                          beta + static_cast<size_t>(i0) * p, n_points, zz, g, nullptr, 0, stream));
         for (const auto& grp : P->lds_groups)
             NCHECK(launch_fused(grp.K, true, 0, P->d_cones + grp.first, 0, grp.count * pc, P->d_cut, grp.rowcap,
                                 ea, stream));   // default layout: no tuning runs here

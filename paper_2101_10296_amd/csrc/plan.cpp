@@ -290,6 +290,10 @@ void build_host_plan(int32_t n, int64_t m, const int32_t* eu, const int32_t* ev,
             Cone& c = P.cones[o];
             c.k = static_cast<int32_t>(ball.size());
             c.nodes.assign(ball.begin(), ball.end());
+            for (int32_t d = 0, i = 0; d < 10; ++d) {
+                while (i < c.k && dist[ball[i]] <= d) ++i;
+                c.nd[d] = static_cast<uint8_t>(i);
+            }
             for (int32_t i = 0; i < c.k; ++i) loc[ball[i]] = i;
             int64_t cmin = 0, cmax = 0, ne = 0;
             for (int32_t i = 0; i < c.k; ++i) {

@@ -23,6 +23,7 @@ struct Cone {
     int32_t cut_min = 0, cut_max = 0;      // range of the cut value C(x) over all x (units of delta)
     double cf_min = 0.0, cf_max = 0.0;     // the same range in real weights
     int32_t inst = 0;                      // instance (graph) of a plan over several graphs
+    uint8_t nd[10] = {};                   // qubits within distance d of the edge, d = 0..9 (a prefix)
 };
 
 struct HostPlan {

@@ -3,6 +3,7 @@
 #include "runtime.hpp"
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <map>
@@ -18,7 +19,8 @@ namespace {
 // stream) and the fastest is kept, keyed by (device architecture, what, k, p, gradient,
 // real weights).  what = 0: register bits per LDS stage / workgroup size of the
 // workgroup-resident kernel (fused_variants); what = 1: tiles per workgroup of the
-// device-memory passes.
+// device-memory passes; what = 2: units per wave of cones above k_lds_max qubits that run on
+// their inner qubits (reported under the name of 1: such a unit stands where a tile stood).
 struct TuneKey {
     std::string arch;
     int what, k, p, grad, realw;
@@ -239,6 +241,146 @@ std::mutex g_stage_mu;
 void* g_stage = nullptr;
 size_t g_stage_cap = 0;
 
+// Descriptors of the cones evaluated on their inner qubits (inner.hpp).
+struct InnerHost {
+    std::vector<ConeIn> cones;
+    std::vector<GrpIn> grp;
+    std::vector<int32_t> seg;
+    int64_t tab_units = 0;   // table bytes / 16
+};
+
+// Fills P->in_groups and the descriptors for the orbits in ord; their edges are appended to ea, eb, ew.
+void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, std::vector<int32_t>& ea, std::vector<int32_t>& eb,
+                 std::vector<int32_t>& ew, InnerHost& in) {
+    const HostPlan& hp = P->hp;
+    const int32_t p = hp.p;
+    const bool by_k = P->opt.profile || P->opt.tune == 1;
+    P->in_groups.clear();
+    P->in_inst.clear();
+    P->in_max_k = 0;
+    if (ord.empty()) return;
+    auto kin_of = [&](int64_t m) { return static_cast<int>(hp.cones[m].nd[p - 1]); };
+    std::stable_sort(ord.begin(), ord.end(), [&](int64_t a, int64_t b) {
+        const int x = kin_of(a), y = kin_of(b);
+        return x != y ? x < y : by_k && hp.cones[a].k < hp.cones[b].k;
+    });
+    in.cones.reserve(ord.size());
+    std::vector<uint32_t> rounds;
+    rounds.reserve(ord.size());
+    for (int64_t m : ord) {
+        const Cone& c = hp.cones[m];
+        const int kin = kin_of(m), ns = c.k - kin;
+        ConeIn d{};
+        d.orbit = static_cast<int32_t>(m);
+        d.inst = c.inst;
+        d.kin = kin;
+        d.edge_off = static_cast<int32_t>(ea.size());
+        d.n_edges = static_cast<int32_t>(c.ea.size());
+        d.shell_norm = std::ldexp(1.0, -ns);
+        for (int l = 1; l <= p; ++l) d.mixed[l] = c.nd[p - l];
+        int32_t h[30][8] = {};
+        double w_all = 0.0;
+        for (size_t e = 0; e < c.ea.size(); ++e) {
+            if (c.eb[e] < kin) continue;
+            if (c.ea[e] >= kin) continue;   // both ends in the shell: no part in the term
+            h[c.eb[e] - kin][c.ea[e] - 2] = c.ew[e];
+            w_all += c.ew[e];
+        }
+        for (int l = 2; l <= p; ++l) {
+            int32_t cmin = 0;
+            double wl = 0.0;
+            for (size_t e = 0; e < c.ea.size(); ++e)
+                if (c.eb[e] < d.mixed[l - 1]) {
+                    cmin += std::min(c.ew[e], 0);
+                    wl += c.ew[e];
+                }
+            d.base[l] = static_cast<int16_t>(cmin - hp.cut_min);
+            d.mid[l] = static_cast<float>(0.5 * wl - hp.cut_min);
+            if (l == 2) {
+                d.base[1] = d.base[2];
+                d.mid[1] = static_cast<float>(0.5 * (wl + w_all) - hp.cut_min);
+            }
+        }
+        d.grp_off = static_cast<int32_t>(in.grp.size());
+        uint32_t nc = 1;
+        for (int s = 0; s < ns; ++s) {
+            bool found = false;
+            for (size_t g = d.grp_off; g < in.grp.size() && !found; ++g)
+                if (std::memcmp(in.grp[g].h, h[s], sizeof(h[s])) == 0) {
+                    in.grp[g].m += 1;
+                    found = true;
+                }
+            if (found) continue;
+            GrpIn G{};
+            G.m = 1;
+            for (int i = 0; i < 8; ++i) {
+                G.h[i] = h[s][i];
+                G.wsum += h[s][i];
+            }
+            in.grp.push_back(G);
+        }
+        d.n_grp = static_cast<int32_t>(in.grp.size()) - d.grp_off;
+        for (int g = 0; g < d.n_grp; ++g) nc *= static_cast<uint32_t>(in.grp[d.grp_off + g].m) + 1u;
+        d.nc = nc;   // at most 2^27: the shell holds at most 27 qubits
+        d.tab_off = static_cast<int32_t>(in.tab_units);
+        in.tab_units += (p - 1) * std::max<int64_t>(1, (int64_t{1} << kin) / 16);
+        const uint32_t cpw = 64u >> std::max(0, kin - 4);
+        rounds.push_back(((nc + 1) / 2 + cpw - 1) / cpw);
+        ea.insert(ea.end(), c.ea.begin(), c.ea.end());
+        eb.insert(eb.end(), c.eb.begin(), c.eb.end());
+        ew.insert(ew.end(), c.ew.begin(), c.ew.end());
+        const int kk = by_k ? c.k : 0;
+        if (P->in_groups.empty() || P->in_groups.back().kin != kin || P->in_groups.back().K != kk) {
+            qaoa_plan_s::InGroup g{};
+            g.kin = kin;
+            g.K = kk;
+            g.first = static_cast<int64_t>(in.cones.size());
+            P->in_groups.push_back(g);
+        }
+        P->in_groups.back().count += 1;
+        P->in_max_k = std::max(P->in_max_k, c.k);
+        P->in_inst.push_back(c.inst);
+        in.cones.push_back(d);
+    }
+    for (auto& g : P->in_groups) {
+        // Units of IN_ROUNDS rounds where a cone has more than 16 (cones of up to 14 qubits never do),
+        // fewer where the class alone keeps 2^15 of them.  Set by the plan alone, so that a term's
+        // sum is the same whatever the number of points.
+        uint32_t most = 1;
+        for (int64_t i = g.first; i < g.first + g.count; ++i) most = std::max(most, rounds[static_cast<size_t>(i)]);
+        int64_t ch = most > 16 ? (most + IN_ROUNDS - 1) / IN_ROUNDS : 1;
+        ch = std::min(ch, std::max<int64_t>(1, (int64_t{1} << 15) / g.count));
+        g.chunks = static_cast<int32_t>(ch);
+        std::vector<int32_t> unit{0}, inst;   // segments of one instance
+        for (int64_t i = 0; i < g.count; ++i) {
+            const int32_t j = in.cones[static_cast<size_t>(g.first + i)].inst;
+            if (inst.empty() || inst.back() != j) {
+                if (!inst.empty()) unit.push_back(static_cast<int32_t>(i * ch));
+                inst.push_back(j);
+            }
+        }
+        unit.push_back(static_cast<int32_t>(g.count * ch));
+        g.n_seg = static_cast<int32_t>(inst.size());
+        for (int j = 0; j < 4; ++j) {
+            const int32_t per = 4 << j;
+            int32_t b = 0;
+            std::vector<int32_t> blk;
+            for (int32_t q = 0; q < g.n_seg; ++q) {
+                blk.push_back(b);
+                b += (unit[q + 1] - unit[q] + per - 1) / per;
+            }
+            blk.push_back(b);
+            g.blocks[j] = b;
+            g.seg[j] = static_cast<int64_t>(in.seg.size());
+            if (g.n_seg > 1) {
+                in.seg.insert(in.seg.end(), unit.begin(), unit.end());
+                in.seg.insert(in.seg.end(), blk.begin(), blk.end());
+                in.seg.insert(in.seg.end(), inst.begin(), inst.end());
+            }
+        }
+    }
+}
+
 qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
@@ -261,10 +403,18 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     const bool d1 = depth1_closed(P);
     P->max_k = 0;
     for (const Cone& c : hp.cones) P->max_k = std::max(P->max_k, c.k);
-    std::vector<int64_t> d1ord;
-    for (int64_t m = 0; m < Mall; ++m)
-        (d1 ? d1ord : hp.cones[m].k <= P->opt.k_lds_max ? ord : hord).push_back(m);
-    std::stable_sort(ord.begin(), ord.end(), [&](int64_t a, int64_t b) { return hp.cones[a].k < hp.cones[b].k; });
+    std::vector<int64_t> d1ord, inord;
+    for (int64_t m = 0; m < Mall; ++m) {
+        const bool small = hp.cones[m].k <= P->opt.k_lds_max;
+        const bool inner = !d1 && inner_cone(P, hp.cones[m]);
+        if (inner) inord.push_back(m);
+        if (inner && !(P->opt.tune == 1 && small)) continue;   // the tuner compares both kernels
+        (d1 ? d1ord : small ? ord : hord).push_back(m);
+    }
+    std::stable_sort(ord.begin(), ord.end(), [&](int64_t a, int64_t b) {
+        const Cone &x = hp.cones[a], &y = hp.cones[b];
+        return x.k != y.k ? x.k < y.k : inner_cone(P, x) > inner_cone(P, y);
+    });
     std::stable_sort(hord.begin(), hord.end(), [&](int64_t a, int64_t b) { return hp.cones[a].k < hp.cones[b].k; });
     const int64_t M = static_cast<int64_t>(ord.size());
     std::vector<ConeDev> cd(M);
@@ -301,10 +451,13 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
         ea.insert(ea.end(), c.ea.begin(), c.ea.end());
         eb.insert(eb.end(), c.eb.begin(), c.eb.end());
         ew.insert(ew.end(), c.ew.begin(), c.ew.end());
-        if (P->lds_groups.empty() || P->lds_groups.back().K != c.k) P->lds_groups.push_back({c.k, s, 0, 1});
+        if (P->lds_groups.empty() || P->lds_groups.back().K != c.k) P->lds_groups.push_back({c.k, s, 0, 1, 0});
         P->lds_groups.back().count += 1;
+        if (inner_cone(P, c)) P->lds_groups.back().n_in += 1;
         P->lds_groups.back().rowcap = std::max(P->lds_groups.back().rowcap, d.cut_range);
     }
+    InnerHost in;
+    build_inner(P, inord, ea, eb, ew, in);
     // depth-1 cones: the couplings of the edge's two ends
     std::vector<ConeD1> dc(d1ord.size());
     std::vector<double2> dw;
@@ -333,7 +486,7 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
         }
         const int kk = d1_by_k ? c.k : 0;
         if (P->d1_groups.empty() || P->d1_groups.back().K != kk)
-            P->d1_groups.push_back({kk, static_cast<int64_t>(s), 0, 1});
+            P->d1_groups.push_back({kk, static_cast<int64_t>(s), 0, 1, 0});
         P->d1_groups.back().count += 1;
     }
     // HBM-class descriptors; their edges follow the workgroup-resident ones
@@ -377,7 +530,7 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
         P->hbm_groups.back().count += 1;
         P->hbm_groups.back().rowcap = std::max(P->hbm_groups.back().rowcap, d.cut_range);
     }
-    if (ea.size() > static_cast<size_t>(INT32_MAX) || Mall > INT32_MAX) {
+    if (ea.size() > static_cast<size_t>(INT32_MAX) || Mall > INT32_MAX || in.tab_units > INT32_MAX) {
         msg = "the plan's cones hold " + std::to_string(ea.size()) + " edges over " + std::to_string(Mall) +
               " orbits; descriptors index both with 32-bit integers";
         return QAOA_EINVAL;
@@ -404,7 +557,12 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     const size_t o_ewd = hp.realw ? place(std::max<size_t>(ewd.size(), 1) * sizeof(double)) : 0;
     const size_t o_dc = d1 ? place(dc.size() * sizeof(ConeD1)) : 0;
     const size_t o_dw = d1 ? place(dw.size() * sizeof(double2)) : 0;
+    const bool has_in = !in.cones.empty();
+    const size_t o_in = has_in ? place(in.cones.size() * sizeof(ConeIn)) : 0;
+    const size_t o_ig = has_in ? place(in.grp.size() * sizeof(GrpIn)) : 0;
+    const size_t o_is = has_in ? place(in.seg.size() * sizeof(int32_t)) : 0;
     const size_t copied = arena;
+    const size_t o_it = has_in ? place(static_cast<size_t>(in.tab_units) * 16) : 0;
     const size_t o_cut = place(static_cast<size_t>(std::max<int64_t>(cut_bytes, 16)));
     const size_t o_tt = place(static_cast<size_t>(std::max<int64_t>(tt_bytes, 16)));
     {
@@ -433,6 +591,11 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
         put(o_id, hp.inst_delta.data(), hp.inst_delta.size() * sizeof(double));
         put(o_ones, ones.data(), ones.size() * sizeof(double));
         if (hp.realw) put(o_ewd, ewd.data(), ewd.size() * sizeof(double));
+        if (has_in) {
+            put(o_in, in.cones.data(), in.cones.size() * sizeof(ConeIn));
+            put(o_ig, in.grp.data(), in.grp.size() * sizeof(GrpIn));
+            put(o_is, in.seg.data(), in.seg.size() * sizeof(int32_t));
+        }
         if (d1) {
             put(o_dc, dc.data(), dc.size() * sizeof(ConeD1));
             put(o_dw, dw.data(), dw.size() * sizeof(double2));
@@ -457,6 +620,10 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     P->d_ewd = hp.realw ? reinterpret_cast<double*>(base + o_ewd) : nullptr;
     P->d_d1 = d1 ? reinterpret_cast<ConeD1*>(base + o_dc) : nullptr;
     P->d_d1w = d1 ? reinterpret_cast<double2*>(base + o_dw) : nullptr;
+    P->d_in = has_in ? reinterpret_cast<ConeIn*>(base + o_in) : nullptr;
+    P->d_ingrp = has_in ? reinterpret_cast<GrpIn*>(base + o_ig) : nullptr;
+    P->d_inseg = has_in ? reinterpret_cast<int32_t*>(base + o_is) : nullptr;
+    P->d_intab = has_in ? base + o_it : nullptr;
     P->d_cut = base + o_cut;
     P->d_tt = base + o_tt;
     if (d1) {
@@ -470,6 +637,9 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
         QCHECK(launch_cut_tables(P->d_cones, M, P->d_ea, P->d_eb, P->d_ew, P->d_cut, nullptr));
         QCHECK(launch_tt_tables(P->d_hcones, static_cast<int64_t>(hc.size()), max_groups, P->d_ea, P->d_eb,
                                 P->d_ew, P->d_tt, nullptr));
+        if (has_in)
+            QCHECK(launch_inner_tables(P->d_in, static_cast<int64_t>(in.cones.size()), P->d_ea, P->d_eb, P->d_ew, hp.p,
+                                       hp.cut_min, P->d_intab, nullptr));
     }
     QCHECK(hipDeviceSynchronize());
     P->resident_bytes = arena;
@@ -505,6 +675,65 @@ struct GroupTimer {
 };
 
 }  // namespace
+
+hipError_t launch_inner_group(const qaoa_plan_s* P, const qaoa_plan_s::InGroup& grp, bool grad, int upw_log2,
+                              int64_t n_points, const double* gamma, const double* beta, int64_t gamma_P, double* zz,
+                              double* g, double* part, size_t part_cap, hipStream_t st) {
+    const HostPlan& hp = P->hp;
+    InArgs a{};
+    a.cones = P->d_in + grp.first;
+    a.grp = P->d_ingrp;
+    a.tab = P->d_intab;
+    a.gamma = gamma;
+    a.beta = beta;
+    a.gamma_P = gamma_P;
+    a.deltas = P->d_inst_delta;
+    a.p = hp.p;
+    a.R = hp.cut_max - hp.cut_min + 1;
+    a.cut_min = hp.cut_min;
+    a.M = static_cast<int32_t>(hp.cones.size());
+    a.chunks = grp.chunks;
+    a.zz = zz;
+    a.g = g;
+    a.part = part;
+    const int64_t nv = grad ? 2 * hp.p + 1 : 1;
+    auto run = [&](int64_t p0, int64_t np, int64_t cones) {
+        a.point0 = static_cast<int32_t>(p0);
+        a.P = static_cast<int32_t>(np);
+        hipError_t e = launch_inner(grp.kin, grad, a, st);
+        if (e == hipSuccess && grp.chunks > 1) e = launch_inner_sum(a, static_cast<int32_t>(cones), grad, st);
+        return e;
+    };
+    if (P->opt.one_cone_at_a_time) {
+        a.n_seg = 1;
+        a.units = grp.chunks;
+        a.upw = 1;
+        a.blocks = (grp.chunks + 3) / 4;
+        for (int64_t i = 0; i < grp.count; ++i) {
+            a.cones = P->d_in + grp.first + i;
+            a.inst0 = P->in_inst[static_cast<size_t>(grp.first + i)];
+            for (int64_t pt = 0; pt < n_points; ++pt) {
+                const hipError_t e = run(pt, 1, 1);
+                if (e != hipSuccess) return e;
+            }
+        }
+        return hipSuccess;
+    }
+    a.units = static_cast<int32_t>(grp.count * grp.chunks);
+    a.upw = 1 << upw_log2;
+    a.blocks = grp.blocks[upw_log2];
+    a.n_seg = grp.n_seg;
+    a.inst0 = P->in_inst[static_cast<size_t>(grp.first)];
+    a.seg = grp.n_seg > 1 ? P->d_inseg + grp.seg[upw_log2] : nullptr;
+    // points per launch: a grid holds fewer than 2^32 threads, and the partial sums their room
+    int64_t slab = std::max<int64_t>(1, (static_cast<int64_t>(UINT32_MAX) / 256) / a.blocks);
+    if (grp.chunks > 1) slab = std::min(slab, static_cast<int64_t>(part_cap) / (a.units * nv));
+    for (int64_t p0 = 0; p0 < n_points; p0 += slab) {
+        const hipError_t e = run(p0, std::min(slab, n_points - p0), grp.count);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 
 qaoa_status kernel_times(qaoa_plan_s* P, int32_t cap, int32_t* k_out, int64_t* items_out, double* ms_out,
                          int32_t* n_out, std::string& msg) {
@@ -628,9 +857,13 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
     const int32_t p = hp.p;
     const int32_t M = static_cast<int32_t>(hp.cones.size());
     const int32_t R = hp.cut_max - hp.cut_min + 1;
+    if (P->in_max_k > P->opt.k_lds_max && budget_refuses(P, P->in_max_k, grad, msg)) return QAOA_ENOMEM;
     const size_t npl = static_cast<size_t>(hp.n_inst) * n_points * p;   // (instance, point, layer) rows
-    if ((st = grow(P->d_phase, P->cap_phase, npl * R, msg)) != QAOA_OK) return st;
-    if ((st = grow(P->d_mix, P->cap_mix, npl, msg)) != QAOA_OK) return st;
+    const bool tables = P->in_groups.empty() || !P->lds_groups.empty() || !P->hbm_groups.empty();
+    if (tables) {
+        if ((st = grow(P->d_phase, P->cap_phase, npl * R, msg)) != QAOA_OK) return st;
+        if ((st = grow(P->d_mix, P->cap_mix, npl, msg)) != QAOA_OK) return st;
+    }
     double* zz = term_zz;
     if (!zz) {
         if ((st = grow(P->d_zz, P->cap_zz, static_cast<size_t>(n_points) * M, msg)) != QAOA_OK) return st;
@@ -643,14 +876,66 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         if ((st = grow(P->d_g, P->cap_g, static_cast<size_t>(n_points) * 2 * p * M, msg)) != QAOA_OK) return st;
         g = P->d_g;
     }
+    // partial sums of cones in several units: a point's at least, 2^25 values at most
+    size_t part_need = 0;
+    const size_t nv = grad ? 2 * static_cast<size_t>(p) + 1 : 1;
+    for (const auto& grp : P->in_groups)
+        if (grp.chunks > 1) {
+            const size_t one = static_cast<size_t>(grp.count) * grp.chunks * nv;
+            part_need = std::max(part_need, std::max(one, std::min<size_t>(one * n_points, size_t{1} << 25)));
+        }
+    if (part_need && (st = grow(P->d_part, P->cap_part, part_need, msg)) != QAOA_OK) return st;
     GroupTimer tm(P, stream);
-    QCHECK(tm.begin(-1, static_cast<int64_t>(npl)));
-    QCHECK(launch_tables(gamma, beta, static_cast<int64_t>(npl), R, hp.cut_min, P->d_inst_delta,
-                         static_cast<int64_t>(n_points) * p, P->d_phase, P->d_mix, stream));
-    QCHECK(tm.end());
+    if (tables) {
+        QCHECK(tm.begin(-1, static_cast<int64_t>(npl)));
+        QCHECK(launch_tables(gamma, beta, static_cast<int64_t>(npl), R, hp.cut_min, P->d_inst_delta,
+                             static_cast<int64_t>(n_points) * p, P->d_phase, P->d_mix, stream));
+        QCHECK(tm.end());
+    }
     EvalArgs ea{static_cast<int32_t>(n_points), p, M, R, P->d_phase, P->d_mix, gamma,
                 static_cast<int32_t>(n_points), hp.realw ? 1 : 0, zz, g};
     const std::string arch = P->opt.tune == 1 ? device_arch(P->device) : std::string();
+    // units per wave: the workgroup's set-up (phase rows) is shared by more units once the waves
+    // fill the chip several times over
+    auto inner_upw = [&](const qaoa_plan_s::InGroup& grp) {
+        const int64_t units = grp.count * grp.chunks * n_points;
+        int j = 0;
+        while (j < 2 && (units >> (j + 1)) >= (int64_t{1} << 15)) ++j;
+        return j;
+    };
+    auto run_inner = [&](const qaoa_plan_s::InGroup& grp, int j) {
+        return launch_inner_group(P, grp, grad, j, n_points, gamma, beta, n_points, zz, g, P->d_part, P->cap_part, stream);
+    };
+    for (const auto& grp : P->in_groups) {
+        if (P->opt.tune == 1 && grp.K <= P->opt.k_lds_max) continue;   // with the other cones of its size, below
+        int j = inner_upw(grp);
+        if (P->opt.tune == 1) {
+            const TuneKey key{arch, 2, grp.K, p, grad ? 1 : 0, 0};
+            int upw = 1 << j;
+            if (!tune_lookup(key, upw) && !fixed_batches)
+                QCHECK(tune_pick(key, {1, 2, 4, 8}, grp.count * n_points, stream,
+                                 [&](int v) { return run_inner(grp, __builtin_ctz(static_cast<unsigned>(v))); }, upw));
+            j = __builtin_ctz(static_cast<unsigned>(std::min(upw, 8)));
+        }
+        QCHECK(tm.begin(grp.K, grp.count * n_points));
+        QCHECK(run_inner(grp, j));
+        QCHECK(tm.end());
+    }
+    // all cones of one size in layout v; the default (0) takes the cones with a shell on their inner
+    // qubits (tune = 1 plans hold them in both forms)
+    auto run_size = [&](const qaoa_plan_s::Group& grp, int v, int64_t n) {
+        int64_t done = 0;
+        if (v == 0 && grp.n_in > 0) {
+            for (const auto& ig : P->in_groups)
+                if (ig.K == grp.K) {
+                    const hipError_t e = run_inner(ig, inner_upw(ig));
+                    if (e != hipSuccess) return e;
+                }
+            done = grp.n_in * n_points;
+        }
+        if (done >= n) return hipSuccess;
+        return launch_fused(grp.K, grad, v, P->d_cones + grp.first, done, n, P->d_cut, grp.rowcap, ea, stream);
+    };
     for (const auto& grp : P->lds_groups) {
         const ConeDev* cones = P->d_cones + grp.first;
         const int64_t items = grp.count * n_points;
@@ -665,7 +950,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
                     // timed on up to 2^16 items of this call (their results are written again below)
                     const int64_t ns = std::min<int64_t>(items, int64_t{1} << 16);
                     QCHECK(tune_pick(key, cand, ns, stream, [&](int v) {
-                        return launch_fused(grp.K, grad, v, cones, 0, ns, P->d_cut, grp.rowcap, ea, stream);
+                        return run_size(grp, v, ns);
                     }, variant));
                 }
             }
@@ -675,7 +960,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
             for (int64_t it = 0; it < items; ++it)
                 QCHECK(launch_fused(grp.K, grad, 0, cones, it, it + 1, P->d_cut, grp.rowcap, ea, stream));
         } else {
-            QCHECK(launch_fused(grp.K, grad, variant, cones, 0, items, P->d_cut, grp.rowcap, ea, stream));
+            QCHECK(run_size(grp, variant, items));
         }
         QCHECK(tm.end());
     }
@@ -924,6 +1209,7 @@ void release_device(qaoa_plan_s* P) {
     hipFree(P->d_phi);
     hipFree(P->d_lam);
     hipFree(P->d_gpart);
+    hipFree(P->d_part);
     P->d_arena = nullptr;
     P->d_cones = nullptr;
     P->d_d1 = nullptr;
@@ -939,6 +1225,12 @@ void release_device(qaoa_plan_s* P) {
     P->d_ones = nullptr;
     P->d_phi = P->d_lam = nullptr;
     P->d_gpart = nullptr;
+    P->d_part = nullptr;
+    P->cap_part = 0;
+    P->d_in = nullptr;
+    P->d_ingrp = nullptr;
+    P->d_intab = nullptr;
+    P->d_inseg = nullptr;
     P->cap_phi = P->cap_lam = P->cap_gpart = 0;
     P->d_phase = nullptr;
     P->d_mix = nullptr;

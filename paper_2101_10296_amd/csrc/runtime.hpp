@@ -9,6 +9,7 @@
 #include "depth1.hpp"
 #include "device.hpp"
 #include "hbm_impl.hpp"
+#include "inner.hpp"
 #include "plan.hpp"
 #include "qaoa.h"
 
@@ -26,6 +27,7 @@ struct qaoa_plan_s {
         int64_t first;  // first slot in d_cones
         int64_t count;  // cones in this group
         int32_t rowcap; // largest cut range of the group's cones
+        int64_t n_in = 0;   // tune = 1: the first n_in cones are also in in_groups (their default)
     };
     std::vector<Group> lds_groups;      // workgroup-resident cones, grouped by K
     qaoa::ConeDev* d_cones = nullptr;
@@ -35,6 +37,25 @@ struct qaoa_plan_s {
     qaoa::ConeD1* d_d1 = nullptr;
     double2* d_d1w = nullptr;
     std::vector<Group> d1_groups;       // by k (sorted plans), else one group with K = 0
+    // cones with a shell and at most IN_KMAX inner qubits, grouped by inner qubits (and by k where
+    // launches are timed per cone size: profile, tune = 1)
+    struct InGroup {
+        int kin, K;         // inner qubits; cone qubits, or 0
+        int64_t first, count;
+        int32_t chunks;     // units of work per cone
+        int32_t n_seg;      // instances
+        int64_t seg[4];     // n_seg > 1: offset of the segment tables for 1, 2, 4, 8 units per wave
+        int32_t blocks[4];  // workgroups per point
+    };
+    std::vector<InGroup> in_groups;
+    std::vector<int32_t> in_inst;       // instance of each cone in d_in
+    int32_t in_max_k = 0;               // largest of them (cone qubits)
+    qaoa::ConeIn* d_in = nullptr;
+    qaoa::GrpIn* d_ingrp = nullptr;
+    uint8_t* d_intab = nullptr;
+    int32_t* d_inseg = nullptr;
+    size_t cap_part = 0;
+    double* d_part = nullptr;           // partial sums of cones in several units
     // HBM-resident cones, grouped by k
     struct HGroup {
         int K;
@@ -105,6 +126,23 @@ qaoa_status run_energy(qaoa_plan_s* plan, int64_t n_points, const double* gamma,
 
 // Depth-1 plans evaluated in closed form; tune = 2..5 asks for a layout of the statevector kernel.
 inline bool depth1_closed(const qaoa_plan_s* P) { return P->hp.p == 1 && P->opt.tune < 2; }
+
+// Cones evaluated on their inner qubits: those with a shell (else there is nothing to average
+// over, and the kernels for whole cones store half of the state) whose inner state fits the
+// registers of one wave.  Every such cone measured faster there: 14 qubits, p = 2 (6 inner)
+// 10.7x, 18 qubits (8 inner) 2.1x, 26 qubits (8 inner) 50x; C_10000(1,2) at one point, 10-11
+// qubits with as many amplitudes as before, 26.7 -> 21.6 us for the call.  Real weights and
+// forced layouts (tune >= 2) keep the kernels for whole cones.
+inline bool inner_cone(const qaoa_plan_s* P, const Cone& c) {
+    const int32_t p = P->hp.p;
+    return p >= 2 && p <= IN_PMAX && !P->hp.realw && P->opt.tune < 2 && c.nd[p - 1] <= IN_KMAX && c.nd[p - 1] < c.k;
+}
+
+// One class of them (grp) for a call's points: terms into zz, g; part: room for the partial sums of
+// at least one point (null where every cone is one unit).
+hipError_t launch_inner_group(const qaoa_plan_s* P, const qaoa_plan_s::InGroup& grp, bool grad, int upw_log2,
+                              int64_t n_points, const double* gamma, const double* beta, int64_t gamma_P, double* zz,
+                              double* g, double* part, size_t part_cap, hipStream_t st);
 
 void release_device(qaoa_plan_s* plan);
 
