@@ -91,13 +91,13 @@ hipError_t launch_cut_tables_real(const ConeDev* cones, int64_t n_cones, const i
 
 // Per (instance j, point i) block, over the orbits m of instance j:
 // block y == 0: energy = sum_m W_m (1 - zz[i][m]) / 2            (Sec. 3 reduced sum)
-// block y == 1 + l: -1/2 sum_m W_m g[i][l][m] -> dgamma (l < p, times the instance's weight
+// block y == 1 + l: -1/2 sum_m Wg_m g[i][l][m] -> dgamma (l < p, times the instance's weight
 // unit: cut values are counted in it) or dbeta (l >= p).
 // Term rows i run over the Pc points of this call's chunk; results go to point i0 + i of an
 // output with P_out points per instance.  Blocks b0 + blockIdx.x = j * Pc + i.
 // Fixed-order reduction (deterministic): thread t sums m = t, t + 256, ...; then a tree.
 __global__ void __launch_bounds__(256)
-k_combine(const double* __restrict__ W, const double* __restrict__ zz, const double* __restrict__ g,
+k_combine(const double* __restrict__ W, const double* __restrict__ Wg, const double* __restrict__ zz, const double* __restrict__ g,
           int32_t M, int32_t p, const int64_t* __restrict__ inst_orbit, const double* __restrict__ deltas,
           int64_t Pc, int64_t P_out, int64_t i0, int64_t b0, double* __restrict__ energy,
           double* __restrict__ dgamma, double* __restrict__ dbeta) {
@@ -111,7 +111,7 @@ k_combine(const double* __restrict__ W, const double* __restrict__ zz, const dou
     const int64_t m0 = inst_orbit[j], m1 = inst_orbit[j + 1];
     double acc = 0.0;
     for (int64_t m = m0 + threadIdx.x; m < m1; m += 256) {
-        acc += (y == 0) ? W[m] * (1.0 - src[m]) * 0.5 : -0.5 * W[m] * src[m];
+        acc += (y == 0) ? W[m] * (1.0 - src[m]) * 0.5 : -0.5 * Wg[m] * src[m];
     }
     sh[threadIdx.x] = acc;
     __syncthreads();
@@ -183,7 +183,7 @@ hipError_t launch_scale_gamma_terms(double* g, int64_t P, int32_t p, int32_t M, 
 
 int64_t combine_chunk(uint32_t ny) { return static_cast<int64_t>(UINT32_MAX) / (256 * static_cast<int64_t>(ny)); }
 
-hipError_t launch_combine(const double* W, const double* zz, const double* g, int32_t M, int32_t p,
+hipError_t launch_combine(const double* W, const double* Wg, const double* zz, const double* g, int32_t M, int32_t p,
                           const int64_t* inst_orbit, const double* deltas, int32_t n_inst, int64_t Pc,
                           int64_t P_out, int64_t i0, double* energy, double* dgamma, double* dbeta, hipStream_t st) {
     const unsigned ny = (g != nullptr) ? static_cast<unsigned>(1 + 2 * p) : 1u;
@@ -192,7 +192,7 @@ hipError_t launch_combine(const double* W, const double* zz, const double* g, in
     const int64_t nb = static_cast<int64_t>(n_inst) * Pc;
     for (int64_t b0 = 0; b0 < nb; b0 += CH) {
         const unsigned nx = static_cast<unsigned>(nb - b0 < CH ? nb - b0 : CH);
-        hipLaunchKernelGGL(k_combine, dim3(nx, ny), dim3(256), 0, st, W, zz, g, M, p, inst_orbit, deltas, Pc, P_out,
+        hipLaunchKernelGGL(k_combine, dim3(nx, ny), dim3(256), 0, st, W, Wg, zz, g, M, p, inst_orbit, deltas, Pc, P_out,
                            i0, b0, energy, dgamma, dbeta);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

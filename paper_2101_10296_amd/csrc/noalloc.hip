@@ -110,7 +110,7 @@ qaoa_status run_energy_grad_noalloc(qaoa_plan_s* P, int64_t n_points, const doub
             // rows i0 .. i0 + pc - 1 of each instance's block of n_points angles
             D1Args da{P->d_d1, P->d_d1w, M, gamma + i0, beta + i0, n_points, P->d_inst_delta, pc, M, zz, g, 1.0};
             NCHECK(launch_depth1_terms(da, 0, pc * M, true, stream));
-            NCHECK(launch_combine(P->d_W, zz, g, M, p, P->d_inst_orbit, P->d_inst_delta, ni, pc, n_points, i0, energy,
+            NCHECK(launch_combine(P->d_W, P->d_W, zz, g, M, p, P->d_inst_orbit, P->d_inst_delta, ni, pc, n_points, i0, energy,
                                   dgamma, dbeta, stream));
             continue;
         }
@@ -127,13 +127,18 @@ qaoa_status run_energy_grad_noalloc(qaoa_plan_s* P, int64_t n_points, const doub
         const EvalArgs ea{static_cast<int32_t>(pc), p, M, R, phase, mix, gamma + static_cast<size_t>(i0) * p,
                           static_cast<int32_t>(n_points), hp.realw ? 1 : 0, zz, g};
         for (const auto& grp : P->in_groups)
-            if (P->opt.tune != 1)   // a tuned plan holds these cones in lds_groups too
+            if (P->opt.tune != 1 && !(grp.wh && whole_used(P, false)))   // a tuned plan holds these cones in lds_groups too
                 NCHECK(launch_inner_group(P, grp, true, 0, pc, gamma + static_cast<size_t>(i0) * p,
                                           beta + static_cast<size_t>(i0) * p, n_points, zz, g, nullptr, 0, stream));
-        for (const auto& grp : P->lds_groups)
-            NCHECK(launch_fused(grp.K, true, 0, P->d_cones + grp.first, 0, grp.count * pc, P->d_cut, grp.rowcap,
-                                ea, stream));   // default layout: no tuning runs here
-        NCHECK(launch_combine(P->d_W, zz, g, M, p, P->d_inst_orbit, P->d_inst_delta, ni, pc, n_points, i0, energy,
+        const bool wh = whole_used(P, false);
+        for (const auto& grp : P->lds_groups)   // default layout: no tuning runs here
+            NCHECK(launch_fused(grp.K, true, 0, P->d_cones + grp.first, (wh ? grp.n_wh : grp.n_skip) * pc, grp.count * pc, P->d_cut,
+                                grp.rowcap, ea, stream));
+        for (const auto& grp : P->wh_groups)
+            if (wh)
+                NCHECK(launch_whole_group(P, grp, true, pc, gamma + static_cast<size_t>(i0) * p,
+                                          beta + static_cast<size_t>(i0) * p, n_points, zz, g, stream));
+        NCHECK(launch_combine(P->d_W, wh ? P->d_Wg : P->d_W, zz, g, M, p, P->d_inst_orbit, P->d_inst_delta, ni, pc, n_points, i0, energy,
                               dgamma, dbeta, stream));
     }
 #undef NCHECK

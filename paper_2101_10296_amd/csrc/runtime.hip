@@ -241,6 +241,97 @@ std::mutex g_stage_mu;
 void* g_stage = nullptr;
 size_t g_stage_cap = 0;
 
+// Groups of at least WH_MEMBERS cones with the same qubits (whole.hpp).
+struct WholeHost {
+    std::vector<char> member;    // per orbit; empty: none
+    std::vector<GroupWh> groups;
+    std::vector<MemWh> mem;
+    std::vector<int64_t> rep;    // representative orbit of each group
+    std::vector<double> Wg;
+    int64_t obs = 0;             // floats of the observable tables
+};
+
+void build_whole(qaoa_plan_s* P, WholeHost& w) {
+    const HostPlan& hp = P->hp;
+    P->wh_groups.clear();
+    if (hp.p < 2 || P->opt.tune != 0) return;   // layouts of the cones on their own are asked for
+    // cones of one size whose node ids agree in a commutative hash, then exactly
+    struct Key {
+        int32_t k;
+        uint64_t h;
+        int64_t m;
+    };
+    std::vector<Key> keys;
+    for (size_t m = 0; m < hp.cones.size(); ++m) {
+        const Cone& c = hp.cones[m];
+        if (c.k < WH_KMIN || c.k > WH_KMAX) continue;
+        uint64_t h = 0;
+        for (int32_t x : c.nodes) {
+            uint64_t z = static_cast<uint64_t>(x) * 0x9E3779B97F4A7C15ull + 0x632BE59BD9B4E019ull;
+            z ^= z >> 29;
+            h += z * 0xBF58476D1CE4E5B9ull;
+        }
+        keys.push_back({c.k, h, static_cast<int64_t>(m)});
+    }
+    std::sort(keys.begin(), keys.end(), [](const Key& a, const Key& b) {
+        return std::tie(a.k, a.h, a.m) < std::tie(b.k, b.h, b.m);
+    });
+    auto nodes = [&](int64_t m) {
+        std::vector<int32_t> v = hp.cones[static_cast<size_t>(m)].nodes;
+        std::sort(v.begin(), v.end());
+        return v;
+    };
+    for (size_t i = 0, j; i < keys.size(); i = j) {
+        for (j = i + 1; j < keys.size() && keys[j].k == keys[i].k && keys[j].h == keys[i].h; ++j) {}
+        if (j - i < WH_MEMBERS) continue;
+        const int64_t rep = keys[i].m;
+        const Cone& c = hp.cones[static_cast<size_t>(rep)];
+        const std::vector<int32_t> want = nodes(rep);
+        GroupWh g{};
+        g.inst = c.inst;
+        g.rep = static_cast<int32_t>(rep);
+        g.mem_off = static_cast<int32_t>(w.mem.size());
+        for (size_t q = i; q < j; ++q) {
+            if (nodes(keys[q].m) != want) continue;   // a hash collision: stays on its own
+            const Cone& x = hp.cones[static_cast<size_t>(keys[q].m)];
+            MemWh e{};
+            e.orbit = static_cast<int32_t>(keys[q].m);
+            e.u = static_cast<int32_t>(std::find(c.nodes.begin(), c.nodes.end(), x.nodes[0]) - c.nodes.begin());
+            e.v = static_cast<int32_t>(std::find(c.nodes.begin(), c.nodes.end(), x.nodes[1]) - c.nodes.begin());
+            e.W = hp.W[static_cast<size_t>(keys[q].m)];
+            w.mem.push_back(e);
+        }
+        g.n_mem = static_cast<int32_t>(w.mem.size()) - g.mem_off;
+        const int32_t range = hp.realw ? 1 : c.cut_max - c.cut_min + 1;
+        if (g.n_mem < WH_MEMBERS || !whole_fits(c.k, hp.p, range, hp.realw)) {
+            w.mem.resize(static_cast<size_t>(g.mem_off));
+            continue;
+        }
+        g.cut_row = hp.realw ? 0 : c.cut_min - hp.cut_min;
+        g.cut_range = range;
+        g.mid = static_cast<float>(0.5 * (range - 1));
+        g.c0 = static_cast<float>(0.5 * (c.cf_min + c.cf_max));
+        g.v_off = w.obs;
+        w.obs += int64_t{1} << (c.k - 1);
+        if (P->wh_groups.empty() || P->wh_groups.back().K != c.k)
+            P->wh_groups.push_back({c.k, static_cast<int64_t>(w.groups.size()), 0, 0, 1});
+        auto& cls = P->wh_groups.back();
+        cls.count += 1;
+        cls.members += g.n_mem;
+        cls.rowcap = std::max(cls.rowcap, range);
+        w.rep.push_back(rep);
+        w.groups.push_back(g);
+    }
+    if (w.groups.empty()) return;
+    w.member.assign(hp.cones.size(), 0);
+    w.Wg = hp.W;
+    for (const MemWh& e : w.mem) {
+        w.member[static_cast<size_t>(e.orbit)] = 1;
+        w.Wg[static_cast<size_t>(e.orbit)] = 0.0;
+    }
+    for (int64_t r : w.rep) w.Wg[static_cast<size_t>(r)] = 1.0;
+}
+
 // Descriptors of the cones evaluated on their inner qubits (inner.hpp).
 struct InnerHost {
     std::vector<ConeIn> cones;
@@ -250,7 +341,7 @@ struct InnerHost {
 };
 
 // Fills P->in_groups and the descriptors for the orbits in ord; their edges are appended to ea, eb, ew.
-void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, std::vector<int32_t>& ea, std::vector<int32_t>& eb,
+void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<char>& member, std::vector<int32_t>& ea, std::vector<int32_t>& eb,
                  std::vector<int32_t>& ew, InnerHost& in) {
     const HostPlan& hp = P->hp;
     const int32_t p = hp.p;
@@ -259,10 +350,13 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, std::vector<int32_t>
     P->in_inst.clear();
     P->in_max_k = 0;
     if (ord.empty()) return;
+    auto is_wh = [&](int64_t m) { return !member.empty() && member[static_cast<size_t>(m)] != 0; };
     auto kin_of = [&](int64_t m) { return static_cast<int>(hp.cones[m].nd[p - 1]); };
     std::stable_sort(ord.begin(), ord.end(), [&](int64_t a, int64_t b) {
         const int x = kin_of(a), y = kin_of(b);
-        return x != y ? x < y : by_k && hp.cones[a].k < hp.cones[b].k;
+        if (x != y) return x < y;
+        if (by_k && hp.cones[a].k != hp.cones[b].k) return hp.cones[a].k < hp.cones[b].k;
+        return is_wh(a) < is_wh(b);
     });
     in.cones.reserve(ord.size());
     std::vector<uint32_t> rounds;
@@ -330,10 +424,12 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, std::vector<int32_t>
         eb.insert(eb.end(), c.eb.begin(), c.eb.end());
         ew.insert(ew.end(), c.ew.begin(), c.ew.end());
         const int kk = by_k ? c.k : 0;
-        if (P->in_groups.empty() || P->in_groups.back().kin != kin || P->in_groups.back().K != kk) {
+        if (P->in_groups.empty() || P->in_groups.back().kin != kin || P->in_groups.back().K != kk ||
+            P->in_groups.back().wh != is_wh(m)) {
             qaoa_plan_s::InGroup g{};
             g.kin = kin;
             g.K = kk;
+            g.wh = is_wh(m);
             g.first = static_cast<int64_t>(in.cones.size());
             P->in_groups.push_back(g);
         }
@@ -403,17 +499,23 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     const bool d1 = depth1_closed(P);
     P->max_k = 0;
     for (const Cone& c : hp.cones) P->max_k = std::max(P->max_k, c.k);
+    WholeHost wh;
+    build_whole(P, wh);
+    auto member = [&](int64_t m) { return !wh.member.empty() && wh.member[static_cast<size_t>(m)]; };
     std::vector<int64_t> d1ord, inord;
     for (int64_t m = 0; m < Mall; ++m) {
         const bool small = hp.cones[m].k <= P->opt.k_lds_max;
         const bool inner = !d1 && inner_cone(P, hp.cones[m]);
         if (inner) inord.push_back(m);
-        if (inner && !(P->opt.tune == 1 && small)) continue;   // the tuner compares both kernels
+        // (the tuner compares both kernels; a group's state reads its representative's cut table)
+        if (inner && !(P->opt.tune == 1 && small) && !member(m)) continue;
         (d1 ? d1ord : small ? ord : hord).push_back(m);
     }
     std::stable_sort(ord.begin(), ord.end(), [&](int64_t a, int64_t b) {
         const Cone &x = hp.cones[a], &y = hp.cones[b];
-        return x.k != y.k ? x.k < y.k : inner_cone(P, x) > inner_cone(P, y);
+        if (x.k != y.k) return x.k < y.k;
+        if (member(a) != member(b)) return member(a) != 0;
+        return inner_cone(P, x) > inner_cone(P, y);
     });
     std::stable_sort(hord.begin(), hord.end(), [&](int64_t a, int64_t b) { return hp.cones[a].k < hp.cones[b].k; });
     const int64_t M = static_cast<int64_t>(ord.size());
@@ -451,13 +553,18 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
         ea.insert(ea.end(), c.ea.begin(), c.ea.end());
         eb.insert(eb.end(), c.eb.begin(), c.eb.end());
         ew.insert(ew.end(), c.ew.begin(), c.ew.end());
-        if (P->lds_groups.empty() || P->lds_groups.back().K != c.k) P->lds_groups.push_back({c.k, s, 0, 1, 0});
+        if (P->lds_groups.empty() || P->lds_groups.back().K != c.k) P->lds_groups.push_back({c.k, s, 0, 1});
         P->lds_groups.back().count += 1;
-        if (inner_cone(P, c)) P->lds_groups.back().n_in += 1;
+        if (member(ord[s])) {
+            P->lds_groups.back().n_wh += 1;
+            if (inner_cone(P, c)) P->lds_groups.back().n_skip += 1;
+        } else if (inner_cone(P, c)) {
+            P->lds_groups.back().n_in += 1;
+        }
         P->lds_groups.back().rowcap = std::max(P->lds_groups.back().rowcap, d.cut_range);
     }
     InnerHost in;
-    build_inner(P, inord, ea, eb, ew, in);
+    build_inner(P, inord, wh.member, ea, eb, ew, in);
     // depth-1 cones: the couplings of the edge's two ends
     std::vector<ConeD1> dc(d1ord.size());
     std::vector<double2> dw;
@@ -486,7 +593,7 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
         }
         const int kk = d1_by_k ? c.k : 0;
         if (P->d1_groups.empty() || P->d1_groups.back().K != kk)
-            P->d1_groups.push_back({kk, static_cast<int64_t>(s), 0, 1, 0});
+            P->d1_groups.push_back({kk, static_cast<int64_t>(s), 0, 1});
         P->d1_groups.back().count += 1;
     }
     // HBM-class descriptors; their edges follow the workgroup-resident ones
@@ -557,11 +664,20 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     const size_t o_ewd = hp.realw ? place(std::max<size_t>(ewd.size(), 1) * sizeof(double)) : 0;
     const size_t o_dc = d1 ? place(dc.size() * sizeof(ConeD1)) : 0;
     const size_t o_dw = d1 ? place(dw.size() * sizeof(double2)) : 0;
+    for (size_t i = 0; i < wh.groups.size(); ++i) {   // their cut tables
+        const auto at = std::find_if(cd.begin(), cd.end(), [&](const ConeDev& d) { return d.orbit == wh.rep[i]; });
+        wh.groups[i].cut_off = at->cut_off;
+    }
+    const bool has_wh = !wh.groups.empty();
+    const size_t o_wg = has_wh ? place(wh.groups.size() * sizeof(GroupWh)) : 0;
+    const size_t o_wm = has_wh ? place(wh.mem.size() * sizeof(MemWh)) : 0;
+    const size_t o_ww = has_wh ? place(wh.Wg.size() * sizeof(double)) : 0;
     const bool has_in = !in.cones.empty();
     const size_t o_in = has_in ? place(in.cones.size() * sizeof(ConeIn)) : 0;
     const size_t o_ig = has_in ? place(in.grp.size() * sizeof(GrpIn)) : 0;
     const size_t o_is = has_in ? place(in.seg.size() * sizeof(int32_t)) : 0;
     const size_t copied = arena;
+    const size_t o_wo = has_wh ? place(static_cast<size_t>(wh.obs) * sizeof(float)) : 0;
     const size_t o_it = has_in ? place(static_cast<size_t>(in.tab_units) * 16) : 0;
     const size_t o_cut = place(static_cast<size_t>(std::max<int64_t>(cut_bytes, 16)));
     const size_t o_tt = place(static_cast<size_t>(std::max<int64_t>(tt_bytes, 16)));
@@ -591,6 +707,11 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
         put(o_id, hp.inst_delta.data(), hp.inst_delta.size() * sizeof(double));
         put(o_ones, ones.data(), ones.size() * sizeof(double));
         if (hp.realw) put(o_ewd, ewd.data(), ewd.size() * sizeof(double));
+        if (has_wh) {
+            put(o_wg, wh.groups.data(), wh.groups.size() * sizeof(GroupWh));
+            put(o_wm, wh.mem.data(), wh.mem.size() * sizeof(MemWh));
+            put(o_ww, wh.Wg.data(), wh.Wg.size() * sizeof(double));
+        }
         if (has_in) {
             put(o_in, in.cones.data(), in.cones.size() * sizeof(ConeIn));
             put(o_ig, in.grp.data(), in.grp.size() * sizeof(GrpIn));
@@ -620,6 +741,10 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     P->d_ewd = hp.realw ? reinterpret_cast<double*>(base + o_ewd) : nullptr;
     P->d_d1 = d1 ? reinterpret_cast<ConeD1*>(base + o_dc) : nullptr;
     P->d_d1w = d1 ? reinterpret_cast<double2*>(base + o_dw) : nullptr;
+    P->d_wh = has_wh ? reinterpret_cast<GroupWh*>(base + o_wg) : nullptr;
+    P->d_whmem = has_wh ? reinterpret_cast<MemWh*>(base + o_wm) : nullptr;
+    P->d_Wg = has_wh ? reinterpret_cast<double*>(base + o_ww) : nullptr;
+    P->d_whobs = has_wh ? reinterpret_cast<float*>(base + o_wo) : nullptr;
     P->d_in = has_in ? reinterpret_cast<ConeIn*>(base + o_in) : nullptr;
     P->d_ingrp = has_in ? reinterpret_cast<GrpIn*>(base + o_ig) : nullptr;
     P->d_inseg = has_in ? reinterpret_cast<int32_t*>(base + o_is) : nullptr;
@@ -641,6 +766,8 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
             QCHECK(launch_inner_tables(P->d_in, static_cast<int64_t>(in.cones.size()), P->d_ea, P->d_eb, P->d_ew, hp.p,
                                        hp.cut_min, P->d_intab, nullptr));
     }
+    for (const auto& g : P->wh_groups)
+        QCHECK(launch_whole_obs(P->d_wh + g.first, g.count, P->d_whmem, g.K, P->d_whobs, nullptr));
     QCHECK(hipDeviceSynchronize());
     P->resident_bytes = arena;
     P->device = dev;
@@ -675,6 +802,38 @@ struct GroupTimer {
 };
 
 }  // namespace
+
+hipError_t launch_whole_group(const qaoa_plan_s* P, const qaoa_plan_s::WhGroup& grp, bool grad, int64_t n_points,
+                              const double* gamma, const double* beta, int64_t gamma_P, double* zz, double* g,
+                              hipStream_t st) {
+    const HostPlan& hp = P->hp;
+    WhArgs a{};
+    a.groups = P->d_wh + grp.first;
+    a.mem = P->d_whmem;
+    a.cut = P->d_cut;
+    a.obs = P->d_whobs;
+    a.gamma = gamma;
+    a.beta = beta;
+    a.gamma_P = gamma_P;
+    a.deltas = P->d_inst_delta;
+    a.p = hp.p;
+    a.cut_min = hp.cut_min;
+    a.rowcap = grp.rowcap;
+    a.realw = hp.realw ? 1 : 0;
+    a.P = static_cast<int32_t>(n_points);
+    a.M = static_cast<int32_t>(hp.cones.size());
+    a.n_items = grp.count * n_points;
+    a.zz = zz;
+    a.g = g;
+    if (!P->opt.one_cone_at_a_time) return launch_whole(grp.K, grad, a, st);
+    for (int64_t n = a.n_items, it = 0; it < n; ++it) {
+        a.item0 = it;
+        a.n_items = it + 1;
+        const hipError_t e = launch_whole(grp.K, grad, a, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 
 hipError_t launch_inner_group(const qaoa_plan_s* P, const qaoa_plan_s::InGroup& grp, bool grad, int upw_log2,
                               int64_t n_points, const double* gamma, const double* beta, int64_t gamma_P, double* zz,
@@ -779,7 +938,7 @@ bool budget_refuses(const qaoa_plan_s* P, int k, bool grad, std::string& msg) {
 
 // Orbit-weighted sums of the term rows zz, g (null: energies only) into E and dE.
 qaoa_status finish_sums(qaoa_plan_s* P, int64_t n_points, double* zz, double* g, double* energy, double* dgamma,
-                        double* dbeta, bool terms_read, GroupTimer& tm, hipStream_t stream, std::string& msg) {
+                        double* dbeta, bool terms_read, const double* Wg, GroupTimer& tm, hipStream_t stream, std::string& msg) {
     const HostPlan& hp = P->hp;
     const int32_t p = hp.p, M = static_cast<int32_t>(hp.cones.size());
     const double* deltas = P->d_inst_delta;
@@ -794,11 +953,14 @@ qaoa_status finish_sums(qaoa_plan_s* P, int64_t n_points, double* zz, double* g,
             deltas = P->d_ones;
         }
     }
-    QCHECK(launch_combine(P->d_W, zz, g, M, p, P->d_inst_orbit, deltas, hp.n_inst, n_points, n_points, 0, energy,
+    QCHECK(launch_combine(P->d_W, Wg, zz, g, M, p, P->d_inst_orbit, deltas, hp.n_inst, n_points, n_points, 0, energy,
                           dgamma, dbeta, stream));
     QCHECK(tm.end());
     return QAOA_OK;
 }
+
+// First cone of a size class that the kernel for whole cones runs.
+int64_t lds_from(const qaoa_plan_s::Group& grp, bool use_wh) { return use_wh ? grp.n_wh : grp.n_skip; }
 
 // The launches of a depth-1 call.  One instance of few orbits: terms and weighted sums in one
 // launch (2048 orbits are eight per thread of the point's workgroup; larger plans fill the chip
@@ -839,7 +1001,7 @@ qaoa_status enqueue_depth1(qaoa_plan_s* P, int64_t n_points, const double* gamma
         }
         QCHECK(tm.end());
     }
-    return finish_sums(P, n_points, a.zz, a.g, energy, dgamma, dbeta, term_grad != nullptr, tm, stream, msg);
+    return finish_sums(P, n_points, a.zz, a.g, energy, dgamma, dbeta, term_grad != nullptr, P->d_W, tm, stream, msg);
 }
 
 // The launch sequence of one energy call.  With fixed_batches the HBM groups reuse the
@@ -859,7 +1021,10 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
     const int32_t R = hp.cut_max - hp.cut_min + 1;
     if (P->in_max_k > P->opt.k_lds_max && budget_refuses(P, P->in_max_k, grad, msg)) return QAOA_ENOMEM;
     const size_t npl = static_cast<size_t>(hp.n_inst) * n_points * p;   // (instance, point, layer) rows
-    const bool tables = P->in_groups.empty() || !P->lds_groups.empty() || !P->hbm_groups.empty();
+    const bool use_wh = whole_used(P, grad && term_grad);
+    // phase and mixer tables, for the kernels that read them
+    bool tables = !P->hbm_groups.empty();
+    for (const auto& grp : P->lds_groups) tables = tables || lds_from(grp, use_wh) < grp.count;
     if (tables) {
         if ((st = grow(P->d_phase, P->cap_phase, npl * R, msg)) != QAOA_OK) return st;
         if ((st = grow(P->d_mix, P->cap_mix, npl, msg)) != QAOA_OK) return st;
@@ -907,6 +1072,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         return launch_inner_group(P, grp, grad, j, n_points, gamma, beta, n_points, zz, g, P->d_part, P->cap_part, stream);
     };
     for (const auto& grp : P->in_groups) {
+        if (grp.wh && use_wh) continue;
         if (P->opt.tune == 1 && grp.K <= P->opt.k_lds_max) continue;   // with the other cones of its size, below
         int j = inner_upw(grp);
         if (P->opt.tune == 1) {
@@ -921,10 +1087,16 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         QCHECK(run_inner(grp, j));
         QCHECK(tm.end());
     }
+    if (use_wh)
+        for (const auto& grp : P->wh_groups) {
+            QCHECK(tm.begin(grp.K, grp.members * n_points));
+            QCHECK(launch_whole_group(P, grp, grad, n_points, gamma, beta, n_points, zz, g, stream));
+            QCHECK(tm.end());
+        }
     // all cones of one size in layout v; the default (0) takes the cones with a shell on their inner
     // qubits (tune = 1 plans hold them in both forms)
     auto run_size = [&](const qaoa_plan_s::Group& grp, int v, int64_t n) {
-        int64_t done = 0;
+        int64_t done = lds_from(grp, use_wh) * n_points;
         if (v == 0 && grp.n_in > 0) {
             for (const auto& ig : P->in_groups)
                 if (ig.K == grp.K) {
@@ -939,6 +1111,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
     for (const auto& grp : P->lds_groups) {
         const ConeDev* cones = P->d_cones + grp.first;
         const int64_t items = grp.count * n_points;
+        if (lds_from(grp, use_wh) >= grp.count) continue;
         int variant = P->opt.tune >= 2 ? P->opt.tune - 2 : 0;   // tune 2, 3, 4: a fixed layout variant
         if (P->opt.tune == 1 && !P->opt.one_cone_at_a_time) {
             const TuneKey key{arch, 0, grp.K, p, grad ? 1 : 0, hp.realw ? 1 : 0};
@@ -955,9 +1128,9 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
                 }
             }
         }
-        QCHECK(tm.begin(grp.K, items));
+        QCHECK(tm.begin(grp.K, items - lds_from(grp, use_wh) * n_points));
         if (P->opt.one_cone_at_a_time) {
-            for (int64_t it = 0; it < items; ++it)
+            for (int64_t it = lds_from(grp, use_wh) * n_points; it < items; ++it)
                 QCHECK(launch_fused(grp.K, grad, 0, cones, it, it + 1, P->d_cut, grp.rowcap, ea, stream));
         } else {
             QCHECK(run_size(grp, variant, items));
@@ -1115,7 +1288,8 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         }
         QCHECK(tm.end());
     }
-    return finish_sums(P, n_points, zz, g, energy, dgamma, dbeta, grad && term_grad, tm, stream, msg);
+    return finish_sums(P, n_points, zz, g, energy, dgamma, dbeta, grad && term_grad, use_wh ? P->d_Wg : P->d_W, tm, stream,
+                       msg);
 }
 
 void drop_graph(qaoa_plan_s* P) {

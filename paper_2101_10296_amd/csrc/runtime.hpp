@@ -12,6 +12,7 @@
 #include "inner.hpp"
 #include "plan.hpp"
 #include "qaoa.h"
+#include "whole.hpp"
 
 struct qaoa_plan_s {
     qaoa::HostPlan hp;
@@ -27,7 +28,10 @@ struct qaoa_plan_s {
         int64_t first;  // first slot in d_cones
         int64_t count;  // cones in this group
         int32_t rowcap; // largest cut range of the group's cones
-        int64_t n_in = 0;   // tune = 1: the first n_in cones are also in in_groups (their default)
+        int64_t n_skip = 0; // the first n_skip cones are members of wh_groups with a form of their own in
+                            // in_groups: here for their group's cut table only
+        int64_t n_wh = 0;   // the first n_wh cones are members of wh_groups
+        int64_t n_in = 0;   // tune = 1 (no wh_groups): the first n_in cones are also in in_groups
     };
     std::vector<Group> lds_groups;      // workgroup-resident cones, grouped by K
     qaoa::ConeDev* d_cones = nullptr;
@@ -41,6 +45,7 @@ struct qaoa_plan_s {
     // launches are timed per cone size: profile, tune = 1)
     struct InGroup {
         int kin, K;         // inner qubits; cone qubits, or 0
+        bool wh;            // cones that are members of wh_groups
         int64_t first, count;
         int32_t chunks;     // units of work per cone
         int32_t n_seg;      // instances
@@ -56,6 +61,19 @@ struct qaoa_plan_s {
     int32_t* d_inseg = nullptr;
     size_t cap_part = 0;
     double* d_part = nullptr;           // partial sums of cones in several units
+    // groups of cones with the same qubits, by k: they share one state wherever the caller does not
+    // ask for every term's own gradient (such calls take the members' own forms)
+    struct WhGroup {
+        int K;
+        int64_t first, count;   // groups
+        int64_t members;        // their cones
+        int32_t rowcap;
+    };
+    std::vector<WhGroup> wh_groups;
+    qaoa::GroupWh* d_wh = nullptr;
+    qaoa::MemWh* d_whmem = nullptr;
+    float* d_whobs = nullptr;
+    double* d_Wg = nullptr;             // orbit weights of the gradient sums: 1 at a group's column
     // HBM-resident cones, grouped by k
     struct HGroup {
         int K;
@@ -138,6 +156,14 @@ inline bool inner_cone(const qaoa_plan_s* P, const Cone& c) {
     return p >= 2 && p <= IN_PMAX && !P->hp.realw && P->opt.tune < 2 && c.nd[p - 1] <= IN_KMAX && c.nd[p - 1] < c.k;
 }
 
+// Whether a call may evaluate the groups of wh_groups on their shared state.
+inline bool whole_used(const qaoa_plan_s* P, bool terms_read) {
+    return !P->wh_groups.empty() && !terms_read;
+}
+hipError_t launch_whole_group(const qaoa_plan_s* P, const qaoa_plan_s::WhGroup& grp, bool grad, int64_t n_points,
+                              const double* gamma, const double* beta, int64_t gamma_P, double* zz, double* g,
+                              hipStream_t st);
+
 // One class of them (grp) for a call's points: terms into zz, g; part: room for the partial sums of
 // at least one point (null where every cone is one unit).
 hipError_t launch_inner_group(const qaoa_plan_s* P, const qaoa_plan_s::InGroup& grp, bool grad, int upw_log2,
@@ -195,8 +221,8 @@ hipError_t launch_scale_gamma_terms(double* g, int64_t P, int32_t p, int32_t M, 
 // points per k_combine launch with ny blocks per point (grid below 2^32 work-items)
 int64_t combine_chunk(uint32_t ny);
 // energy [n_inst][P_out], dgamma / dbeta [n_inst][P_out][p]: points i0 .. i0 + Pc - 1 of
-// each instance from the term rows zz [Pc][M], g [Pc][2p][M]
-hipError_t launch_combine(const double* W, const double* zz, const double* g, int32_t M, int32_t p,
+// each instance from the term rows zz [Pc][M] (weights W) and g [Pc][2p][M] (weights Wg)
+hipError_t launch_combine(const double* W, const double* Wg, const double* zz, const double* g, int32_t M, int32_t p,
                           const int64_t* inst_orbit, const double* deltas, int32_t n_inst, int64_t Pc,
                           int64_t P_out, int64_t i0, double* energy, double* dgamma, double* dbeta, hipStream_t st);
 

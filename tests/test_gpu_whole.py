@@ -1,0 +1,103 @@
+"""Cones with the same qubits on one shared state (GPU): against the FP64 oracle and the members' own forms.
+
+Tolerances of test_gpu_parity.py.  Every cone size of the kernel (5-14 qubits: items of part of a
+wave, one wave and several waves, 8 and 16 amplitudes per thread), even and odd depths, integer
+and Gaussian couplings; groups next to cones on their own, reduced plans (orbit weights), batches,
+and rows too long for LDS (the members' own kernels).
+"""
+import numpy as np
+import pytest
+
+import workloads as W
+from test_gpu_parity import ZZ_TOL, check_energy, dev
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def Q():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2101_10296_amd as Q
+    return Q
+
+
+def _ring_with_chords(n, seed):
+    i = np.arange(n)
+    e = {(min(a, b), max(a, b)) for a, b in zip(i, (i + 1) % n)}
+    rng = np.random.default_rng(seed)
+    while len(e) < n + 3:
+        a, b = sorted(rng.choice(n, 2, replace=False))
+        e.add((int(a), int(b)))
+    return W.Graph("chords%d" % n, n, np.array(sorted(e), np.int32))
+
+
+@pytest.mark.parametrize("weights", ["unit", "int", "gauss"])
+@pytest.mark.parametrize("n", range(5, 15))
+def test_every_cone_size(Q, n, weights):
+    g = _ring_with_chords(n, n)
+    rng = np.random.default_rng(n)
+    w = {"unit": None, "int": rng.choice([-1.0, 2.0, 3.0], g.m), "gauss": rng.normal(size=g.m)}[weights]
+    for p in (n // 2, n // 2 + 1) if n < 12 else (4 + n % 2,):
+        ga, be = W.draw_angles(3, p, 800 + n + p)
+        pl, E, zz = check_energy(Q, g, p, ga, be, reduce=False, weights=w, grad=True)
+        # per-term gradients take the members' own forms: their weighted sum is the same gradient
+        E1, dg, db = pl.energy_grad(dev(ga), dev(be))
+        E2, dg2, db2, zz2, tg = pl.energy_grad_terms(dev(ga), dev(be))
+        Wt = float(g.m if w is None else np.abs(w).sum())
+        assert np.abs(zz2.cpu().numpy() - zz).max() <= ZZ_TOL
+        scale = max(dg2.abs().max().item(), db2.abs().max().item(), 1e-3 * Wt)
+        assert max((dg - dg2).abs().max().item(), (db - db2).abs().max().item()) <= 1e-4 * scale
+
+
+def test_reduced_weights_and_two_components(Q):
+    # two copies of one graph, orbits over both: the group's weights count both; and a plan where some
+    # cones are the whole graph and others are not
+    for n, m in ((7, 3), (12, 2)):
+        base = W.circulant(n, (1, 2)) if n > 7 else W.complete(n)
+        e = np.concatenate([base.edges, base.edges + n]).astype(np.int32)
+        swap = np.concatenate([np.arange(n, 2 * n), np.arange(n)])
+        gens = np.concatenate([np.concatenate([base.gens(), base.gens() + n], 1), swap[None]]).astype(np.int32)
+        g = W.Graph("pair%d" % n, 2 * n, e, None, gens)
+        ga, be = W.draw_angles(2, m + 2, 840 + n)
+        check_energy(Q, g, m + 2, ga, be, grad=True)
+        check_energy(Q, g, m + 2, ga, be, reduce=False, grad=True)
+    g = W.random_regular(14, 3, 6)
+    for p in (2, 3, 4):
+        ga, be = W.draw_angles(3, p, 850 + p)
+        check_energy(Q, g, p, ga, be, reduce=False, grad=True)
+
+
+def test_batches_items_and_replay(Q):
+    gs = [W.random_regular(n, 3, n) for n in (6, 8, 10, 12, 14)]
+    p = 5
+    rng = np.random.default_rng(1)
+    ga, be = rng.uniform(0, np.pi, (len(gs), 7, p)), rng.uniform(0, np.pi / 2, (len(gs), 7, p))
+    bp = Q.Plan.batch([(g.n, g.edges) for g in gs], p)
+    out = bp.energy_grad(dev(ga), dev(be))
+    for j, g in enumerate(gs):
+        one = Q.Plan(g.n, g.edges, p=p)
+        own = one.energy_grad(dev(ga[j]), dev(be[j]))
+        few = one.energy_grad(dev(ga[j][2:3]), dev(be[j][2:3]))
+        for x, y, z in zip(out, own, few):
+            assert (x[j] - y).abs().max().item() <= 1e-11 * g.m and torch.equal(y[2:3], z)
+    gt, bt = dev(ga[3]), dev(be[3])
+    rep = Q.Plan(gs[3].n, gs[3].edges, p=p, graph=True)
+    buf = (torch.empty(7, dtype=torch.float64, device="cuda"), torch.empty_like(gt), torch.empty_like(bt))
+    for it in range(4):
+        gt.copy_(dev(ga[3] + 0.2 * it))
+        rep.energy_grad(gt, bt, out=buf)
+        torch.cuda.synchronize()
+        want = Q.Plan(gs[3].n, gs[3].edges, p=p).energy_grad(gt, bt)
+        torch.cuda.synchronize()
+        assert all(torch.equal(x, y) for x, y in zip(buf, want)), it
+    assert rep.info()["graph_replays"] == 3
+
+
+def test_rows_beyond_lds(Q):
+    # weights of 9 and p = 120: the phase rows of the shared state would not fit; own kernels, same values
+    g = _ring_with_chords(8, 3)
+    w = np.full(g.m, 9.0)
+    ga, be = W.draw_angles(1, 120, 870)
+    check_energy(Q, g, 120, ga, be, reduce=False, weights=w, grad=False)
