@@ -22,6 +22,8 @@ struct ConeIn {
     int32_t tab_off;           // first table in units of 16 bytes
     int32_t kin;               // inner qubits
     int32_t edge_off, n_edges; // cone edges (pairs of qubits, the first the smaller)
+    int32_t cfg_off;           // listed configurations, or -1: all nc, decoded where they are used
+    uint32_t n_cfg;            // listed entries: a whole number of rounds (weight 0 beyond the last)
     int32_t pad0_;
     double shell_norm;         // 2^-(shell qubits)
     int16_t base[IN_PMAX + 1]; // [l], l = 2..p: phase row index of table value 0 of layer l; [1] = [2]
@@ -36,8 +38,17 @@ struct GrpIn {
     int32_t h[8];     // coupling to inner qubit 2 + i
 };
 
+// One listed configuration: the shifts that the shell makes (see GrpIn) and its weight.
+struct alignas(16) CfgList {
+    int16_t h[8];
+    int32_t c0;
+    int32_t pad_;
+    double w;
+};
+
 struct InArgs {
     const ConeIn* cones;       // cones of this class (inner qubits), from the launch's first
+    const CfgList* cfg;
     const GrpIn* grp;
     const uint8_t* tab;
     const double* gamma;       // [inst][gamma_P][p]

@@ -10,9 +10,11 @@
 //   C_1(x; y) = C_in(x) + c(y) + sum_a x_a h_a(y).
 // Shell qubits with equal couplings count by how many are 1 (t of m, weight binom(m, t)), and
 // flipping every qubit of the cone pairs y with its complement: half of the configurations
-// are run at twice the weight.  On a 3-regular graph at p = 2 (2 + 4 inner qubits, 8 shell
-// qubits in 4 groups) that is 41 states of 2^6 amplitudes with 6 mixed qubits in place of
-// 2^13 stored amplitudes with 14.
+// are run at twice the weight.  Where the cone has symmetries of its own (twins, u and v swapped),
+// the configurations are listed up to them on the host (list_configurations in runtime.hip).  On a
+// 3-regular graph at p = 2 (2 + 4 inner qubits, 8 shell
+// qubits in 4 groups) that is 12 states of 2^6 amplitudes (41 before the cone's own
+// symmetries) with 6 mixed qubits in place of 2^13 stored amplitudes with 14.
 //
 // Layout: A = 2^min(4, kin) amplitudes per lane (register bits: qubits 0..3), qubits 4..7 on
 // the lanes of a 16-lane row, 8 and 9 on lane bits 4 and 5; a wave runs 64 >> (kin - 4)
@@ -31,10 +33,10 @@
 //
 // Bound: vector instruction issue (about 70 instructions per amplitude with the gradient at
 // kin = 6, p = 2).  Measured on one MI355X against the statevector kernels that these cones ran
-// on: random 3-regular n = 10000, p = 2, 256 points, energy and gradient 215.6 -> 20.2 ms;
-// energies of a random 4-regular n = 60, p = 2 (cones of up to 26 qubits, as passes over device
-// memory before) 5.27 -> 0.11 ms; the 18-qubit cone of a torus at 32 points, with the gradient,
-// 93 -> 44 us.
+// on: random 3-regular n = 10000, p = 2, 256 points, energy and gradient 215.6 -> 20.2 ms, 7.5 ms
+// with listed configurations; energies of a random 4-regular n = 60, p = 2 (cones of up to 26
+// qubits, as passes over device memory before) 5.27 -> 0.11 -> 0.094 ms; the 18-qubit cone of a
+// torus at 32 points, with the gradient, 93 -> 44 -> 24 us.
 #pragma once
 
 #include "fused_impl.hpp"
@@ -86,6 +88,40 @@ __device__ __forceinline__ double wave_sum(double x) {
     step(std::integral_constant<int, 1>{});
     step(std::integral_constant<int, 2>{});
     step(std::integral_constant<int, 3>{});
+    x += __shfl_xor(x, 16, 64);
+    x += __shfl_xor(x, 32, 64);
+    return x;
+}
+
+// Sums of eight values over the wave at once: value i lands in the lanes whose bits 0, 1 and 3 spell
+// i.  Each of the first three steps halves the values a lane holds, where eight separate
+// sums would take six steps each.
+__device__ __forceinline__ double wave_sum8(double (&v)[8], int lane) {
+    auto step = [&](auto I, int n, bool up) {   // keep the upper half of the values where up
+        constexpr int i = decltype(I)::value;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (j >= n) continue;
+            const double mine = up ? v[j + n] : v[j], other = up ? v[j] : v[j + n];
+            const long long b = __double_as_longlong(other);
+            float lo = __int_as_float(static_cast<int>(b)), hi = __int_as_float(static_cast<int>(b >> 32));
+            if constexpr (i < 2) {
+                lo = row_flip<i>(lo);
+                hi = row_flip<i>(hi);
+            } else {   // lane xor 8: rotate the row by 8
+                lo = dppf<0x128>(lo);
+                hi = dppf<0x128>(hi);
+            }
+            const long long o = (static_cast<long long>(__float_as_int(hi)) << 32) |
+                                static_cast<long long>(static_cast<unsigned>(__float_as_int(lo)));
+            v[j] = mine + __longlong_as_double(o);
+        }
+    };
+    step(std::integral_constant<int, 2>{}, 4, (lane & 8) != 0);
+    step(std::integral_constant<int, 1>{}, 2, (lane & 2) != 0);
+    step(std::integral_constant<int, 0>{}, 1, (lane & 1) != 0);
+    double x = v[0];
+    x += __shfl_xor(x, 4, 64);
     x += __shfl_xor(x, 16, 64);
     x += __shfl_xor(x, 32, 64);
     return x;
@@ -272,6 +308,38 @@ __device__ const double kBinom[30 * 30] = {
 #include "binom30.inc"
 };
 
+// The configurations c .. of the next rounds, one per lane, for the lane groups that run them: mixed
+// radix digits (how many of each group's qubits are 1); the first half, at twice the weight.
+template <int KIN>
+__device__ __forceinline__ void in_decode(CfgIn* cfg, const GrpIn* __restrict__ grp, int n_grp, uint32_t nc, uint32_t c,
+                                          int lane) {
+    const uint32_t nch = (nc + 1) >> 1;
+    uint32_t rem = c < nch ? c : nch - 1;
+    CfgIn e;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) e.h[i] = 0;
+    e.c0 = 0;
+    e.pad_ = 0;
+    e.w = c < nch ? (((nc & 1u) && c == nch - 1) ? 1.0 : 2.0) : 0.0;
+    for (int q = 0; q < n_grp; ++q) {
+        const GrpIn& G = grp[q];
+        const uint32_t d = static_cast<uint32_t>(G.m) + 1u;
+        const uint32_t nx = rem / d;
+        const int t = static_cast<int>(rem - nx * d);
+        rem = nx;
+        const int s = G.m - 2 * t;
+        e.c0 += t * G.wsum;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (i + 2 < KIN) e.h[i] += s * G.h[i];
+        e.w *= G.m < 4 ? ((t == 0 || t == G.m) ? 1.0 : static_cast<double>(G.m)) : kBinom[G.m * 30 + t];
+    }
+    __builtin_amdgcn_wave_barrier();
+    cfg[lane] = e;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // PP = 2: depth 2, sums in registers; PP = 0: depth 3..IN_PMAX, sums per lane in LDS.
 template <int KIN, bool GRAD, int PP>
 __global__ void __launch_bounds__(256, GRAD && PP == 0 ? 2 : 4) k_inner(InArgs a) {
@@ -367,7 +435,9 @@ __global__ void __launch_bounds__(256, GRAD && PP == 0 ? 2 : 4) k_inner(InArgs a
         const int u = __builtin_amdgcn_readfirstlane(uu);
         const int slot = u / a.chunks, ch = u - slot * a.chunks;
         const ConeIn& cd = a.cones[slot];
-        const uint32_t nc = cd.nc, nch = (nc + 1) >> 1;
+        const uint32_t nc = cd.nc;
+        const bool listed = cd.cfg_off >= 0;
+        const uint32_t nch = listed ? cd.n_cfg : (nc + 1) >> 1;
         const uint32_t rounds = (nch + Z::CPW - 1) / Z::CPW;
         const uint32_t rp = (rounds + a.chunks - 1) / a.chunks;
         const uint32_t r0 = ch * rp, r1 = min(rounds, r0 + rp);
@@ -391,35 +461,18 @@ __global__ void __launch_bounds__(256, GRAD && PP == 0 ? 2 : 4) k_inner(InArgs a
             for (int i = 0; i < 2 * p + 1; ++i) lsum[i * 64 + lane] = 0.0;
 
         for (uint32_t r = r0; r < r1; ++r) {
-            const uint32_t sub = (r - r0) % (64 / Z::CPW);
-            if (sub == 0) {   // the next 64 configurations, one per lane
-                const uint32_t c = r * Z::CPW + lane;
-                uint32_t rem = c < nch ? c : nch - 1;
-                CfgIn e;
+            CfgIn e;
+            if (listed) {
+                const CfgList c = a.cfg[cd.cfg_off + r * Z::CPW + (lane >> Z::LB)];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) e.h[i] = 0;
-                e.c0 = 0;
-                e.pad_ = 0;
-                e.w = c < nch ? (((nc & 1u) && c == nch - 1) ? 1.0 : 2.0) : 0.0;
-                for (int q = 0; q < cd.n_grp; ++q) {
-                    const GrpIn& G = a.grp[cd.grp_off + q];
-                    const uint32_t d = static_cast<uint32_t>(G.m) + 1u;
-                    const uint32_t nx = rem / d;
-                    const int t = static_cast<int>(rem - nx * d);
-                    rem = nx;
-                    const int s = G.m - 2 * t;
-                    e.c0 += t * G.wsum;
-#pragma unroll
-                    for (int i = 0; i < 8; ++i)
-                        if (i + 2 < KIN) e.h[i] += s * G.h[i];
-                    e.w *= G.m < 4 ? ((t == 0 || t == G.m) ? 1.0 : static_cast<double>(G.m)) : kBinom[G.m * 30 + t];
-                }
-                __builtin_amdgcn_wave_barrier();
-                cfg[lane] = e;
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                __builtin_amdgcn_wave_barrier();
+                for (int i = 0; i < 8; ++i) e.h[i] = c.h[i];
+                e.c0 = c.c0;
+                e.w = c.w;
+            } else {
+                const uint32_t sub = (r - r0) % (64 / Z::CPW);
+                if (sub == 0) in_decode<KIN>(cfg, a.grp + cd.grp_off, cd.n_grp, nc, r * Z::CPW + lane, lane);
+                e = cfg[sub * Z::CPW + (lane >> Z::LB)];
             }
-            const CfgIn& e = cfg[sub * Z::CPW + (lane >> Z::LB)];
             const double wt = e.w;
             // row index of table value 0 in layer 1 for this lane, and the shifts of qubits 2, 3
             int lb = e.c0 + cd.base[1];
@@ -568,25 +621,33 @@ __global__ void __launch_bounds__(256, GRAD && PP == 0 ? 2 : 4) k_inner(InArgs a
         const int nv = GRAD ? 2 * p + 1 : 1;
         double* out = a.chunks > 1 ? a.part + (static_cast<size_t>(point - a.point0) * a.units + u) * nv : nullptr;
         auto put = [&](int code, double x) {   // 0: <ZZ>; j >= 1: gradient entry j - 1
-            if (lane != 0) return;
             if (out) out[code] = x;
             else if (code == 0) a.zz[static_cast<size_t>(point) * a.M + cd.orbit] = x;
             else a.g[(static_cast<size_t>(point) * 2 * p + (code - 1)) * a.M + cd.orbit] = x;
         };
         const double C = s_cs[0], S = s_cs[1];
-        const double zs = wave_sum(Zs), is = wave_sum(Is), ds = wave_sum(Ds);
-        put(0, nz * (zs + 2.0 * C * S * is + S * S * ds));
+        // linear in the last layer's three sums, so combined per lane before the wave's sum
+        double v[8] = {nz * (Zs + 2.0 * C * S * Is + S * S * Ds), 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
         if constexpr (GRAD) {
-            put(2 * p, nz * 2.0 * (2.0 * (C * C - S * S) * is + 2.0 * C * S * ds));
-            put(p, 2.0 * nz * wave_sum(Gp));
-            put(p + 1, 2.0 * nz * wave_sum(B1));
-            put(1, 2.0 * n1 * wave_sum(G1));
+            v[1] = nz * 2.0 * (2.0 * (C * C - S * S) * Is + 2.0 * C * S * Ds);
+            v[2] = 2.0 * nz * Gp;
+            v[3] = 2.0 * nz * B1;
+            v[4] = 2.0 * n1 * G1;
+            const double x = wave_sum8(v, lane);
+            const int i = (lane & 8 ? 4 : 0) | (lane & 2) | (lane & 1);   // the value that this lane holds
+            if ((lane & ~11) == 0 && i < 5) put(i == 0 ? 0 : i == 1 ? 2 * p : i == 2 ? p : i == 3 ? p + 1 : 1, x);
             if constexpr (PP == 0) {
                 for (int ly = 2; ly < p; ++ly) {
-                    put(ly, 2.0 * n0 * wave_sum(lsum[ly * 64 + lane]));
-                    put(p + ly, 2.0 * n0 * wave_sum(lsum[(p + ly) * 64 + lane]));
+                    const double ga = wave_sum(lsum[ly * 64 + lane]), be = wave_sum(lsum[(p + ly) * 64 + lane]);
+                    if (lane == 0) {
+                        put(ly, 2.0 * n0 * ga);
+                        put(p + ly, 2.0 * n0 * be);
+                    }
                 }
             }
+        } else {
+            const double x = wave_sum(v[0]);
+            if (lane == 0) put(0, x);
         }
     }
 }

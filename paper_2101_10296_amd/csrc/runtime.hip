@@ -10,6 +10,7 @@
 #include <mutex>
 #include <numeric>
 #include <tuple>
+#include <unordered_map>
 
 namespace qaoa {
 namespace {
@@ -337,8 +338,250 @@ struct InnerHost {
     std::vector<ConeIn> cones;
     std::vector<GrpIn> grp;
     std::vector<int32_t> seg;
+    std::vector<CfgList> cfg;
     int64_t tab_units = 0;   // table bytes / 16
 };
+
+// Inner couplings and shell groups of a cone: cones that agree in them share a list of
+// configurations.
+struct InnerSig {
+    int kin = 0;
+    uint8_t level[IN_KMAX] = {};             // distance class of each inner qubit
+    int16_t w[IN_KMAX][IN_KMAX] = {};        // couplings between inner qubits
+    std::vector<GrpIn> grp;                  // sorted by their couplings
+    uint32_t nc = 0;
+    int32_t cfg_off = -1;
+    uint32_t n_cfg = 0;
+
+    bool same(const InnerSig& o) const {
+        return kin == o.kin && grp.size() == o.grp.size() && std::memcmp(level, o.level, sizeof(level)) == 0 &&
+               std::memcmp(w, o.w, sizeof(w)) == 0 &&
+               (grp.empty() || std::memcmp(grp.data(), o.grp.data(), grp.size() * sizeof(GrpIn)) == 0);
+    }
+    uint64_t hash() const {
+        uint64_t h = static_cast<uint64_t>(kin);
+        auto mix = [&](uint64_t x) { h = (h ^ x) * 0x9E3779B97F4A7C15ull; h ^= h >> 32; };
+        for (int i = 0; i < kin; ++i)
+            for (int j = i + 1; j < kin; ++j)
+                if (w[i][j]) mix(static_cast<uint64_t>(static_cast<uint16_t>(w[i][j])) << 16 | static_cast<uint64_t>(i * 16 + j));
+        for (const GrpIn& g : grp) {
+            mix(static_cast<uint64_t>(g.m));
+            for (int i = 0; i < 8; ++i)
+                if (g.h[i]) mix(static_cast<uint64_t>(static_cast<uint32_t>(g.h[i])) << 8 | static_cast<uint64_t>(i));
+        }
+        return h;
+    }
+};
+
+// The configurations of a shell up to the symmetries that keep a term: automorphisms of the inner
+// qubits with their couplings, distance classes and shell groups (which may swap u and v), and the
+// flip of all qubits.  Configurations are tuples of digits, one per group (how many of its
+// qubits are 1).  Twins (qubits of one class that a transposition swaps, each with groups of its
+// own) are kept sorted by their digits; the remaining automorphisms, found by backtracking up to
+// orders of twins, and the flip map sorted tuples to each other, and the smallest image of each
+// orbit is listed with the weight of all its members.  What is listed depends on the signature
+// alone, so a term is the same in every plan.  Up to 1024 configurations are always listed
+// (under 0.3 ms of host time); beyond, where at least 16 symmetries shorten the list enough to
+// pay for it.  Returns false where there is no list.
+bool list_configurations(const InnerSig& g, uint32_t cpw, std::vector<CfgList>& out) {
+    const int kin = g.kin, ng = static_cast<int>(g.grp.size());
+    if (ng > 16) return false;
+    for (const GrpIn& q : g.grp)
+        if (q.m > 15) return false;
+    // groups private to one inner qubit, and twin classes
+    std::vector<int> owner(ng, -1);
+    std::vector<std::vector<int>> priv(kin);
+    for (int q = 0; q < ng; ++q) {
+        int n = 0, at = -1;
+        for (int i = 0; i < 8; ++i)
+            if (g.grp[q].h[i]) { ++n; at = i + 2; }
+        if (n == 1) {
+            owner[q] = at;
+            priv[at].push_back(q);
+        }
+    }
+    auto swapped = [](int x, int a, int b) { return x == a ? b : x == b ? a : x; };
+    auto find_group = [&](const GrpIn& want) {
+        for (int q = 0; q < ng; ++q)
+            if (std::memcmp(&g.grp[q], &want, sizeof(GrpIn)) == 0) return q;
+        return -1;
+    };
+    // image of group q under the qubit map sigma, or -1
+    auto image = [&](int q, const int* sigma) {
+        GrpIn x = g.grp[q];
+        for (int i = 0; i < 8; ++i) x.h[i] = 0;
+        for (int i = 0; i < 8; ++i)
+            if (g.grp[q].h[i]) x.h[sigma[i + 2] - 2] = g.grp[q].h[i];
+        return find_group(x);
+    };
+    std::vector<int> cls(kin, -1);
+    std::vector<std::vector<int>> classes;
+    for (int a = 2; a < kin; ++a) {
+        if (cls[a] >= 0) continue;
+        std::vector<int> c{a};
+        for (int b = a + 1; b < kin; ++b) {
+            if (cls[b] >= 0 || g.level[a] != g.level[b] || priv[a].size() != priv[b].size() || priv[a].empty()) continue;
+            bool ok = true;
+            for (int i = 0; i < kin && ok; ++i)
+                if (i != a && i != b) ok = g.w[a][i] == g.w[b][i];
+            int sg[IN_KMAX];
+            for (int i = 0; i < kin; ++i) sg[i] = swapped(i, a, b);
+            for (int q = 0; q < ng && ok; ++q) {
+                const int im = image(q, sg);
+                ok = im >= 0 && (owner[q] == a || owner[q] == b || im == q);
+            }
+            if (ok) c.push_back(b);
+        }
+        if (c.size() > 1) {
+            for (int x : c) cls[x] = static_cast<int>(classes.size());
+            classes.push_back(c);
+        }
+    }
+    // a member's private groups in the order of the first member's
+    for (auto& c : classes)
+        for (int x : c) {
+            std::vector<int> m;
+            for (int q : priv[c[0]]) {
+                int sg[IN_KMAX];
+                for (int i = 0; i < kin; ++i) sg[i] = swapped(i, c[0], x);
+                m.push_back(x == c[0] ? q : image(q, sg));
+            }
+            priv[x] = m;
+        }
+    // automorphisms up to orders of twins: permutations of the groups
+    std::vector<std::vector<int>> H;
+    int sigma[IN_KMAX], used = 0;
+    bool many = false;
+    auto search = [&](auto&& self, int i) -> void {
+        if (many) return;
+        if (i == kin) {
+            std::vector<int> pi(ng);
+            for (int q = 0; q < ng; ++q)
+                if ((pi[q] = image(q, sigma)) < 0) return;
+            H.push_back(pi);
+            many = H.size() > 32;
+            return;
+        }
+        for (int j = 0; j < kin; ++j) {
+            if ((used >> j) & 1 || (i < 2) != (j < 2) || g.level[i] != g.level[j]) continue;
+            if ((cls[i] < 0) != (cls[j] < 0) || priv[i].size() != priv[j].size()) continue;
+            bool ok = true;
+            for (int t = 0; t < i && ok; ++t) {
+                ok = g.w[i][t] == g.w[j][sigma[t]];
+                // twins go to twins in increasing order
+                if (cls[i] >= 0 && cls[t] == cls[i]) ok = ok && cls[sigma[t]] == cls[j] && sigma[t] < j;
+            }
+            if (!ok) continue;
+            sigma[i] = j;
+            used |= 1 << j;
+            self(self, i + 1);
+            used &= ~(1 << j);
+        }
+    };
+    search(search, 0);
+    if (many || H.empty()) return false;
+    // the symmetries' order: what listing saves at most, beside a factor 2 of the flip
+    double order = static_cast<double>(H.size());
+    for (const auto& c : classes)
+        for (size_t i = 2; i <= c.size(); ++i) order *= static_cast<double>(i);
+    if (g.nc > 1024 && order < 16.0) return false;
+    // a tuple as one word, group q's digit in nibble q
+    auto digit = [](uint64_t t, int q) { return static_cast<int>((t >> (4 * q)) & 15u); };
+    auto block = [&](uint64_t t, int x) {   // a twin's digits
+        uint64_t b = 0;
+        for (int q : priv[x]) b = b << 4 | static_cast<uint64_t>(digit(t, q));
+        return b;
+    };
+    auto set_block = [&](uint64_t& t, int x, uint64_t b) {
+        for (size_t i = priv[x].size(); i-- > 0; b >>= 4) {
+            const int q = priv[x][i];
+            t = (t & ~(uint64_t{15} << (4 * q))) | (b & 15u) << (4 * q);
+        }
+    };
+    auto sort_twins = [&](uint64_t t) {
+        uint64_t b[IN_KMAX];
+        for (const auto& c : classes) {
+            for (size_t i = 0; i < c.size(); ++i) {
+                const uint64_t x = block(t, c[i]);
+                size_t j = i;
+                for (; j > 0 && b[j - 1] > x; --j) b[j] = b[j - 1];
+                b[j] = x;
+            }
+            for (size_t i = 0; i < c.size(); ++i) set_block(t, c[i], b[i]);
+        }
+        return t;
+    };
+    uint64_t full = 0;   // every qubit 1: the flip of t is full - t, nibble by nibble
+    for (int q = 0; q < ng; ++q) full |= static_cast<uint64_t>(g.grp[q].m) << (4 * q);
+    uint64_t t = 0;
+    std::vector<uint64_t> seen;
+    double total = 0.0;
+    int bits = 0;
+    for (const GrpIn& q : g.grp) bits += q.m;
+    const size_t first = out.size();
+    for (uint32_t n = 0; n < g.nc; ++n) {
+        if (n)
+            for (int q = 0;; ++q) {
+                if (digit(t, q) < g.grp[q].m) {
+                    t += uint64_t{1} << (4 * q);
+                    break;
+                }
+                t &= ~(uint64_t{15} << (4 * q));
+            }
+        bool sorted = true;
+        for (const auto& c : classes)
+            for (size_t i = 1; i < c.size() && sorted; ++i) sorted = block(t, c[i - 1]) <= block(t, c[i]);
+        if (!sorted) continue;
+        seen.clear();
+        bool least = true;
+        for (const auto& pi : H) {
+            uint64_t im = 0;
+            for (int q = 0; q < ng; ++q) im |= static_cast<uint64_t>(digit(t, q)) << (4 * pi[q]);
+            uint64_t fl = full;   // groups map to groups of their size
+            fl = sort_twins(fl - im);
+            im = sort_twins(im);
+            if (im < t || fl < t) {
+                least = false;
+                break;
+            }
+            if (std::find(seen.begin(), seen.end(), im) == seen.end()) seen.push_back(im);
+            if (std::find(seen.begin(), seen.end(), fl) == seen.end()) seen.push_back(fl);
+        }
+        if (!least) continue;
+        double w = static_cast<double>(seen.size());
+        for (const auto& c : classes) {   // arrangements of the members' blocks
+            double a = 1.0;
+            int run = 1;
+            for (size_t i = 1; i < c.size(); ++i) {
+                run = block(t, c[i]) == block(t, c[i - 1]) ? run + 1 : 1;
+                a *= static_cast<double>(i + 1) / run;
+            }
+            w *= a;
+        }
+        CfgList e{};
+        for (int q = 0; q < ng; ++q) {
+            const GrpIn& G = g.grp[q];
+            double b = 1.0;
+            for (int i = 0; i < digit(t, q); ++i) b = b * (G.m - i) / (i + 1);
+            w *= b;
+            e.c0 += digit(t, q) * G.wsum;
+            for (int i = 0; i < 8; ++i) e.h[i] = static_cast<int16_t>(e.h[i] + (G.m - 2 * digit(t, q)) * G.h[i]);
+        }
+        e.w = std::round(w);
+        total += e.w;
+        out.push_back(e);
+    }
+    if (total != std::ldexp(1.0, bits)) {
+        out.resize(first);
+        return false;
+    }
+    while ((out.size() - first) % cpw) {   // whole rounds
+        CfgList e = out[first];
+        e.w = 0.0;
+        out.push_back(e);
+    }
+    return true;
+}
 
 // Fills P->in_groups and the descriptors for the orbits in ord; their edges are appended to ea, eb, ew.
 void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<char>& member, std::vector<int32_t>& ea, std::vector<int32_t>& eb,
@@ -359,6 +602,10 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         return is_wh(a) < is_wh(b);
     });
     in.cones.reserve(ord.size());
+    std::vector<InnerSig> sigs;
+    std::unordered_map<uint64_t, int32_t> sig_at;
+    std::vector<int32_t> sig_of(ord.size(), -1);
+    InnerSig sig;
     std::vector<uint32_t> rounds;
     rounds.reserve(ord.size());
     for (int64_t m : ord) {
@@ -416,6 +663,27 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         d.n_grp = static_cast<int32_t>(in.grp.size()) - d.grp_off;
         for (int g = 0; g < d.n_grp; ++g) nc *= static_cast<uint32_t>(in.grp[d.grp_off + g].m) + 1u;
         d.nc = nc;   // at most 2^27: the shell holds at most 27 qubits
+        d.cfg_off = -1;
+        if (nc > 2 && nc <= 4096) {
+            sig.kin = kin;
+            sig.nc = nc;
+            std::memset(sig.w, 0, sizeof(sig.w));
+            std::memset(sig.level, 0, sizeof(sig.level));
+            for (int q = 0, l = 0; q < kin; ++q) {
+                while (q >= c.nd[l]) ++l;
+                sig.level[q] = static_cast<uint8_t>(l);
+            }
+            for (size_t e = 0; e < c.ea.size(); ++e)
+                if (c.eb[e] < kin) sig.w[c.ea[e]][c.eb[e]] = sig.w[c.eb[e]][c.ea[e]] = static_cast<int16_t>(c.ew[e]);
+            sig.grp.assign(in.grp.begin() + d.grp_off, in.grp.end());
+            std::sort(sig.grp.begin(), sig.grp.end(),
+                      [](const GrpIn& a, const GrpIn& b) { return std::memcmp(a.h, b.h, sizeof(a.h)) < 0; });
+            const auto at = sig_at.emplace(sig.hash(), static_cast<int32_t>(sigs.size()));
+            if (at.second) sigs.push_back(sig);
+            if (sigs[static_cast<size_t>(at.first->second)].same(sig)) {   // else a hash collision: no list
+                sig_of[in.cones.size()] = at.first->second;
+            }
+        }
         d.tab_off = static_cast<int32_t>(in.tab_units);
         in.tab_units += (p - 1) * std::max<int64_t>(1, (int64_t{1} << kin) / 16);
         const uint32_t cpw = 64u >> std::max(0, kin - 4);
@@ -438,13 +706,39 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         P->in_inst.push_back(c.inst);
         in.cones.push_back(d);
     }
+    // lists of configurations up to symmetry
+    {
+        for (InnerSig& q : sigs) {
+            const size_t off = in.cfg.size();
+            if (!list_configurations(q, 64u >> std::max(0, q.kin - 4), in.cfg)) continue;
+            q.cfg_off = static_cast<int32_t>(off);
+            q.n_cfg = static_cast<uint32_t>(in.cfg.size() - off);
+        }
+        for (size_t i = 0; i < in.cones.size(); ++i) {
+            if (sig_of[i] < 0 || sigs[static_cast<size_t>(sig_of[i])].cfg_off < 0) continue;
+            ConeIn& d = in.cones[i];
+            d.cfg_off = sigs[static_cast<size_t>(sig_of[i])].cfg_off;
+            d.n_cfg = sigs[static_cast<size_t>(sig_of[i])].n_cfg;
+            rounds[i] = d.n_cfg / (64u >> std::max(0, d.kin - 4));
+        }
+    }
     for (auto& g : P->in_groups) {
-        // Units of IN_ROUNDS rounds where a cone has more than 16 (cones of up to 14 qubits never do),
-        // fewer where the class alone keeps 2^15 of them.  Set by the plan alone, so that a term's
-        // sum is the same whatever the number of points.
+        // Units of work: a cone's rounds in parts of 8, of 2 where that leaves a point with fewer than
+        // 1024 units (latency: the 18-qubit cone of a torus at 32 points 42 -> 24 us), at most 2^15
+        // of them.  Set by the plan alone, so that a term's sum is the same whatever the number of
+        // points.  Classes of cones that fit the allocation-free call (k_lds_max qubits: 16
+        // rounds at most) stay whole, as parts need room for their sums.
         uint32_t most = 1;
-        for (int64_t i = g.first; i < g.first + g.count; ++i) most = std::max(most, rounds[static_cast<size_t>(i)]);
-        int64_t ch = most > 16 ? (most + IN_ROUNDS - 1) / IN_ROUNDS : 1;
+        int32_t max_k = 0;
+        for (int64_t i = g.first; i < g.first + g.count; ++i) {
+            most = std::max(most, rounds[static_cast<size_t>(i)]);
+            max_k = std::max(max_k, hp.cones[static_cast<size_t>(in.cones[static_cast<size_t>(i)].orbit)].k);
+        }
+        int64_t ch = 1;
+        if (max_k > P->opt.k_lds_max) {
+            ch = (most + IN_ROUNDS - 1) / IN_ROUNDS;
+            if (ch * g.count < 1024) ch = std::min<int64_t>((most + 1) / 2, std::max<int64_t>(ch, 1024 / g.count));
+        }
         ch = std::min(ch, std::max<int64_t>(1, (int64_t{1} << 15) / g.count));
         g.chunks = static_cast<int32_t>(ch);
         std::vector<int32_t> unit{0}, inst;   // segments of one instance
@@ -675,6 +969,7 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     const bool has_in = !in.cones.empty();
     const size_t o_in = has_in ? place(in.cones.size() * sizeof(ConeIn)) : 0;
     const size_t o_ig = has_in ? place(in.grp.size() * sizeof(GrpIn)) : 0;
+    const size_t o_ic = has_in ? place(in.cfg.size() * sizeof(CfgList)) : 0;
     const size_t o_is = has_in ? place(in.seg.size() * sizeof(int32_t)) : 0;
     const size_t copied = arena;
     const size_t o_wo = has_wh ? place(static_cast<size_t>(wh.obs) * sizeof(float)) : 0;
@@ -715,6 +1010,7 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
         if (has_in) {
             put(o_in, in.cones.data(), in.cones.size() * sizeof(ConeIn));
             put(o_ig, in.grp.data(), in.grp.size() * sizeof(GrpIn));
+            put(o_ic, in.cfg.data(), in.cfg.size() * sizeof(CfgList));
             put(o_is, in.seg.data(), in.seg.size() * sizeof(int32_t));
         }
         if (d1) {
@@ -747,6 +1043,7 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     P->d_whobs = has_wh ? reinterpret_cast<float*>(base + o_wo) : nullptr;
     P->d_in = has_in ? reinterpret_cast<ConeIn*>(base + o_in) : nullptr;
     P->d_ingrp = has_in ? reinterpret_cast<GrpIn*>(base + o_ig) : nullptr;
+    P->d_incfg = has_in ? reinterpret_cast<CfgList*>(base + o_ic) : nullptr;
     P->d_inseg = has_in ? reinterpret_cast<int32_t*>(base + o_is) : nullptr;
     P->d_intab = has_in ? base + o_it : nullptr;
     P->d_cut = base + o_cut;
@@ -841,6 +1138,7 @@ hipError_t launch_inner_group(const qaoa_plan_s* P, const qaoa_plan_s::InGroup& 
     const HostPlan& hp = P->hp;
     InArgs a{};
     a.cones = P->d_in + grp.first;
+    a.cfg = P->d_incfg;
     a.grp = P->d_ingrp;
     a.tab = P->d_intab;
     a.gamma = gamma;
@@ -1065,7 +1363,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
     auto inner_upw = [&](const qaoa_plan_s::InGroup& grp) {
         const int64_t units = grp.count * grp.chunks * n_points;
         int j = 0;
-        while (j < 2 && (units >> (j + 1)) >= (int64_t{1} << 15)) ++j;
+        while (j < 3 && (units >> (j + 1)) >= (int64_t{1} << 15)) ++j;
         return j;
     };
     auto run_inner = [&](const qaoa_plan_s::InGroup& grp, int j) {
@@ -1404,6 +1702,7 @@ void release_device(qaoa_plan_s* P) {
     P->d_in = nullptr;
     P->d_ingrp = nullptr;
     P->d_intab = nullptr;
+    P->d_incfg = nullptr;
     P->d_inseg = nullptr;
     P->cap_phi = P->cap_lam = P->cap_gpart = 0;
     P->d_phase = nullptr;

@@ -57,6 +57,7 @@ struct qaoa_plan_s {
     int32_t in_max_k = 0;               // largest of them (cone qubits)
     qaoa::ConeIn* d_in = nullptr;
     qaoa::GrpIn* d_ingrp = nullptr;
+    qaoa::CfgList* d_incfg = nullptr;
     uint8_t* d_intab = nullptr;
     int32_t* d_inseg = nullptr;
     size_t cap_part = 0;
