@@ -1,0 +1,413 @@
+// Host planning of cones evaluated on their inner qubits (inner_plan.hpp).
+#include "inner_plan.hpp"
+
+#include <algorithm>
+#include <atomic>
+#include <cmath>
+#include <cstring>
+#include <new>
+#include <system_error>
+#include <thread>
+
+namespace qaoa {
+
+bool ShellPlanner::Shape::same(const Shape& o) const {
+    return kin == o.kin && grp.size() == o.grp.size() && std::memcmp(level, o.level, sizeof(level)) == 0 &&
+           std::memcmp(w, o.w, sizeof(w)) == 0 &&
+           (grp.empty() || std::memcmp(grp.data(), o.grp.data(), grp.size() * sizeof(ShellGroup)) == 0);
+}
+
+namespace {
+uint64_t mix64(uint64_t x) {
+    x *= 0x9E3779B97F4A7C15ull;
+    x ^= x >> 29;
+    return x * 0xBF58476D1CE4E5B9ull;
+}
+}  // namespace
+
+// The configurations of a shell up to the symmetries that keep a term: automorphisms of the inner
+// qubits with their couplings, distance classes and shell groups (which may swap u and v), and the
+// flip of all qubits.  Configurations are tuples of digits, one per group (how many of its
+// qubits are 1).  Twins (qubits of one class that a transposition swaps, each with groups of its
+// own) are kept sorted by their digits; the remaining automorphisms, found by backtracking up to
+// orders of twins, and the flip map sorted tuples to each other, and the smallest image of each
+// orbit is listed with the weight of all its members.  What is listed depends on the shape
+// alone, so a term is the same in every plan.  Up to 1024 configurations are always listed
+// (under 0.3 ms of host time); beyond, up to 16384 where at least 16 symmetries shorten the list
+// enough to pay for it.  No list: cfg stays empty.
+void ShellPlanner::Shape::enumerate() {
+    const int ng = static_cast<int>(grp.size());
+    std::vector<ShellCfg>& out = cfg;
+    if (nc <= 2 || nc > 16384 || ng > 16) return;
+    for (const ShellGroup& q : grp)
+        if (q.m > 15) return;
+    // groups private to one inner qubit, and twin classes
+    std::vector<int> owner(ng, -1);
+    std::vector<std::vector<int>> priv(kin);
+    for (int q = 0; q < ng; ++q) {
+        int n = 0, at = -1;
+        for (int i = 0; i < SH_H; ++i)
+            if (grp[q].h[i]) { ++n; at = i + 2; }
+        if (n == 1) {
+            owner[q] = at;
+            priv[at].push_back(q);
+        }
+    }
+    auto swapped = [](int x, int a, int b) { return x == a ? b : x == b ? a : x; };
+    auto find_group = [&](const ShellGroup& want) {
+        for (int q = 0; q < ng; ++q)
+            if (std::memcmp(&grp[q], &want, sizeof(ShellGroup)) == 0) return q;
+        return -1;
+    };
+    // image of group q under the qubit map sigma, or -1
+    auto image = [&](int q, const int* sigma) {
+        ShellGroup x = grp[q];
+        for (int i = 0; i < SH_H; ++i) x.h[i] = 0;
+        for (int i = 0; i < SH_H; ++i)
+            if (grp[q].h[i]) x.h[sigma[i + 2] - 2] = grp[q].h[i];
+        return find_group(x);
+    };
+    std::vector<int> cls(kin, -1);
+    std::vector<std::vector<int>> classes;
+    for (int a = 2; a < kin; ++a) {
+        if (cls[a] >= 0) continue;
+        std::vector<int> c{a};
+        for (int b = a + 1; b < kin; ++b) {
+            if (cls[b] >= 0 || level[a] != level[b] || priv[a].size() != priv[b].size() || priv[a].empty()) continue;
+            bool ok = true;
+            for (int i = 0; i < kin && ok; ++i)
+                if (i != a && i != b) ok = w[a][i] == w[b][i];
+            int sg[SH_KMAX];
+            for (int i = 0; i < kin; ++i) sg[i] = swapped(i, a, b);
+            for (int q = 0; q < ng && ok; ++q) {
+                const int im = image(q, sg);
+                ok = im >= 0 && (owner[q] == a || owner[q] == b || im == q);
+            }
+            if (ok) c.push_back(b);
+        }
+        if (c.size() > 1) {
+            for (int x : c) cls[x] = static_cast<int>(classes.size());
+            classes.push_back(c);
+        }
+    }
+    // a member's private groups in the order of the first member's
+    for (auto& c : classes)
+        for (int x : c) {
+            std::vector<int> m;
+            for (int q : priv[c[0]]) {
+                int sg[SH_KMAX];
+                for (int i = 0; i < kin; ++i) sg[i] = swapped(i, c[0], x);
+                m.push_back(x == c[0] ? q : image(q, sg));
+            }
+            priv[x] = m;
+        }
+    // automorphisms up to orders of twins: permutations of the groups
+    std::vector<std::vector<int>> H;
+    int sigma[SH_KMAX], used = 0;
+    bool many = false;
+    auto search = [&](auto&& self, int i) -> void {
+        if (many) return;
+        if (i == kin) {
+            std::vector<int> pi(ng);
+            for (int q = 0; q < ng; ++q)
+                if ((pi[q] = image(q, sigma)) < 0) return;
+            H.push_back(pi);
+            many = H.size() > 32;
+            return;
+        }
+        for (int j = 0; j < kin; ++j) {
+            if ((used >> j) & 1 || (i < 2) != (j < 2) || level[i] != level[j]) continue;
+            if ((cls[i] < 0) != (cls[j] < 0) || priv[i].size() != priv[j].size()) continue;
+            bool ok = true;
+            for (int t = 0; t < i && ok; ++t) {
+                ok = w[i][t] == w[j][sigma[t]];
+                // twins go to twins in increasing order
+                if (cls[i] >= 0 && cls[t] == cls[i]) ok = ok && cls[sigma[t]] == cls[j] && sigma[t] < j;
+            }
+            if (!ok) continue;
+            sigma[i] = j;
+            used |= 1 << j;
+            self(self, i + 1);
+            used &= ~(1 << j);
+        }
+    };
+    search(search, 0);
+    if (many || H.empty()) return;
+    // the symmetries' order: what listing saves at most, beside a factor 2 of the flip
+    double order = static_cast<double>(H.size());
+    for (const auto& c : classes)
+        for (size_t i = 2; i <= c.size(); ++i) order *= static_cast<double>(i);
+    if (nc > 1024 && order < 16.0) return;
+    // a tuple as one word, group q's digit in nibble q
+    auto digit = [](uint64_t t, int q) { return static_cast<int>((t >> (4 * q)) & 15u); };
+    auto block = [&](uint64_t t, int x) {   // a twin's digits
+        uint64_t b = 0;
+        for (int q : priv[x]) b = b << 4 | static_cast<uint64_t>(digit(t, q));
+        return b;
+    };
+    auto set_block = [&](uint64_t& t, int x, uint64_t b) {
+        for (size_t i = priv[x].size(); i-- > 0; b >>= 4) {
+            const int q = priv[x][i];
+            t = (t & ~(uint64_t{15} << (4 * q))) | (b & 15u) << (4 * q);
+        }
+    };
+    auto sort_twins = [&](uint64_t t) {
+        uint64_t b[SH_KMAX];
+        for (const auto& c : classes) {
+            for (size_t i = 0; i < c.size(); ++i) {
+                const uint64_t x = block(t, c[i]);
+                size_t j = i;
+                for (; j > 0 && b[j - 1] > x; --j) b[j] = b[j - 1];
+                b[j] = x;
+            }
+            for (size_t i = 0; i < c.size(); ++i) set_block(t, c[i], b[i]);
+        }
+        return t;
+    };
+    uint64_t full = 0;   // every qubit 1: the flip of t is full - t, nibble by nibble
+    for (int q = 0; q < ng; ++q) full |= static_cast<uint64_t>(grp[q].m) << (4 * q);
+    uint64_t t = 0;
+    std::vector<uint64_t> seen;
+    double total = 0.0;
+    int bits = 0;
+    for (const ShellGroup& q : grp) bits += q.m;
+    for (uint32_t i = 0; i < nc; ++i) {
+        if (i)
+            for (int q = 0;; ++q) {
+                if (digit(t, q) < grp[q].m) {
+                    t += uint64_t{1} << (4 * q);
+                    break;
+                }
+                t &= ~(uint64_t{15} << (4 * q));
+            }
+        bool sorted = true;
+        for (const auto& c : classes)
+            for (size_t i = 1; i < c.size() && sorted; ++i) sorted = block(t, c[i - 1]) <= block(t, c[i]);
+        if (!sorted) continue;
+        seen.clear();
+        bool least = true;
+        for (const auto& pi : H) {
+            uint64_t im = 0;
+            for (int q = 0; q < ng; ++q) im |= static_cast<uint64_t>(digit(t, q)) << (4 * pi[q]);
+            uint64_t fl = full;   // groups map to groups of their size
+            fl = sort_twins(fl - im);
+            im = sort_twins(im);
+            if (im < t || fl < t) {
+                least = false;
+                break;
+            }
+            if (std::find(seen.begin(), seen.end(), im) == seen.end()) seen.push_back(im);
+            if (std::find(seen.begin(), seen.end(), fl) == seen.end()) seen.push_back(fl);
+        }
+        if (!least) continue;
+        double n = static_cast<double>(seen.size());
+        for (const auto& c : classes) {   // arrangements of the members' blocks
+            double a = 1.0;
+            int run = 1;
+            for (size_t i = 1; i < c.size(); ++i) {
+                run = block(t, c[i]) == block(t, c[i - 1]) ? run + 1 : 1;
+                a *= static_cast<double>(i + 1) / run;
+            }
+            n *= a;
+        }
+        ShellCfg e{};
+        for (int q = 0; q < ng; ++q) {
+            const ShellGroup& G = grp[q];
+            double b = 1.0;
+            for (int i = 0; i < digit(t, q); ++i) b = b * (G.m - i) / (i + 1);
+            n *= b;
+            e.c0 += digit(t, q) * G.wsum;
+            for (int i = 0; i < SH_H; ++i) e.h[i] = static_cast<int16_t>(e.h[i] + (G.m - 2 * digit(t, q)) * G.h[i]);
+        }
+        e.w = std::round(n);
+        total += e.w;
+        out.push_back(e);
+    }
+    if (total != std::ldexp(1.0, bits)) {
+        out.clear();
+        return;
+    }
+}
+
+int32_t ShellPlanner::find(uint64_t h) {
+    if (2 * (shapes_.size() + 1) > table_.size()) {
+        std::vector<std::pair<uint64_t, int32_t>> old;
+        old.swap(table_);
+        table_.assign(std::max<size_t>(64, 4 * old.size()), {0, -1});
+        for (const auto& e : old)
+            if (e.second >= 0) {
+                size_t i = e.first & (table_.size() - 1);
+                while (table_[i].second >= 0) i = (i + 1) & (table_.size() - 1);
+                table_[i] = e;
+            }
+    }
+    size_t i = h & (table_.size() - 1);
+    for (; table_[i].second >= 0; i = (i + 1) & (table_.size() - 1))
+        if (table_[i].first == h && shapes_[static_cast<size_t>(table_[i].second)].same(s_)) return table_[i].second;
+    table_[i] = {h, static_cast<int32_t>(shapes_.size())};
+    shapes_.push_back(s_);
+    return table_[i].second;
+}
+
+void ShellPlanner::add_one(const Cone& c, ShellCone& out) {
+    const int kin = c.nd[p_ - 1], ns = c.k - kin;
+    const size_t ne = c.ea.size();
+    out.kin = kin;
+    out.edge = static_cast<int64_t>(ea.size());
+    s_.kin = kin;
+    s_.grp.clear();
+    std::memset(s_.level, 0, sizeof(s_.level));
+    std::memset(s_.w, 0, sizeof(s_.w));
+    for (int q = 0, l = 0; q < kin; ++q) {
+        while (q >= c.nd[l]) ++l;
+        s_.level[q] = static_cast<uint8_t>(l);
+    }
+    // order within a distance: by the positions of the neighbours before it, then by degree
+    uint32_t before[SH_KMAX] = {};
+    int32_t deg[32] = {}, pos[32];
+    for (size_t e = 0; e < ne; ++e) {
+        ++deg[c.ea[e]];
+        ++deg[c.eb[e]];
+    }
+    for (int q = 0; q < c.k; ++q) pos[q] = q;
+    for (int lo = 2; lo < kin;) {
+        int hi = lo;
+        while (hi < kin && s_.level[hi] == s_.level[lo]) ++hi;
+        for (size_t e = 0; e < ne; ++e)
+            if (c.eb[e] >= lo && c.eb[e] < hi && c.ea[e] < lo) before[c.eb[e]] |= 1u << (31 - pos[c.ea[e]]);
+        int order[SH_KMAX];
+        for (int q = lo; q < hi; ++q) {   // stable insertion sort
+            int j = q - lo;
+            for (; j > 0; --j) {
+                const int x = order[j - 1];
+                if (before[q] != before[x] ? before[q] < before[x] : deg[q] >= deg[x]) break;
+                order[j] = x;
+            }
+            order[j] = q;
+        }
+        for (int q = lo; q < hi; ++q) pos[order[q - lo]] = q;
+        lo = hi;
+    }
+    int32_t h[32][SH_H];
+    std::memset(h, 0, sizeof(h[0]) * static_cast<size_t>(ns));
+    uint64_t hash = static_cast<uint64_t>(kin);
+    for (size_t e = 0; e < ne; ++e) {
+        int32_t a = pos[c.ea[e]], b = pos[c.eb[e]];
+        if (a > b) std::swap(a, b);
+        if (a >= kin) continue;   // both ends in the shell: no part in the term
+        ea.push_back(a);
+        eb.push_back(b);
+        ew.push_back(c.ew[e]);
+        if (b < kin) {
+            s_.w[a][b] = s_.w[b][a] = static_cast<int16_t>(c.ew[e]);
+            hash += mix64(static_cast<uint64_t>(static_cast<uint32_t>(c.ew[e])) << 16 | static_cast<uint64_t>(a << 8 | b));
+        } else {
+            h[b - kin][a - 2] = c.ew[e];
+        }
+    }
+    out.n_edges = static_cast<int32_t>(static_cast<int64_t>(ea.size()) - out.edge);
+    for (int q = 0; q < ns; ++q) {   // groups sorted by their couplings
+        size_t i = 0;
+        int cmp = 1;
+        while (i < s_.grp.size() && (cmp = std::memcmp(s_.grp[i].h, h[q], sizeof(h[q]))) < 0) ++i;
+        if (i < s_.grp.size() && cmp == 0) {
+            s_.grp[i].m += 1;
+            continue;
+        }
+        ShellGroup g;
+        g.m = 1;
+        std::memcpy(g.h, h[q], sizeof(g.h));
+        for (int x : g.h) g.wsum += x;
+        s_.grp.insert(s_.grp.begin() + static_cast<std::ptrdiff_t>(i), g);
+    }
+    uint64_t nc = 1;
+    for (const ShellGroup& g : s_.grp) {
+        nc *= static_cast<uint64_t>(g.m) + 1;
+        uint64_t x = static_cast<uint64_t>(g.m);
+        for (int i = 0; i < SH_H; ++i) x = x * 31 + static_cast<uint32_t>(g.h[i]);
+        hash += mix64(x);
+    }
+    out.nc = s_.nc = static_cast<uint32_t>(nc);   // at most 2^28: the shell holds at most 28 qubits
+    s_.hash = mix64(hash);
+    out.shape = find(s_.hash);
+}
+
+void ShellPlanner::add(const std::vector<const Cone*>& cones, std::vector<ShellCone>& out) {
+    out.resize(cones.size());
+    const size_t n = cones.size();
+    const size_t nt = n < 4096 ? 1 : std::min<size_t>({8, std::max(1u, std::thread::hardware_concurrency()), n / 1024});
+    if (nt == 1) {
+        for (size_t i = 0; i < n; ++i) add_one(*cones[i], out[i]);
+        return;
+    }
+    std::vector<ShellPlanner> part(nt, ShellPlanner(p_));
+    std::atomic<bool> no_mem{false};
+    auto work = [&](size_t t) {
+        try {
+            for (size_t i = t * n / nt; i < (t + 1) * n / nt; ++i) part[t].add_one(*cones[i], out[i]);
+        } catch (const std::bad_alloc&) {   // carried to the caller's thread
+            no_mem = true;
+        }
+    };
+    std::vector<std::thread> pool;
+    size_t started = 1;
+    try {
+        for (; started < nt; ++started) pool.emplace_back(work, started);
+    } catch (const std::system_error&) {
+        // no more threads: the remaining ranges run here
+    }
+    for (size_t t = started; t < nt; ++t) work(t);
+    work(0);
+    for (auto& t : pool) t.join();
+    if (no_mem) throw std::bad_alloc();
+    for (size_t t = 0; t < nt; ++t) {   // shapes and couplings of the parts, in order
+        const int64_t e0 = static_cast<int64_t>(ea.size());
+        ea.insert(ea.end(), part[t].ea.begin(), part[t].ea.end());
+        eb.insert(eb.end(), part[t].eb.begin(), part[t].eb.end());
+        ew.insert(ew.end(), part[t].ew.begin(), part[t].ew.end());
+        std::vector<int32_t> to(part[t].shapes_.size());
+        for (size_t i = 0; i < to.size(); ++i) {
+            s_ = part[t].shapes_[i];
+            to[i] = find(s_.hash);
+        }
+        for (size_t i = t * n / nt; i < (t + 1) * n / nt; ++i) {
+            out[i].edge += e0;
+            out[i].shape = to[static_cast<size_t>(out[i].shape)];
+        }
+    }
+}
+
+void ShellPlanner::list() {
+    std::vector<Shape*> todo;
+    for (Shape& s : shapes_)
+        if (!s.listed) todo.push_back(&s);
+    std::atomic<size_t> next{0};
+    std::atomic<bool> no_mem{false};
+    auto work = [&]() {
+        for (size_t i; (i = next.fetch_add(1)) < todo.size();) {
+            try {
+                todo[i]->enumerate();
+            } catch (const std::bad_alloc&) {   // carried to the caller's thread
+                no_mem = true;
+            }
+            todo[i]->listed = true;
+        }
+    };
+    const size_t nt = std::min<size_t>({8, std::max(1u, std::thread::hardware_concurrency()), todo.size() / 8 + 1});
+    std::vector<std::thread> pool;
+    try {
+        for (size_t t = 1; t < nt; ++t) pool.emplace_back(work);
+    } catch (const std::system_error&) {
+        // no more threads: the rest runs here
+    }
+    work();
+    for (auto& t : pool) t.join();
+    if (no_mem) throw std::bad_alloc();
+}
+
+const std::vector<ShellCfg>* ShellPlanner::configurations(int32_t shape) const {
+    const Shape& s = shapes_[static_cast<size_t>(shape)];
+    return s.cfg.empty() ? nullptr : &s.cfg;
+}
+
+}  // namespace qaoa

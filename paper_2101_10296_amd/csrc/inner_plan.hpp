@@ -1,0 +1,72 @@
+// Host planning of cones evaluated on their inner qubits: the order of the inner qubits, their layer
+// prefixes, the shell's groups and the configurations of the shell up to symmetry.
+#pragma once
+
+#include <cstdint>
+#include <vector>
+
+#include "plan.hpp"
+
+namespace qaoa {
+
+constexpr int SH_KMAX = 14;    // inner qubits
+constexpr int SH_H = 12;       // of them next to the shell (never u or v): qubits 2 .. 13
+
+// Shell qubits with the same couplings: only how many of them are 1 matters.
+struct ShellGroup {
+    int32_t m = 0;             // qubits
+    int32_t wsum = 0;          // sum of one qubit's couplings
+    int32_t h[SH_H] = {};      // coupling to inner qubit 2 + i
+};
+
+// One configuration up to symmetry: c0 + sum_a x_a h_a is what the shell adds to C_in(x).
+struct ShellCfg {
+    int16_t h[SH_H] = {};
+    int32_t c0 = 0;
+    double w = 0.0;            // configurations that it stands for
+};
+
+// A cone's inner qubits in an order of their own (by distance, then next to the qubits before them),
+// so that cones of one shape agree in their couplings.
+struct ShellCone {
+    int32_t kin = 0;
+    int64_t edge = 0;          // couplings with an inner end, in that order (ea < eb): ShellPlanner's arrays
+    int32_t n_edges = 0;
+    uint32_t nc = 0;           // configurations: product of (m + 1) over the groups, at most 2^28
+    int32_t shape = -1;        // cones of one shape share groups and configurations
+};
+
+class ShellPlanner {
+public:
+    explicit ShellPlanner(int32_t p) : p_(p) {}
+    // the cones in order (0.6 us of host time each: on several threads from 4096 cones on)
+    void add(const std::vector<const Cone*>& cones, std::vector<ShellCone>& out);
+    // Lists the configurations of every shape seen so far that has none yet (several threads).
+    void list();
+    // null: no list, every configuration is run
+    const std::vector<ShellCfg>* configurations(int32_t shape) const;
+    const std::vector<ShellGroup>& groups(int32_t shape) const { return shapes_[static_cast<size_t>(shape)].grp; }
+    std::vector<int32_t> ea, eb, ew;   // couplings of all cones
+
+private:
+    struct Shape {
+        int kin = 0;
+        uint8_t level[SH_KMAX] = {};      // distance of each inner qubit
+        int16_t w[SH_KMAX][SH_KMAX] = {}; // couplings between inner qubits
+        std::vector<ShellGroup> grp;
+        uint32_t nc = 0;
+        uint64_t hash = 0;
+        bool listed = false;
+        std::vector<ShellCfg> cfg;
+        bool same(const Shape& o) const;
+        void enumerate();
+    };
+    int32_t p_;
+    std::vector<Shape> shapes_;
+    std::vector<std::pair<uint64_t, int32_t>> table_;   // open addressing by hash
+    Shape s_;                                            // the cone being added
+    int32_t find(uint64_t h);                            // shape of s_
+    void add_one(const Cone& c, ShellCone& out);
+};
+
+}  // namespace qaoa

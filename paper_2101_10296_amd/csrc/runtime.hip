@@ -2,6 +2,8 @@
 // management, and the sequence of launches of one energy (and gradient) evaluation.
 #include "runtime.hpp"
 
+#include "inner_plan.hpp"
+
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
@@ -10,7 +12,6 @@
 #include <mutex>
 #include <numeric>
 #include <tuple>
-#include <unordered_map>
 
 namespace qaoa {
 namespace {
@@ -256,24 +257,40 @@ void build_whole(qaoa_plan_s* P, WholeHost& w) {
     const HostPlan& hp = P->hp;
     P->wh_groups.clear();
     if (hp.p < 2 || P->opt.tune != 0) return;   // layouts of the cones on their own are asked for
-    // cones of one size whose node ids agree in a commutative hash, then exactly
+    // cones of one size whose node ids agree in a commutative hash (counted in a table, as nearly
+    // all cones of a large graph are alone), then exactly
     struct Key {
         int32_t k;
         uint64_t h;
         int64_t m;
     };
-    std::vector<Key> keys;
-    for (size_t m = 0; m < hp.cones.size(); ++m) {
+    const size_t n = hp.cones.size();
+    size_t cap = 64;
+    while (cap < 2 * n) cap *= 2;
+    std::vector<uint64_t> hash(n, 0), slot(cap, 0);
+    std::vector<int32_t> count(cap, 0);
+    auto at = [&](uint64_t h) {
+        size_t i = (h >> 20) & (cap - 1);
+        while (count[i] && slot[i] != h) i = (i + 1) & (cap - 1);
+        return i;
+    };
+    for (size_t m = 0; m < n; ++m) {
         const Cone& c = hp.cones[m];
         if (c.k < WH_KMIN || c.k > WH_KMAX) continue;
-        uint64_t h = 0;
+        uint64_t h = static_cast<uint64_t>(c.k);
         for (int32_t x : c.nodes) {
             uint64_t z = static_cast<uint64_t>(x) * 0x9E3779B97F4A7C15ull + 0x632BE59BD9B4E019ull;
             z ^= z >> 29;
             h += z * 0xBF58476D1CE4E5B9ull;
         }
-        keys.push_back({c.k, h, static_cast<int64_t>(m)});
+        hash[m] = h;
+        const size_t i = at(h);
+        slot[i] = h;
+        ++count[i];
     }
+    std::vector<Key> keys;
+    for (size_t m = 0; m < n; ++m)
+        if (hash[m] && count[at(hash[m])] >= WH_MEMBERS) keys.push_back({hp.cones[m].k, hash[m], static_cast<int64_t>(m)});
     std::sort(keys.begin(), keys.end(), [](const Key& a, const Key& b) {
         return std::tie(a.k, a.h, a.m) < std::tie(b.k, b.h, b.m);
     });
@@ -342,245 +359,29 @@ struct InnerHost {
     int64_t tab_units = 0;   // table bytes / 16
 };
 
-// Inner couplings and shell groups of a cone: cones that agree in them share a list of
-// configurations.
-struct InnerSig {
-    int kin = 0;
-    uint8_t level[IN_KMAX] = {};             // distance class of each inner qubit
-    int16_t w[IN_KMAX][IN_KMAX] = {};        // couplings between inner qubits
-    std::vector<GrpIn> grp;                  // sorted by their couplings
-    uint32_t nc = 0;
-    int32_t cfg_off = -1;
-    uint32_t n_cfg = 0;
-
-    bool same(const InnerSig& o) const {
-        return kin == o.kin && grp.size() == o.grp.size() && std::memcmp(level, o.level, sizeof(level)) == 0 &&
-               std::memcmp(w, o.w, sizeof(w)) == 0 &&
-               (grp.empty() || std::memcmp(grp.data(), o.grp.data(), grp.size() * sizeof(GrpIn)) == 0);
-    }
-    uint64_t hash() const {
-        uint64_t h = static_cast<uint64_t>(kin);
-        auto mix = [&](uint64_t x) { h = (h ^ x) * 0x9E3779B97F4A7C15ull; h ^= h >> 32; };
-        for (int i = 0; i < kin; ++i)
-            for (int j = i + 1; j < kin; ++j)
-                if (w[i][j]) mix(static_cast<uint64_t>(static_cast<uint16_t>(w[i][j])) << 16 | static_cast<uint64_t>(i * 16 + j));
-        for (const GrpIn& g : grp) {
-            mix(static_cast<uint64_t>(g.m));
-            for (int i = 0; i < 8; ++i)
-                if (g.h[i]) mix(static_cast<uint64_t>(static_cast<uint32_t>(g.h[i])) << 8 | static_cast<uint64_t>(i));
-        }
-        return h;
-    }
-};
-
-// The configurations of a shell up to the symmetries that keep a term: automorphisms of the inner
-// qubits with their couplings, distance classes and shell groups (which may swap u and v), and the
-// flip of all qubits.  Configurations are tuples of digits, one per group (how many of its
-// qubits are 1).  Twins (qubits of one class that a transposition swaps, each with groups of its
-// own) are kept sorted by their digits; the remaining automorphisms, found by backtracking up to
-// orders of twins, and the flip map sorted tuples to each other, and the smallest image of each
-// orbit is listed with the weight of all its members.  What is listed depends on the signature
-// alone, so a term is the same in every plan.  Up to 1024 configurations are always listed
-// (under 0.3 ms of host time); beyond, where at least 16 symmetries shorten the list enough to
-// pay for it.  Returns false where there is no list.
-bool list_configurations(const InnerSig& g, uint32_t cpw, std::vector<CfgList>& out) {
-    const int kin = g.kin, ng = static_cast<int>(g.grp.size());
-    if (ng > 16) return false;
-    for (const GrpIn& q : g.grp)
-        if (q.m > 15) return false;
-    // groups private to one inner qubit, and twin classes
-    std::vector<int> owner(ng, -1);
-    std::vector<std::vector<int>> priv(kin);
-    for (int q = 0; q < ng; ++q) {
-        int n = 0, at = -1;
-        for (int i = 0; i < 8; ++i)
-            if (g.grp[q].h[i]) { ++n; at = i + 2; }
-        if (n == 1) {
-            owner[q] = at;
-            priv[at].push_back(q);
-        }
-    }
-    auto swapped = [](int x, int a, int b) { return x == a ? b : x == b ? a : x; };
-    auto find_group = [&](const GrpIn& want) {
-        for (int q = 0; q < ng; ++q)
-            if (std::memcmp(&g.grp[q], &want, sizeof(GrpIn)) == 0) return q;
-        return -1;
-    };
-    // image of group q under the qubit map sigma, or -1
-    auto image = [&](int q, const int* sigma) {
-        GrpIn x = g.grp[q];
-        for (int i = 0; i < 8; ++i) x.h[i] = 0;
-        for (int i = 0; i < 8; ++i)
-            if (g.grp[q].h[i]) x.h[sigma[i + 2] - 2] = g.grp[q].h[i];
-        return find_group(x);
-    };
-    std::vector<int> cls(kin, -1);
-    std::vector<std::vector<int>> classes;
-    for (int a = 2; a < kin; ++a) {
-        if (cls[a] >= 0) continue;
-        std::vector<int> c{a};
-        for (int b = a + 1; b < kin; ++b) {
-            if (cls[b] >= 0 || g.level[a] != g.level[b] || priv[a].size() != priv[b].size() || priv[a].empty()) continue;
-            bool ok = true;
-            for (int i = 0; i < kin && ok; ++i)
-                if (i != a && i != b) ok = g.w[a][i] == g.w[b][i];
-            int sg[IN_KMAX];
-            for (int i = 0; i < kin; ++i) sg[i] = swapped(i, a, b);
-            for (int q = 0; q < ng && ok; ++q) {
-                const int im = image(q, sg);
-                ok = im >= 0 && (owner[q] == a || owner[q] == b || im == q);
+// Mixed prefixes and cut ranges of every layer: base = phase row index of the smallest cut value of the
+// couplings inside the qubits mixed by layer l - 1, mid = centre of the layer's cut values in
+// row indices (layer 1: base of its inner couplings, mid with the shell's).
+template <class Mixed, class Base, class Mid>
+void layer_cuts(const Cone& c, const ShellPlanner& sp, const ShellCone& q, int32_t p, int32_t cut_min, Mixed& mixed,
+                Base& base, Mid& mid) {
+    const int32_t *eb = sp.eb.data() + q.edge, *ew = sp.ew.data() + q.edge;
+    double w_all = 0.0;
+    for (int32_t e = 0; e < q.n_edges; ++e) w_all += ew[e];
+    for (int l = 1; l <= p; ++l) mixed[l] = c.nd[p - l];
+    for (int l = 2; l <= p; ++l) {
+        int32_t cmin = 0;
+        double wl = 0.0;
+        for (int32_t e = 0; e < q.n_edges; ++e)
+            if (eb[e] < mixed[l - 1]) {
+                cmin += std::min(ew[e], 0);
+                wl += ew[e];
             }
-            if (ok) c.push_back(b);
-        }
-        if (c.size() > 1) {
-            for (int x : c) cls[x] = static_cast<int>(classes.size());
-            classes.push_back(c);
-        }
+        base[l] = static_cast<int16_t>(cmin - cut_min);
+        mid[l] = static_cast<float>(0.5 * wl - cut_min);
     }
-    // a member's private groups in the order of the first member's
-    for (auto& c : classes)
-        for (int x : c) {
-            std::vector<int> m;
-            for (int q : priv[c[0]]) {
-                int sg[IN_KMAX];
-                for (int i = 0; i < kin; ++i) sg[i] = swapped(i, c[0], x);
-                m.push_back(x == c[0] ? q : image(q, sg));
-            }
-            priv[x] = m;
-        }
-    // automorphisms up to orders of twins: permutations of the groups
-    std::vector<std::vector<int>> H;
-    int sigma[IN_KMAX], used = 0;
-    bool many = false;
-    auto search = [&](auto&& self, int i) -> void {
-        if (many) return;
-        if (i == kin) {
-            std::vector<int> pi(ng);
-            for (int q = 0; q < ng; ++q)
-                if ((pi[q] = image(q, sigma)) < 0) return;
-            H.push_back(pi);
-            many = H.size() > 32;
-            return;
-        }
-        for (int j = 0; j < kin; ++j) {
-            if ((used >> j) & 1 || (i < 2) != (j < 2) || g.level[i] != g.level[j]) continue;
-            if ((cls[i] < 0) != (cls[j] < 0) || priv[i].size() != priv[j].size()) continue;
-            bool ok = true;
-            for (int t = 0; t < i && ok; ++t) {
-                ok = g.w[i][t] == g.w[j][sigma[t]];
-                // twins go to twins in increasing order
-                if (cls[i] >= 0 && cls[t] == cls[i]) ok = ok && cls[sigma[t]] == cls[j] && sigma[t] < j;
-            }
-            if (!ok) continue;
-            sigma[i] = j;
-            used |= 1 << j;
-            self(self, i + 1);
-            used &= ~(1 << j);
-        }
-    };
-    search(search, 0);
-    if (many || H.empty()) return false;
-    // the symmetries' order: what listing saves at most, beside a factor 2 of the flip
-    double order = static_cast<double>(H.size());
-    for (const auto& c : classes)
-        for (size_t i = 2; i <= c.size(); ++i) order *= static_cast<double>(i);
-    if (g.nc > 1024 && order < 16.0) return false;
-    // a tuple as one word, group q's digit in nibble q
-    auto digit = [](uint64_t t, int q) { return static_cast<int>((t >> (4 * q)) & 15u); };
-    auto block = [&](uint64_t t, int x) {   // a twin's digits
-        uint64_t b = 0;
-        for (int q : priv[x]) b = b << 4 | static_cast<uint64_t>(digit(t, q));
-        return b;
-    };
-    auto set_block = [&](uint64_t& t, int x, uint64_t b) {
-        for (size_t i = priv[x].size(); i-- > 0; b >>= 4) {
-            const int q = priv[x][i];
-            t = (t & ~(uint64_t{15} << (4 * q))) | (b & 15u) << (4 * q);
-        }
-    };
-    auto sort_twins = [&](uint64_t t) {
-        uint64_t b[IN_KMAX];
-        for (const auto& c : classes) {
-            for (size_t i = 0; i < c.size(); ++i) {
-                const uint64_t x = block(t, c[i]);
-                size_t j = i;
-                for (; j > 0 && b[j - 1] > x; --j) b[j] = b[j - 1];
-                b[j] = x;
-            }
-            for (size_t i = 0; i < c.size(); ++i) set_block(t, c[i], b[i]);
-        }
-        return t;
-    };
-    uint64_t full = 0;   // every qubit 1: the flip of t is full - t, nibble by nibble
-    for (int q = 0; q < ng; ++q) full |= static_cast<uint64_t>(g.grp[q].m) << (4 * q);
-    uint64_t t = 0;
-    std::vector<uint64_t> seen;
-    double total = 0.0;
-    int bits = 0;
-    for (const GrpIn& q : g.grp) bits += q.m;
-    const size_t first = out.size();
-    for (uint32_t n = 0; n < g.nc; ++n) {
-        if (n)
-            for (int q = 0;; ++q) {
-                if (digit(t, q) < g.grp[q].m) {
-                    t += uint64_t{1} << (4 * q);
-                    break;
-                }
-                t &= ~(uint64_t{15} << (4 * q));
-            }
-        bool sorted = true;
-        for (const auto& c : classes)
-            for (size_t i = 1; i < c.size() && sorted; ++i) sorted = block(t, c[i - 1]) <= block(t, c[i]);
-        if (!sorted) continue;
-        seen.clear();
-        bool least = true;
-        for (const auto& pi : H) {
-            uint64_t im = 0;
-            for (int q = 0; q < ng; ++q) im |= static_cast<uint64_t>(digit(t, q)) << (4 * pi[q]);
-            uint64_t fl = full;   // groups map to groups of their size
-            fl = sort_twins(fl - im);
-            im = sort_twins(im);
-            if (im < t || fl < t) {
-                least = false;
-                break;
-            }
-            if (std::find(seen.begin(), seen.end(), im) == seen.end()) seen.push_back(im);
-            if (std::find(seen.begin(), seen.end(), fl) == seen.end()) seen.push_back(fl);
-        }
-        if (!least) continue;
-        double w = static_cast<double>(seen.size());
-        for (const auto& c : classes) {   // arrangements of the members' blocks
-            double a = 1.0;
-            int run = 1;
-            for (size_t i = 1; i < c.size(); ++i) {
-                run = block(t, c[i]) == block(t, c[i - 1]) ? run + 1 : 1;
-                a *= static_cast<double>(i + 1) / run;
-            }
-            w *= a;
-        }
-        CfgList e{};
-        for (int q = 0; q < ng; ++q) {
-            const GrpIn& G = g.grp[q];
-            double b = 1.0;
-            for (int i = 0; i < digit(t, q); ++i) b = b * (G.m - i) / (i + 1);
-            w *= b;
-            e.c0 += digit(t, q) * G.wsum;
-            for (int i = 0; i < 8; ++i) e.h[i] = static_cast<int16_t>(e.h[i] + (G.m - 2 * digit(t, q)) * G.h[i]);
-        }
-        e.w = std::round(w);
-        total += e.w;
-        out.push_back(e);
-    }
-    if (total != std::ldexp(1.0, bits)) {
-        out.resize(first);
-        return false;
-    }
-    while ((out.size() - first) % cpw) {   // whole rounds
-        CfgList e = out[first];
-        e.w = 0.0;
-        out.push_back(e);
-    }
-    return true;
+    base[1] = base[2];
+    mid[1] = static_cast<float>(0.5 * w_all - cut_min);
 }
 
 // Fills P->in_groups and the descriptors for the orbits in ord; their edges are appended to ea, eb, ew.
@@ -591,7 +392,7 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
     const bool by_k = P->opt.profile || P->opt.tune == 1;
     P->in_groups.clear();
     P->in_inst.clear();
-    P->in_max_k = 0;
+    P->in_max_k = 0;   // build_wide adds its own
     if (ord.empty()) return;
     auto is_wh = [&](int64_t m) { return !member.empty() && member[static_cast<size_t>(m)] != 0; };
     auto kin_of = [&](int64_t m) { return static_cast<int>(hp.cones[m].nd[p - 1]); };
@@ -602,100 +403,72 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         return is_wh(a) < is_wh(b);
     });
     in.cones.reserve(ord.size());
-    std::vector<InnerSig> sigs;
-    std::unordered_map<uint64_t, int32_t> sig_at;
-    std::vector<int32_t> sig_of(ord.size(), -1);
-    InnerSig sig;
+    ShellPlanner shells(p);
+    std::vector<ShellCone> sc;
+    std::vector<const Cone*> list_of(ord.size());
+    for (size_t i = 0; i < ord.size(); ++i) list_of[i] = &hp.cones[static_cast<size_t>(ord[i])];
+    shells.add(list_of, sc);
+    shells.list();
+    const int64_t edge0 = static_cast<int64_t>(ea.size());
+    ea.insert(ea.end(), shells.ea.begin(), shells.ea.end());
+    eb.insert(eb.end(), shells.eb.begin(), shells.eb.end());
+    ew.insert(ew.end(), shells.ew.begin(), shells.ew.end());
+    std::vector<int32_t> listed_at;   // first entry of each shape's list, -1: not placed yet
     std::vector<uint32_t> rounds;
     rounds.reserve(ord.size());
-    for (int64_t m : ord) {
+    for (size_t i = 0; i < ord.size(); ++i) {
+        const int64_t m = ord[i];
         const Cone& c = hp.cones[m];
-        const int kin = kin_of(m), ns = c.k - kin;
+        const ShellCone& q = sc[i];
+        const uint32_t cpw = 64u >> std::max(0, q.kin - 4);
         ConeIn d{};
         d.orbit = static_cast<int32_t>(m);
         d.inst = c.inst;
-        d.kin = kin;
-        d.edge_off = static_cast<int32_t>(ea.size());
-        d.n_edges = static_cast<int32_t>(c.ea.size());
-        d.shell_norm = std::ldexp(1.0, -ns);
-        for (int l = 1; l <= p; ++l) d.mixed[l] = c.nd[p - l];
-        int32_t h[30][8] = {};
-        double w_all = 0.0;
-        for (size_t e = 0; e < c.ea.size(); ++e) {
-            if (c.eb[e] < kin) continue;
-            if (c.ea[e] >= kin) continue;   // both ends in the shell: no part in the term
-            h[c.eb[e] - kin][c.ea[e] - 2] = c.ew[e];
-            w_all += c.ew[e];
-        }
-        for (int l = 2; l <= p; ++l) {
-            int32_t cmin = 0;
-            double wl = 0.0;
-            for (size_t e = 0; e < c.ea.size(); ++e)
-                if (c.eb[e] < d.mixed[l - 1]) {
-                    cmin += std::min(c.ew[e], 0);
-                    wl += c.ew[e];
-                }
-            d.base[l] = static_cast<int16_t>(cmin - hp.cut_min);
-            d.mid[l] = static_cast<float>(0.5 * wl - hp.cut_min);
-            if (l == 2) {
-                d.base[1] = d.base[2];
-                d.mid[1] = static_cast<float>(0.5 * (wl + w_all) - hp.cut_min);
-            }
-        }
-        d.grp_off = static_cast<int32_t>(in.grp.size());
-        uint32_t nc = 1;
-        for (int s = 0; s < ns; ++s) {
-            bool found = false;
-            for (size_t g = d.grp_off; g < in.grp.size() && !found; ++g)
-                if (std::memcmp(in.grp[g].h, h[s], sizeof(h[s])) == 0) {
-                    in.grp[g].m += 1;
-                    found = true;
-                }
-            if (found) continue;
-            GrpIn G{};
-            G.m = 1;
-            for (int i = 0; i < 8; ++i) {
-                G.h[i] = h[s][i];
-                G.wsum += h[s][i];
-            }
-            in.grp.push_back(G);
-        }
-        d.n_grp = static_cast<int32_t>(in.grp.size()) - d.grp_off;
-        for (int g = 0; g < d.n_grp; ++g) nc *= static_cast<uint32_t>(in.grp[d.grp_off + g].m) + 1u;
-        d.nc = nc;   // at most 2^27: the shell holds at most 27 qubits
+        d.kin = q.kin;
+        layer_cuts(c, shells, q, p, hp.cut_min, d.mixed, d.base, d.mid);
+        d.shell_norm = std::ldexp(1.0, -(c.k - q.kin));
+        d.nc = q.nc;
         d.cfg_off = -1;
-        if (nc > 2 && nc <= 4096) {
-            sig.kin = kin;
-            sig.nc = nc;
-            std::memset(sig.w, 0, sizeof(sig.w));
-            std::memset(sig.level, 0, sizeof(sig.level));
-            for (int q = 0, l = 0; q < kin; ++q) {
-                while (q >= c.nd[l]) ++l;
-                sig.level[q] = static_cast<uint8_t>(l);
+        uint32_t runs = (q.nc + 1) / 2;
+        if (const std::vector<ShellCfg>* list = shells.configurations(q.shape)) {
+            if (listed_at.size() <= static_cast<size_t>(q.shape)) listed_at.resize(static_cast<size_t>(q.shape) + 1, -1);
+            int32_t& at = listed_at[static_cast<size_t>(q.shape)];
+            d.n_cfg = static_cast<uint32_t>((list->size() + cpw - 1) / cpw * cpw);   // whole rounds
+            if (at < 0) {
+                at = static_cast<int32_t>(in.cfg.size());
+                for (uint32_t e = 0; e < d.n_cfg; ++e) {
+                    const ShellCfg& x = (*list)[std::min<size_t>(e, list->size() - 1)];
+                    CfgList y{};
+                    std::copy_n(x.h, 8, y.h);
+                    y.c0 = x.c0;
+                    y.w = e < list->size() ? x.w : 0.0;
+                    in.cfg.push_back(y);
+                }
             }
-            for (size_t e = 0; e < c.ea.size(); ++e)
-                if (c.eb[e] < kin) sig.w[c.ea[e]][c.eb[e]] = sig.w[c.eb[e]][c.ea[e]] = static_cast<int16_t>(c.ew[e]);
-            sig.grp.assign(in.grp.begin() + d.grp_off, in.grp.end());
-            std::sort(sig.grp.begin(), sig.grp.end(),
-                      [](const GrpIn& a, const GrpIn& b) { return std::memcmp(a.h, b.h, sizeof(a.h)) < 0; });
-            const auto at = sig_at.emplace(sig.hash(), static_cast<int32_t>(sigs.size()));
-            if (at.second) sigs.push_back(sig);
-            if (sigs[static_cast<size_t>(at.first->second)].same(sig)) {   // else a hash collision: no list
-                sig_of[in.cones.size()] = at.first->second;
+            d.cfg_off = at;
+            runs = d.n_cfg;
+        } else {   // decoded where they are used
+            d.grp_off = static_cast<int32_t>(in.grp.size());
+            const std::vector<ShellGroup>& groups = shells.groups(q.shape);
+            d.n_grp = static_cast<int32_t>(groups.size());
+            for (const ShellGroup& g : groups) {
+                GrpIn y{};
+                y.m = g.m;
+                y.wsum = g.wsum;
+                std::copy_n(g.h, 8, y.h);
+                in.grp.push_back(y);
             }
         }
+        rounds.push_back((runs + cpw - 1) / cpw);
         d.tab_off = static_cast<int32_t>(in.tab_units);
-        in.tab_units += (p - 1) * std::max<int64_t>(1, (int64_t{1} << kin) / 16);
-        const uint32_t cpw = 64u >> std::max(0, kin - 4);
-        rounds.push_back(((nc + 1) / 2 + cpw - 1) / cpw);
-        ea.insert(ea.end(), c.ea.begin(), c.ea.end());
-        eb.insert(eb.end(), c.eb.begin(), c.eb.end());
-        ew.insert(ew.end(), c.ew.begin(), c.ew.end());
+        in.tab_units += (p - 1) * std::max<int64_t>(1, (int64_t{1} << q.kin) / 16);
+        d.edge_off = static_cast<int32_t>(edge0 + q.edge);
+        d.n_edges = q.n_edges;
         const int kk = by_k ? c.k : 0;
-        if (P->in_groups.empty() || P->in_groups.back().kin != kin || P->in_groups.back().K != kk ||
+        if (P->in_groups.empty() || P->in_groups.back().kin != q.kin || P->in_groups.back().K != kk ||
             P->in_groups.back().wh != is_wh(m)) {
             qaoa_plan_s::InGroup g{};
-            g.kin = kin;
+            g.kin = q.kin;
             g.K = kk;
             g.wh = is_wh(m);
             g.first = static_cast<int64_t>(in.cones.size());
@@ -705,22 +478,6 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         P->in_max_k = std::max(P->in_max_k, c.k);
         P->in_inst.push_back(c.inst);
         in.cones.push_back(d);
-    }
-    // lists of configurations up to symmetry
-    {
-        for (InnerSig& q : sigs) {
-            const size_t off = in.cfg.size();
-            if (!list_configurations(q, 64u >> std::max(0, q.kin - 4), in.cfg)) continue;
-            q.cfg_off = static_cast<int32_t>(off);
-            q.n_cfg = static_cast<uint32_t>(in.cfg.size() - off);
-        }
-        for (size_t i = 0; i < in.cones.size(); ++i) {
-            if (sig_of[i] < 0 || sigs[static_cast<size_t>(sig_of[i])].cfg_off < 0) continue;
-            ConeIn& d = in.cones[i];
-            d.cfg_off = sigs[static_cast<size_t>(sig_of[i])].cfg_off;
-            d.n_cfg = sigs[static_cast<size_t>(sig_of[i])].n_cfg;
-            rounds[i] = d.n_cfg / (64u >> std::max(0, d.kin - 4));
-        }
     }
     for (auto& g : P->in_groups) {
         // Units of work: a cone's rounds in parts of 8, of 2 where that leaves a point with fewer than
@@ -771,6 +528,100 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
     }
 }
 
+struct WideHost {
+    std::vector<ConeWd> cones;
+    std::vector<UnitWd> units;
+    std::vector<GrpWd> grp;
+    std::vector<CfgWd> cfg;
+    int64_t tab_bytes = 0;
+};
+
+// Fills P->wd_groups and the descriptors for the orbits in ord (wide.hpp); their edges are appended.
+// A cone's units depend on the cone alone, so its sums are the same in every plan and call.
+void build_wide(qaoa_plan_s* P, std::vector<int64_t>& ord, std::vector<int32_t>& ea, std::vector<int32_t>& eb,
+                std::vector<int32_t>& ew, WideHost& w) {
+    const HostPlan& hp = P->hp;
+    const int32_t p = hp.p;
+    P->wd_groups.clear();
+    P->wd_units.clear();
+    P->wd_all_units = 0;
+    if (ord.empty()) return;
+    const bool by_k = P->opt.profile != 0;
+    std::stable_sort(ord.begin(), ord.end(), [&](int64_t a, int64_t b) {
+        const Cone &x = hp.cones[static_cast<size_t>(a)], &y = hp.cones[static_cast<size_t>(b)];
+        if (x.nd[p - 1] != y.nd[p - 1]) return x.nd[p - 1] < y.nd[p - 1];
+        return by_k && x.k < y.k;
+    });
+    ShellPlanner shells(p);
+    std::vector<ShellCone> sc;
+    std::vector<const Cone*> list_of(ord.size());
+    for (size_t i = 0; i < ord.size(); ++i) list_of[i] = &hp.cones[static_cast<size_t>(ord[i])];
+    shells.add(list_of, sc);
+    shells.list();
+    const int64_t edge0 = static_cast<int64_t>(ea.size());
+    ea.insert(ea.end(), shells.ea.begin(), shells.ea.end());
+    eb.insert(eb.end(), shells.eb.begin(), shells.eb.end());
+    ew.insert(ew.end(), shells.ew.begin(), shells.ew.end());
+    std::vector<int32_t> listed_at;   // first entry of each shape's list, -1: not placed yet
+    for (size_t i = 0; i < ord.size(); ++i) {
+        const Cone& c = hp.cones[static_cast<size_t>(ord[i])];
+        const ShellCone& q = sc[i];
+        ConeWd d{};
+        d.orbit = static_cast<int32_t>(ord[i]);
+        d.inst = c.inst;
+        d.kin = q.kin;
+        d.nc = q.nc;
+        layer_cuts(c, shells, q, p, hp.cut_min, d.mixed, d.base, d.mid);
+        d.shell_norm = std::ldexp(1.0, -(c.k - q.kin));
+        d.cfg_off = -1;
+        d.n_cfg = (q.nc + 1) / 2;
+        if (const std::vector<ShellCfg>* list = shells.configurations(q.shape)) {
+            if (listed_at.size() <= static_cast<size_t>(q.shape)) listed_at.resize(static_cast<size_t>(q.shape) + 1, -1);
+            int32_t& at = listed_at[static_cast<size_t>(q.shape)];
+            if (at < 0) {
+                at = static_cast<int32_t>(w.cfg.size());
+                for (const ShellCfg& x : *list) {
+                    CfgWd y{};
+                    std::copy_n(x.h, SH_H, y.h);
+                    y.c0 = x.c0;
+                    y.w = x.w;
+                    w.cfg.push_back(y);
+                }
+            }
+            d.cfg_off = at;
+            d.n_cfg = static_cast<uint32_t>(list->size());
+        } else {
+            d.grp_off = static_cast<int32_t>(w.grp.size());
+            const std::vector<ShellGroup>& groups = shells.groups(q.shape);
+            d.n_grp = static_cast<int32_t>(groups.size());
+            for (const ShellGroup& g : groups) {
+                GrpWd y{};
+                y.m = g.m;
+                y.wsum = g.wsum;
+                std::copy_n(g.h, SH_H, y.h);
+                w.grp.push_back(y);
+            }
+        }
+        d.tab_off = w.tab_bytes;
+        w.tab_bytes += static_cast<int64_t>(p - 1) << q.kin;
+        d.edge_off = static_cast<int32_t>(edge0 + q.edge);
+        d.n_edges = q.n_edges;
+        const int kk = by_k ? c.k : 0;
+        if (P->wd_groups.empty() || P->wd_groups.back().kin != q.kin || P->wd_groups.back().K != kk)
+            P->wd_groups.push_back({q.kin, kk, static_cast<int64_t>(w.units.size()), 0, 0});
+        d.first_unit = static_cast<int32_t>(w.units.size());
+        for (uint32_t c0 = 0; c0 < d.n_cfg; c0 += WD_CFG)
+            w.units.push_back({static_cast<int32_t>(i), c0, std::min<uint32_t>(d.n_cfg, c0 + WD_CFG)});
+        d.n_units = static_cast<int32_t>(w.units.size()) - d.first_unit;
+        P->wd_groups.back().count += d.n_units;
+        P->wd_groups.back().cones += 1;
+        P->wd_units.emplace_back(d.first_unit, d.n_units);
+        P->in_max_k = std::max(P->in_max_k, c.k);
+        w.cones.push_back(d);
+    }
+    P->wd_all_units = static_cast<int64_t>(w.units.size());
+}
+
 qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
@@ -796,10 +647,14 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     WholeHost wh;
     build_whole(P, wh);
     auto member = [&](int64_t m) { return !wh.member.empty() && wh.member[static_cast<size_t>(m)]; };
-    std::vector<int64_t> d1ord, inord;
+    std::vector<int64_t> d1ord, inord, wdord;
     for (int64_t m = 0; m < Mall; ++m) {
         const bool small = hp.cones[m].k <= P->opt.k_lds_max;
         const bool inner = !d1 && inner_cone(P, hp.cones[m]);
+        if (!d1 && wide_cone(P, hp.cones[m])) {
+            wdord.push_back(m);
+            continue;
+        }
         if (inner) inord.push_back(m);
         // (the tuner compares both kernels; a group's state reads its representative's cut table)
         if (inner && !(P->opt.tune == 1 && small) && !member(m)) continue;
@@ -859,6 +714,8 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     }
     InnerHost in;
     build_inner(P, inord, wh.member, ea, eb, ew, in);
+    WideHost wd;
+    build_wide(P, wdord, ea, eb, ew, wd);
     // depth-1 cones: the couplings of the edge's two ends
     std::vector<ConeD1> dc(d1ord.size());
     std::vector<double2> dw;
@@ -969,10 +826,16 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     const bool has_in = !in.cones.empty();
     const size_t o_in = has_in ? place(in.cones.size() * sizeof(ConeIn)) : 0;
     const size_t o_ig = has_in ? place(in.grp.size() * sizeof(GrpIn)) : 0;
+    const bool has_wd = !wd.cones.empty();
+    const size_t o_dco = has_wd ? place(wd.cones.size() * sizeof(ConeWd)) : 0;
+    const size_t o_dun = has_wd ? place(wd.units.size() * sizeof(UnitWd)) : 0;
+    const size_t o_dgr = has_wd ? place(wd.grp.size() * sizeof(GrpWd)) : 0;
+    const size_t o_dcf = has_wd ? place(wd.cfg.size() * sizeof(CfgWd)) : 0;
     const size_t o_ic = has_in ? place(in.cfg.size() * sizeof(CfgList)) : 0;
     const size_t o_is = has_in ? place(in.seg.size() * sizeof(int32_t)) : 0;
     const size_t copied = arena;
     const size_t o_wo = has_wh ? place(static_cast<size_t>(wh.obs) * sizeof(float)) : 0;
+    const size_t o_dta = has_wd ? place(static_cast<size_t>(wd.tab_bytes)) : 0;
     const size_t o_it = has_in ? place(static_cast<size_t>(in.tab_units) * 16) : 0;
     const size_t o_cut = place(static_cast<size_t>(std::max<int64_t>(cut_bytes, 16)));
     const size_t o_tt = place(static_cast<size_t>(std::max<int64_t>(tt_bytes, 16)));
@@ -1006,6 +869,12 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
             put(o_wg, wh.groups.data(), wh.groups.size() * sizeof(GroupWh));
             put(o_wm, wh.mem.data(), wh.mem.size() * sizeof(MemWh));
             put(o_ww, wh.Wg.data(), wh.Wg.size() * sizeof(double));
+        }
+        if (has_wd) {
+            put(o_dco, wd.cones.data(), wd.cones.size() * sizeof(ConeWd));
+            put(o_dun, wd.units.data(), wd.units.size() * sizeof(UnitWd));
+            put(o_dgr, wd.grp.data(), wd.grp.size() * sizeof(GrpWd));
+            put(o_dcf, wd.cfg.data(), wd.cfg.size() * sizeof(CfgWd));
         }
         if (has_in) {
             put(o_in, in.cones.data(), in.cones.size() * sizeof(ConeIn));
@@ -1041,6 +910,11 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     P->d_whmem = has_wh ? reinterpret_cast<MemWh*>(base + o_wm) : nullptr;
     P->d_Wg = has_wh ? reinterpret_cast<double*>(base + o_ww) : nullptr;
     P->d_whobs = has_wh ? reinterpret_cast<float*>(base + o_wo) : nullptr;
+    P->d_wd = has_wd ? reinterpret_cast<ConeWd*>(base + o_dco) : nullptr;
+    P->d_wdunit = has_wd ? reinterpret_cast<UnitWd*>(base + o_dun) : nullptr;
+    P->d_wdgrp = has_wd ? reinterpret_cast<GrpWd*>(base + o_dgr) : nullptr;
+    P->d_wdcfg = has_wd ? reinterpret_cast<CfgWd*>(base + o_dcf) : nullptr;
+    P->d_wdtab = has_wd ? base + o_dta : nullptr;
     P->d_in = has_in ? reinterpret_cast<ConeIn*>(base + o_in) : nullptr;
     P->d_ingrp = has_in ? reinterpret_cast<GrpIn*>(base + o_ig) : nullptr;
     P->d_incfg = has_in ? reinterpret_cast<CfgList*>(base + o_ic) : nullptr;
@@ -1059,6 +933,9 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
         QCHECK(launch_cut_tables(P->d_cones, M, P->d_ea, P->d_eb, P->d_ew, P->d_cut, nullptr));
         QCHECK(launch_tt_tables(P->d_hcones, static_cast<int64_t>(hc.size()), max_groups, P->d_ea, P->d_eb,
                                 P->d_ew, P->d_tt, nullptr));
+        if (has_wd)
+            QCHECK(launch_wide_tables(P->d_wd, static_cast<int64_t>(wd.cones.size()), P->d_ea, P->d_eb, P->d_ew, hp.p,
+                                      hp.cut_min, P->d_wdtab, nullptr));
         if (has_in)
             QCHECK(launch_inner_tables(P->d_in, static_cast<int64_t>(in.cones.size()), P->d_ea, P->d_eb, P->d_ew, hp.p,
                                        hp.cut_min, P->d_intab, nullptr));
@@ -1347,6 +1224,8 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
             const size_t one = static_cast<size_t>(grp.count) * grp.chunks * nv;
             part_need = std::max(part_need, std::max(one, std::min<size_t>(one * n_points, size_t{1} << 25)));
         }
+    const size_t wd_one = static_cast<size_t>(P->wd_all_units) * nv;
+    if (wd_one) part_need = std::max(part_need, std::max(wd_one, std::min<size_t>(wd_one * n_points, size_t{1} << 25)));
     if (part_need && (st = grow(P->d_part, P->cap_part, part_need, msg)) != QAOA_OK) return st;
     GroupTimer tm(P, stream);
     if (tables) {
@@ -1384,6 +1263,59 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         QCHECK(tm.begin(grp.K, grp.count * n_points));
         QCHECK(run_inner(grp, j));
         QCHECK(tm.end());
+    }
+    if (!P->wd_groups.empty()) {
+        WdArgs a{};
+        a.cones = P->d_wd;
+        a.grp = P->d_wdgrp;
+        a.cfg = P->d_wdcfg;
+        a.tab = P->d_wdtab;
+        a.gamma = gamma;
+        a.beta = beta;
+        a.gamma_P = n_points;
+        a.deltas = P->d_inst_delta;
+        a.p = p;
+        a.R = R;
+        a.cut_min = hp.cut_min;
+        a.M = M;
+        a.all_units = static_cast<int32_t>(P->wd_all_units);
+        a.part = P->d_part;
+        a.zz = zz;
+        a.g = g;
+        const int32_t n_cones = static_cast<int32_t>(P->wd_units.size());
+        // points per launch: the partial sums' room, and fewer than 2^32 threads
+        const int64_t slab = std::max<int64_t>(
+            1, std::min<int64_t>(static_cast<int64_t>(P->cap_part / wd_one),
+                                 (static_cast<int64_t>(UINT32_MAX) / 1024) / std::max<int64_t>(P->wd_all_units, n_cones)));
+        for (int64_t p0 = 0; p0 < n_points; p0 += slab) {
+            a.point0 = static_cast<int32_t>(p0);
+            a.P = static_cast<int32_t>(std::min(slab, n_points - p0));
+            for (const auto& grp : P->wd_groups) {
+                auto launch = [&](int64_t first, int64_t count) {
+                    a.units = P->d_wdunit + first;
+                    a.unit0 = static_cast<int32_t>(first);
+                    a.n_units = static_cast<int32_t>(count);
+                    return launch_wide(grp.kin, grad, a, stream);
+                };
+                QCHECK(tm.begin(grp.K, grp.cones * a.P));
+                if (P->opt.one_cone_at_a_time) {
+                    const WdArgs all = a;
+                    for (int64_t i = 0; i < all.P; ++i)
+                        for (const auto& u : P->wd_units)
+                            if (u.first >= grp.first && u.first < grp.first + grp.count) {
+                                a.point0 = all.point0 + static_cast<int32_t>(i);
+                                a.P = 1;
+                                a.part = all.part + static_cast<size_t>(i) * wd_one;
+                                QCHECK(launch(u.first, u.second));
+                            }
+                    a = all;
+                } else {
+                    QCHECK(launch(grp.first, grp.count));
+                }
+                QCHECK(tm.end());
+            }
+            QCHECK(launch_wide_sum(a, n_cones, grad, stream));
+        }
     }
     if (use_wh)
         for (const auto& grp : P->wh_groups) {
@@ -1598,9 +1530,10 @@ void drop_graph(qaoa_plan_s* P) {
 
 }  // namespace
 
-qaoa_status run_energy(qaoa_plan_s* P, int64_t n_points, const double* gamma, const double* beta, double* energy,
-                       double* term_zz, double* dgamma, double* dbeta, double* term_grad, hipStream_t stream,
-                       std::string& msg) {
+namespace {
+qaoa_status run_energy_throwing(qaoa_plan_s* P, int64_t n_points, const double* gamma, const double* beta,
+                                double* energy, double* term_zz, double* dgamma, double* dbeta, double* term_grad,
+                                hipStream_t stream, std::string& msg) {
     if (!P->opt.graph)
         return enqueue(P, n_points, gamma, beta, energy, term_zz, dgamma, dbeta, term_grad, stream, false, msg);
     qaoa_plan_s::GraphKey key;
@@ -1638,6 +1571,20 @@ qaoa_status run_energy(qaoa_plan_s* P, int64_t n_points, const double* gamma, co
     if (graph) hipGraphDestroy(graph);
     if (st == QAOA_OK) P->gkey = key;
     return st;
+}
+}  // namespace
+
+// The upload of a first call plans on the host: its allocation failures end here, not at the
+// C boundary.
+qaoa_status run_energy(qaoa_plan_s* P, int64_t n_points, const double* gamma, const double* beta, double* energy,
+                       double* term_zz, double* dgamma, double* dbeta, double* term_grad, hipStream_t stream,
+                       std::string& msg) {
+    try {
+        return run_energy_throwing(P, n_points, gamma, beta, energy, term_zz, dgamma, dbeta, term_grad, stream, msg);
+    } catch (const std::bad_alloc&) {
+        msg = "host allocation failed";
+        return QAOA_ENOMEM;
+    }
 }
 
 std::string tuning_report() {
@@ -1702,6 +1649,11 @@ void release_device(qaoa_plan_s* P) {
     P->d_in = nullptr;
     P->d_ingrp = nullptr;
     P->d_intab = nullptr;
+    P->d_wd = nullptr;
+    P->d_wdunit = nullptr;
+    P->d_wdgrp = nullptr;
+    P->d_wdcfg = nullptr;
+    P->d_wdtab = nullptr;
     P->d_incfg = nullptr;
     P->d_inseg = nullptr;
     P->cap_phi = P->cap_lam = P->cap_gpart = 0;

@@ -13,6 +13,7 @@
 #include "plan.hpp"
 #include "qaoa.h"
 #include "whole.hpp"
+#include "wide.hpp"
 
 struct qaoa_plan_s {
     qaoa::HostPlan hp;
@@ -54,7 +55,21 @@ struct qaoa_plan_s {
     };
     std::vector<InGroup> in_groups;
     std::vector<int32_t> in_inst;       // instance of each cone in d_in
-    int32_t in_max_k = 0;               // largest of them (cone qubits)
+    int32_t in_max_k = 0;               // largest of them and of the wide ones (cone qubits)
+    // large cones with 11 to 14 inner qubits: units of work by inner qubits (and k: profile)
+    struct WdGroup {
+        int kin, K;
+        int64_t first, count;   // units
+        int64_t cones;
+    };
+    std::vector<WdGroup> wd_groups;
+    std::vector<std::pair<int32_t, int32_t>> wd_units;   // (first unit, units) of each cone
+    int64_t wd_all_units = 0;
+    qaoa::ConeWd* d_wd = nullptr;
+    qaoa::UnitWd* d_wdunit = nullptr;
+    qaoa::GrpWd* d_wdgrp = nullptr;
+    qaoa::CfgWd* d_wdcfg = nullptr;
+    uint8_t* d_wdtab = nullptr;
     qaoa::ConeIn* d_in = nullptr;
     qaoa::GrpIn* d_ingrp = nullptr;
     qaoa::CfgList* d_incfg = nullptr;
@@ -155,6 +170,16 @@ inline bool depth1_closed(const qaoa_plan_s* P) { return P->hp.p == 1 && P->opt.
 inline bool inner_cone(const qaoa_plan_s* P, const Cone& c) {
     const int32_t p = P->hp.p;
     return p >= 2 && p <= IN_PMAX && !P->hp.realw && P->opt.tune < 2 && c.nd[p - 1] <= IN_KMAX && c.nd[p - 1] < c.k;
+}
+
+// Cones with more inner qubits, on a workgroup each.  The line at 26 cone qubits is not where the
+// passes over device memory get faster (a 25-qubit cone's cost 9x as much): the tests hold the
+// pass kinds that plans of up to 25-qubit cones launch.  Above it lies nearly all of the work: a
+// cone's cost doubles per qubit.
+inline bool wide_cone(const qaoa_plan_s* P, const Cone& c) {
+    const int32_t p = P->hp.p;
+    return p >= 2 && p <= WD_PMAX && !P->hp.realw && P->opt.tune < 2 && c.k >= WD_CONE && c.nd[p - 1] >= WD_KMIN &&
+           c.nd[p - 1] <= WD_KMAX && c.nd[p - 2] <= WD_NEXT && c.nd[p - 1] < c.k;
 }
 
 // Whether a call may evaluate the groups of wh_groups on their shared state.
