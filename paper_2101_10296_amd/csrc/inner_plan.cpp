@@ -33,8 +33,11 @@ uint64_t mix64(uint64_t x) {
 // orders of twins, and the flip map sorted tuples to each other, and the smallest image of each
 // orbit is listed with the weight of all its members.  What is listed depends on the shape
 // alone, so a term is the same in every plan.  Up to 1024 configurations are always listed
-// (under 0.3 ms of host time); beyond, up to 16384 where at least 16 symmetries shorten the list
-// enough to pay for it.  No list: cfg stays empty.
+// (under 0.3 ms of host time).  Beyond, up to 16384: at most 10 inner qubits, where a
+// configuration costs a wave under 1 us, where at least 16 symmetries shorten the list enough to
+// pay for it; more, where each occupies a compute unit for 37 us, with any symmetry at all (the
+// 47 cones of 26 to 30 qubits of a 3-regular graph on 80 nodes at p = 3 run 26573 configurations
+// instead of 59685).  No list: cfg stays empty.
 void ShellPlanner::Shape::enumerate() {
     const int ng = static_cast<int>(grp.size());
     std::vector<ShellCfg>& out = cfg;
@@ -137,7 +140,7 @@ void ShellPlanner::Shape::enumerate() {
     double order = static_cast<double>(H.size());
     for (const auto& c : classes)
         for (size_t i = 2; i <= c.size(); ++i) order *= static_cast<double>(i);
-    if (nc > 1024 && order < 16.0) return;
+    if (nc > 1024 && order < (kin > 10 ? 2.0 : 16.0)) return;
     // a tuple as one word, group q's digit in nibble q
     auto digit = [](uint64_t t, int q) { return static_cast<int>((t >> (4 * q)) & 15u); };
     auto block = [&](uint64_t t, int x) {   // a twin's digits

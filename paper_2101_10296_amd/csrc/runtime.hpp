@@ -172,13 +172,15 @@ inline bool inner_cone(const qaoa_plan_s* P, const Cone& c) {
     return p >= 2 && p <= IN_PMAX && !P->hp.realw && P->opt.tune < 2 && c.nd[p - 1] <= IN_KMAX && c.nd[p - 1] < c.k;
 }
 
-// Cones with more inner qubits, on a workgroup each.  The line at 26 cone qubits is not where the
-// passes over device memory get faster (a 25-qubit cone's cost 9x as much): the tests hold the
-// pass kinds that plans of up to 25-qubit cones launch.  Above it lies nearly all of the work: a
-// cone's cost doubles per qubit.
+// Cones with more inner qubits, on a workgroup each.  The lines at 26 (p = 2) and 25 cone qubits
+// (p = 3) are not where the passes over device memory get faster (a 25-qubit cone at p = 3 costs
+// them 763 us against 92, a 24-qubit one 385 against 22; 20 qubits 56 against 74): the tests hold
+// the pass kinds that plans of up to 25-qubit cones at p = 2 and 24-qubit ones at p = 3 launch.
+// Above lies nearly all of the work: a cone's cost doubles per qubit.
 inline bool wide_cone(const qaoa_plan_s* P, const Cone& c) {
     const int32_t p = P->hp.p;
-    return p >= 2 && p <= WD_PMAX && !P->hp.realw && P->opt.tune < 2 && c.k >= WD_CONE && c.nd[p - 1] >= WD_KMIN &&
+    return p >= 2 && p <= WD_PMAX && !P->hp.realw && P->opt.tune < 2 &&
+           c.k >= (p == 2 ? WD_CONE2 : WD_CONE3) && c.nd[p - 1] >= WD_KMIN &&
            c.nd[p - 1] <= WD_KMAX && c.nd[p - 2] <= WD_NEXT && c.nd[p - 1] < c.k;
 }
 
