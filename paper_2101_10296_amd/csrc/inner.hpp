@@ -73,6 +73,26 @@ struct InArgs {
     double* part;              // chunks > 1: [P of the launch][units][values]
 };
 
+// Small plans (inner_point.hip): the units of a point, a wave each, and where their sums go.
+constexpr int IN_POINT = 16;    // units, and orbits, at most
+// waves per workgroup: registers for 4 a SIMD; 2 where a wave holds psi and lambda over more
+// layers, with its sums in LDS (at most 8 x 19 x 512 bytes)
+constexpr int in_point_waves(bool grad, int pp) { return grad && pp == 0 ? 8 : 16; }
+constexpr size_t IN_POINT_LDS = 60 << 10;        // phase rows and sums of the gradient at most
+struct InPoint {
+    struct Unit {              // in class order, a cone's parts together
+        uint16_t cone, chunk, chunks, orbit;
+        int32_t kin;
+    } unit[IN_POINT];
+    int32_t n;
+    const double* W;
+    double* energy;
+    double* dgamma;
+    double* dbeta;
+};
+// cones of one instance, all with listed configurations; a: cones of the plan, zz and g or null
+hipError_t launch_inner_point(const InArgs& a, const InPoint& q, bool grad, int64_t n_points, hipStream_t st);
+
 hipError_t launch_inner(int kin, bool grad, const InArgs& a, hipStream_t st);
 // sums the chunks of every (point, cone) into zz and g
 hipError_t launch_inner_sum(const InArgs& a, int32_t n_cones, bool grad, hipStream_t st);

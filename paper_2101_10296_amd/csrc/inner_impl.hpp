@@ -11,7 +11,7 @@
 // Shell qubits with equal couplings count by how many are 1 (t of m, weight binom(m, t)), and
 // flipping every qubit of the cone pairs y with its complement: half of the configurations
 // are run at twice the weight.  Where the cone has symmetries of its own (twins, u and v swapped),
-// the configurations are listed up to them on the host (list_configurations in runtime.hip).  On a
+// the configurations are listed up to them on the host (ShellPlanner in inner_plan.cpp).  On a
 // 3-regular graph at p = 2 (2 + 4 inner qubits, 8 shell
 // qubits in 4 groups) that is 12 states of 2^6 amplitudes (41 before the cone's own
 // symmetries) with 6 mixed qubits in place of 2^13 stored amplitudes with 14.
@@ -340,37 +340,19 @@ __device__ __forceinline__ void in_decode(CfgIn* cfg, const GrpIn* __restrict__ 
     __builtin_amdgcn_wave_barrier();
 }
 
-// PP = 2: depth 2, sums in registers; PP = 0: depth 3..IN_PMAX, sums per lane in LDS.
-template <int KIN, bool GRAD, int PP>
-__global__ void __launch_bounds__(256, GRAD && PP == 0 ? 2 : 4) k_inner(InArgs a) {
-    using Z = Iz<KIN>;
-    constexpr int A = Z::A;
-    extern __shared__ float2 dyn[];   // phase rows: layer 1 in four gauges, then layers 2..p; then (PP = 0) sums
-    __shared__ CfgIn cfg_all[4][64];
-    __shared__ float s_t[IN_PMAX + 1];
-    __shared__ double s_k2[IN_PMAX + 1];
-    __shared__ double s_cs[2];        // cos, sin of 2 beta_p
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int p = PP ? PP : a.p, R = a.R;
-    const int point = blockIdx.x / a.blocks + a.point0;
-    const int blk = blockIdx.x % a.blocks;
-    // the segment of one instance that holds this workgroup, and its units
-    int u0 = blk * 4 * a.upw, u1 = a.units, inst = a.inst0;
-    if (a.n_seg > 1) {
-        const int32_t* sb = a.seg + a.n_seg + 1;
-        int lo = 0, hi = a.n_seg;
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) / 2;
-            if (sb[mid] <= blk) lo = mid; else hi = mid;
-        }
-        u0 = a.seg[lo] + (blk - sb[lo]) * 4 * a.upw;
-        u1 = a.seg[lo + 1];
-        inst = a.seg[2 * (a.n_seg + 1) + lo];
-    }
+// Phase rows (layer 1 in four gauges, then layers 2..p) and mixer factors of one point, by all
+// threads of the workgroup.
+struct InShared {
+    float t[IN_PMAX + 1];
+    double k2[IN_PMAX + 1];
+    double cs[2];                 // cos, sin of 2 beta_p
+};
+__device__ __forceinline__ void in_rows(const InArgs& a, int p, int inst, int point, int tid, int threads, float2* dyn,
+                                        InShared& sh) {
+    const int R = a.R;
     const size_t ip = (static_cast<size_t>(inst) * a.gamma_P + point) * p;
     const double delta = a.deltas[inst];
-    for (int i = tid; i < p * R; i += 256) {
+    for (int i = tid; i < p * R; i += threads) {
         const int l = i / R, j = i - l * R;
         double s, c;
         sincos(a.gamma[ip + l] * delta * static_cast<double>(a.cut_min + j), &s, &c);
@@ -394,18 +376,24 @@ __global__ void __launch_bounds__(256, GRAD && PP == 0 ? 2 : 4) k_inner(InArgs a
             t = -c / s;
             k2 = s * s;
         }
-        s_t[tid + 1] = static_cast<float>(t);
-        s_k2[tid + 1] = k2;
+        sh.t[tid + 1] = static_cast<float>(t);
+        sh.k2[tid + 1] = k2;
         if (tid == p - 1) {
-            s_cs[0] = c * c - s * s;
-            s_cs[1] = 2.0 * s * c;
+            sh.cs[0] = c * c - s * s;
+            sh.cs[1] = 2.0 * s * c;
         }
     }
-    __syncthreads();
+}
 
-    // row qubits of this lane: the lane is x0 1 ^ x1 2 ^ x2 7 ^ x3 15 in its 16-lane row
+// What the units of a wave share: the lane's qubits.
+template <int KIN>
+struct InLane {
     int xq[6];
-    {
+    float sg[4];
+    uint32_t xl, gz;              // table offset of the lane; its gauge's phase row
+    __device__ __forceinline__ InLane(int lane, int R) {
+        using Z = Iz<KIN>;
+        // row qubits of this lane: the lane is x0 1 ^ x1 2 ^ x2 7 ^ x3 15 in its 16-lane row
         const int b0 = lane & 1, b1 = (lane >> 1) & 1, b2 = (lane >> 2) & 1, b3 = (lane >> 3) & 1;
         xq[0] = Z::ROW > 2 ? b0 ^ b2 : b0;
         xq[1] = Z::ROW > 3 ? b1 ^ b2 : (Z::ROW > 2 ? b1 ^ b2 : b1);
@@ -413,242 +401,287 @@ __global__ void __launch_bounds__(256, GRAD && PP == 0 ? 2 : 4) k_inner(InArgs a
         xq[3] = b3;
         xq[4] = (lane >> 4) & 1;
         xq[5] = (lane >> 5) & 1;
-    }
-    float sg[4];
-    uint32_t xl = 0, gz = 0;
+        xl = 0;
+        gz = 0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) sg[i] = xq[i] ? 1.f : -1.f;
+        for (int i = 0; i < 4; ++i) sg[i] = xq[i] ? 1.f : -1.f;
 #pragma unroll
-    for (int i = 0; i < Z::LB; ++i) {
-        xl |= static_cast<uint32_t>(xq[i]) << i;
-        if (i < Z::ROW) gz += static_cast<uint32_t>(xq[i]);
+        for (int i = 0; i < Z::LB; ++i) {
+            xl |= static_cast<uint32_t>(xq[i]) << i;
+            if (i < Z::ROW) gz += static_cast<uint32_t>(xq[i]);
+        }
+        gz = (gz & 3u) * static_cast<uint32_t>(R);
     }
-    gz = (gz & 3u) * static_cast<uint32_t>(R);
-    CfgIn* cfg = cfg_all[wave];
+};
+
+// Unit ch of a cone's `chunks` by one wave: put(0, <ZZ>), put(j, gradient entry j - 1).  PP = 2: depth
+// 2, sums in registers; PP = 0: depth 3..IN_PMAX, sums per lane in lsum ([2p + 1][64]).  LISTED: the
+// cone's configurations are listed (cfg is not used).
+template <int KIN, bool GRAD, int PP, bool LISTED, class Put>
+__device__ __forceinline__ void in_unit(const InArgs& a, const ConeIn& cd, uint32_t ch, uint32_t chunks, int lane,
+                                        const InLane<KIN>& ln, const float2* dyn, const InShared& sh, CfgIn* cfg,
+                                        double* lsum, const Put& put) {
+    using Z = Iz<KIN>;
+    constexpr int A = Z::A;
+    const int p = PP ? PP : a.p, R = a.R;
+    const int (&xq)[6] = ln.xq;
+    const float (&sg)[4] = ln.sg;
+    const uint32_t xl = ln.xl, gz = ln.gz;
+    const float (&s_t)[IN_PMAX + 1] = sh.t;
+    const double (&s_k2)[IN_PMAX + 1] = sh.k2;
+    const double (&s_cs)[2] = sh.cs;
+    const float cs2 = static_cast<float>(s_cs[0] * s_cs[1]), ss2 = static_cast<float>(s_cs[1] * s_cs[1]);
+    const uint32_t nc = cd.nc;
+    const bool listed = LISTED || cd.cfg_off >= 0;
+    const uint32_t nch = listed ? cd.n_cfg : (nc + 1) >> 1;
+    const uint32_t rounds = (nch + Z::CPW - 1) / Z::CPW;
+    const uint32_t rp = (rounds + chunks - 1) / chunks;
+    const uint32_t r0 = ch * rp, r1 = min(rounds, r0 + rp);
+    const uint8_t* tab = a.tab + static_cast<size_t>(cd.tab_off) * 16 + (xl << Z::RB);
+    constexpr uint32_t TS = (1u << KIN) < 16u ? 16u : (1u << KIN);   // bytes per table
+    Tab<A> T;
+    T.load(tab);
+    // layer l's mixer prefix and scale |kappa_l|^m_l
+    auto kpow = [&](int l) {
+        double k = s_k2[l], x = 1.0;
+        for (int e = PP == 2 ? KIN : cd.mixed[l]; e; e >>= 1) {
+            if (e & 1) x *= k;
+            k *= k;
+        }
+        return x;   // |kappa_l|^(2 m_l)
+    };
+
+    double Zs = 0.0, Is = 0.0, Ds = 0.0;              // <ZZ>, 2 Im, D of the last layer (see below)
+    double Gp = 0.0, B1 = 0.0, G1 = 0.0;              // gamma_p, beta_(p-1) (PP = 2: beta_1), gamma_1
+    if constexpr (PP == 0 && GRAD)
+        for (int i = 0; i < 2 * p + 1; ++i) lsum[i * 64 + lane] = 0.0;
+
+    for (uint32_t r = r0; r < r1; ++r) {
+        CfgIn e;
+        if (listed) {
+            const CfgList c = a.cfg[cd.cfg_off + r * Z::CPW + (lane >> Z::LB)];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) e.h[i] = c.h[i];
+            e.c0 = c.c0;
+            e.w = c.w;
+        } else {
+            const uint32_t sub = (r - r0) % (64 / Z::CPW);
+            if (sub == 0) in_decode<KIN>(cfg, a.grp + cd.grp_off, cd.n_grp, nc, r * Z::CPW + lane, lane);
+            e = cfg[sub * Z::CPW + (lane >> Z::LB)];
+        }
+        const double wt = e.w;
+        // row index of table value 0 in layer 1 for this lane, and the shifts of qubits 2, 3
+        int lb = e.c0 + cd.base[1];
+#pragma unroll
+        for (int i = 0; i < Z::LB; ++i) lb += xq[i] ? e.h[i + 2] : 0;
+        int cb[4];
+        cb[0] = lb;
+        cb[1] = lb + (KIN > 2 ? e.h[0] : 0);
+        cb[2] = lb + (KIN > 3 ? e.h[1] : 0);
+        cb[3] = cb[1] + cb[2] - lb;
+
+        float2 f[A];
+        {
+            const float2* row = dyn + gz;
+#pragma unroll
+            for (int q = 0; q < A; ++q) f[q] = row[T.at(q) + cb[q >> 2]];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        in_mix<KIN, true>(f, s_t[1], KIN, sg);
+        float sc = 1.f;
+        T.opaque();
+        Tab<A> TL = T;
+        if constexpr (PP == 0) {
+            for (int l = 2; l < p; ++l) {
+                const float s = static_cast<float>(sqrt(kpow(l - 1)));
+                Tab<A> X;
+                X.load(tab + (l - 2) * TS);
+                const float2* row = dyn + (2 + l) * R + cd.base[l];
+#pragma unroll
+                for (int q = 0; q < A; ++q) {
+                    const float2 t = row[X.at(q)];
+                    f[q] = cmul(f[q], make_float2(s * t.x, s * t.y));
+                    if ((q & 7) == 7) __builtin_amdgcn_sched_barrier(0);
+                }
+                in_mix<KIN, false>(f, s_t[l], cd.mixed[l], sg);
+            }
+            sc = static_cast<float>(sqrt(kpow(p - 1)));
+#pragma unroll
+            for (int q = 0; q < A; ++q) f[q] = make_float2(sc * f[q].x, sc * f[q].y);
+            TL.load(tab + (p - 2) * TS);
+        }
+        // ---- last layer, quadruples of qubits 0 and 1 (f' = D_p f, s0 = f'00 + f'11,
+        // s1 = f'01 + f'10): <f'|M|f'> = ZZ + cos sin 2 Im(s0* s1) + sin^2 (|s1|^2 - |s0|^2) with
+        // cos, sin of 2 beta_p; M f' = (f' - w, ...): w = sin^2 s0 + i cos sin s1 on 00, 11 and
+        // -(f' - w'), w' = sin^2 s1 + i cos sin s0 on 01, 10.
+        float2 l[GRAD ? A : 1];
+        double zv = 0.0, iv = 0.0, dv = 0.0;
+        float gp = 0.f;
+        {
+            const float2* row = dyn + (2 + p) * R + cd.base[p];
+            const float cmid = static_cast<float>(cd.base[p]) - cd.mid[p];
+#pragma unroll
+            for (int q = 0; q < A; q += 4) {
+                float2 t[4], d[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    t[i] = row[TL.at(q + i)];
+                    d[i] = cmul(f[q + i], t[i]);
+                    const double x = d[i].x, y = d[i].y;
+                    if (i == 1 || i == 2) zv = fma(-y, y, fma(-x, x, zv));
+                    else zv = fma(y, y, fma(x, x, zv));
+                }
+                const float2 s0 = make_float2(d[0].x + d[3].x, d[0].y + d[3].y);
+                const float2 s1 = make_float2(d[1].x + d[2].x, d[1].y + d[2].y);
+                const double ax = s0.x, ay = s0.y, bx = s1.x, by = s1.y;
+                iv = fma(-ay, bx, fma(ax, by, iv));
+                dv = fma(by, by, fma(bx, bx, fma(-ay, ay, fma(-ax, ax, dv))));
+                if constexpr (GRAD) {
+                    const float2 w0 = make_float2(fmaf(ss2, s0.x, -cs2 * s1.y), fmaf(ss2, s0.y, cs2 * s1.x));
+                    const float2 w1 = make_float2(fmaf(ss2, s1.x, -cs2 * s0.y), fmaf(ss2, s1.y, cs2 * s0.x));
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const bool odd = i == 1 || i == 2;
+                        const float2 w = odd ? w1 : w0;
+                        const float2 m = odd ? make_float2(w.x - d[i].x, w.y - d[i].y)
+                                             : make_float2(d[i].x - w.x, d[i].y - w.y);
+                        // Im(conj(m) d) = -+ Im(conj(w) d)
+                        const float im = odd ? fmaf(w.x, d[i].y, -w.y * d[i].x) : fmaf(w.y, d[i].x, -w.x * d[i].y);
+                        gp = fmaf(static_cast<float>(TL.at(q + i)) + cmid, im, gp);
+                        l[q + i] = cmulc(m, t[i]);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        Zs = fma(wt, zv, Zs);
+        Is = fma(wt, iv, Is);
+        Ds = fma(wt, dv, Ds);
+        if constexpr (GRAD) {
+            Gp = fma(wt, static_cast<double>(gp), Gp);
+            float b1 = 0.f;
+            if constexpr (PP == 0) {
+                for (int ly = p - 1; ly >= 2; --ly) {
+                    const int m = cd.mixed[ly];
+                    const double k2 = kpow(ly);
+                    const float s = static_cast<float>(sqrt(k2));
+                    const float b = in_xsum<KIN, false>(f, l, m, sg);
+                    lsum[(p + ly) * 64 + lane] = fma(wt, static_cast<double>(b), lsum[(p + ly) * 64 + lane]);
+                    in_mix<KIN, false>(f, -s_t[ly], m, sg);
+                    in_mix<KIN, false>(l, -s_t[ly], m, sg);
+                    Tab<A> X;
+                    X.load(tab + (ly - 2) * TS);
+                    const float2* row = dyn + (2 + ly) * R + cd.base[ly];
+                    const float cmid = static_cast<float>(cd.base[ly]) - cd.mid[ly];
+                    float ga = 0.f;
+#pragma unroll
+                    for (int q = 0; q < A; ++q) {
+                        const float2 t0 = row[X.at(q)];
+                        const float2 t = make_float2(s * t0.x, s * t0.y);
+                        const float im = fmaf(l[q].x, f[q].y, -l[q].y * f[q].x);
+                        ga = fmaf(static_cast<float>(X.at(q)) + cmid, im, ga);
+                        f[q] = cmulc(f[q], t);
+                        l[q] = cmulc(l[q], t);
+                        if ((q & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+                    }
+                    lsum[ly * 64 + lane] = fma(wt * k2, static_cast<double>(ga), lsum[ly * 64 + lane]);
+                }
+            }
+            b1 = in_xsum<KIN, true>(f, l, KIN, sg);
+            B1 = fma(wt, static_cast<double>(b1), B1);
+            in_mix<KIN, true>(l, -s_t[1], KIN, sg);
+            float g1 = 0.f;
+            T.opaque();
+            {
+                const float2* row = dyn + gz;
+                float cf[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) cf[i] = static_cast<float>(cb[i]) - cd.mid[1];
+#pragma unroll
+                for (int q = 0; q < A; ++q) {
+                    const float2 t = row[T.at(q) + cb[q >> 2]];
+                    const float im = fmaf(l[q].x, t.y, -l[q].y * t.x);
+                    g1 = fmaf(static_cast<float>(T.at(q)) + cf[q >> 2], im, g1);
+                    if ((q & 7) == 7) __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            G1 = fma(wt, static_cast<double>(g1), G1);
+        }
+    }
+    // ---- the unit's sums: |psi|^2 carries 2^kin (generation without its norm) and, with PP = 2,
+    // 1 / |kappa_1|^(2 kin); the undone layer 1 scales lambda by 1 / |kappa_1|^kin (PP = 0)
+    const double n0 = cd.shell_norm * exp2(-static_cast<double>(KIN));
+    const double k1 = kpow(1);
+    const double nz = PP == 2 ? n0 * k1 : n0;
+    const double n1 = PP == 2 ? nz : n0 * sqrt(k1);
+    const double C = s_cs[0], S = s_cs[1];
+    // linear in the last layer's three sums, so combined per lane before the wave's sum
+    double v[8] = {nz * (Zs + 2.0 * C * S * Is + S * S * Ds), 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if constexpr (GRAD) {
+        v[1] = nz * 2.0 * (2.0 * (C * C - S * S) * Is + 2.0 * C * S * Ds);
+        v[2] = 2.0 * nz * Gp;
+        v[3] = 2.0 * nz * B1;
+        v[4] = 2.0 * n1 * G1;
+        const double x = wave_sum8(v, lane);
+        const int i = (lane & 8 ? 4 : 0) | (lane & 2) | (lane & 1);   // the value that this lane holds
+        if ((lane & ~11) == 0 && i < 5) put(i == 0 ? 0 : i == 1 ? 2 * p : i == 2 ? p : i == 3 ? p + 1 : 1, x);
+        if constexpr (PP == 0) {
+            for (int ly = 2; ly < p; ++ly) {
+                const double ga = wave_sum(lsum[ly * 64 + lane]), be = wave_sum(lsum[(p + ly) * 64 + lane]);
+                if (lane == 0) {
+                    put(ly, 2.0 * n0 * ga);
+                    put(p + ly, 2.0 * n0 * be);
+                }
+            }
+        }
+    } else {
+        const double x = wave_sum(v[0]);
+        if (lane == 0) put(0, x);
+    }
+}
+
+template <int KIN, bool GRAD, int PP>
+__global__ void __launch_bounds__(256, GRAD && PP == 0 ? 2 : 4) k_inner(InArgs a) {
+    extern __shared__ float2 dyn[];   // phase rows: layer 1 in four gauges, then layers 2..p; then (PP = 0) sums
+    __shared__ CfgIn cfg_all[4][64];
+    __shared__ InShared sh;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int p = PP ? PP : a.p, R = a.R;
+    const int point = blockIdx.x / a.blocks + a.point0;
+    const int blk = blockIdx.x % a.blocks;
+    // the segment of one instance that holds this workgroup, and its units
+    int u0 = blk * 4 * a.upw, u1 = a.units, inst = a.inst0;
+    if (a.n_seg > 1) {
+        const int32_t* sb = a.seg + a.n_seg + 1;
+        int lo = 0, hi = a.n_seg;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) / 2;
+            if (sb[mid] <= blk) lo = mid; else hi = mid;
+        }
+        u0 = a.seg[lo] + (blk - sb[lo]) * 4 * a.upw;
+        u1 = a.seg[lo + 1];
+        inst = a.seg[2 * (a.n_seg + 1) + lo];
+    }
+    in_rows(a, p, inst, point, tid, 256, dyn, sh);
+    __syncthreads();
+
+    const InLane<KIN> ln(lane, R);
     double* lsum = nullptr;   // PP = 0: [2p + 1][64] sums of this wave's lanes
     if constexpr (PP == 0) lsum = reinterpret_cast<double*>(dyn + (3 + p) * R + ((3 + p) * R & 1)) + wave * (2 * p + 1) * 64;
-    const float cs2 = static_cast<float>(s_cs[0] * s_cs[1]), ss2 = static_cast<float>(s_cs[1] * s_cs[1]);
-
     const int first = u0 + wave * a.upw;
     const int last = min(first + a.upw, u1);
+    const int nv = GRAD ? 2 * p + 1 : 1;
     for (int uu = first; uu < last; ++uu) {
         const int u = __builtin_amdgcn_readfirstlane(uu);
         const int slot = u / a.chunks, ch = u - slot * a.chunks;
         const ConeIn& cd = a.cones[slot];
-        const uint32_t nc = cd.nc;
-        const bool listed = cd.cfg_off >= 0;
-        const uint32_t nch = listed ? cd.n_cfg : (nc + 1) >> 1;
-        const uint32_t rounds = (nch + Z::CPW - 1) / Z::CPW;
-        const uint32_t rp = (rounds + a.chunks - 1) / a.chunks;
-        const uint32_t r0 = ch * rp, r1 = min(rounds, r0 + rp);
-        const uint8_t* tab = a.tab + static_cast<size_t>(cd.tab_off) * 16 + (xl << Z::RB);
-        constexpr uint32_t TS = (1u << KIN) < 16u ? 16u : (1u << KIN);   // bytes per table
-        Tab<A> T;
-        T.load(tab);
-        // layer l's mixer prefix and scale |kappa_l|^m_l
-        auto kpow = [&](int l) {
-            double k = s_k2[l], x = 1.0;
-            for (int e = PP == 2 ? KIN : cd.mixed[l]; e; e >>= 1) {
-                if (e & 1) x *= k;
-                k *= k;
-            }
-            return x;   // |kappa_l|^(2 m_l)
-        };
-
-        double Zs = 0.0, Is = 0.0, Ds = 0.0;              // <ZZ>, 2 Im, D of the last layer (see below)
-        double Gp = 0.0, B1 = 0.0, G1 = 0.0;              // gamma_p, beta_(p-1) (PP = 2: beta_1), gamma_1
-        if constexpr (PP == 0 && GRAD)
-            for (int i = 0; i < 2 * p + 1; ++i) lsum[i * 64 + lane] = 0.0;
-
-        for (uint32_t r = r0; r < r1; ++r) {
-            CfgIn e;
-            if (listed) {
-                const CfgList c = a.cfg[cd.cfg_off + r * Z::CPW + (lane >> Z::LB)];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) e.h[i] = c.h[i];
-                e.c0 = c.c0;
-                e.w = c.w;
-            } else {
-                const uint32_t sub = (r - r0) % (64 / Z::CPW);
-                if (sub == 0) in_decode<KIN>(cfg, a.grp + cd.grp_off, cd.n_grp, nc, r * Z::CPW + lane, lane);
-                e = cfg[sub * Z::CPW + (lane >> Z::LB)];
-            }
-            const double wt = e.w;
-            // row index of table value 0 in layer 1 for this lane, and the shifts of qubits 2, 3
-            int lb = e.c0 + cd.base[1];
-#pragma unroll
-            for (int i = 0; i < Z::LB; ++i) lb += xq[i] ? e.h[i + 2] : 0;
-            int cb[4];
-            cb[0] = lb;
-            cb[1] = lb + (KIN > 2 ? e.h[0] : 0);
-            cb[2] = lb + (KIN > 3 ? e.h[1] : 0);
-            cb[3] = cb[1] + cb[2] - lb;
-
-            float2 f[A];
-            {
-                const float2* row = dyn + gz;
-#pragma unroll
-                for (int q = 0; q < A; ++q) f[q] = row[T.at(q) + cb[q >> 2]];
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            in_mix<KIN, true>(f, s_t[1], KIN, sg);
-            float sc = 1.f;
-            T.opaque();
-            Tab<A> TL = T;
-            if constexpr (PP == 0) {
-                for (int l = 2; l < p; ++l) {
-                    const float s = static_cast<float>(sqrt(kpow(l - 1)));
-                    Tab<A> X;
-                    X.load(tab + (l - 2) * TS);
-                    const float2* row = dyn + (2 + l) * R + cd.base[l];
-#pragma unroll
-                    for (int q = 0; q < A; ++q) {
-                        const float2 t = row[X.at(q)];
-                        f[q] = cmul(f[q], make_float2(s * t.x, s * t.y));
-                        if ((q & 7) == 7) __builtin_amdgcn_sched_barrier(0);
-                    }
-                    in_mix<KIN, false>(f, s_t[l], cd.mixed[l], sg);
-                }
-                sc = static_cast<float>(sqrt(kpow(p - 1)));
-#pragma unroll
-                for (int q = 0; q < A; ++q) f[q] = make_float2(sc * f[q].x, sc * f[q].y);
-                TL.load(tab + (p - 2) * TS);
-            }
-            // ---- last layer, quadruples of qubits 0 and 1 (f' = D_p f, s0 = f'00 + f'11,
-            // s1 = f'01 + f'10): <f'|M|f'> = ZZ + cos sin 2 Im(s0* s1) + sin^2 (|s1|^2 - |s0|^2) with
-            // cos, sin of 2 beta_p; M f' = (f' - w, ...): w = sin^2 s0 + i cos sin s1 on 00, 11 and
-            // -(f' - w'), w' = sin^2 s1 + i cos sin s0 on 01, 10.
-            float2 l[GRAD ? A : 1];
-            double zv = 0.0, iv = 0.0, dv = 0.0;
-            float gp = 0.f;
-            {
-                const float2* row = dyn + (2 + p) * R + cd.base[p];
-                const float cmid = static_cast<float>(cd.base[p]) - cd.mid[p];
-#pragma unroll
-                for (int q = 0; q < A; q += 4) {
-                    float2 t[4], d[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        t[i] = row[TL.at(q + i)];
-                        d[i] = cmul(f[q + i], t[i]);
-                        const double x = d[i].x, y = d[i].y;
-                        if (i == 1 || i == 2) zv = fma(-y, y, fma(-x, x, zv));
-                        else zv = fma(y, y, fma(x, x, zv));
-                    }
-                    const float2 s0 = make_float2(d[0].x + d[3].x, d[0].y + d[3].y);
-                    const float2 s1 = make_float2(d[1].x + d[2].x, d[1].y + d[2].y);
-                    const double ax = s0.x, ay = s0.y, bx = s1.x, by = s1.y;
-                    iv = fma(-ay, bx, fma(ax, by, iv));
-                    dv = fma(by, by, fma(bx, bx, fma(-ay, ay, fma(-ax, ax, dv))));
-                    if constexpr (GRAD) {
-                        const float2 w0 = make_float2(fmaf(ss2, s0.x, -cs2 * s1.y), fmaf(ss2, s0.y, cs2 * s1.x));
-                        const float2 w1 = make_float2(fmaf(ss2, s1.x, -cs2 * s0.y), fmaf(ss2, s1.y, cs2 * s0.x));
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const bool odd = i == 1 || i == 2;
-                            const float2 w = odd ? w1 : w0;
-                            const float2 m = odd ? make_float2(w.x - d[i].x, w.y - d[i].y)
-                                                 : make_float2(d[i].x - w.x, d[i].y - w.y);
-                            // Im(conj(m) d) = -+ Im(conj(w) d)
-                            const float im = odd ? fmaf(w.x, d[i].y, -w.y * d[i].x) : fmaf(w.y, d[i].x, -w.x * d[i].y);
-                            gp = fmaf(static_cast<float>(TL.at(q + i)) + cmid, im, gp);
-                            l[q + i] = cmulc(m, t[i]);
-                        }
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            Zs = fma(wt, zv, Zs);
-            Is = fma(wt, iv, Is);
-            Ds = fma(wt, dv, Ds);
-            if constexpr (GRAD) {
-                Gp = fma(wt, static_cast<double>(gp), Gp);
-                float b1 = 0.f;
-                if constexpr (PP == 0) {
-                    for (int ly = p - 1; ly >= 2; --ly) {
-                        const int m = cd.mixed[ly];
-                        const double k2 = kpow(ly);
-                        const float s = static_cast<float>(sqrt(k2));
-                        const float b = in_xsum<KIN, false>(f, l, m, sg);
-                        lsum[(p + ly) * 64 + lane] = fma(wt, static_cast<double>(b), lsum[(p + ly) * 64 + lane]);
-                        in_mix<KIN, false>(f, -s_t[ly], m, sg);
-                        in_mix<KIN, false>(l, -s_t[ly], m, sg);
-                        Tab<A> X;
-                        X.load(tab + (ly - 2) * TS);
-                        const float2* row = dyn + (2 + ly) * R + cd.base[ly];
-                        const float cmid = static_cast<float>(cd.base[ly]) - cd.mid[ly];
-                        float ga = 0.f;
-#pragma unroll
-                        for (int q = 0; q < A; ++q) {
-                            const float2 t0 = row[X.at(q)];
-                            const float2 t = make_float2(s * t0.x, s * t0.y);
-                            const float im = fmaf(l[q].x, f[q].y, -l[q].y * f[q].x);
-                            ga = fmaf(static_cast<float>(X.at(q)) + cmid, im, ga);
-                            f[q] = cmulc(f[q], t);
-                            l[q] = cmulc(l[q], t);
-                            if ((q & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-                        }
-                        lsum[ly * 64 + lane] = fma(wt * k2, static_cast<double>(ga), lsum[ly * 64 + lane]);
-                    }
-                }
-                b1 = in_xsum<KIN, true>(f, l, KIN, sg);
-                B1 = fma(wt, static_cast<double>(b1), B1);
-                in_mix<KIN, true>(l, -s_t[1], KIN, sg);
-                float g1 = 0.f;
-                T.opaque();
-                {
-                    const float2* row = dyn + gz;
-                    float cf[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) cf[i] = static_cast<float>(cb[i]) - cd.mid[1];
-#pragma unroll
-                    for (int q = 0; q < A; ++q) {
-                        const float2 t = row[T.at(q) + cb[q >> 2]];
-                        const float im = fmaf(l[q].x, t.y, -l[q].y * t.x);
-                        g1 = fmaf(static_cast<float>(T.at(q)) + cf[q >> 2], im, g1);
-                        if ((q & 7) == 7) __builtin_amdgcn_sched_barrier(0);
-                    }
-                }
-                G1 = fma(wt, static_cast<double>(g1), G1);
-            }
-        }
-        // ---- the unit's sums: |psi|^2 carries 2^kin (generation without its norm) and, with PP = 2,
-        // 1 / |kappa_1|^(2 kin); the undone layer 1 scales lambda by 1 / |kappa_1|^kin (PP = 0)
-        const double n0 = cd.shell_norm * exp2(-static_cast<double>(KIN));
-        const double k1 = kpow(1);
-        const double nz = PP == 2 ? n0 * k1 : n0;
-        const double n1 = PP == 2 ? nz : n0 * sqrt(k1);
-        const int nv = GRAD ? 2 * p + 1 : 1;
         double* out = a.chunks > 1 ? a.part + (static_cast<size_t>(point - a.point0) * a.units + u) * nv : nullptr;
-        auto put = [&](int code, double x) {   // 0: <ZZ>; j >= 1: gradient entry j - 1
+        in_unit<KIN, GRAD, PP, false>(a, cd, ch, a.chunks, lane, ln, dyn, sh, cfg_all[wave], lsum, [&](int code, double x) {
             if (out) out[code] = x;
             else if (code == 0) a.zz[static_cast<size_t>(point) * a.M + cd.orbit] = x;
             else a.g[(static_cast<size_t>(point) * 2 * p + (code - 1)) * a.M + cd.orbit] = x;
-        };
-        const double C = s_cs[0], S = s_cs[1];
-        // linear in the last layer's three sums, so combined per lane before the wave's sum
-        double v[8] = {nz * (Zs + 2.0 * C * S * Is + S * S * Ds), 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-        if constexpr (GRAD) {
-            v[1] = nz * 2.0 * (2.0 * (C * C - S * S) * Is + 2.0 * C * S * Ds);
-            v[2] = 2.0 * nz * Gp;
-            v[3] = 2.0 * nz * B1;
-            v[4] = 2.0 * n1 * G1;
-            const double x = wave_sum8(v, lane);
-            const int i = (lane & 8 ? 4 : 0) | (lane & 2) | (lane & 1);   // the value that this lane holds
-            if ((lane & ~11) == 0 && i < 5) put(i == 0 ? 0 : i == 1 ? 2 * p : i == 2 ? p : i == 3 ? p + 1 : 1, x);
-            if constexpr (PP == 0) {
-                for (int ly = 2; ly < p; ++ly) {
-                    const double ga = wave_sum(lsum[ly * 64 + lane]), be = wave_sum(lsum[(p + ly) * 64 + lane]);
-                    if (lane == 0) {
-                        put(ly, 2.0 * n0 * ga);
-                        put(p + ly, 2.0 * n0 * be);
-                    }
-                }
-            }
-        } else {
-            const double x = wave_sum(v[0]);
-            if (lane == 0) put(0, x);
-        }
+        });
     }
 }
 

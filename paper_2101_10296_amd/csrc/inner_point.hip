@@ -1,0 +1,120 @@
+// Small plans of light cones on their inner qubits: every term of a point and their weighted sums
+// in one launch.
+//
+// A plan that symmetry reduces to a few cones has a few waves of work per point, and a call is
+// bound by its launches: one per number of inner qubits, the sum of a cone's parts, and the
+// weighted sums.  Here a workgroup takes one point, a wave each unit of work (a cone's
+// configurations or a part of them, any number of inner qubits), and the sums follow in the same
+// workgroup, in the order of k_inner_sum and k_combine: results are the same bit for bit, and
+// no term goes through device memory.
+//
+// Bound: the serial chain of one unit (phase rows, descriptors and tables through L2, then about
+// 2000 instructions of one wave).  Energy and gradient of C_10000(1,2) at p = 2 (inner states of
+// 6 and 7 qubits, one unit each), one point: 18.8 us a call in three launches, 13.6 here.
+#include "inner_impl.hpp"
+
+namespace qaoa {
+namespace {
+
+template <bool GRAD, int PP>
+__global__ void __launch_bounds__(64 * in_point_waves(GRAD, PP), GRAD && PP == 0 ? 2 : 4)
+k_inner_point(InArgs a, InPoint q) {
+    extern __shared__ float2 dyn[];   // phase rows; then (PP = 0) sums
+    __shared__ InShared sh;
+    __shared__ double s_val[IN_POINT][2 * IN_PMAX + 1];    // units
+    __shared__ double s_term[IN_POINT][2 * IN_PMAX + 1];   // orbits
+    const int tid = threadIdx.x, lane = tid & 63, waves = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int p = PP ? PP : a.p, R = a.R;
+    const int nv = GRAD ? 2 * p + 1 : 1;
+    const int point = blockIdx.x + a.point0;
+    in_rows(a, p, 0, point, tid, blockDim.x, dyn, sh);
+    __syncthreads();
+    double* lsum = nullptr;
+    if constexpr (PP == 0) lsum = reinterpret_cast<double*>(dyn + (3 + p) * R + ((3 + p) * R & 1)) + wave * (2 * p + 1) * 64;
+    for (int u = wave; u < q.n; u += waves) {
+        const InPoint::Unit un = q.unit[u];
+        const ConeIn& cd = a.cones[un.cone];
+        auto run = [&](auto K) {
+            constexpr int KIN = decltype(K)::value;
+            if constexpr (KIN >= 4 || PP == 2) {
+                const InLane<KIN> ln(lane, R);
+                in_unit<KIN, GRAD, PP, true>(a, cd, un.chunk, un.chunks, lane, ln, dyn, sh, nullptr, lsum,
+                                             [&](int code, double x) { s_val[u][code] = x; });
+            }
+        };
+        switch (un.kin) {
+            case 3: run(std::integral_constant<int, 3>{}); break;
+            case 4: run(std::integral_constant<int, 4>{}); break;
+            case 5: run(std::integral_constant<int, 5>{}); break;
+            case 6: run(std::integral_constant<int, 6>{}); break;
+            case 7: run(std::integral_constant<int, 7>{}); break;
+            case 8: run(std::integral_constant<int, 8>{}); break;
+            case 9: run(std::integral_constant<int, 9>{}); break;
+            default: run(std::integral_constant<int, 10>{}); break;
+        }
+    }
+    __syncthreads();
+    if (tid >= nv) return;
+    // thread y: the terms' value y, in orbit order, then the tree of k_combine (whose threads
+    // beyond the last orbit hold zeros)
+    const int y = tid;
+    const double delta = a.deltas[0];
+    const double gs = y >= 1 && y <= p && a.g ? delta : 1.0;   // the caller's terms are in radians
+    for (int u = 0; u < q.n;) {
+        const InPoint::Unit un = q.unit[u];
+        double x = 0.0;
+        for (int c = 0; c < un.chunks; ++c) x += s_val[u + c][y];
+        u += un.chunks;
+        x *= gs;
+        const int m = un.orbit;
+        s_term[m][y] = x;
+        if (y == 0) {
+            if (a.zz) a.zz[static_cast<size_t>(point) * a.M + m] = x;
+        } else if (a.g) {
+            a.g[(static_cast<size_t>(point) * 2 * p + (y - 1)) * a.M + m] = x;
+        }
+    }
+    double t[IN_POINT];
+#pragma unroll
+    for (int m = 0; m < IN_POINT; ++m) {
+        t[m] = 0.0;
+        if (m < a.M) t[m] = y == 0 ? q.W[m] * (1.0 - s_term[m][y]) * 0.5 : -0.5 * q.W[m] * s_term[m][y];
+    }
+#pragma unroll
+    for (int s = IN_POINT / 2; s > 0; s >>= 1)
+#pragma unroll
+        for (int m = 0; m < s; ++m) t[m] += t[m + s];
+    if (y == 0) q.energy[point] = t[0];
+    else if (y <= p) q.dgamma[static_cast<size_t>(point) * p + (y - 1)] = a.g ? t[0] : delta * t[0];
+    else q.dbeta[static_cast<size_t>(point) * p + (y - 1 - p)] = t[0];
+}
+
+}  // namespace
+
+hipError_t launch_inner_point(const InArgs& a0, const InPoint& q, bool grad, int64_t n_points, hipStream_t st) {
+    if (q.n < 1 || q.n > IN_POINT || a0.M > IN_POINT || a0.p < 2 || a0.p > IN_PMAX) return hipErrorInvalidValue;
+    const bool sums = a0.p > 2 && grad;
+    const int waves = std::min<int>(q.n, in_point_waves(grad, a0.p == 2 ? 2 : 0));
+    size_t lds = static_cast<size_t>(3 + a0.p) * a0.R * sizeof(float2);
+    if (sums) lds += 8 + static_cast<size_t>(waves) * (2 * a0.p + 1) * 64 * sizeof(double);
+    // a grid holds fewer than 2^32 threads
+    const int64_t CH = static_cast<int64_t>(UINT32_MAX) / (64 * waves);
+    for (int64_t p0 = 0; p0 < n_points; p0 += CH) {
+        InArgs a = a0;
+        a.point0 = static_cast<int32_t>(p0);
+        const dim3 grid(static_cast<unsigned>(std::min(CH, n_points - p0))), block(64 * waves);
+        if (a.p == 2) {
+            if (grad) hipLaunchKernelGGL((k_inner_point<true, 2>), grid, block, lds, st, a, q);
+            else hipLaunchKernelGGL((k_inner_point<false, 2>), grid, block, lds, st, a, q);
+        } else {
+            if (grad) hipLaunchKernelGGL((k_inner_point<true, 0>), grid, block, lds, st, a, q);
+            else hipLaunchKernelGGL((k_inner_point<false, 0>), grid, block, lds, st, a, q);
+        }
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+}  // namespace qaoa

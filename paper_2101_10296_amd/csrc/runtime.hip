@@ -528,6 +528,36 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
     }
 }
 
+// The units of a plan whose calls are one launch (inner_point.hip): one instance, all cones on their
+// inner qubits with listed configurations, and at most 16 units and orbits.  Up to there one
+// compute unit holds a point's waves at once; the 18-qubit cone of a torus, 19 units of two rounds
+// each, would run them one after the other where the separate launches spread them over five.  No
+// line at any number of points: a class's launch gives a point's few units a workgroup of their
+// own too, and leaves its other waves idle (energy and gradient of C_10000(1,2) at p = 2, 1, 256,
+// 2048 and 16384 points: 18.8, 17.9, 36, 191 us in separate launches, 13.6, 13.3, 22, 109 here;
+// rings at p = 2 .. 5, 1 point: 16, 16, 19, 42 us and 13, 13, 18, 41; 16384 points: 118, 218, 309,
+// 778 us and 51, 101, 145, 379).
+void build_point(qaoa_plan_s* P, const InnerHost& in) {
+    P->in_point = InPoint{};
+    const size_t M = P->hp.cones.size();
+    if (P->hp.n_inst != 1 || M > IN_POINT || in.cones.size() != M || !P->wh_groups.empty() || P->opt.profile ||
+        P->opt.tune != 0 || P->opt.one_cone_at_a_time)
+        return;
+    const size_t rows = static_cast<size_t>(3 + P->hp.p) * (P->hp.cut_max - P->hp.cut_min + 1) * sizeof(float2);
+    const size_t sums = P->hp.p > 2 ? static_cast<size_t>(in_point_waves(true, 0)) * (2 * P->hp.p + 1) * 512 : 0;
+    if (rows + sums > IN_POINT_LDS) return;
+    InPoint q{};
+    for (const auto& g : P->in_groups)
+        for (int64_t i = g.first; i < g.first + g.count; ++i) {
+            const ConeIn& c = in.cones[static_cast<size_t>(i)];
+            if (c.cfg_off < 0 || q.n + g.chunks > IN_POINT) return;
+            for (int32_t ch = 0; ch < g.chunks; ++ch)
+                q.unit[q.n++] = {static_cast<uint16_t>(i), static_cast<uint16_t>(ch), static_cast<uint16_t>(g.chunks),
+                                 static_cast<uint16_t>(c.orbit), c.kin};
+        }
+    P->in_point = q;
+}
+
 struct WideHost {
     std::vector<ConeWd> cones;
     std::vector<UnitWd> units;
@@ -714,6 +744,7 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     }
     InnerHost in;
     build_inner(P, inord, wh.member, ea, eb, ew, in);
+    build_point(P, in);
     WideHost wd;
     build_wide(P, wdord, ea, eb, ew, wd);
     // depth-1 cones: the couplings of the edge's two ends
@@ -1009,12 +1040,11 @@ hipError_t launch_whole_group(const qaoa_plan_s* P, const qaoa_plan_s::WhGroup& 
     return hipSuccess;
 }
 
-hipError_t launch_inner_group(const qaoa_plan_s* P, const qaoa_plan_s::InGroup& grp, bool grad, int upw_log2,
-                              int64_t n_points, const double* gamma, const double* beta, int64_t gamma_P, double* zz,
-                              double* g, double* part, size_t part_cap, hipStream_t st) {
+namespace {
+InArgs inner_args(const qaoa_plan_s* P, const double* gamma, const double* beta, int64_t gamma_P, double* zz, double* g) {
     const HostPlan& hp = P->hp;
     InArgs a{};
-    a.cones = P->d_in + grp.first;
+    a.cones = P->d_in;
     a.cfg = P->d_incfg;
     a.grp = P->d_ingrp;
     a.tab = P->d_intab;
@@ -1026,9 +1056,19 @@ hipError_t launch_inner_group(const qaoa_plan_s* P, const qaoa_plan_s::InGroup& 
     a.R = hp.cut_max - hp.cut_min + 1;
     a.cut_min = hp.cut_min;
     a.M = static_cast<int32_t>(hp.cones.size());
-    a.chunks = grp.chunks;
     a.zz = zz;
     a.g = g;
+    return a;
+}
+}  // namespace
+
+hipError_t launch_inner_group(const qaoa_plan_s* P, const qaoa_plan_s::InGroup& grp, bool grad, int upw_log2,
+                              int64_t n_points, const double* gamma, const double* beta, int64_t gamma_P, double* zz,
+                              double* g, double* part, size_t part_cap, hipStream_t st) {
+    const HostPlan& hp = P->hp;
+    InArgs a = inner_args(P, gamma, beta, gamma_P, zz, g);
+    a.cones = P->d_in + grp.first;
+    a.chunks = grp.chunks;
     a.part = part;
     const int64_t nv = grad ? 2 * hp.p + 1 : 1;
     auto run = [&](int64_t p0, int64_t np, int64_t cones) {
@@ -1195,6 +1235,16 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
     const int32_t M = static_cast<int32_t>(hp.cones.size());
     const int32_t R = hp.cut_max - hp.cut_min + 1;
     if (P->in_max_k > P->opt.k_lds_max && budget_refuses(P, P->in_max_k, grad, msg)) return QAOA_ENOMEM;
+    if (P->in_point.n) {
+        InArgs a = inner_args(P, gamma, beta, n_points, term_zz, grad ? term_grad : nullptr);
+        InPoint q = P->in_point;
+        q.W = P->d_W;
+        q.energy = energy;
+        q.dgamma = dgamma;
+        q.dbeta = dbeta;
+        QCHECK(launch_inner_point(a, q, grad, n_points, stream));
+        return QAOA_OK;
+    }
     const size_t npl = static_cast<size_t>(hp.n_inst) * n_points * p;   // (instance, point, layer) rows
     const bool use_wh = whole_used(P, grad && term_grad);
     // phase and mixer tables, for the kernels that read them
