@@ -5,6 +5,8 @@
 
 #include <cstdint>
 
+#include "shell.hpp"
+
 namespace qaoa {
 
 constexpr int IN_KMIN = 3;     // inner qubits of a cone with a shell at p >= 2
@@ -18,14 +20,16 @@ struct ConeIn {
     int32_t orbit;             // term index m (output column)
     int32_t inst;              // instance of the cone
     int32_t n_grp, grp_off;    // shell groups
-    uint32_t nc;               // configurations: product of (m_g + 1)
+    uint32_t nc;               // states of the groups: product of (m_g + 1)
     int32_t tab_off;           // first table in units of 16 bytes
     int32_t kin;               // inner qubits
     int32_t edge_off, n_edges; // cone edges (pairs of qubits, the first the smaller)
-    int32_t cfg_off;           // listed configurations, or -1: all nc, decoded where they are used
+    int32_t cfg_off;           // listed configurations, or -1: decoded where they are used
     uint32_t n_cfg;            // listed entries: a whole number of rounds (weight 0 beyond the last)
+    uint32_t zmask;            // inner qubits with leaves
+    int32_t z_off;             // their leaves: 16 entries from here
     int32_t pad0_;
-    double shell_norm;         // 2^-(shell qubits)
+    double shell_norm;         // 2^-(qubits of the groups)
     int16_t base[IN_PMAX + 1]; // [l], l = 2..p: phase row index of table value 0 of layer l; [1] = [2]
     float mid[IN_PMAX + 1];    // [l]: centre of layer l's cut values, relative to row index 0
     uint8_t mixed[IN_PMAX + 3];// [l]: qubits that layer l mixes (a prefix): those closer than p - l + 1
@@ -42,19 +46,43 @@ struct GrpIn {
 struct alignas(16) CfgList {
     int16_t h[8];
     int32_t c0;
-    int32_t pad_;
+    uint32_t z;                // signs of the qubits with leaves
     double w;
+};
+
+// Cones whose shell is leaves only, at depth 2 (inner_tree_impl.hpp).  The limits are the cone's own, so
+// that its kernel is the same in every plan: 7 inner qubits would leave a row 4 states for up to
+// 32 signs, and 6 leaves of couplings up to 3 are 84 choices, which the workgroup turns into
+// weights once, whatever the plan.
+constexpr int TR_KMIN = 4, TR_KMAX = 6;   // inner qubits
+constexpr int TR_M = 6, TR_W = 3;         // leaves of one inner qubit and their couplings at most
+constexpr int TR_TYPES = 84;              // choices of them
+struct alignas(16) ConeTr {
+    int32_t orbit;
+    int32_t tab_off;           // as in ConeIn
+    int32_t cfg_off, n_cfg;    // listed signs: z | their number << 8
+    uint32_t types;            // of the leaves of inner qubits 2 .. 5, a byte each (0: none)
+    int32_t base;              // phase row index of table value 0
+    float mid;                 // centre of the cut values, relative to row index 0
+    int32_t pad_;
 };
 
 struct InArgs {
     const ConeIn* cones;       // cones of this class (inner qubits), from the launch's first
     const CfgList* cfg;
     const GrpIn* grp;
+    const ZLeaf* leaf;
+    const ConeTr* tr;          // the class's, if it is one of those
+    const uint32_t* trcfg;
+    const ZLeaf* types;        // [n_types], the first empty
+    int32_t n_types;
     const uint8_t* tab;
     const double* gamma;       // [inst][gamma_P][p]
     const double* beta;
     int64_t gamma_P;
     const double* deltas;
+    int32_t signs;             // the class's cones have leaves
+    int32_t wz;                // largest coupling of a leaf
     int32_t p, R, cut_min;     // depth; phase row length and the cut value of entry 0
     int32_t P;                 // points of the launch
     int32_t point0;            // first of them
@@ -74,17 +102,21 @@ struct InArgs {
 };
 
 // Small plans (inner_point.hip): the units of a point, a wave each, and where their sums go.
-constexpr int IN_POINT = 16;    // units, and orbits, at most
+constexpr int IN_POINT = 16;    // units, parts of cones, and orbits, at most
 // waves per workgroup: registers for 4 a SIMD; 2 where a wave holds psi and lambda over more
 // layers, with its sums in LDS (at most 8 x 19 x 512 bytes)
 constexpr int in_point_waves(bool grad, int pp) { return grad && pp == 0 ? 8 : 16; }
 constexpr size_t IN_POINT_LDS = 60 << 10;        // phase rows and sums of the gradient at most
 struct InPoint {
     struct Unit {              // in class order, a cone's parts together
-        uint16_t cone, chunk, chunks, orbit;
-        int32_t kin;
+        uint16_t cone, chunk, chunks, part;
+        uint8_t kin;
+        uint8_t rows;          // 0, or up to four cones from `cone` on, a row of the wave each
     } unit[IN_POINT];
-    int32_t n;
+    struct Part {              // their values: the parts of a cone together
+        uint16_t chunks, orbit;
+    } part[IN_POINT];
+    int32_t n, n_part;
     const double* W;
     double* energy;
     double* dgamma;
@@ -94,6 +126,7 @@ struct InPoint {
 hipError_t launch_inner_point(const InArgs& a, const InPoint& q, bool grad, int64_t n_points, hipStream_t st);
 
 hipError_t launch_inner(int kin, bool grad, const InArgs& a, hipStream_t st);
+hipError_t launch_inner_tree(int kin, bool grad, const InArgs& a, hipStream_t st);
 // sums the chunks of every (point, cone) into zz and g
 hipError_t launch_inner_sum(const InArgs& a, int32_t n_cones, bool grad, hipStream_t st);
 // Table of layer l (2..p) of every cone: the cut of the couplings inside the qubits mixed by

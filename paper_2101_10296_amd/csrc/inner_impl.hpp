@@ -8,13 +8,14 @@
 // never mixed: it stays in |+> and only shifts phases, so the term is the mean over its
 // configurations y of a simulation of the kin = n_(p-1) inner qubits with layer-1 cut values
 //   C_1(x; y) = C_in(x) + c(y) + sum_a x_a h_a(y).
-// Shell qubits with equal couplings count by how many are 1 (t of m, weight binom(m, t)), and
-// flipping every qubit of the cone pairs y with its complement: half of the configurations
-// are run at twice the weight.  Where the cone has symmetries of its own (twins, u and v swapped),
-// the configurations are listed up to them on the host (ShellPlanner in inner_plan.cpp).  On a
-// 3-regular graph at p = 2 (2 + 4 inner qubits, 8 shell
-// qubits in 4 groups) that is 12 states of 2^6 amplitudes (41 before the cone's own
-// symmetries) with 6 mixed qubits in place of 2^13 stored amplitudes with 14.
+// Leaves, shell qubits that couple to one inner qubit only, are two signs of that qubit whatever their
+// number (shell.hpp).  Other shell qubits with equal couplings count by how many are 1 (t of m,
+// weight binom(m, t)), and flipping every qubit of the cone pairs y with its complement: half of
+// the configurations are run at twice the weight.  Where the cone has symmetries of its own (twins,
+// u and v swapped), the configurations are listed up to them on the host (inner_plan.cpp).  A
+// 26-qubit cone of a 4-regular graph at p = 2 (2 + 6 inner qubits, 18 leaves) is 10 states of 2^8
+// amplitudes with 8 mixed qubits in place of 2^25 stored amplitudes with 26.  (At p = 2 and up to
+// 6 inner qubits, cones with leaves only are inner_tree_impl.hpp's.)
 //
 // Layout: A = 2^min(4, kin) amplitudes per lane (register bits: qubits 0..3), qubits 4..7 on
 // the lanes of a 16-lane row, 8 and 9 on lane bits 4 and 5; a wave runs 64 >> (kin - 4)
@@ -31,12 +32,11 @@
 // factorisation leaves on the mixed prefix commutes with everything behind it (no couplings
 // outside the prefix are left there).
 //
-// Bound: vector instruction issue (about 70 instructions per amplitude with the gradient at
-// kin = 6, p = 2).  Measured on one MI355X against the statevector kernels that these cones ran
-// on: random 3-regular n = 10000, p = 2, 256 points, energy and gradient 215.6 -> 20.2 ms, 7.5 ms
-// with listed configurations; energies of a random 4-regular n = 60, p = 2 (cones of up to 26
-// qubits, as passes over device memory before) 5.27 -> 0.11 -> 0.094 ms; the 18-qubit cone of a
-// torus at 32 points, with the gradient, 93 -> 44 -> 24 us.
+// Bound: vector instruction issue (about 100 instructions per amplitude with the gradient at
+// kin = 8, p = 2).  Measured on one MI355X against the statevector kernels that these cones ran
+// on: energies of a random 4-regular n = 60, p = 2 (cones of up to 26 qubits, passes over device
+// memory before) 5.27 -> 0.090 ms, with the leaves as signs 0.036; the 18-qubit cone of a torus at
+// 32 points, with the gradient, 93 -> 23 us.
 #pragma once
 
 #include "fused_impl.hpp"
@@ -56,7 +56,7 @@ struct Iz {
 struct alignas(16) CfgIn {   // one configuration of the shell
     int32_t h[8];
     int32_t c0;
-    int32_t pad_;
+    uint32_t z;
     double w;                // weight; 0 beyond the last configuration
 };
 
@@ -93,10 +93,11 @@ __device__ __forceinline__ double wave_sum(double x) {
     return x;
 }
 
-// Sums of eight values over the wave at once: value i lands in the lanes whose bits 0, 1 and 3 spell
-// i.  Each of the first three steps halves the values a lane holds, where eight separate
+// Sums of eight values over the wave (or each of its 16-lane rows) at once: value i lands in the lanes
+// whose bits 0, 1 and 3 spell i.  Each of the first three steps halves the values a lane holds, where eight separate
 // sums would take six steps each.
-__device__ __forceinline__ double wave_sum8(double (&v)[8], int lane) {
+template <bool WAVE>
+__device__ __forceinline__ double lane_sum8(double (&v)[8], int lane) {
     auto step = [&](auto I, int n, bool up) {   // keep the upper half of the values where up
         constexpr int i = decltype(I)::value;
 #pragma unroll
@@ -122,10 +123,13 @@ __device__ __forceinline__ double wave_sum8(double (&v)[8], int lane) {
     step(std::integral_constant<int, 0>{}, 1, (lane & 1) != 0);
     double x = v[0];
     x += __shfl_xor(x, 4, 64);
-    x += __shfl_xor(x, 16, 64);
-    x += __shfl_xor(x, 32, 64);
+    if constexpr (WAVE) {
+        x += __shfl_xor(x, 16, 64);
+        x += __shfl_xor(x, 32, 64);
+    }
     return x;
 }
+__device__ __forceinline__ double wave_sum8(double (&v)[8], int lane) { return lane_sum8<true>(v, lane); }
 
 // Exchange lane bit 4 (W32: 5) with register bit B (an involution).
 template <bool W32, int B, int A>
@@ -309,18 +313,21 @@ __device__ const double kBinom[30 * 30] = {
 };
 
 // The configurations c .. of the next rounds, one per lane, for the lane groups that run them: mixed
-// radix digits (how many of each group's qubits are 1); the first half, at twice the weight.
+// radix digits (how many of each group's qubits are 1), the first half of them at twice the weight,
+// then the signs.
 template <int KIN>
-__device__ __forceinline__ void in_decode(CfgIn* cfg, const GrpIn* __restrict__ grp, int n_grp, uint32_t nc, uint32_t c,
-                                          int lane) {
-    const uint32_t nch = (nc + 1) >> 1;
-    uint32_t rem = c < nch ? c : nch - 1;
+__device__ __forceinline__ void in_decode(CfgIn* cfg, const GrpIn* __restrict__ grp, int n_grp, uint32_t nc, uint32_t zmask,
+                                          uint32_t c, int lane) {
+    const uint32_t nh = (nc + 1) >> 1, n = nh << __builtin_popcount(zmask);
+    uint32_t zz = c < n ? c / nh : 0u;
+    uint32_t rem = c < n ? c - zz * nh : 0u;
     CfgIn e;
 #pragma unroll
     for (int i = 0; i < 8; ++i) e.h[i] = 0;
     e.c0 = 0;
-    e.pad_ = 0;
-    e.w = c < nch ? (((nc & 1u) && c == nch - 1) ? 1.0 : 2.0) : 0.0;
+    e.z = 0;
+    e.w = c < n ? (((nc & 1u) && rem == nh - 1) ? 1.0 : 2.0) : 0.0;
+    for (uint32_t m = zmask; m; m &= m - 1, zz >>= 1) e.z |= (zz & 1u) << __builtin_ctz(m);
     for (int q = 0; q < n_grp; ++q) {
         const GrpIn& G = grp[q];
         const uint32_t d = static_cast<uint32_t>(G.m) + 1u;
@@ -340,8 +347,12 @@ __device__ __forceinline__ void in_decode(CfgIn* cfg, const GrpIn* __restrict__ 
     __builtin_amdgcn_wave_barrier();
 }
 
-// Phase rows (layer 1 in four gauges, then layers 2..p) and mixer factors of one point, by all
-// threads of the workgroup.
+// The leaves' cosines, then the phase rows (layer 1 in four gauges, then layers 2..p), and the mixer
+// factors of one point, by all threads of the workgroup.
+__device__ __forceinline__ float2* in_phase(const InArgs& a, float2* dyn) { return dyn + (a.wz ? 2 * (a.wz + 1) : 0); }
+inline size_t in_rows_bytes(const InArgs& a) {
+    return (static_cast<size_t>(3 + a.p) * a.R + (a.wz ? 2 * (a.wz + 1) : 0)) * sizeof(float2);
+}
 struct InShared {
     float t[IN_PMAX + 1];
     double k2[IN_PMAX + 1];
@@ -350,6 +361,8 @@ struct InShared {
 __device__ __forceinline__ void in_rows(const InArgs& a, int p, int inst, int point, int tid, int threads, float2* dyn,
                                         InShared& sh) {
     const int R = a.R;
+    double2* ct = reinterpret_cast<double2*>(dyn);
+    dyn = in_phase(a, dyn);
     const size_t ip = (static_cast<size_t>(inst) * a.gamma_P + point) * p;
     const double delta = a.deltas[inst];
     for (int i = tid; i < p * R; i += threads) {
@@ -366,6 +379,9 @@ __device__ __forceinline__ void in_rows(const InArgs& a, int p, int inst, int po
             dyn[(3 + l) * R + j] = make_float2(x, y);
         }
     }
+    if (a.wz)
+        for (int j = tid; j <= a.wz; j += threads)
+            sincos(a.gamma[ip] * delta * static_cast<double>(j), &ct[j].y, &ct[j].x);
     if (tid < p) {   // exp(-i beta X) = kappa X^e (1 - i tau X), |tau| <= 1 (see k_tables)
         double s, c, t, k2;
         sincos(a.beta[ip + tid], &s, &c);
@@ -390,8 +406,8 @@ template <int KIN>
 struct InLane {
     int xq[6];
     float sg[4];
-    uint32_t xl, gz;              // table offset of the lane; its gauge's phase row
-    __device__ __forceinline__ InLane(int lane, int R) {
+    uint32_t xl, gz;              // table offset of the lane; its gauge, qubits that are 1
+    __device__ __forceinline__ explicit InLane(int lane) {
         using Z = Iz<KIN>;
         // row qubits of this lane: the lane is x0 1 ^ x1 2 ^ x2 7 ^ x3 15 in its 16-lane row
         const int b0 = lane & 1, b1 = (lane >> 1) & 1, b2 = (lane >> 2) & 1, b3 = (lane >> 3) & 1;
@@ -410,30 +426,75 @@ struct InLane {
             xl |= static_cast<uint32_t>(xq[i]) << i;
             if (i < Z::ROW) gz += static_cast<uint32_t>(xq[i]);
         }
-        gz = (gz & 3u) * static_cast<uint32_t>(R);
     }
 };
 
+// ---- last layer, quadruples of qubits 0 and 1 (f' = D_p f, s0 = f'00 + f'11, s1 = f'01 + f'10):
+// <f'|M|f'> = ZZ + cos sin 2 Im(s0* s1) + sin^2 (|s1|^2 - |s0|^2) with cos, sin of 2 beta_p (sums
+// zv, iv, dv); M f' = (f' - w, ...): w = sin^2 s0 + i cos sin s1 on 00, 11 and -(f' - w'),
+// w' = sin^2 s1 + i cos sin s0 on 01, 10; l = D_p* M f', gp: the gamma_p derivative.
+template <bool GRAD, int A, int AL>
+__device__ __forceinline__ void in_last(const float2 (&f)[A], float2 (&l)[AL], const Tab<A>& T, const float2* row, float cmid,
+                                        float cs2, float ss2, double& zv, double& iv, double& dv, float& gp) {
+#pragma unroll
+    for (int q = 0; q < A; q += 4) {
+        float2 t[4], d[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            t[i] = row[T.at(q + i)];
+            d[i] = cmul(f[q + i], t[i]);
+            const double x = d[i].x, y = d[i].y;
+            if (i == 1 || i == 2) zv = fma(-y, y, fma(-x, x, zv));
+            else zv = fma(y, y, fma(x, x, zv));
+        }
+        const float2 s0 = make_float2(d[0].x + d[3].x, d[0].y + d[3].y);
+        const float2 s1 = make_float2(d[1].x + d[2].x, d[1].y + d[2].y);
+        const double ax = s0.x, ay = s0.y, bx = s1.x, by = s1.y;
+        iv = fma(-ay, bx, fma(ax, by, iv));
+        dv = fma(by, by, fma(bx, bx, fma(-ay, ay, fma(-ax, ax, dv))));
+        if constexpr (GRAD) {
+            const float2 w0 = make_float2(fmaf(ss2, s0.x, -cs2 * s1.y), fmaf(ss2, s0.y, cs2 * s1.x));
+            const float2 w1 = make_float2(fmaf(ss2, s1.x, -cs2 * s0.y), fmaf(ss2, s1.y, cs2 * s0.x));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const bool odd = i == 1 || i == 2;
+                const float2 w = odd ? w1 : w0;
+                const float2 m = odd ? make_float2(w.x - d[i].x, w.y - d[i].y)
+                                     : make_float2(d[i].x - w.x, d[i].y - w.y);
+                // Im(conj(m) d) = -+ Im(conj(w) d)
+                const float im = odd ? fmaf(w.x, d[i].y, -w.y * d[i].x) : fmaf(w.y, d[i].x, -w.x * d[i].y);
+                gp = fmaf(static_cast<float>(T.at(q + i)) + cmid, im, gp);
+                l[q + i] = cmulc(m, t[i]);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 // Unit ch of a cone's `chunks` by one wave: put(0, <ZZ>), put(j, gradient entry j - 1).  PP = 2: depth
 // 2, sums in registers; PP = 0: depth 3..IN_PMAX, sums per lane in lsum ([2p + 1][64]).  LISTED: the
-// cone's configurations are listed (cfg is not used).
-template <int KIN, bool GRAD, int PP, bool LISTED, class Put>
+// cone's configurations are listed (cfg is not used).  SIGNS: it has leaves.
+template <int KIN, bool GRAD, int PP, bool LISTED, bool SIGNS, class Put>
 __device__ __forceinline__ void in_unit(const InArgs& a, const ConeIn& cd, uint32_t ch, uint32_t chunks, int lane,
-                                        const InLane<KIN>& ln, const float2* dyn, const InShared& sh, CfgIn* cfg,
-                                        double* lsum, const Put& put) {
+                                        const InLane<KIN>& ln, const float2* dyn0, const InShared& sh, CfgIn* cfg,
+                                        double2* zfac, double* lsum, const Put& put) {
     using Z = Iz<KIN>;
     constexpr int A = Z::A;
     const int p = PP ? PP : a.p, R = a.R;
     const int (&xq)[6] = ln.xq;
     const float (&sg)[4] = ln.sg;
     const uint32_t xl = ln.xl, gz = ln.gz;
+    const double2* ct = reinterpret_cast<const double2*>(dyn0);
+    const float2* dyn = in_phase(a, const_cast<float2*>(dyn0));
+    const float2* row1 = SIGNS ? dyn : dyn + (gz & 3u) * static_cast<uint32_t>(R);   // layer 1
     const float (&s_t)[IN_PMAX + 1] = sh.t;
     const double (&s_k2)[IN_PMAX + 1] = sh.k2;
     const double (&s_cs)[2] = sh.cs;
     const float cs2 = static_cast<float>(s_cs[0] * s_cs[1]), ss2 = static_cast<float>(s_cs[1] * s_cs[1]);
     const uint32_t nc = cd.nc;
     const bool listed = LISTED || cd.cfg_off >= 0;
-    const uint32_t nch = listed ? cd.n_cfg : (nc + 1) >> 1;
+    const uint32_t zmask = cd.zmask;
+    const uint32_t nch = listed ? cd.n_cfg : ((nc + 1) >> 1) << __builtin_popcount(zmask);
     const uint32_t rounds = (nch + Z::CPW - 1) / Z::CPW;
     const uint32_t rp = (rounds + chunks - 1) / chunks;
     const uint32_t r0 = ch * rp, r1 = min(rounds, r0 + rp);
@@ -453,6 +514,13 @@ __device__ __forceinline__ void in_unit(const InArgs& a, const ConeIn& cd, uint3
 
     double Zs = 0.0, Is = 0.0, Ds = 0.0;              // <ZZ>, 2 Im, D of the last layer (see below)
     double Gp = 0.0, B1 = 0.0, G1 = 0.0;              // gamma_p, beta_(p-1) (PP = 2: beta_1), gamma_1
+    double Wd = 0.0;                                  // gamma_1 through the weights
+    if constexpr (SIGNS) {
+        __builtin_amdgcn_wave_barrier();              // the last unit's weights are read
+        if (lane < 16) zfac[lane] = z_factor(a.leaf[cd.z_off + lane], ct);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
     if constexpr (PP == 0 && GRAD)
         for (int i = 0; i < 2 * p + 1; ++i) lsum[i * 64 + lane] = 0.0;
 
@@ -463,28 +531,39 @@ __device__ __forceinline__ void in_unit(const InArgs& a, const ConeIn& cd, uint3
 #pragma unroll
             for (int i = 0; i < 8; ++i) e.h[i] = c.h[i];
             e.c0 = c.c0;
+            e.z = c.z;
             e.w = c.w;
         } else {
             const uint32_t sub = (r - r0) % (64 / Z::CPW);
-            if (sub == 0) in_decode<KIN>(cfg, a.grp + cd.grp_off, cd.n_grp, nc, r * Z::CPW + lane, lane);
+            if (sub == 0) in_decode<KIN>(cfg, a.grp + cd.grp_off, cd.n_grp, nc, zmask, r * Z::CPW + lane, lane);
             e = cfg[sub * Z::CPW + (lane >> Z::LB)];
         }
-        const double wt = e.w;
+        double wt = e.w, dwt = 0.0;
+        if constexpr (SIGNS) dwt = z_weight(zmask, e.z, zfac, wt);
         // row index of table value 0 in layer 1 for this lane, and the shifts of qubits 2, 3
         int lb = e.c0 + cd.base[1];
 #pragma unroll
         for (int i = 0; i < Z::LB; ++i) lb += xq[i] ? e.h[i + 2] : 0;
-        int cb[4];
-        cb[0] = lb;
-        cb[1] = lb + (KIN > 2 ? e.h[0] : 0);
-        cb[2] = lb + (KIN > 3 ? e.h[1] : 0);
-        cb[3] = cb[1] + cb[2] - lb;
+        int cs[4], cb[4];   // without and with the gauge; the signs are two steps of it
+        cs[0] = lb;
+        cs[1] = lb + (KIN > 2 ? e.h[0] : 0);
+        cs[2] = lb + (KIN > 3 ? e.h[1] : 0);
+        cs[3] = cs[1] + cs[2] - lb;
+        if constexpr (SIGNS) {
+            const uint32_t g0 = gz + 2u * static_cast<uint32_t>(__builtin_popcount((e.z >> Z::RB) & xl));
+            const uint32_t s2 = KIN > 2 ? (e.z >> 1) & 2u : 0u, s3 = KIN > 3 ? (e.z >> 2) & 2u : 0u;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                cb[i] = cs[i] + static_cast<int>((g0 + (i & 1 ? s2 : 0u) + (i & 2 ? s3 : 0u)) & 3u) * R;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) cb[i] = cs[i];
+        }
 
         float2 f[A];
         {
-            const float2* row = dyn + gz;
 #pragma unroll
-            for (int q = 0; q < A; ++q) f[q] = row[T.at(q) + cb[q >> 2]];
+            for (int q = 0; q < A; ++q) f[q] = row1[T.at(q) + cb[q >> 2]];
             __builtin_amdgcn_sched_barrier(0);
         }
         in_mix<KIN, true>(f, s_t[1], KIN, sg);
@@ -510,54 +589,16 @@ __device__ __forceinline__ void in_unit(const InArgs& a, const ConeIn& cd, uint3
             for (int q = 0; q < A; ++q) f[q] = make_float2(sc * f[q].x, sc * f[q].y);
             TL.load(tab + (p - 2) * TS);
         }
-        // ---- last layer, quadruples of qubits 0 and 1 (f' = D_p f, s0 = f'00 + f'11,
-        // s1 = f'01 + f'10): <f'|M|f'> = ZZ + cos sin 2 Im(s0* s1) + sin^2 (|s1|^2 - |s0|^2) with
-        // cos, sin of 2 beta_p; M f' = (f' - w, ...): w = sin^2 s0 + i cos sin s1 on 00, 11 and
-        // -(f' - w'), w' = sin^2 s1 + i cos sin s0 on 01, 10.
         float2 l[GRAD ? A : 1];
         double zv = 0.0, iv = 0.0, dv = 0.0;
         float gp = 0.f;
-        {
-            const float2* row = dyn + (2 + p) * R + cd.base[p];
-            const float cmid = static_cast<float>(cd.base[p]) - cd.mid[p];
-#pragma unroll
-            for (int q = 0; q < A; q += 4) {
-                float2 t[4], d[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    t[i] = row[TL.at(q + i)];
-                    d[i] = cmul(f[q + i], t[i]);
-                    const double x = d[i].x, y = d[i].y;
-                    if (i == 1 || i == 2) zv = fma(-y, y, fma(-x, x, zv));
-                    else zv = fma(y, y, fma(x, x, zv));
-                }
-                const float2 s0 = make_float2(d[0].x + d[3].x, d[0].y + d[3].y);
-                const float2 s1 = make_float2(d[1].x + d[2].x, d[1].y + d[2].y);
-                const double ax = s0.x, ay = s0.y, bx = s1.x, by = s1.y;
-                iv = fma(-ay, bx, fma(ax, by, iv));
-                dv = fma(by, by, fma(bx, bx, fma(-ay, ay, fma(-ax, ax, dv))));
-                if constexpr (GRAD) {
-                    const float2 w0 = make_float2(fmaf(ss2, s0.x, -cs2 * s1.y), fmaf(ss2, s0.y, cs2 * s1.x));
-                    const float2 w1 = make_float2(fmaf(ss2, s1.x, -cs2 * s0.y), fmaf(ss2, s1.y, cs2 * s0.x));
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const bool odd = i == 1 || i == 2;
-                        const float2 w = odd ? w1 : w0;
-                        const float2 m = odd ? make_float2(w.x - d[i].x, w.y - d[i].y)
-                                             : make_float2(d[i].x - w.x, d[i].y - w.y);
-                        // Im(conj(m) d) = -+ Im(conj(w) d)
-                        const float im = odd ? fmaf(w.x, d[i].y, -w.y * d[i].x) : fmaf(w.y, d[i].x, -w.x * d[i].y);
-                        gp = fmaf(static_cast<float>(TL.at(q + i)) + cmid, im, gp);
-                        l[q + i] = cmulc(m, t[i]);
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
+        in_last<GRAD>(f, l, TL, dyn + (2 + p) * R + cd.base[p], static_cast<float>(cd.base[p]) - cd.mid[p], cs2, ss2, zv, iv, dv,
+                      gp);
         Zs = fma(wt, zv, Zs);
         Is = fma(wt, iv, Is);
         Ds = fma(wt, dv, Ds);
         if constexpr (GRAD) {
+            if constexpr (SIGNS) Wd = fma(dwt, zv + 2.0 * s_cs[0] * s_cs[1] * iv + s_cs[1] * s_cs[1] * dv, Wd);
             Gp = fma(wt, static_cast<double>(gp), Gp);
             float b1 = 0.f;
             if constexpr (PP == 0) {
@@ -593,13 +634,12 @@ __device__ __forceinline__ void in_unit(const InArgs& a, const ConeIn& cd, uint3
             float g1 = 0.f;
             T.opaque();
             {
-                const float2* row = dyn + gz;
                 float cf[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) cf[i] = static_cast<float>(cb[i]) - cd.mid[1];
+                for (int i = 0; i < 4; ++i) cf[i] = static_cast<float>(cs[i]) - cd.mid[1];
 #pragma unroll
                 for (int q = 0; q < A; ++q) {
-                    const float2 t = row[T.at(q) + cb[q >> 2]];
+                    const float2 t = row1[T.at(q) + cb[q >> 2]];
                     const float im = fmaf(l[q].x, t.y, -l[q].y * t.x);
                     g1 = fmaf(static_cast<float>(T.at(q)) + cf[q >> 2], im, g1);
                     if ((q & 7) == 7) __builtin_amdgcn_sched_barrier(0);
@@ -621,7 +661,7 @@ __device__ __forceinline__ void in_unit(const InArgs& a, const ConeIn& cd, uint3
         v[1] = nz * 2.0 * (2.0 * (C * C - S * S) * Is + 2.0 * C * S * Ds);
         v[2] = 2.0 * nz * Gp;
         v[3] = 2.0 * nz * B1;
-        v[4] = 2.0 * n1 * G1;
+        v[4] = 2.0 * n1 * G1 + nz * Wd;
         const double x = wave_sum8(v, lane);
         const int i = (lane & 8 ? 4 : 0) | (lane & 2) | (lane & 1);   // the value that this lane holds
         if ((lane & ~11) == 0 && i < 5) put(i == 0 ? 0 : i == 1 ? 2 * p : i == 2 ? p : i == 3 ? p + 1 : 1, x);
@@ -640,18 +680,11 @@ __device__ __forceinline__ void in_unit(const InArgs& a, const ConeIn& cd, uint3
     }
 }
 
-template <int KIN, bool GRAD, int PP>
-__global__ void __launch_bounds__(256, GRAD && PP == 0 ? 2 : 4) k_inner(InArgs a) {
-    extern __shared__ float2 dyn[];   // phase rows: layer 1 in four gauges, then layers 2..p; then (PP = 0) sums
-    __shared__ CfgIn cfg_all[4][64];
-    __shared__ InShared sh;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int p = PP ? PP : a.p, R = a.R;
-    const int point = blockIdx.x / a.blocks + a.point0;
-    const int blk = blockIdx.x % a.blocks;
-    // the segment of one instance that holds this workgroup, and its units
-    int u0 = blk * 4 * a.upw, u1 = a.units, inst = a.inst0;
+// The segment of one instance that holds workgroup blk of `per` units, and its units u0 .. u1 - 1.
+__device__ __forceinline__ void in_segment(const InArgs& a, int blk, int per, int& u0, int& u1, int& inst) {
+    u0 = blk * per;
+    u1 = a.units;
+    inst = a.inst0;
     if (a.n_seg > 1) {
         const int32_t* sb = a.seg + a.n_seg + 1;
         int lo = 0, hi = a.n_seg;
@@ -659,16 +692,31 @@ __global__ void __launch_bounds__(256, GRAD && PP == 0 ? 2 : 4) k_inner(InArgs a
             const int mid = (lo + hi) / 2;
             if (sb[mid] <= blk) lo = mid; else hi = mid;
         }
-        u0 = a.seg[lo] + (blk - sb[lo]) * 4 * a.upw;
+        u0 = a.seg[lo] + (blk - sb[lo]) * per;
         u1 = a.seg[lo + 1];
         inst = a.seg[2 * (a.n_seg + 1) + lo];
     }
+}
+
+template <int KIN, bool GRAD, int PP, bool SIGNS>
+__global__ void __launch_bounds__(256, GRAD && PP == 0 ? 2 : 4) k_inner(InArgs a) {
+    extern __shared__ __attribute__((aligned(16))) float2 dyn[];   // cosines and phase rows (in_rows); then (PP = 0) sums
+    __shared__ CfgIn cfg_all[4][64];
+    __shared__ InShared sh;
+    __shared__ double2 s_z[4][16];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int p = PP ? PP : a.p, R = a.R;
+    const int point = blockIdx.x / a.blocks + a.point0;
+    const int blk = blockIdx.x % a.blocks;
+    int u0, u1, inst;
+    in_segment(a, blk, 4 * a.upw, u0, u1, inst);
     in_rows(a, p, inst, point, tid, 256, dyn, sh);
     __syncthreads();
 
-    const InLane<KIN> ln(lane, R);
+    const InLane<KIN> ln(lane);
     double* lsum = nullptr;   // PP = 0: [2p + 1][64] sums of this wave's lanes
-    if constexpr (PP == 0) lsum = reinterpret_cast<double*>(dyn + (3 + p) * R + ((3 + p) * R & 1)) + wave * (2 * p + 1) * 64;
+    if constexpr (PP == 0) lsum = reinterpret_cast<double*>(in_phase(a, dyn) + (3 + p) * R + ((3 + p) * R & 1)) + wave * (2 * p + 1) * 64;
     const int first = u0 + wave * a.upw;
     const int last = min(first + a.upw, u1);
     const int nv = GRAD ? 2 * p + 1 : 1;
@@ -677,7 +725,7 @@ __global__ void __launch_bounds__(256, GRAD && PP == 0 ? 2 : 4) k_inner(InArgs a
         const int slot = u / a.chunks, ch = u - slot * a.chunks;
         const ConeIn& cd = a.cones[slot];
         double* out = a.chunks > 1 ? a.part + (static_cast<size_t>(point - a.point0) * a.units + u) * nv : nullptr;
-        in_unit<KIN, GRAD, PP, false>(a, cd, ch, a.chunks, lane, ln, dyn, sh, cfg_all[wave], lsum, [&](int code, double x) {
+        in_unit<KIN, GRAD, PP, false, SIGNS>(a, cd, ch, a.chunks, lane, ln, dyn, sh, cfg_all[wave], s_z[wave], lsum, [&](int code, double x) {
             if (out) out[code] = x;
             else if (code == 0) a.zz[static_cast<size_t>(point) * a.M + cd.orbit] = x;
             else a.g[(static_cast<size_t>(point) * 2 * p + (code - 1)) * a.M + cd.orbit] = x;
@@ -689,19 +737,23 @@ template <int KIN>
 hipError_t launch_inner_k(bool grad, const InArgs& a, hipStream_t st) {
     const int64_t blocks = static_cast<int64_t>(a.blocks) * a.P;
     if (blocks <= 0) return hipSuccess;
-    size_t lds = static_cast<size_t>(3 + a.p) * a.R * sizeof(float2);
+    size_t lds = in_rows_bytes(a);
     if (a.p > 2 && grad) lds += 8 + 4 * static_cast<size_t>(2 * a.p + 1) * 64 * sizeof(double);
     const dim3 grid(static_cast<unsigned>(blocks)), block(256);
-    if (a.p == 2) {
-        if (grad) hipLaunchKernelGGL((k_inner<KIN, true, 2>), grid, block, lds, st, a);
-        else hipLaunchKernelGGL((k_inner<KIN, false, 2>), grid, block, lds, st, a);
-    } else if constexpr (KIN >= 4) {   // p >= 3 leaves at least four inner qubits
-        if (grad) hipLaunchKernelGGL((k_inner<KIN, true, 0>), grid, block, lds, st, a);
-        else hipLaunchKernelGGL((k_inner<KIN, false, 0>), grid, block, lds, st, a);
-    } else {
-        return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    auto go = [&](auto S) {
+        constexpr bool SIGNS = decltype(S)::value;
+        if (a.p == 2) {
+            if (grad) hipLaunchKernelGGL((k_inner<KIN, true, 2, SIGNS>), grid, block, lds, st, a);
+            else hipLaunchKernelGGL((k_inner<KIN, false, 2, SIGNS>), grid, block, lds, st, a);
+        } else if constexpr (KIN >= 4) {   // p >= 3 leaves at least four inner qubits
+            if (grad) hipLaunchKernelGGL((k_inner<KIN, true, 0, SIGNS>), grid, block, lds, st, a);
+            else hipLaunchKernelGGL((k_inner<KIN, false, 0, SIGNS>), grid, block, lds, st, a);
+        } else {
+            return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    };
+    return a.signs ? go(std::true_type{}) : go(std::false_type{});
 }
 
 }  // namespace qaoa

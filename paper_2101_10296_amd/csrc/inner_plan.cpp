@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <cstdlib>
 #include <cstring>
 #include <new>
 #include <system_error>
@@ -13,7 +14,7 @@ namespace qaoa {
 
 bool ShellPlanner::Shape::same(const Shape& o) const {
     return kin == o.kin && grp.size() == o.grp.size() && std::memcmp(level, o.level, sizeof(level)) == 0 &&
-           std::memcmp(w, o.w, sizeof(w)) == 0 &&
+           std::memcmp(w, o.w, sizeof(w)) == 0 && std::memcmp(leaf, o.leaf, sizeof(leaf)) == 0 &&
            (grp.empty() || std::memcmp(grp.data(), o.grp.data(), grp.size() * sizeof(ShellGroup)) == 0);
 }
 
@@ -26,22 +27,34 @@ uint64_t mix64(uint64_t x) {
 }  // namespace
 
 // The configurations of a shell up to the symmetries that keep a term: automorphisms of the inner
-// qubits with their couplings, distance classes and shell groups (which may swap u and v), and the
-// flip of all qubits.  Configurations are tuples of digits, one per group (how many of its
-// qubits are 1).  Twins (qubits of one class that a transposition swaps, each with groups of its
-// own) are kept sorted by their digits; the remaining automorphisms, found by backtracking up to
-// orders of twins, and the flip map sorted tuples to each other, and the smallest image of each
-// orbit is listed with the weight of all its members.  What is listed depends on the shape
-// alone, so a term is the same in every plan.  Up to 1024 configurations are always listed
-// (under 0.3 ms of host time).  Beyond, up to 16384: at most 10 inner qubits, where a
-// configuration costs a wave under 1 us, where at least 16 symmetries shorten the list enough to
-// pay for it; more, where each occupies a compute unit for 37 us, with any symmetry at all (the
-// 47 cones of 26 to 30 qubits of a 3-regular graph on 80 nodes at p = 3 run 26573 configurations
-// instead of 59685).  No list: cfg stays empty.
+// qubits with their couplings, distance classes, leaves and shell groups (which may swap u and v),
+// and the flip of all qubits (which keeps a term for any signs).  Configurations are tuples of
+// digits, one per group (how many of its qubits are 1) and one per qubit with leaves (its sign).
+// Twins (qubits of one class that a transposition swaps, each with digits of its own) are kept
+// sorted by their digits; the remaining automorphisms, found by backtracking up to orders of
+// twins, and the flip map sorted tuples to each other, and the smallest image of each orbit is
+// listed with the weight of all its members.  What is listed depends on the shape alone, so a
+// term is the same in every plan.  Up to 1024 configurations are always listed (under 0.3 ms of
+// host time).  Beyond, up to 16384: at most 10 inner qubits, where a configuration costs a wave
+// under 1 us, where at least 16 symmetries shorten the list enough to pay for it; more, where
+// each occupies a compute unit for 37 us, with any symmetry at all.  No list: cfg stays empty.
 void ShellPlanner::Shape::enumerate() {
+    std::vector<ShellGroup> grp = this->grp;   // and one of a single qubit for each sign
+    const int n_real = static_cast<int>(grp.size());
+    for (uint32_t z = zmask; z; z &= z - 1) {
+        const int a = __builtin_ctz(z);
+        int like = 0;
+        while (std::memcmp(&leaf[like], &leaf[a], sizeof(leaf[a])) != 0) ++like;
+        ShellGroup g;
+        g.m = 1;
+        g.wsum = INT32_MIN + like;             // its leaves; no sum of couplings
+        g.h[a - 2] = 1;
+        grp.push_back(g);
+    }
     const int ng = static_cast<int>(grp.size());
+    const uint64_t n_tuple = static_cast<uint64_t>(nc) << (ng - n_real);
     std::vector<ShellCfg>& out = cfg;
-    if (nc <= 2 || nc > 16384 || ng > 16) return;
+    if (n_tuple < 2 || n_tuple > 16384 || ng > 16) return;
     for (const ShellGroup& q : grp)
         if (q.m > 15) return;
     // groups private to one inner qubit, and twin classes
@@ -140,7 +153,7 @@ void ShellPlanner::Shape::enumerate() {
     double order = static_cast<double>(H.size());
     for (const auto& c : classes)
         for (size_t i = 2; i <= c.size(); ++i) order *= static_cast<double>(i);
-    if (nc > 1024 && order < (kin > 10 ? 2.0 : 16.0)) return;
+    if (n_tuple > 1024 && order < (kin > 10 ? 2.0 : 16.0)) return;
     // a tuple as one word, group q's digit in nibble q
     auto digit = [](uint64_t t, int q) { return static_cast<int>((t >> (4 * q)) & 15u); };
     auto block = [&](uint64_t t, int x) {   // a twin's digits
@@ -167,14 +180,16 @@ void ShellPlanner::Shape::enumerate() {
         }
         return t;
     };
-    uint64_t full = 0;   // every qubit 1: the flip of t is full - t, nibble by nibble
-    for (int q = 0; q < ng; ++q) full |= static_cast<uint64_t>(grp[q].m) << (4 * q);
+    // every qubit of the groups 1: the flip of t is full - t, nibble by nibble, and keeps the signs
+    uint64_t full = 0;
+    for (int q = 0; q < n_real; ++q) full |= static_cast<uint64_t>(grp[q].m) << (4 * q);
+    const uint64_t digits = n_real < 16 ? (uint64_t{1} << (4 * n_real)) - 1 : ~uint64_t{0};
     uint64_t t = 0;
     std::vector<uint64_t> seen;
     double total = 0.0;
     int bits = 0;
     for (const ShellGroup& q : grp) bits += q.m;
-    for (uint32_t i = 0; i < nc; ++i) {
+    for (uint64_t i = 0; i < n_tuple; ++i) {
         if (i)
             for (int q = 0;; ++q) {
                 if (digit(t, q) < grp[q].m) {
@@ -193,7 +208,7 @@ void ShellPlanner::Shape::enumerate() {
             uint64_t im = 0;
             for (int q = 0; q < ng; ++q) im |= static_cast<uint64_t>(digit(t, q)) << (4 * pi[q]);
             uint64_t fl = full;   // groups map to groups of their size
-            fl = sort_twins(fl - im);
+            fl = sort_twins((fl - (im & digits)) | (im & ~digits));
             im = sort_twins(im);
             if (im < t || fl < t) {
                 least = false;
@@ -216,6 +231,11 @@ void ShellPlanner::Shape::enumerate() {
         ShellCfg e{};
         for (int q = 0; q < ng; ++q) {
             const ShellGroup& G = grp[q];
+            if (q >= n_real) {
+                for (int j = 0; j < SH_H; ++j)
+                    if (G.h[j] && digit(t, q)) e.z |= 1u << (j + 2);
+                continue;
+            }
             double b = 1.0;
             for (int i = 0; i < digit(t, q); ++i) b = b * (G.m - i) / (i + 1);
             n *= b;
@@ -252,7 +272,97 @@ int32_t ShellPlanner::find(uint64_t h) {
     return table_[i].second;
 }
 
+// A cone's own symmetries as far as they pay: inner qubits with equal couplings to u and v and equal
+// leaves are twins (a class of signs that count by their number), and swapping u and v may map
+// the classes to each other; none of it where neighbours are coupled.
+bool ShellPlanner::add_tree(const Cone& c, ShellCone& out) {
+    const int kin = c.nd[p_ - 1], ns = c.k - kin;
+    if (kin < 4 || kin > 6) return false;
+    int8_t owner[32];
+    std::memset(owner, -1, sizeof(owner));
+    int leaves[6] = {}, n_owned = 0, w0[6] = {}, w1[6] = {};
+    uint16_t code[6] = {};
+    bool coupled = false;
+    const size_t ne = c.ea.size();
+    for (size_t e = 0; e < ne; ++e) {
+        const int a = c.ea[e], b = c.eb[e], w = c.ew[e];
+        if (a >= kin || w == 0) continue;
+        if (b < kin) {
+            if (a == 0) w0[b] = w;
+            else if (a == 1) w1[b] = w;
+            else coupled = true;
+            continue;
+        }
+        const int x = std::abs(w);
+        if (owner[b] >= 0 || x > 3 || ++leaves[a] > 6) return false;
+        owner[b] = static_cast<int8_t>(a);
+        ++n_owned;
+        code[a] = static_cast<uint16_t>(code[a] + (x == 1 ? 1 : x == 2 ? 7 : 49));
+    }
+    if (n_owned != ns) return false;
+    out.kin = kin;
+    out.tree = true;
+    out.nc = 1;
+    out.n_leaf = ns;
+    out.w_leaf = 0;   // they are not among its couplings
+    out.edge = static_cast<int64_t>(ea.size());
+    for (size_t e = 0; e < ne; ++e)
+        if (c.eb[e] < kin) {
+            ea.push_back(c.ea[e]);
+            eb.push_back(c.eb[e]);
+            ew.push_back(c.ew[e]);
+        }
+    out.n_edges = static_cast<int32_t>(static_cast<int64_t>(ea.size()) - out.edge);
+    out.zmask = 0;
+    int cls[4] = {0, 0, 0, 0}, first[4], n_cls = 0, size[4] = {};
+    for (int q = 2; q < kin; ++q) {
+        out.leaf[q - 2] = code[q];
+        if (code[q]) out.zmask |= 1u << q;
+        int i = coupled ? n_cls : 0;
+        while (i < n_cls && (w0[first[i]] != w0[q] || w1[first[i]] != w1[q] || code[first[i]] != code[q])) ++i;
+        if (i == n_cls) first[n_cls++] = q;
+        cls[q - 2] = i;
+        ++size[i];
+    }
+    int swap[4] = {0, 1, 2, 3};
+    bool ok = !coupled;
+    for (int i = 0; i < n_cls && ok; ++i) {
+        int j = 0;
+        while (j < n_cls && (w0[first[i]] != w1[first[j]] || w1[first[i]] != w0[first[j]] || code[first[i]] != code[first[j]])) ++j;
+        ok = j < n_cls && size[i] == size[j];
+        swap[i] = j;
+    }
+    out.signs = out.zmask >> 2;
+    for (int i = 0; i < 4; ++i) out.signs |= static_cast<uint32_t>(cls[i] << (4 + 2 * i) | (ok ? swap[i] : i) << (12 + 2 * i));
+    return true;
+}
+
+std::vector<uint32_t> tree_signs(uint32_t signs) {
+    auto field = [&](int at) { return static_cast<int>((signs >> at) & 3u); };
+    std::vector<uint32_t> out;
+    uint16_t key[16];
+    for (uint32_t z = 0; z < 16; ++z) {
+        if (z & ~signs & 15u) continue;
+        int n[4] = {}, a = 0, b = 0;
+        for (int q = 0; q < 4; ++q) n[field(4 + 2 * q)] += static_cast<int>((z >> q) & 1u);
+        for (int i = 0; i < 4; ++i) {
+            a = a * 8 + n[i];
+            b = b * 8 + n[field(12 + 2 * i)];
+        }
+        const uint16_t k = static_cast<uint16_t>(std::min(a, b));
+        size_t i = 0;
+        while (i < out.size() && key[i] != k) ++i;
+        if (i == out.size()) {
+            key[i] = k;
+            out.push_back(z << 2);
+        }
+        out[i] += 1u << 8;
+    }
+    return out;
+}
+
 void ShellPlanner::add_one(const Cone& c, ShellCone& out) {
+    if (trees_ && add_tree(c, out)) return;
     const int kin = c.nd[p_ - 1], ns = c.k - kin;
     const size_t ne = c.ea.size();
     out.kin = kin;
@@ -309,7 +419,61 @@ void ShellPlanner::add_one(const Cone& c, ShellCone& out) {
         }
     }
     out.n_edges = static_cast<int32_t>(static_cast<int64_t>(ea.size()) - out.edge);
+    // leaves: shell qubits with one coupling, at inner qubits that have two or more
+    int owner[32];
+    std::fill(std::begin(s_.leaf), std::end(s_.leaf), ShellLeaves{});
+    s_.zmask = 0;
+    out.n_leaf = out.w_leaf = 0;
+    int n_of[SH_KMAX] = {};
+    for (int q = 0; q < ns; ++q) {
+        owner[q] = -1;
+        int n = 0, at = 0;
+        for (int i = 0; i < SH_H; ++i)
+            if (h[q][i]) {
+                ++n;
+                at = i + 2;
+            }
+        if (n != 1) continue;
+        owner[q] = at;
+        ++n_of[at];
+    }
+    for (int q = 0; q < ns; ++q) {
+        const int a = owner[q];
+        if (a < 0 || n_of[a] < 2) continue;
+        const int x = std::abs(h[q][a - 2]);
+        ShellLeaves& L = s_.leaf[a];
+        int i = 0;
+        while (i < ZL_W && L.m[i] && L.w[i] != x) ++i;
+        if (i == ZL_W) {   // too many couplings
+            L = ShellLeaves{};
+            n_of[a] = 0;
+            s_.zmask &= ~(1u << a);
+            continue;
+        }
+        L.w[i] = static_cast<int16_t>(x);
+        ++L.m[i];
+        s_.zmask |= 1u << a;
+    }
+    for (int a = 2; a < kin; ++a) {   // by coupling, so that equal leaves compare equal
+        ShellLeaves& L = s_.leaf[a];
+        for (int i = 1; i < ZL_W; ++i)
+            for (int j = i; j > 0 && L.m[j] && L.w[j] < L.w[j - 1]; --j) {
+                std::swap(L.w[j], L.w[j - 1]);
+                std::swap(L.m[j], L.m[j - 1]);
+            }
+        for (int i = 0; i < ZL_W; ++i) {
+            const uint64_t x = static_cast<uint64_t>(a) << 32 | static_cast<uint64_t>(static_cast<uint16_t>(L.w[i])) << 16 |
+                               static_cast<uint16_t>(L.m[i]);
+            if (L.m[i]) hash += mix64(~x);
+        }
+    }
+    out.zmask = s_.zmask;
     for (int q = 0; q < ns; ++q) {   // groups sorted by their couplings
+        if (owner[q] >= 0 && (s_.zmask >> owner[q] & 1u)) {
+            ++out.n_leaf;
+            out.w_leaf += h[q][owner[q] - 2];
+            continue;
+        }
         size_t i = 0;
         int cmp = 1;
         while (i < s_.grp.size() && (cmp = std::memcmp(s_.grp[i].h, h[q], sizeof(h[q]))) < 0) ++i;
@@ -343,7 +507,7 @@ void ShellPlanner::add(const std::vector<const Cone*>& cones, std::vector<ShellC
         for (size_t i = 0; i < n; ++i) add_one(*cones[i], out[i]);
         return;
     }
-    std::vector<ShellPlanner> part(nt, ShellPlanner(p_));
+    std::vector<ShellPlanner> part(nt, ShellPlanner(p_, trees_));
     std::atomic<bool> no_mem{false};
     auto work = [&](size_t t) {
         try {
@@ -375,7 +539,7 @@ void ShellPlanner::add(const std::vector<const Cone*>& cones, std::vector<ShellC
         }
         for (size_t i = t * n / nt; i < (t + 1) * n / nt; ++i) {
             out[i].edge += e0;
-            out[i].shape = to[static_cast<size_t>(out[i].shape)];
+            if (!out[i].tree) out[i].shape = to[static_cast<size_t>(out[i].shape)];
         }
     }
 }
@@ -396,7 +560,7 @@ void ShellPlanner::list() {
             todo[i]->listed = true;
         }
     };
-    const size_t nt = std::min<size_t>({8, std::max(1u, std::thread::hardware_concurrency()), todo.size() / 8 + 1});
+    const size_t nt = std::min<size_t>({8, std::max(1u, std::thread::hardware_concurrency()), todo.size() / 32 + 1});
     std::vector<std::thread> pool;
     try {
         for (size_t t = 1; t < nt; ++t) pool.emplace_back(work);

@@ -6,6 +6,7 @@
 #include <vector>
 
 #include "plan.hpp"
+#include "shell_limits.hpp"
 
 namespace qaoa {
 
@@ -19,10 +20,19 @@ struct ShellGroup {
     int32_t h[SH_H] = {};      // coupling to inner qubit 2 + i
 };
 
-// One configuration up to symmetry: c0 + sum_a x_a h_a is what the shell adds to C_in(x).
+// The shell qubits that couple to one inner qubit only, two or more of them: m[i] of coupling
+// +-w[i] (see shell.hpp; a qubit with more than ZL_W different couplings keeps them as groups).
+struct ShellLeaves {
+    int16_t w[ZL_W] = {};
+    int16_t m[ZL_W] = {};
+};
+
+// One configuration up to symmetry: c0 + sum_a x_a h_a is what the shell's groups add to C_in(x), and
+// z the signs of the inner qubits with leaves.
 struct ShellCfg {
     int16_t h[SH_H] = {};
     int32_t c0 = 0;
+    uint32_t z = 0;
     double w = 0.0;            // configurations that it stands for
 };
 
@@ -32,19 +42,31 @@ struct ShellCone {
     int32_t kin = 0;
     int64_t edge = 0;          // couplings with an inner end, in that order (ea < eb): ShellPlanner's arrays
     int32_t n_edges = 0;
-    uint32_t nc = 0;           // configurations: product of (m + 1) over the groups, at most 2^28
+    uint32_t nc = 0;           // states of the groups: product of (m + 1), at most 2^28
+    uint32_t zmask = 0;        // inner qubits with leaves
+    // the shell is leaves only (see ShellPlanner): the choices of leaves of qubits 2 .. 5 (n_1 + 7 n_2
+    // + 49 n_3, n_w of coupling +-w) and which signs are equal up to symmetry (tree_signs)
+    bool tree = false;
+    uint16_t leaf[4] = {};
+    uint32_t signs = 0;
+    int32_t n_leaf = 0;        // their leaves
+    int32_t w_leaf = 0;        // and the sum of the couplings
+    uint32_t runs() const { return ((nc + 1) / 2) << __builtin_popcount(zmask); }   // without a list
     int32_t shape = -1;        // cones of one shape share groups and configurations
 };
 
 class ShellPlanner {
 public:
-    explicit ShellPlanner(int32_t p) : p_(p) {}
+    // trees: cones of 4 to 6 inner qubits whose shell qubits are all leaves, at most 6 per inner qubit
+    // and of couplings up to 3, get no shape: they keep the cone's order and its inner couplings
+    explicit ShellPlanner(int32_t p, bool trees = false) : p_(p), trees_(trees) {}
     // the cones in order (0.6 us of host time each: on several threads from 4096 cones on)
     void add(const std::vector<const Cone*>& cones, std::vector<ShellCone>& out);
     // Lists the configurations of every shape seen so far that has none yet (several threads).
     void list();
     // null: no list, every configuration is run
     const std::vector<ShellCfg>* configurations(int32_t shape) const;
+    const ShellLeaves* leaves(int32_t shape) const { return shapes_[static_cast<size_t>(shape)].leaf; }   // [SH_KMAX]
     const std::vector<ShellGroup>& groups(int32_t shape) const { return shapes_[static_cast<size_t>(shape)].grp; }
     std::vector<int32_t> ea, eb, ew;   // couplings of all cones
 
@@ -54,6 +76,8 @@ private:
         uint8_t level[SH_KMAX] = {};      // distance of each inner qubit
         int16_t w[SH_KMAX][SH_KMAX] = {}; // couplings between inner qubits
         std::vector<ShellGroup> grp;
+        ShellLeaves leaf[SH_KMAX];
+        uint32_t zmask = 0;
         uint32_t nc = 0;
         uint64_t hash = 0;
         bool listed = false;
@@ -62,11 +86,16 @@ private:
         void enumerate();
     };
     int32_t p_;
+    bool trees_;
     std::vector<Shape> shapes_;
     std::vector<std::pair<uint64_t, int32_t>> table_;   // open addressing by hash
     Shape s_;                                            // the cone being added
     int32_t find(uint64_t h);                            // shape of s_
     void add_one(const Cone& c, ShellCone& out);
+    bool add_tree(const Cone& c, ShellCone& out);
 };
+
+// The signs of a tree up to its symmetries: z | number << 8, from ShellCone::signs.
+std::vector<uint32_t> tree_signs(uint32_t signs);
 
 }  // namespace qaoa

@@ -11,7 +11,7 @@
 // Bound: the serial chain of one unit (phase rows, descriptors and tables through L2, then about
 // 2000 instructions of one wave).  Energy and gradient of C_10000(1,2) at p = 2 (inner states of
 // 6 and 7 qubits, one unit each), one point: 18.8 us a call in three launches, 13.6 here.
-#include "inner_impl.hpp"
+#include "inner_tree_impl.hpp"
 
 namespace qaoa {
 namespace {
@@ -19,9 +19,11 @@ namespace {
 template <bool GRAD, int PP>
 __global__ void __launch_bounds__(64 * in_point_waves(GRAD, PP), GRAD && PP == 0 ? 2 : 4)
 k_inner_point(InArgs a, InPoint q) {
-    extern __shared__ float2 dyn[];   // phase rows; then (PP = 0) sums
+    extern __shared__ __attribute__((aligned(16))) float2 dyn[];   // cosines and phase rows; then (PP = 0) sums
     __shared__ InShared sh;
-    __shared__ double s_val[IN_POINT][2 * IN_PMAX + 1];    // units
+    __shared__ double2 s_z[in_point_waves(GRAD, PP)][16];
+    __shared__ double2 s_typ[PP == 2 ? TR_TYPES : 1];
+    __shared__ double s_val[IN_POINT][2 * IN_PMAX + 1];    // parts of cones
     __shared__ double s_term[IN_POINT][2 * IN_PMAX + 1];   // orbits
     const int tid = threadIdx.x, lane = tid & 63, waves = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -30,17 +32,36 @@ k_inner_point(InArgs a, InPoint q) {
     const int point = blockIdx.x + a.point0;
     in_rows(a, p, 0, point, tid, blockDim.x, dyn, sh);
     __syncthreads();
+    if (PP == 2 && a.n_types) {
+        tr_types(a, tid, blockDim.x, dyn, s_typ);
+        __syncthreads();
+    }
     double* lsum = nullptr;
-    if constexpr (PP == 0) lsum = reinterpret_cast<double*>(dyn + (3 + p) * R + ((3 + p) * R & 1)) + wave * (2 * p + 1) * 64;
+    if constexpr (PP == 0) lsum = reinterpret_cast<double*>(in_phase(a, dyn) + (3 + p) * R + ((3 + p) * R & 1)) + wave * (2 * p + 1) * 64;
     for (int u = wave; u < q.n; u += waves) {
         const InPoint::Unit un = q.unit[u];
+        if constexpr (PP == 2) {
+            if (un.rows) {
+                auto rows = [&](auto K) {
+                    constexpr int KIN = decltype(K)::value;
+                    const InLane<KIN - 1> ln(lane);
+                    const int r = lane >> 4;
+                    tr_row<KIN, GRAD>(a, a.tr + un.cone + min(r, un.rows - 1), r < un.rows, lane, ln, dyn, s_typ, sh,
+                                      [&](int, int code, double x) { s_val[un.part + r][code] = x; });
+                };
+                if (un.kin == 4) rows(std::integral_constant<int, 4>{});
+                else if (un.kin == 5) rows(std::integral_constant<int, 5>{});
+                else rows(std::integral_constant<int, 6>{});
+                continue;
+            }
+        }
         const ConeIn& cd = a.cones[un.cone];
         auto run = [&](auto K) {
             constexpr int KIN = decltype(K)::value;
             if constexpr (KIN >= 4 || PP == 2) {
-                const InLane<KIN> ln(lane, R);
-                in_unit<KIN, GRAD, PP, true>(a, cd, un.chunk, un.chunks, lane, ln, dyn, sh, nullptr, lsum,
-                                             [&](int code, double x) { s_val[u][code] = x; });
+                const InLane<KIN> ln(lane);
+                in_unit<KIN, GRAD, PP, true, true>(a, cd, un.chunk, un.chunks, lane, ln, dyn, sh, nullptr, s_z[wave], lsum,
+                                             [&](int code, double x) { s_val[un.part][code] = x; });
             }
         };
         switch (un.kin) {
@@ -61,13 +82,13 @@ k_inner_point(InArgs a, InPoint q) {
     const int y = tid;
     const double delta = a.deltas[0];
     const double gs = y >= 1 && y <= p && a.g ? delta : 1.0;   // the caller's terms are in radians
-    for (int u = 0; u < q.n;) {
-        const InPoint::Unit un = q.unit[u];
+    for (int u = 0; u < q.n_part;) {
+        const InPoint::Part pt = q.part[u];
         double x = 0.0;
-        for (int c = 0; c < un.chunks; ++c) x += s_val[u + c][y];
-        u += un.chunks;
+        for (int c = 0; c < pt.chunks; ++c) x += s_val[u + c][y];
+        u += pt.chunks;
         x *= gs;
-        const int m = un.orbit;
+        const int m = pt.orbit;
         s_term[m][y] = x;
         if (y == 0) {
             if (a.zz) a.zz[static_cast<size_t>(point) * a.M + m] = x;
@@ -93,10 +114,10 @@ k_inner_point(InArgs a, InPoint q) {
 }  // namespace
 
 hipError_t launch_inner_point(const InArgs& a0, const InPoint& q, bool grad, int64_t n_points, hipStream_t st) {
-    if (q.n < 1 || q.n > IN_POINT || a0.M > IN_POINT || a0.p < 2 || a0.p > IN_PMAX) return hipErrorInvalidValue;
+    if (q.n < 1 || q.n > IN_POINT || q.n_part > IN_POINT || a0.M > IN_POINT || a0.p < 2 || a0.p > IN_PMAX) return hipErrorInvalidValue;
     const bool sums = a0.p > 2 && grad;
     const int waves = std::min<int>(q.n, in_point_waves(grad, a0.p == 2 ? 2 : 0));
-    size_t lds = static_cast<size_t>(3 + a0.p) * a0.R * sizeof(float2);
+    size_t lds = in_rows_bytes(a0);
     if (sums) lds += 8 + static_cast<size_t>(waves) * (2 * a0.p + 1) * 64 * sizeof(double);
     // a grid holds fewer than 2^32 threads
     const int64_t CH = static_cast<int64_t>(UINT32_MAX) / (64 * waves);

@@ -356,6 +356,9 @@ struct InnerHost {
     std::vector<GrpIn> grp;
     std::vector<int32_t> seg;
     std::vector<CfgList> cfg;
+    std::vector<ZLeaf> leaf, types;
+    std::vector<ConeTr> tr;
+    std::vector<uint32_t> trcfg;
     int64_t tab_units = 0;   // table bytes / 16
 };
 
@@ -381,7 +384,26 @@ void layer_cuts(const Cone& c, const ShellPlanner& sp, const ShellCone& q, int32
         mid[l] = static_cast<float>(0.5 * wl - cut_min);
     }
     base[1] = base[2];
-    mid[1] = static_cast<float>(0.5 * w_all - cut_min);
+    mid[1] = static_cast<float>(0.5 * (w_all - q.w_leaf) - cut_min);
+}
+
+// Where the leaves of a cone's shape stand (16 entries, shared by the shape's cones); wz: largest coupling.
+int32_t place_leaves(const ShellPlanner& sp, const ShellCone& q, std::vector<int32_t>& at, std::vector<ZLeaf>& out, int32_t& wz) {
+    if (!q.zmask) return 0;
+    if (at.size() <= static_cast<size_t>(q.shape)) at.resize(static_cast<size_t>(q.shape) + 1, -1);
+    int32_t& a = at[static_cast<size_t>(q.shape)];
+    if (a < 0) {
+        a = static_cast<int32_t>(out.size());
+        out.resize(out.size() + 16, ZLeaf{});
+        const ShellLeaves* L = sp.leaves(q.shape);
+        for (int i = 0; i < q.kin; ++i)
+            for (int j = 0; j < ZL_W; ++j) {
+                out[static_cast<size_t>(a + i)].w[j] = L[i].w[j];
+                out[static_cast<size_t>(a + i)].m[j] = L[i].m[j];
+                wz = std::max<int32_t>(wz, L[i].w[j]);
+            }
+    }
+    return a;
 }
 
 // Fills P->in_groups and the descriptors for the orbits in ord; their edges are appended to ea, eb, ew.
@@ -393,26 +415,44 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
     P->in_groups.clear();
     P->in_inst.clear();
     P->in_max_k = 0;   // build_wide adds its own
+    P->wz = 0;
     if (ord.empty()) return;
     auto is_wh = [&](int64_t m) { return !member.empty() && member[static_cast<size_t>(m)] != 0; };
-    auto kin_of = [&](int64_t m) { return static_cast<int>(hp.cones[m].nd[p - 1]); };
-    std::stable_sort(ord.begin(), ord.end(), [&](int64_t a, int64_t b) {
-        const int x = kin_of(a), y = kin_of(b);
-        if (x != y) return x < y;
-        if (by_k && hp.cones[a].k != hp.cones[b].k) return hp.cones[a].k < hp.cones[b].k;
-        return is_wh(a) < is_wh(b);
-    });
     in.cones.reserve(ord.size());
-    ShellPlanner shells(p);
+    ShellPlanner shells(p, p == 2);
     std::vector<ShellCone> sc;
-    std::vector<const Cone*> list_of(ord.size());
-    for (size_t i = 0; i < ord.size(); ++i) list_of[i] = &hp.cones[static_cast<size_t>(ord[i])];
-    shells.add(list_of, sc);
+    {
+        std::vector<const Cone*> list_of(ord.size());
+        for (size_t i = 0; i < ord.size(); ++i) list_of[i] = &hp.cones[static_cast<size_t>(ord[i])];
+        std::vector<ShellCone> raw;
+        shells.add(list_of, raw);
+        std::vector<std::pair<uint32_t, int32_t>> by(ord.size());   // class, place in ord
+        for (size_t i = 0; i < by.size(); ++i) {
+            const ShellCone& q = raw[i];
+            const uint32_t k = by_k ? static_cast<uint32_t>(list_of[i]->k) : 0u;
+            by[i] = {static_cast<uint32_t>(q.kin) << 9 | k << 3 | (is_wh(ord[i]) ? 4u : 0u) | (q.tree ? 2u : 0u) | (q.zmask ? 1u : 0u),
+                     static_cast<int32_t>(i)};
+        }
+        std::sort(by.begin(), by.end());
+        std::vector<int64_t> sorted(ord.size());
+        sc.resize(ord.size());
+        for (size_t i = 0; i < by.size(); ++i) {
+            sorted[i] = ord[static_cast<size_t>(by[i].second)];
+            sc[i] = raw[static_cast<size_t>(by[i].second)];
+        }
+        ord.swap(sorted);
+    }
     shells.list();
     const int64_t edge0 = static_cast<int64_t>(ea.size());
     ea.insert(ea.end(), shells.ea.begin(), shells.ea.end());
     eb.insert(eb.end(), shells.eb.begin(), shells.eb.end());
     ew.insert(ew.end(), shells.ew.begin(), shells.ew.end());
+    std::vector<int32_t> leaf_at;
+    std::vector<std::pair<uint32_t, std::pair<int32_t, int32_t>>> lists;   // signs of trees: first, number
+    int16_t type_of[512];
+    std::fill(std::begin(type_of), std::end(type_of), int16_t{-1});
+    type_of[0] = 0;
+    in.types.push_back(ZLeaf{});
     std::vector<int32_t> listed_at;   // first entry of each shape's list, -1: not placed yet
     std::vector<uint32_t> rounds;
     rounds.reserve(ord.size());
@@ -426,11 +466,16 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         d.inst = c.inst;
         d.kin = q.kin;
         layer_cuts(c, shells, q, p, hp.cut_min, d.mixed, d.base, d.mid);
-        d.shell_norm = std::ldexp(1.0, -(c.k - q.kin));
+        d.shell_norm = std::ldexp(1.0, -(c.k - q.kin - q.n_leaf));
         d.nc = q.nc;
         d.cfg_off = -1;
-        uint32_t runs = (q.nc + 1) / 2;
-        if (const std::vector<ShellCfg>* list = shells.configurations(q.shape)) {
+        const bool tree = q.tree;
+        d.zmask = q.zmask;
+        if (!tree) d.z_off = place_leaves(shells, q, leaf_at, in.leaf, P->wz);
+        uint32_t runs = q.runs();
+        if (tree) {   // its own list, below
+            runs = 1;
+        } else if (const std::vector<ShellCfg>* list = shells.configurations(q.shape)) {
             if (listed_at.size() <= static_cast<size_t>(q.shape)) listed_at.resize(static_cast<size_t>(q.shape) + 1, -1);
             int32_t& at = listed_at[static_cast<size_t>(q.shape)];
             d.n_cfg = static_cast<uint32_t>((list->size() + cpw - 1) / cpw * cpw);   // whole rounds
@@ -441,6 +486,7 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
                     CfgList y{};
                     std::copy_n(x.h, 8, y.h);
                     y.c0 = x.c0;
+                    y.z = x.z;
                     y.w = e < list->size() ? x.w : 0.0;
                     in.cfg.push_back(y);
                 }
@@ -466,17 +512,47 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         d.n_edges = q.n_edges;
         const int kk = by_k ? c.k : 0;
         if (P->in_groups.empty() || P->in_groups.back().kin != q.kin || P->in_groups.back().K != kk ||
-            P->in_groups.back().wh != is_wh(m)) {
+            P->in_groups.back().wh != is_wh(m) || P->in_groups.back().tree != tree ||
+            P->in_groups.back().signs != (q.zmask != 0)) {
             qaoa_plan_s::InGroup g{};
             g.kin = q.kin;
             g.K = kk;
             g.wh = is_wh(m);
+            g.signs = q.zmask != 0;
+            g.tree = tree;
+            g.tr = static_cast<int64_t>(in.tr.size());
             g.first = static_cast<int64_t>(in.cones.size());
             P->in_groups.push_back(g);
         }
         P->in_groups.back().count += 1;
         P->in_max_k = std::max(P->in_max_k, c.k);
         P->in_inst.push_back(c.inst);
+        if (tree) {
+            size_t l = 0;   // few
+            while (l < lists.size() && lists[l].first != q.signs) ++l;
+            if (l == lists.size()) {
+                const std::vector<uint32_t> z = tree_signs(q.signs);
+                lists.push_back({q.signs, {static_cast<int32_t>(in.trcfg.size()), static_cast<int32_t>(z.size())}});
+                in.trcfg.insert(in.trcfg.end(), z.begin(), z.end());
+            }
+            uint32_t types = 0;
+            for (int i = 0; i < q.kin - 2; ++i) {
+                const int code = q.leaf[i];
+                if (type_of[code] < 0) {
+                    type_of[code] = static_cast<int16_t>(in.types.size());
+                    ZLeaf z{};
+                    for (int x = 1, n = 0, r = code; x <= TR_W; ++x, r /= TR_M + 1)
+                        if (r % (TR_M + 1)) {
+                            z.w[n] = static_cast<int16_t>(x);
+                            z.m[n++] = static_cast<int16_t>(r % (TR_M + 1));
+                            P->wz = std::max(P->wz, x);
+                        }
+                    in.types.push_back(z);
+                }
+                types |= static_cast<uint32_t>(type_of[code]) << (8 * i);
+            }
+            in.tr.push_back({d.orbit, d.tab_off, lists[l].second.first, lists[l].second.second, types, d.base[2], d.mid[2], 0});
+        }
         in.cones.push_back(d);
     }
     for (auto& g : P->in_groups) {
@@ -492,7 +568,7 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
             max_k = std::max(max_k, hp.cones[static_cast<size_t>(in.cones[static_cast<size_t>(i)].orbit)].k);
         }
         int64_t ch = 1;
-        if (max_k > P->opt.k_lds_max) {
+        if (max_k > P->opt.k_lds_max && !g.tree) {
             ch = (most + IN_ROUNDS - 1) / IN_ROUNDS;
             if (ch * g.count < 1024) ch = std::min<int64_t>((most + 1) / 2, std::max<int64_t>(ch, 1024 / g.count));
         }
@@ -509,7 +585,7 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         unit.push_back(static_cast<int32_t>(g.count * ch));
         g.n_seg = static_cast<int32_t>(inst.size());
         for (int j = 0; j < 4; ++j) {
-            const int32_t per = 4 << j;
+            const int32_t per = (g.tree ? 16 : 4) << j;   // a cone per row of a wave
             int32_t b = 0;
             std::vector<int32_t> blk;
             for (int32_t q = 0; q < g.n_seg; ++q) {
@@ -543,17 +619,25 @@ void build_point(qaoa_plan_s* P, const InnerHost& in) {
     if (P->hp.n_inst != 1 || M > IN_POINT || in.cones.size() != M || !P->wh_groups.empty() || P->opt.profile ||
         P->opt.tune != 0 || P->opt.one_cone_at_a_time)
         return;
-    const size_t rows = static_cast<size_t>(3 + P->hp.p) * (P->hp.cut_max - P->hp.cut_min + 1) * sizeof(float2);
+    const size_t rows = static_cast<size_t>(3 + P->hp.p) * (P->hp.cut_max - P->hp.cut_min + 1) * sizeof(float2) +
+                        static_cast<size_t>(P->wz + 1) * sizeof(double2);
     const size_t sums = P->hp.p > 2 ? static_cast<size_t>(in_point_waves(true, 0)) * (2 * P->hp.p + 1) * 512 : 0;
     if (rows + sums > IN_POINT_LDS) return;
     InPoint q{};
+    auto u16 = [](int64_t x) { return static_cast<uint16_t>(x); };
     for (const auto& g : P->in_groups)
         for (int64_t i = g.first; i < g.first + g.count; ++i) {
             const ConeIn& c = in.cones[static_cast<size_t>(i)];
-            if (c.cfg_off < 0 || q.n + g.chunks > IN_POINT) return;
-            for (int32_t ch = 0; ch < g.chunks; ++ch)
-                q.unit[q.n++] = {static_cast<uint16_t>(i), static_cast<uint16_t>(ch), static_cast<uint16_t>(g.chunks),
-                                 static_cast<uint16_t>(c.orbit), c.kin};
+            const int64_t t = i - g.first;   // trees: four of a class to a wave
+            if (!g.tree && c.cfg_off < 0) return;
+            if (q.n_part + g.chunks > IN_POINT || q.n + g.chunks > IN_POINT) return;
+            if (g.tree && t % 4 == 0)
+                q.unit[q.n++] = {u16(g.tr + t), 0, 1, u16(q.n_part), static_cast<uint8_t>(c.kin),
+                                 static_cast<uint8_t>(std::min<int64_t>(4, g.count - t))};
+            for (int32_t ch = 0; ch < g.chunks; ++ch) {
+                if (!g.tree) q.unit[q.n++] = {u16(i), u16(ch), u16(g.chunks), u16(q.n_part), static_cast<uint8_t>(c.kin), 0};
+                q.part[q.n_part++] = {u16(g.chunks), u16(c.orbit)};
+            }
         }
     P->in_point = q;
 }
@@ -563,6 +647,7 @@ struct WideHost {
     std::vector<UnitWd> units;
     std::vector<GrpWd> grp;
     std::vector<CfgWd> cfg;
+    std::vector<ZLeaf> leaf;
     int64_t tab_bytes = 0;
 };
 
@@ -592,6 +677,7 @@ void build_wide(qaoa_plan_s* P, std::vector<int64_t>& ord, std::vector<int32_t>&
     ea.insert(ea.end(), shells.ea.begin(), shells.ea.end());
     eb.insert(eb.end(), shells.eb.begin(), shells.eb.end());
     ew.insert(ew.end(), shells.ew.begin(), shells.ew.end());
+    std::vector<int32_t> leaf_at;
     std::vector<int32_t> listed_at;   // first entry of each shape's list, -1: not placed yet
     for (size_t i = 0; i < ord.size(); ++i) {
         const Cone& c = hp.cones[static_cast<size_t>(ord[i])];
@@ -602,9 +688,11 @@ void build_wide(qaoa_plan_s* P, std::vector<int64_t>& ord, std::vector<int32_t>&
         d.kin = q.kin;
         d.nc = q.nc;
         layer_cuts(c, shells, q, p, hp.cut_min, d.mixed, d.base, d.mid);
-        d.shell_norm = std::ldexp(1.0, -(c.k - q.kin));
+        d.shell_norm = std::ldexp(1.0, -(c.k - q.kin - q.n_leaf));
         d.cfg_off = -1;
-        d.n_cfg = (q.nc + 1) / 2;
+        d.zmask = q.zmask;
+        d.z_off = place_leaves(shells, q, leaf_at, w.leaf, P->wz);
+        d.n_cfg = q.runs();
         if (const std::vector<ShellCfg>* list = shells.configurations(q.shape)) {
             if (listed_at.size() <= static_cast<size_t>(q.shape)) listed_at.resize(static_cast<size_t>(q.shape) + 1, -1);
             int32_t& at = listed_at[static_cast<size_t>(q.shape)];
@@ -614,6 +702,7 @@ void build_wide(qaoa_plan_s* P, std::vector<int64_t>& ord, std::vector<int32_t>&
                     CfgWd y{};
                     std::copy_n(x.h, SH_H, y.h);
                     y.c0 = x.c0;
+                    y.z = x.z;
                     y.w = x.w;
                     w.cfg.push_back(y);
                 }
@@ -861,7 +950,12 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     const size_t o_dco = has_wd ? place(wd.cones.size() * sizeof(ConeWd)) : 0;
     const size_t o_dun = has_wd ? place(wd.units.size() * sizeof(UnitWd)) : 0;
     const size_t o_dgr = has_wd ? place(wd.grp.size() * sizeof(GrpWd)) : 0;
+    const size_t o_dlf = has_wd ? place(wd.leaf.size() * sizeof(ZLeaf)) : 0;
+    const size_t o_ilf = has_in ? place(in.leaf.size() * sizeof(ZLeaf)) : 0;
     const size_t o_dcf = has_wd ? place(wd.cfg.size() * sizeof(CfgWd)) : 0;
+    const size_t o_itr = has_in ? place(in.tr.size() * sizeof(ConeTr)) : 0;
+    const size_t o_itc = has_in ? place(in.trcfg.size() * sizeof(uint32_t)) : 0;
+    const size_t o_ity = has_in ? place(in.types.size() * sizeof(ZLeaf)) : 0;
     const size_t o_ic = has_in ? place(in.cfg.size() * sizeof(CfgList)) : 0;
     const size_t o_is = has_in ? place(in.seg.size() * sizeof(int32_t)) : 0;
     const size_t copied = arena;
@@ -905,11 +999,16 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
             put(o_dco, wd.cones.data(), wd.cones.size() * sizeof(ConeWd));
             put(o_dun, wd.units.data(), wd.units.size() * sizeof(UnitWd));
             put(o_dgr, wd.grp.data(), wd.grp.size() * sizeof(GrpWd));
+            put(o_dlf, wd.leaf.data(), wd.leaf.size() * sizeof(ZLeaf));
             put(o_dcf, wd.cfg.data(), wd.cfg.size() * sizeof(CfgWd));
         }
         if (has_in) {
             put(o_in, in.cones.data(), in.cones.size() * sizeof(ConeIn));
             put(o_ig, in.grp.data(), in.grp.size() * sizeof(GrpIn));
+            put(o_itr, in.tr.data(), in.tr.size() * sizeof(ConeTr));
+            put(o_itc, in.trcfg.data(), in.trcfg.size() * sizeof(uint32_t));
+            put(o_ity, in.types.data(), in.types.size() * sizeof(ZLeaf));
+            put(o_ilf, in.leaf.data(), in.leaf.size() * sizeof(ZLeaf));
             put(o_ic, in.cfg.data(), in.cfg.size() * sizeof(CfgList));
             put(o_is, in.seg.data(), in.seg.size() * sizeof(int32_t));
         }
@@ -944,10 +1043,16 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     P->d_wd = has_wd ? reinterpret_cast<ConeWd*>(base + o_dco) : nullptr;
     P->d_wdunit = has_wd ? reinterpret_cast<UnitWd*>(base + o_dun) : nullptr;
     P->d_wdgrp = has_wd ? reinterpret_cast<GrpWd*>(base + o_dgr) : nullptr;
+    P->d_wdleaf = has_wd ? reinterpret_cast<ZLeaf*>(base + o_dlf) : nullptr;
     P->d_wdcfg = has_wd ? reinterpret_cast<CfgWd*>(base + o_dcf) : nullptr;
     P->d_wdtab = has_wd ? base + o_dta : nullptr;
     P->d_in = has_in ? reinterpret_cast<ConeIn*>(base + o_in) : nullptr;
     P->d_ingrp = has_in ? reinterpret_cast<GrpIn*>(base + o_ig) : nullptr;
+    P->d_tr = has_in ? reinterpret_cast<ConeTr*>(base + o_itr) : nullptr;
+    P->d_trcfg = has_in ? reinterpret_cast<uint32_t*>(base + o_itc) : nullptr;
+    P->d_types = has_in ? reinterpret_cast<ZLeaf*>(base + o_ity) : nullptr;
+    P->n_types = static_cast<int32_t>(in.types.size());
+    P->d_leaf = has_in ? reinterpret_cast<ZLeaf*>(base + o_ilf) : nullptr;
     P->d_incfg = has_in ? reinterpret_cast<CfgList*>(base + o_ic) : nullptr;
     P->d_inseg = has_in ? reinterpret_cast<int32_t*>(base + o_is) : nullptr;
     P->d_intab = has_in ? base + o_it : nullptr;
@@ -1047,6 +1152,12 @@ InArgs inner_args(const qaoa_plan_s* P, const double* gamma, const double* beta,
     a.cones = P->d_in;
     a.cfg = P->d_incfg;
     a.grp = P->d_ingrp;
+    a.leaf = P->d_leaf;
+    a.wz = P->wz;
+    a.tr = P->d_tr;
+    a.trcfg = P->d_trcfg;
+    a.types = P->d_types;
+    a.n_types = P->n_types;
     a.tab = P->d_intab;
     a.gamma = gamma;
     a.beta = beta;
@@ -1068,13 +1179,15 @@ hipError_t launch_inner_group(const qaoa_plan_s* P, const qaoa_plan_s::InGroup& 
     const HostPlan& hp = P->hp;
     InArgs a = inner_args(P, gamma, beta, gamma_P, zz, g);
     a.cones = P->d_in + grp.first;
+    a.signs = grp.signs ? 1 : 0;
+    if (grp.tree) a.tr = P->d_tr + grp.tr;
     a.chunks = grp.chunks;
     a.part = part;
     const int64_t nv = grad ? 2 * hp.p + 1 : 1;
     auto run = [&](int64_t p0, int64_t np, int64_t cones) {
         a.point0 = static_cast<int32_t>(p0);
         a.P = static_cast<int32_t>(np);
-        hipError_t e = launch_inner(grp.kin, grad, a, st);
+        hipError_t e = grp.tree ? launch_inner_tree(grp.kin, grad, a, st) : launch_inner(grp.kin, grad, a, st);
         if (e == hipSuccess && grp.chunks > 1) e = launch_inner_sum(a, static_cast<int32_t>(cones), grad, st);
         return e;
     };
@@ -1085,6 +1198,7 @@ hipError_t launch_inner_group(const qaoa_plan_s* P, const qaoa_plan_s::InGroup& 
         a.blocks = (grp.chunks + 3) / 4;
         for (int64_t i = 0; i < grp.count; ++i) {
             a.cones = P->d_in + grp.first + i;
+            if (grp.tree) a.tr = P->d_tr + grp.tr + i;
             a.inst0 = P->in_inst[static_cast<size_t>(grp.first + i)];
             for (int64_t pt = 0; pt < n_points; ++pt) {
                 const hipError_t e = run(pt, 1, 1);
@@ -1290,7 +1404,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
     // units per wave: the workgroup's set-up (phase rows) is shared by more units once the waves
     // fill the chip several times over
     auto inner_upw = [&](const qaoa_plan_s::InGroup& grp) {
-        const int64_t units = grp.count * grp.chunks * n_points;
+        const int64_t units = grp.count * grp.chunks * n_points / (grp.tree ? 4 : 1);
         int j = 0;
         while (j < 3 && (units >> (j + 1)) >= (int64_t{1} << 15)) ++j;
         return j;
@@ -1318,6 +1432,8 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         WdArgs a{};
         a.cones = P->d_wd;
         a.grp = P->d_wdgrp;
+        a.leaf = P->d_wdleaf;
+        a.wz = P->wz;
         a.cfg = P->d_wdcfg;
         a.tab = P->d_wdtab;
         a.gamma = gamma;
@@ -1698,6 +1814,9 @@ void release_device(qaoa_plan_s* P) {
     P->cap_part = 0;
     P->d_in = nullptr;
     P->d_ingrp = nullptr;
+    P->d_leaf = P->d_wdleaf = P->d_types = nullptr;
+    P->d_tr = nullptr;
+    P->d_trcfg = nullptr;
     P->d_intab = nullptr;
     P->d_wd = nullptr;
     P->d_wdunit = nullptr;

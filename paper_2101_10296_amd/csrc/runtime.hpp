@@ -47,6 +47,9 @@ struct qaoa_plan_s {
     struct InGroup {
         int kin, K;         // inner qubits; cone qubits, or 0
         bool wh;            // cones that are members of wh_groups
+        bool signs;         // cones with leaves (shell.hpp)
+        bool tree;          // inner_tree.hip; from d_tr + tr on
+        int64_t tr;
         int64_t first, count;
         int32_t chunks;     // units of work per cone
         int32_t n_seg;      // instances
@@ -69,6 +72,13 @@ struct qaoa_plan_s {
     qaoa::ConeWd* d_wd = nullptr;
     qaoa::UnitWd* d_wdunit = nullptr;
     qaoa::GrpWd* d_wdgrp = nullptr;
+    qaoa::ZLeaf* d_wdleaf = nullptr;
+    qaoa::ZLeaf* d_leaf = nullptr;       // of the cones in d_in
+    int32_t wz = 0;                      // largest coupling of a leaf
+    qaoa::ConeTr* d_tr = nullptr;        // those whose shell is leaves only, their signs and choices of leaves
+    uint32_t* d_trcfg = nullptr;
+    qaoa::ZLeaf* d_types = nullptr;
+    int32_t n_types = 0;
     qaoa::CfgWd* d_wdcfg = nullptr;
     uint8_t* d_wdtab = nullptr;
     qaoa::ConeIn* d_in = nullptr;
@@ -165,8 +175,8 @@ inline bool depth1_closed(const qaoa_plan_s* P) { return P->hp.p == 1 && P->opt.
 // Cones evaluated on their inner qubits: those with a shell (else there is nothing to average
 // over, and the kernels for whole cones store half of the state) whose inner state fits the
 // registers of one wave.  Every such cone measured faster there: 14 qubits, p = 2 (6 inner)
-// 10.7x, 18 qubits (8 inner) 2.1x, 26 qubits (8 inner) 50x; C_10000(1,2) at one point, 10-11
-// qubits with as many amplitudes as before, 26.7 -> 21.6 us for the call.  Real weights and
+// 93x, 18 qubits (8 inner) 4x, 26 qubits (8 inner) 150x; C_10000(1,2) at one point, 10-11 qubits
+// with as many amplitudes as before, 26.7 -> 16 us for the call.  Real weights and
 // forced layouts (tune >= 2) keep the kernels for whole cones.
 inline bool inner_cone(const qaoa_plan_s* P, const Cone& c) {
     const int32_t p = P->hp.p;

@@ -5,6 +5,8 @@
 
 #include <cstdint>
 
+#include "shell.hpp"
+
 namespace qaoa {
 
 constexpr int WD_KMIN = 11;     // inner qubits
@@ -18,9 +20,11 @@ constexpr int WD_CFG = 8;       // configurations per unit of work
 struct ConeWd {
     int32_t orbit, inst;
     int32_t n_grp, grp_off;     // shell groups (no list)
-    uint32_t nc;                // configurations
+    uint32_t nc;                // states of the groups
+    uint32_t zmask;             // inner qubits with leaves
+    int32_t z_off;              // their leaves
     int32_t cfg_off;            // listed configurations, or -1
-    uint32_t n_cfg;             // their number (unlisted: (nc + 1) / 2 are run)
+    uint32_t n_cfg;             // their number (unlisted: half of nc for every choice of signs)
     int32_t first_unit, n_units;
     int32_t edge_off, n_edges;
     int32_t kin;
@@ -40,8 +44,9 @@ struct GrpWd {
 struct CfgWd {
     int16_t h[12];
     int32_t c0;
-    int32_t pad_;
+    uint32_t z;                 // signs of the qubits with leaves
     double w;
+    double dw;                  // (in the kernel) derivative of the weight
 };
 
 // One unit: configurations c0 .. c1 - 1 of a cone.
@@ -55,6 +60,8 @@ struct WdArgs {
     const UnitWd* units;        // of this class, from the launch's first
     const GrpWd* grp;
     const CfgWd* cfg;
+    const ZLeaf* leaf;
+    int32_t wz;                 // largest coupling of a leaf
     const uint8_t* tab;
     const double* gamma;        // [inst][gamma_P][p]
     const double* beta;

@@ -8,9 +8,11 @@
 // cos Z + sin Y (of 2 beta_p) is the real cos Z - sin X.  The beta_1 terms of the upper qubits
 // are taken at the start of layer 1 with D_1 |+> made again, those of qubits 0-7 behind it.
 //
-// A 30-qubit cone of a 3-regular graph at p = 3 has 14 inner qubits and a shell of 16: 6561
-// configurations up to equal leaves, 111 up to the cone's symmetries, of 2^14 amplitudes that
-// never leave the compute unit, in place of seven sweeps over 2^29 amplitudes in device memory.
+// A 30-qubit cone of a 3-regular graph at p = 3 has 14 inner qubits and a shell of 16 leaves: 256
+// choices of signs, 21 up to the cone's symmetries, of 2^14 amplitudes that never leave the compute
+// unit, in place of seven sweeps over 2^29 amplitudes in device memory.  90 terms of 19 to 30
+// qubits, energy and gradient: 257 -> 20.5 ms with listed configurations of the leaves, 8.9 with
+// lists up to any symmetry, 7.5 with signs (5.5 of it in the passes of cones of up to 24 qubits).
 // Bound: vector instruction issue (about 200 per amplitude with the gradient) at one to two
 // workgroups per CU (LDS).
 #pragma once
@@ -132,10 +134,13 @@ __global__ void __launch_bounds__((Uz<KIN>::W), Uz<KIN>::W > 512 ? 4 : 3) k_wide
     __shared__ CfgWd s_cfg[WD_CFG];
     __shared__ float s_t[4];
     __shared__ double s_k2[4], s_cs[2];
+    __shared__ double2 s_z[16];
     __shared__ double s_sum[NWV][8];
-    extern __shared__ float2 dyn[];   // phase rows: layer 1 in four gauges, then layers 2..p
+    extern __shared__ __attribute__((aligned(16))) float2 dyn0[];   // cosines of the leaves' couplings; phase rows: layer 1 in four gauges, then layers 2..p
     const int tid = threadIdx.x, lane = tid & 63;
     const int R = a.R;
+    double2* ct = reinterpret_cast<double2*>(dyn0);
+    float2* dyn = dyn0 + 2 * (a.wz + 1);
     const int pt = blockIdx.x / a.n_units, un = blockIdx.x - pt * a.n_units;
     const int point = pt + a.point0;
     const UnitWd unit = a.units[un];
@@ -156,6 +161,8 @@ __global__ void __launch_bounds__((Uz<KIN>::W), Uz<KIN>::W > 512 ? 4 : 3) k_wide
             dyn[(3 + l) * R + j] = make_float2(x, y);
         }
     }
+    for (int j = tid; j <= a.wz; j += Z::W)
+        sincos(a.gamma[ip] * delta * static_cast<double>(j), &ct[j].y, &ct[j].x);
     if (tid < PP) {
         double s, c, t, k2;
         sincos(a.beta[ip + tid], &s, &c);
@@ -173,16 +180,22 @@ __global__ void __launch_bounds__((Uz<KIN>::W), Uz<KIN>::W > 512 ? 4 : 3) k_wide
             s_cs[1] = 2.0 * s * c;
         }
     }
-    // the unit's configurations
+    __syncthreads();
+    // the unit's configurations and their weights (the first wave)
+    if (tid < 16 && cd.zmask) s_z[tid] = z_factor(a.leaf[cd.z_off + tid], ct);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     if (tid < WD_CFG) {
         CfgWd e{};
         const uint32_t c = unit.c0 + tid;
         if (c < unit.c1 && cd.cfg_off >= 0) {
             e = a.cfg[cd.cfg_off + c];
-        } else if (c < unit.c1) {   // mixed radix digits (how many of each group's qubits are 1)
-            uint32_t rem = c;
+        } else if (c < unit.c1) {   // mixed radix digits (how many of each group's qubits are 1), then signs
+            const uint32_t nh = (cd.nc + 1) / 2;
+            uint32_t zz = c / nh, rem = c - zz * nh;
             int h[12] = {};
-            e.w = ((cd.nc & 1u) && c == (cd.nc - 1) / 2) ? 1.0 : 2.0;
+            e.w = ((cd.nc & 1u) && rem == nh - 1) ? 1.0 : 2.0;
+            for (uint32_t m = cd.zmask; m; m &= m - 1, zz >>= 1) e.z |= (zz & 1u) << __builtin_ctz(m);
             for (int q = 0; q < cd.n_grp; ++q) {
                 const GrpWd& G = a.grp[cd.grp_off + q];
                 const uint32_t d = static_cast<uint32_t>(G.m) + 1u;
@@ -197,6 +210,7 @@ __global__ void __launch_bounds__((Uz<KIN>::W), Uz<KIN>::W > 512 ? 4 : 3) k_wide
 #pragma unroll
             for (int i = 0; i < 12; ++i) e.h[i] = static_cast<int16_t>(h[i]);
         }
+        e.dw = z_weight(cd.zmask, e.z, s_z, e.w);
         s_cfg[tid] = e;
     }
     const WhThread th = wh_thread<Z>(static_cast<uint32_t>(tid));
@@ -229,7 +243,7 @@ __global__ void __launch_bounds__((Uz<KIN>::W), Uz<KIN>::W > 512 ? 4 : 3) k_wide
     const double k2_1 = kpow(1);
     const float mu1 = static_cast<float>(sqrt(k2_1));
     const float cs2 = static_cast<float>(s_cs[0] * s_cs[1]), ss2 = static_cast<float>(s_cs[1] * s_cs[1]);
-    double Zs = 0.0, Is = 0.0, Ds = 0.0, Gp = 0.0, B1 = 0.0, B1u = 0.0, G1 = 0.0;
+    double Zs = 0.0, Is = 0.0, Ds = 0.0, Gp = 0.0, B1 = 0.0, B1u = 0.0, G1 = 0.0, Wd = 0.0;
     double B2 = 0.0, G2 = 0.0;   // PP = 3
 
     for (uint32_t ci = 0; ci < unit.c1 - unit.c0; ++ci) {
@@ -252,8 +266,13 @@ __global__ void __launch_bounds__((Uz<KIN>::W), Uz<KIN>::W > 512 ? 4 : 3) k_wide
         cb[1] = hr(2);
         cb[2] = hr(3);
         cb[3] = cb[1] + cb[2];
+        // signs: of the thread's qubits two steps of the gauge, of the register qubits a factor
+        const uint32_t z = __builtin_amdgcn_readfirstlane(e.z);
+        const int pz = pc + 2 * __builtin_popcount(z & y1);
         auto gen = [&](int r) {   // D_1 |+>, gauged, without its norm
-            return dyn[((pc + __builtin_popcount(r)) & 3) * R + static_cast<int>(T1(r)) + ca[r & 3] + cb[r >> 2]];
+            const float2 t = dyn[((pz + __builtin_popcount(r)) & 3) * R + static_cast<int>(T1(r)) + ca[r & 3] + cb[r >> 2]];
+            const float x = __builtin_popcount(z & wreg<Z, 1>(r)) & 1 ? -1.f : 1.f;
+            return make_float2(x * t.x, x * t.y);
         };
         float2 f[A];
 #pragma unroll
@@ -326,6 +345,7 @@ __global__ void __launch_bounds__((Uz<KIN>::W), Uz<KIN>::W > 512 ? 4 : 3) k_wide
         Is = fma(wt, iv, Is);
         Ds = fma(wt, dv, Ds);
         if constexpr (GRAD) {
+            Wd = fma(e.dw, zv + 2.0 * s_cs[0] * s_cs[1] * iv + s_cs[1] * s_cs[1] * dv, Wd);
             Gp = fma(wt, static_cast<double>(gp), Gp);
             if constexpr (PP == 3) {
                 const int m = cd.mixed[2];
@@ -388,7 +408,7 @@ __global__ void __launch_bounds__((Uz<KIN>::W), Uz<KIN>::W > 512 ? 4 : 3) k_wide
         v[1] = n0 * 2.0 * (2.0 * (C * C - S * S) * Is + 2.0 * C * S * Ds);
         v[2] = 2.0 * n0 * Gp;
         v[3] = 2.0 * (n0 * B1 + n1 * B1u);
-        v[4] = 2.0 * n1 * G1;
+        v[4] = 2.0 * n1 * G1 + n0 * Wd;
         v[5] = 2.0 * n0 * B2;
         v[6] = 2.0 * n0 * G2;
         const double x = wave_sum8(v, lane);
@@ -415,7 +435,7 @@ template <int KIN>
 hipError_t launch_wide_k(bool grad, const WdArgs& a, hipStream_t st) {
     const int64_t blocks = static_cast<int64_t>(a.n_units) * a.P;
     if (blocks <= 0) return hipSuccess;
-    const size_t lds = static_cast<size_t>(3 + a.p) * a.R * sizeof(float2);
+    const size_t lds = (static_cast<size_t>(3 + a.p) * a.R + 2 * (a.wz + 1)) * sizeof(float2);
     const dim3 grid(static_cast<unsigned>(blocks)), block(Uz<KIN>::W);
     if (a.p == 2) {
         if (grad) hipLaunchKernelGGL((k_wide<KIN, true, 2>), grid, block, lds, st, a);
