@@ -5,6 +5,7 @@
 
 #include <cstdint>
 
+#include "depth2.hpp"
 #include "shell.hpp"
 
 namespace qaoa {
@@ -50,32 +51,11 @@ struct alignas(16) CfgList {
     double w;
 };
 
-// Cones whose shell is leaves only, at depth 2 (inner_tree_impl.hpp).  The limits are the cone's own, so
-// that its kernel is the same in every plan: 7 inner qubits would leave a row 4 states for up to
-// 32 signs, and 6 leaves of couplings up to 3 are 84 choices, which the workgroup turns into
-// weights once, whatever the plan.
-constexpr int TR_KMIN = 4, TR_KMAX = 6;   // inner qubits
-constexpr int TR_M = 6, TR_W = 3;         // leaves of one inner qubit and their couplings at most
-constexpr int TR_TYPES = 84;              // choices of them
-struct alignas(16) ConeTr {
-    int32_t orbit;
-    int32_t tab_off;           // as in ConeIn
-    int32_t cfg_off, n_cfg;    // listed signs: z | their number << 8
-    uint32_t types;            // of the leaves of inner qubits 2 .. 5, a byte each (0: none)
-    int32_t base;              // phase row index of table value 0
-    float mid;                 // centre of the cut values, relative to row index 0
-    int32_t pad_;
-};
-
 struct InArgs {
     const ConeIn* cones;       // cones of this class (inner qubits), from the launch's first
     const CfgList* cfg;
     const GrpIn* grp;
     const ZLeaf* leaf;
-    const ConeTr* tr;          // the class's, if it is one of those
-    const uint32_t* trcfg;
-    const ZLeaf* types;        // [n_types], the first empty
-    int32_t n_types;
     const uint8_t* tab;
     const double* gamma;       // [inst][gamma_P][p]
     const double* beta;
@@ -111,7 +91,7 @@ struct InPoint {
     struct Unit {              // in class order, a cone's parts together
         uint16_t cone, chunk, chunks, part;
         uint8_t kin;
-        uint8_t rows;          // 0, or up to four cones from `cone` on, a row of the wave each
+        uint8_t trees;         // 0, or cones in the closed form (depth2_impl.hpp) from `cone` on, a lane each
     } unit[IN_POINT];
     struct Part {              // their values: the parts of a cone together
         uint16_t chunks, orbit;
@@ -123,10 +103,9 @@ struct InPoint {
     double* dbeta;
 };
 // cones of one instance, all with listed configurations; a: cones of the plan, zz and g or null
-hipError_t launch_inner_point(const InArgs& a, const InPoint& q, bool grad, int64_t n_points, hipStream_t st);
+hipError_t launch_inner_point(const InArgs& a, const D2Args& d, const InPoint& q, bool grad, int64_t n_points, hipStream_t st);
 
 hipError_t launch_inner(int kin, bool grad, const InArgs& a, hipStream_t st);
-hipError_t launch_inner_tree(int kin, bool grad, const InArgs& a, hipStream_t st);
 // sums the chunks of every (point, cone) into zz and g
 hipError_t launch_inner_sum(const InArgs& a, int32_t n_cones, bool grad, hipStream_t st);
 // Table of layer l (2..p) of every cone: the cut of the couplings inside the qubits mixed by

@@ -14,8 +14,8 @@
 // the configurations are run at twice the weight.  Where the cone has symmetries of its own (twins,
 // u and v swapped), the configurations are listed up to them on the host (inner_plan.cpp).  A
 // 26-qubit cone of a 4-regular graph at p = 2 (2 + 6 inner qubits, 18 leaves) is 10 states of 2^8
-// amplitudes with 8 mixed qubits in place of 2^25 stored amplitudes with 26.  (At p = 2 and up to
-// 6 inner qubits, cones with leaves only are inner_tree_impl.hpp's.)
+// amplitudes with 8 mixed qubits in place of 2^25 stored amplitudes with 26.  (At p = 2,
+// trees have the closed form of depth2_impl.hpp.)
 //
 // Layout: A = 2^min(4, kin) amplitudes per lane (register bits: qubits 0..3), qubits 4..7 on
 // the lanes of a 16-lane row, 8 and 9 on lane bits 4 and 5; a wave runs 64 >> (kin - 4)
@@ -93,11 +93,10 @@ __device__ __forceinline__ double wave_sum(double x) {
     return x;
 }
 
-// Sums of eight values over the wave (or each of its 16-lane rows) at once: value i lands in the lanes
-// whose bits 0, 1 and 3 spell i.  Each of the first three steps halves the values a lane holds, where eight separate
+// Sums of eight values over the wave at once: value i lands in the lanes whose bits 0, 1 and 3 spell
+// i.  Each of the first three steps halves the values a lane holds, where eight separate
 // sums would take six steps each.
-template <bool WAVE>
-__device__ __forceinline__ double lane_sum8(double (&v)[8], int lane) {
+__device__ __forceinline__ double wave_sum8(double (&v)[8], int lane) {
     auto step = [&](auto I, int n, bool up) {   // keep the upper half of the values where up
         constexpr int i = decltype(I)::value;
 #pragma unroll
@@ -123,13 +122,10 @@ __device__ __forceinline__ double lane_sum8(double (&v)[8], int lane) {
     step(std::integral_constant<int, 0>{}, 1, (lane & 1) != 0);
     double x = v[0];
     x += __shfl_xor(x, 4, 64);
-    if constexpr (WAVE) {
-        x += __shfl_xor(x, 16, 64);
-        x += __shfl_xor(x, 32, 64);
-    }
+    x += __shfl_xor(x, 16, 64);
+    x += __shfl_xor(x, 32, 64);
     return x;
 }
-__device__ __forceinline__ double wave_sum8(double (&v)[8], int lane) { return lane_sum8<true>(v, lane); }
 
 // Exchange lane bit 4 (W32: 5) with register bit B (an involution).
 template <bool W32, int B, int A>

@@ -34,11 +34,36 @@ uint64_t mix64(uint64_t x) {
 // sorted by their digits; the remaining automorphisms, found by backtracking up to orders of
 // twins, and the flip map sorted tuples to each other, and the smallest image of each orbit is
 // listed with the weight of all its members.  What is listed depends on the shape alone, so a
-// term is the same in every plan.  Up to 1024 configurations are always listed (under 0.3 ms of
+// term is the same in every plan.  Where a wave holds them all at once, only the flip is used (the
+// search for symmetries takes 4 us of host time a shape).  Up to 1024 configurations are always listed (under 0.3 ms of
 // host time).  Beyond, up to 16384: at most 10 inner qubits, where a configuration costs a wave
 // under 1 us, where at least 16 symmetries shorten the list enough to pay for it; more, where
 // each occupies a compute unit for 37 us, with any symmetry at all.  No list: cfg stays empty.
 void ShellPlanner::Shape::enumerate() {
+    const uint32_t nh = (nc + 1) / 2, n_sign = 1u << __builtin_popcount(zmask);
+    if (kin <= 10 && nh <= 64u && nh * n_sign <= (64u >> std::max(0, kin - 4))) {
+        for (const ShellGroup& q : grp)
+            if (q.m > 29) return;
+        for (uint32_t d = 0; d < nh; ++d) {
+            ShellCfg e{};
+            e.w = (nc & 1u) && d == nh - 1 ? 1.0 : 2.0;
+            uint32_t rem = d;
+            for (const ShellGroup& G : grp) {
+                const int t = static_cast<int>(rem % static_cast<uint32_t>(G.m + 1));
+                rem /= static_cast<uint32_t>(G.m + 1);
+                e.c0 += t * G.wsum;
+                for (int i = 0; i < SH_H; ++i) e.h[i] = static_cast<int16_t>(e.h[i] + (G.m - 2 * t) * G.h[i]);
+                for (int i = 0; i < t; ++i) e.w = e.w * (G.m - i) / (i + 1);
+            }
+            for (uint32_t s = 0; s < n_sign; ++s) {
+                e.z = 0;
+                uint32_t r = s;
+                for (uint32_t z = zmask; z; z &= z - 1, r >>= 1) e.z |= (r & 1u) << __builtin_ctz(z);
+                cfg.push_back(e);
+            }
+        }
+        return;
+    }
     std::vector<ShellGroup> grp = this->grp;   // and one of a single qubit for each sign
     const int n_real = static_cast<int>(grp.size());
     for (uint32_t z = zmask; z; z &= z - 1) {
@@ -272,93 +297,69 @@ int32_t ShellPlanner::find(uint64_t h) {
     return table_[i].second;
 }
 
-// A cone's own symmetries as far as they pay: inner qubits with equal couplings to u and v and equal
-// leaves are twins (a class of signs that count by their number), and swapping u and v may map
-// the classes to each other; none of it where neighbours are coupled.
-bool ShellPlanner::add_tree(const Cone& c, ShellCone& out) {
-    const int kin = c.nd[p_ - 1], ns = c.k - kin;
-    if (kin < 4 || kin > 6) return false;
-    int8_t owner[32];
-    std::memset(owner, -1, sizeof(owner));
-    int leaves[6] = {}, n_owned = 0, w0[6] = {}, w1[6] = {};
-    uint16_t code[6] = {};
-    bool coupled = false;
-    const size_t ne = c.ea.size();
-    for (size_t e = 0; e < ne; ++e) {
-        const int a = c.ea[e], b = c.eb[e], w = c.ew[e];
-        if (a >= kin || w == 0) continue;
-        if (b < kin) {
-            if (a == 0) w0[b] = w;
-            else if (a == 1) w1[b] = w;
-            else coupled = true;
+namespace {
+// Where each qubit of a tree hangs (u and v: -1) and its coupling there; false: no tree.
+bool tree_owners(const Cone& c, bool real, int (&owner)[32], double (&w)[32], double& w_uv) {
+    const int kin = c.nd[1];
+    for (int q = 0; q < c.k; ++q) owner[q] = -1;
+    w_uv = 0.0;
+    int n = 0;
+    for (size_t e = 0; e < c.ea.size(); ++e) {
+        const int a = c.ea[e], b = c.eb[e];
+        const double x = real ? c.wf[e] : static_cast<double>(c.ew[e]);
+        if (x == 0.0 || a >= kin) continue;   // couplings within the shell have no part in the term
+        if (b == 1) {
+            w_uv = x;
             continue;
         }
-        const int x = std::abs(w);
-        if (owner[b] >= 0 || x > 3 || ++leaves[a] > 6) return false;
-        owner[b] = static_cast<int8_t>(a);
-        ++n_owned;
-        code[a] = static_cast<uint16_t>(code[a] + (x == 1 ? 1 : x == 2 ? 7 : 49));
+        if (owner[b] >= 0 || (b < kin && a > 1)) return false;
+        owner[b] = a;
+        w[b] = x;
+        ++n;
     }
-    if (n_owned != ns) return false;
-    out.kin = kin;
-    out.tree = true;
-    out.nc = 1;
-    out.n_leaf = ns;
-    out.w_leaf = 0;   // they are not among its couplings
-    out.edge = static_cast<int64_t>(ea.size());
-    for (size_t e = 0; e < ne; ++e)
-        if (c.eb[e] < kin) {
-            ea.push_back(c.ea[e]);
-            eb.push_back(c.eb[e]);
-            ew.push_back(c.ew[e]);
-        }
-    out.n_edges = static_cast<int32_t>(static_cast<int64_t>(ea.size()) - out.edge);
-    out.zmask = 0;
-    int cls[4] = {0, 0, 0, 0}, first[4], n_cls = 0, size[4] = {};
-    for (int q = 2; q < kin; ++q) {
-        out.leaf[q - 2] = code[q];
-        if (code[q]) out.zmask |= 1u << q;
-        int i = coupled ? n_cls : 0;
-        while (i < n_cls && (w0[first[i]] != w0[q] || w1[first[i]] != w1[q] || code[first[i]] != code[q])) ++i;
-        if (i == n_cls) first[n_cls++] = q;
-        cls[q - 2] = i;
-        ++size[i];
-    }
-    int swap[4] = {0, 1, 2, 3};
-    bool ok = !coupled;
-    for (int i = 0; i < n_cls && ok; ++i) {
-        int j = 0;
-        while (j < n_cls && (w0[first[i]] != w1[first[j]] || w1[first[i]] != w0[first[j]] || code[first[i]] != code[first[j]])) ++j;
-        ok = j < n_cls && size[i] == size[j];
-        swap[i] = j;
-    }
-    out.signs = out.zmask >> 2;
-    for (int i = 0; i < 4; ++i) out.signs |= static_cast<uint32_t>(cls[i] << (4 + 2 * i) | (ok ? swap[i] : i) << (12 + 2 * i));
-    return true;
+    return n == c.k - 2;
+}
+}  // namespace
+
+bool tree_cone(const Cone& c, bool real) {
+    int owner[32];
+    double w[32], w_uv;
+    return tree_owners(c, real, owner, w, w_uv);
 }
 
-std::vector<uint32_t> tree_signs(uint32_t signs) {
-    auto field = [&](int at) { return static_cast<int>((signs >> at) & 3u); };
-    std::vector<uint32_t> out;
-    uint16_t key[16];
-    for (uint32_t z = 0; z < 16; ++z) {
-        if (z & ~signs & 15u) continue;
-        int n[4] = {}, a = 0, b = 0;
-        for (int q = 0; q < 4; ++q) n[field(4 + 2 * q)] += static_cast<int>((z >> q) & 1u);
-        for (int i = 0; i < 4; ++i) {
-            a = a * 8 + n[i];
-            b = b * 8 + n[field(12 + 2 * i)];
+bool ShellPlanner::add_tree(const Cone& c, ShellCone& out) {
+    int owner[32];
+    double w[32];
+    if (!tree_owners(c, real_, owner, w, out.w_uv)) return false;
+    const int kin = c.nd[1];
+    out.tree = true;
+    out.kin = 0;   // one class
+    out.br = static_cast<int32_t>(branches.size());
+    int at[32] = {};
+    for (int r = 0; r < 2; ++r)
+        for (int q = 2; q < kin; ++q) {
+            if (owner[q] != r) continue;
+            ++(r ? out.nv : out.nu);
+            at[q] = static_cast<int>(branches.size());
+            ShellBranch b;
+            b.w = w[q];
+            if (!real_ && std::abs(w[q]) <= 3.0) b.code = static_cast<int16_t>((static_cast<int>(w[q]) + 3) * 343);
+            branches.push_back(b);
         }
-        const uint16_t k = static_cast<uint16_t>(std::min(a, b));
-        size_t i = 0;
-        while (i < out.size() && key[i] != k) ++i;
-        if (i == out.size()) {
-            key[i] = k;
-            out.push_back(z << 2);
-        }
-        out[i] += 1u << 8;
+    for (int q = kin; q < c.k; ++q) {
+        ShellBranch& b = branches[static_cast<size_t>(at[owner[q]])];
+        const double x = std::abs(w[q]);
+        ++b.n_leaf;
+        if (b.code >= 0) b.code = b.n_leaf > 6 || x > 3.0 ? int16_t{-1} : static_cast<int16_t>(b.code + (x == 1.0 ? 1 : x == 2.0 ? 7 : 49));
     }
-    return out;
+    for (int i = 0; i < out.nu + out.nv; ++i) {
+        ShellBranch& b = branches[static_cast<size_t>(out.br + i)];
+        if (b.code >= 0) continue;
+        b.leaf = static_cast<int32_t>(leaf_w.size());
+        for (int q = kin; q < c.k; ++q)
+            if (at[owner[q]] == out.br + i) leaf_w.push_back(std::abs(w[q]));
+    }
+    return true;
 }
 
 void ShellPlanner::add_one(const Cone& c, ShellCone& out) {
@@ -507,7 +508,7 @@ void ShellPlanner::add(const std::vector<const Cone*>& cones, std::vector<ShellC
         for (size_t i = 0; i < n; ++i) add_one(*cones[i], out[i]);
         return;
     }
-    std::vector<ShellPlanner> part(nt, ShellPlanner(p_, trees_));
+    std::vector<ShellPlanner> part(nt, ShellPlanner(p_, trees_, real_));
     std::atomic<bool> no_mem{false};
     auto work = [&](size_t t) {
         try {
@@ -532,6 +533,12 @@ void ShellPlanner::add(const std::vector<const Cone*>& cones, std::vector<ShellC
         ea.insert(ea.end(), part[t].ea.begin(), part[t].ea.end());
         eb.insert(eb.end(), part[t].eb.begin(), part[t].eb.end());
         ew.insert(ew.end(), part[t].ew.begin(), part[t].ew.end());
+        const int32_t b0 = static_cast<int32_t>(branches.size()), l0 = static_cast<int32_t>(leaf_w.size());
+        for (ShellBranch b : part[t].branches) {
+            b.leaf += l0;
+            branches.push_back(b);
+        }
+        leaf_w.insert(leaf_w.end(), part[t].leaf_w.begin(), part[t].leaf_w.end());
         std::vector<int32_t> to(part[t].shapes_.size());
         for (size_t i = 0; i < to.size(); ++i) {
             s_ = part[t].shapes_[i];
@@ -539,6 +546,7 @@ void ShellPlanner::add(const std::vector<const Cone*>& cones, std::vector<ShellC
         }
         for (size_t i = t * n / nt; i < (t + 1) * n / nt; ++i) {
             out[i].edge += e0;
+            out[i].br += b0;
             if (!out[i].tree) out[i].shape = to[static_cast<size_t>(out[i].shape)];
         }
     }
@@ -560,7 +568,8 @@ void ShellPlanner::list() {
             todo[i]->listed = true;
         }
     };
-    const size_t nt = std::min<size_t>({8, std::max(1u, std::thread::hardware_concurrency()), todo.size() / 32 + 1});
+    // (a thread takes some 30 us to start)
+    const size_t nt = std::min<size_t>({8, std::max(1u, std::thread::hardware_concurrency()), todo.size() / 64 + 1});
     std::vector<std::thread> pool;
     try {
         for (size_t t = 1; t < nt; ++t) pool.emplace_back(work);

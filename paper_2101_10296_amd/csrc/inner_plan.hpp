@@ -44,22 +44,32 @@ struct ShellCone {
     int32_t n_edges = 0;
     uint32_t nc = 0;           // states of the groups: product of (m + 1), at most 2^28
     uint32_t zmask = 0;        // inner qubits with leaves
-    // the shell is leaves only (see ShellPlanner): the choices of leaves of qubits 2 .. 5 (n_1 + 7 n_2
-    // + 49 n_3, n_w of coupling +-w) and which signs are equal up to symmetry (tree_signs)
+    // a tree (see ShellPlanner): the edge's coupling and the neighbours of u, then of v, from `br` on
     bool tree = false;
-    uint16_t leaf[4] = {};
-    uint32_t signs = 0;
+    int16_t nu = 0, nv = 0;
+    int32_t br = 0;
+    double w_uv = 0.0;
     int32_t n_leaf = 0;        // their leaves
     int32_t w_leaf = 0;        // and the sum of the couplings
     uint32_t runs() const { return ((nc + 1) / 2) << __builtin_popcount(zmask); }   // without a list
     int32_t shape = -1;        // cones of one shape share groups and configurations
 };
 
+// A neighbour of u or v and its leaves.  Integer couplings of the neighbour up to +-3 and of at most six
+// leaves up to +-3 have a code: (w + 3) 343 + n_1 + 7 n_2 + 49 n_3, n_x leaves of coupling +-x.
+constexpr int SH_CODES = 7 * 343;
+struct ShellBranch {
+    double w = 0.0;
+    int16_t code = -1;
+    int16_t n_leaf = 0;        // code < 0: couplings leaf_w[leaf ..]
+    int32_t leaf = 0;
+};
+
 class ShellPlanner {
 public:
-    // trees: cones of 4 to 6 inner qubits whose shell qubits are all leaves, at most 6 per inner qubit
-    // and of couplings up to 3, get no shape: they keep the cone's order and its inner couplings
-    explicit ShellPlanner(int32_t p, bool trees = false) : p_(p), trees_(trees) {}
+    // trees: cones whose inner qubits couple to u or v alone and whose shell qubits are leaves get no
+    // shape but a list of branches; real: couplings are Cone::wf (then every cone has to be a tree)
+    explicit ShellPlanner(int32_t p, bool trees = false, bool real = false) : p_(p), trees_(trees), real_(real) {}
     // the cones in order (0.6 us of host time each: on several threads from 4096 cones on)
     void add(const std::vector<const Cone*>& cones, std::vector<ShellCone>& out);
     // Lists the configurations of every shape seen so far that has none yet (several threads).
@@ -69,6 +79,8 @@ public:
     const ShellLeaves* leaves(int32_t shape) const { return shapes_[static_cast<size_t>(shape)].leaf; }   // [SH_KMAX]
     const std::vector<ShellGroup>& groups(int32_t shape) const { return shapes_[static_cast<size_t>(shape)].grp; }
     std::vector<int32_t> ea, eb, ew;   // couplings of all cones
+    std::vector<ShellBranch> branches; // of all trees
+    std::vector<double> leaf_w;        // the couplings of leaves without a code
 
 private:
     struct Shape {
@@ -86,7 +98,7 @@ private:
         void enumerate();
     };
     int32_t p_;
-    bool trees_;
+    bool trees_, real_;
     std::vector<Shape> shapes_;
     std::vector<std::pair<uint64_t, int32_t>> table_;   // open addressing by hash
     Shape s_;                                            // the cone being added
@@ -95,7 +107,7 @@ private:
     bool add_tree(const Cone& c, ShellCone& out);
 };
 
-// The signs of a tree up to its symmetries: z | number << 8, from ShellCone::signs.
-std::vector<uint32_t> tree_signs(uint32_t signs);
+// Whether a depth-2 cone with a shell is a tree in that sense.
+bool tree_cone(const Cone& c, bool real);
 
 }  // namespace qaoa

@@ -11,18 +11,18 @@
 // Bound: the serial chain of one unit (phase rows, descriptors and tables through L2, then about
 // 2000 instructions of one wave).  Energy and gradient of C_10000(1,2) at p = 2 (inner states of
 // 6 and 7 qubits, one unit each), one point: 18.8 us a call in three launches, 13.6 here.
-#include "inner_tree_impl.hpp"
+#include "depth2_impl.hpp"
+#include "inner_impl.hpp"
 
 namespace qaoa {
 namespace {
 
 template <bool GRAD, int PP>
 __global__ void __launch_bounds__(64 * in_point_waves(GRAD, PP), GRAD && PP == 0 ? 2 : 4)
-k_inner_point(InArgs a, InPoint q) {
+k_inner_point(InArgs a, D2Args d, InPoint q) {
     extern __shared__ __attribute__((aligned(16))) float2 dyn[];   // cosines and phase rows; then (PP = 0) sums
     __shared__ InShared sh;
     __shared__ double2 s_z[in_point_waves(GRAD, PP)][16];
-    __shared__ double2 s_typ[PP == 2 ? TR_TYPES : 1];
     __shared__ double s_val[IN_POINT][2 * IN_PMAX + 1];    // parts of cones
     __shared__ double s_term[IN_POINT][2 * IN_PMAX + 1];   // orbits
     const int tid = threadIdx.x, lane = tid & 63, waves = blockDim.x >> 6;
@@ -32,26 +32,20 @@ k_inner_point(InArgs a, InPoint q) {
     const int point = blockIdx.x + a.point0;
     in_rows(a, p, 0, point, tid, blockDim.x, dyn, sh);
     __syncthreads();
-    if (PP == 2 && a.n_types) {
-        tr_types(a, tid, blockDim.x, dyn, s_typ);
-        __syncthreads();
-    }
     double* lsum = nullptr;
     if constexpr (PP == 0) lsum = reinterpret_cast<double*>(in_phase(a, dyn) + (3 + p) * R + ((3 + p) * R & 1)) + wave * (2 * p + 1) * 64;
     for (int u = wave; u < q.n; u += waves) {
         const InPoint::Unit un = q.unit[u];
         if constexpr (PP == 2) {
-            if (un.rows) {
-                auto rows = [&](auto K) {
-                    constexpr int KIN = decltype(K)::value;
-                    const InLane<KIN - 1> ln(lane);
-                    const int r = lane >> 4;
-                    tr_row<KIN, GRAD>(a, a.tr + un.cone + min(r, un.rows - 1), r < un.rows, lane, ln, dyn, s_typ, sh,
-                                      [&](int, int code, double x) { s_val[un.part + r][code] = x; });
-                };
-                if (un.kin == 4) rows(std::integral_constant<int, 4>{});
-                else if (un.kin == 5) rows(std::integral_constant<int, 5>{});
-                else rows(std::integral_constant<int, 6>{});
+            if (un.trees) {
+                if (lane < un.trees) {
+                    const double delta = a.deltas[0];
+                    const size_t ip = static_cast<size_t>(point) * 2;
+                    double v[5];
+                    d2_cone<GRAD>(d, d.cones[un.cone + lane], a.gamma[ip] * delta, a.gamma[ip + 1] * delta,
+                                  d2_angles(a.beta[ip], a.beta[ip + 1]), v);
+                    for (int i = 0; i < nv; ++i) s_val[un.part + lane][i] = v[i];
+                }
                 continue;
             }
         }
@@ -113,7 +107,7 @@ k_inner_point(InArgs a, InPoint q) {
 
 }  // namespace
 
-hipError_t launch_inner_point(const InArgs& a0, const InPoint& q, bool grad, int64_t n_points, hipStream_t st) {
+hipError_t launch_inner_point(const InArgs& a0, const D2Args& d, const InPoint& q, bool grad, int64_t n_points, hipStream_t st) {
     if (q.n < 1 || q.n > IN_POINT || q.n_part > IN_POINT || a0.M > IN_POINT || a0.p < 2 || a0.p > IN_PMAX) return hipErrorInvalidValue;
     const bool sums = a0.p > 2 && grad;
     const int waves = std::min<int>(q.n, in_point_waves(grad, a0.p == 2 ? 2 : 0));
@@ -126,11 +120,11 @@ hipError_t launch_inner_point(const InArgs& a0, const InPoint& q, bool grad, int
         a.point0 = static_cast<int32_t>(p0);
         const dim3 grid(static_cast<unsigned>(std::min(CH, n_points - p0))), block(64 * waves);
         if (a.p == 2) {
-            if (grad) hipLaunchKernelGGL((k_inner_point<true, 2>), grid, block, lds, st, a, q);
-            else hipLaunchKernelGGL((k_inner_point<false, 2>), grid, block, lds, st, a, q);
+            if (grad) hipLaunchKernelGGL((k_inner_point<true, 2>), grid, block, lds, st, a, d, q);
+            else hipLaunchKernelGGL((k_inner_point<false, 2>), grid, block, lds, st, a, d, q);
         } else {
-            if (grad) hipLaunchKernelGGL((k_inner_point<true, 0>), grid, block, lds, st, a, q);
-            else hipLaunchKernelGGL((k_inner_point<false, 0>), grid, block, lds, st, a, q);
+            if (grad) hipLaunchKernelGGL((k_inner_point<true, 0>), grid, block, lds, st, a, d, q);
+            else hipLaunchKernelGGL((k_inner_point<false, 0>), grid, block, lds, st, a, d, q);
         }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

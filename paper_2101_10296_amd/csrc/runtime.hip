@@ -290,7 +290,7 @@ void build_whole(qaoa_plan_s* P, WholeHost& w) {
     }
     std::vector<Key> keys;
     for (size_t m = 0; m < n; ++m)
-        if (hash[m] && count[at(hash[m])] >= WH_MEMBERS) keys.push_back({hp.cones[m].k, hash[m], static_cast<int64_t>(m)});
+        if (hash[m] && count[at(hash[m])] >= WH_MEMBERS && !closed_tree(P, hp.cones[m])) keys.push_back({hp.cones[m].k, hash[m], static_cast<int64_t>(m)});
     std::sort(keys.begin(), keys.end(), [](const Key& a, const Key& b) {
         return std::tie(a.k, a.h, a.m) < std::tie(b.k, b.h, b.m);
     });
@@ -356,9 +356,11 @@ struct InnerHost {
     std::vector<GrpIn> grp;
     std::vector<int32_t> seg;
     std::vector<CfgList> cfg;
-    std::vector<ZLeaf> leaf, types;
-    std::vector<ConeTr> tr;
-    std::vector<uint32_t> trcfg;
+    std::vector<ZLeaf> leaf;
+    std::vector<D2Cone> tr;
+    std::vector<int32_t> branch;
+    std::vector<D2Type> types;
+    std::vector<D2Leaf> leaf2;
     int64_t tab_units = 0;   // table bytes / 16
 };
 
@@ -414,12 +416,13 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
     const bool by_k = P->opt.profile || P->opt.tune == 1;
     P->in_groups.clear();
     P->in_inst.clear();
+    P->tr_inst.clear();
     P->in_max_k = 0;   // build_wide adds its own
     P->wz = 0;
     if (ord.empty()) return;
     auto is_wh = [&](int64_t m) { return !member.empty() && member[static_cast<size_t>(m)] != 0; };
     in.cones.reserve(ord.size());
-    ShellPlanner shells(p, p == 2);
+    ShellPlanner shells(p, p == 2, hp.realw);
     std::vector<ShellCone> sc;
     {
         std::vector<const Cone*> list_of(ord.size());
@@ -448,11 +451,41 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
     eb.insert(eb.end(), shells.eb.begin(), shells.eb.end());
     ew.insert(ew.end(), shells.ew.begin(), shells.ew.end());
     std::vector<int32_t> leaf_at;
-    std::vector<std::pair<uint32_t, std::pair<int32_t, int32_t>>> lists;   // signs of trees: first, number
-    int16_t type_of[512];
-    std::fill(std::begin(type_of), std::end(type_of), int16_t{-1});
-    type_of[0] = 0;
-    in.types.push_back(ZLeaf{});
+    std::vector<int32_t> type_of(SH_CODES, -1);   // of branches with a code
+    auto leaf = [&](double w, int m) { in.leaf2.push_back({w, m, 0}); };
+    auto type = [&](double w, int32_t first) {
+        in.types.push_back({w, first, static_cast<int32_t>(in.leaf2.size()) - first});
+        return static_cast<int32_t>(in.types.size() - 1);
+    };
+    auto branch_type = [&](const ShellBranch& b) {
+        const int32_t first = static_cast<int32_t>(in.leaf2.size());
+        if (b.code < 0) {
+            for (int i = 0; i < b.n_leaf; ++i) leaf(shells.leaf_w[static_cast<size_t>(b.leaf + i)], 1);
+            return type(b.w, first);
+        }
+        int32_t& t = type_of[static_cast<size_t>(b.code)];
+        if (t < 0) {
+            for (int x = 1, r = b.code % 343; x <= 3; ++x, r /= 7)
+                if (r % 7) leaf(x, r % 7);
+            t = type(b.w, first);
+        }
+        return t;
+    };
+    // a group of in_groups continues where its key does
+    auto group = [&](int kin, int kk, bool wh, bool tree, bool signs, int64_t first) -> qaoa_plan_s::InGroup& {
+        if (P->in_groups.empty() || P->in_groups.back().kin != kin || P->in_groups.back().K != kk ||
+            P->in_groups.back().wh != wh || P->in_groups.back().tree != tree || P->in_groups.back().signs != signs) {
+            qaoa_plan_s::InGroup g{};
+            g.kin = kin;
+            g.K = kk;
+            g.wh = wh;
+            g.tree = tree;
+            g.signs = signs;
+            g.first = first;
+            P->in_groups.push_back(g);
+        }
+        return P->in_groups.back();
+    };
     std::vector<int32_t> listed_at;   // first entry of each shape's list, -1: not placed yet
     std::vector<uint32_t> rounds;
     rounds.reserve(ord.size());
@@ -460,6 +493,20 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         const int64_t m = ord[i];
         const Cone& c = hp.cones[m];
         const ShellCone& q = sc[i];
+        if (q.tree) {
+            D2Cone d{static_cast<int32_t>(m), 0, static_cast<int32_t>(in.branch.size()), q.nu, q.nv};
+            ShellBranch edge;   // without leaves
+            edge.w = q.w_uv;
+            if (!hp.realw && std::abs(q.w_uv) <= 3.0) edge.code = static_cast<int16_t>((static_cast<int>(q.w_uv) + 3) * 343);
+            d.edge = branch_type(edge);
+            for (int j = 0; j < q.nu + q.nv; ++j) in.branch.push_back(branch_type(shells.branches[static_cast<size_t>(q.br + j)]));
+            qaoa_plan_s::InGroup& g = group(0, by_k ? c.k : 0, is_wh(m), true, false, static_cast<int64_t>(in.tr.size()));
+            g.count += 1;
+            P->in_max_k = std::max(P->in_max_k, c.k);
+            P->tr_inst.push_back(c.inst);
+            in.tr.push_back(d);
+            continue;
+        }
         const uint32_t cpw = 64u >> std::max(0, q.kin - 4);
         ConeIn d{};
         d.orbit = static_cast<int32_t>(m);
@@ -469,13 +516,10 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         d.shell_norm = std::ldexp(1.0, -(c.k - q.kin - q.n_leaf));
         d.nc = q.nc;
         d.cfg_off = -1;
-        const bool tree = q.tree;
         d.zmask = q.zmask;
-        if (!tree) d.z_off = place_leaves(shells, q, leaf_at, in.leaf, P->wz);
+        d.z_off = place_leaves(shells, q, leaf_at, in.leaf, P->wz);
         uint32_t runs = q.runs();
-        if (tree) {   // its own list, below
-            runs = 1;
-        } else if (const std::vector<ShellCfg>* list = shells.configurations(q.shape)) {
+        if (const std::vector<ShellCfg>* list = shells.configurations(q.shape)) {
             if (listed_at.size() <= static_cast<size_t>(q.shape)) listed_at.resize(static_cast<size_t>(q.shape) + 1, -1);
             int32_t& at = listed_at[static_cast<size_t>(q.shape)];
             d.n_cfg = static_cast<uint32_t>((list->size() + cpw - 1) / cpw * cpw);   // whole rounds
@@ -511,48 +555,9 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         d.edge_off = static_cast<int32_t>(edge0 + q.edge);
         d.n_edges = q.n_edges;
         const int kk = by_k ? c.k : 0;
-        if (P->in_groups.empty() || P->in_groups.back().kin != q.kin || P->in_groups.back().K != kk ||
-            P->in_groups.back().wh != is_wh(m) || P->in_groups.back().tree != tree ||
-            P->in_groups.back().signs != (q.zmask != 0)) {
-            qaoa_plan_s::InGroup g{};
-            g.kin = q.kin;
-            g.K = kk;
-            g.wh = is_wh(m);
-            g.signs = q.zmask != 0;
-            g.tree = tree;
-            g.tr = static_cast<int64_t>(in.tr.size());
-            g.first = static_cast<int64_t>(in.cones.size());
-            P->in_groups.push_back(g);
-        }
-        P->in_groups.back().count += 1;
+        group(q.kin, kk, is_wh(m), false, q.zmask != 0, static_cast<int64_t>(in.cones.size())).count += 1;
         P->in_max_k = std::max(P->in_max_k, c.k);
         P->in_inst.push_back(c.inst);
-        if (tree) {
-            size_t l = 0;   // few
-            while (l < lists.size() && lists[l].first != q.signs) ++l;
-            if (l == lists.size()) {
-                const std::vector<uint32_t> z = tree_signs(q.signs);
-                lists.push_back({q.signs, {static_cast<int32_t>(in.trcfg.size()), static_cast<int32_t>(z.size())}});
-                in.trcfg.insert(in.trcfg.end(), z.begin(), z.end());
-            }
-            uint32_t types = 0;
-            for (int i = 0; i < q.kin - 2; ++i) {
-                const int code = q.leaf[i];
-                if (type_of[code] < 0) {
-                    type_of[code] = static_cast<int16_t>(in.types.size());
-                    ZLeaf z{};
-                    for (int x = 1, n = 0, r = code; x <= TR_W; ++x, r /= TR_M + 1)
-                        if (r % (TR_M + 1)) {
-                            z.w[n] = static_cast<int16_t>(x);
-                            z.m[n++] = static_cast<int16_t>(r % (TR_M + 1));
-                            P->wz = std::max(P->wz, x);
-                        }
-                    in.types.push_back(z);
-                }
-                types |= static_cast<uint32_t>(type_of[code]) << (8 * i);
-            }
-            in.tr.push_back({d.orbit, d.tab_off, lists[l].second.first, lists[l].second.second, types, d.base[2], d.mid[2], 0});
-        }
         in.cones.push_back(d);
     }
     for (auto& g : P->in_groups) {
@@ -563,12 +568,12 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         // rounds at most) stay whole, as parts need room for their sums.
         uint32_t most = 1;
         int32_t max_k = 0;
-        for (int64_t i = g.first; i < g.first + g.count; ++i) {
+        for (int64_t i = g.first; i < g.first + g.count && !g.tree; ++i) {
             most = std::max(most, rounds[static_cast<size_t>(i)]);
             max_k = std::max(max_k, hp.cones[static_cast<size_t>(in.cones[static_cast<size_t>(i)].orbit)].k);
         }
         int64_t ch = 1;
-        if (max_k > P->opt.k_lds_max && !g.tree) {
+        if (max_k > P->opt.k_lds_max) {
             ch = (most + IN_ROUNDS - 1) / IN_ROUNDS;
             if (ch * g.count < 1024) ch = std::min<int64_t>((most + 1) / 2, std::max<int64_t>(ch, 1024 / g.count));
         }
@@ -576,7 +581,7 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         g.chunks = static_cast<int32_t>(ch);
         std::vector<int32_t> unit{0}, inst;   // segments of one instance
         for (int64_t i = 0; i < g.count; ++i) {
-            const int32_t j = in.cones[static_cast<size_t>(g.first + i)].inst;
+            const int32_t j = (g.tree ? P->tr_inst : P->in_inst)[static_cast<size_t>(g.first + i)];
             if (inst.empty() || inst.back() != j) {
                 if (!inst.empty()) unit.push_back(static_cast<int32_t>(i * ch));
                 inst.push_back(j);
@@ -585,7 +590,7 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         unit.push_back(static_cast<int32_t>(g.count * ch));
         g.n_seg = static_cast<int32_t>(inst.size());
         for (int j = 0; j < 4; ++j) {
-            const int32_t per = (g.tree ? 16 : 4) << j;   // a cone per row of a wave
+            const int32_t per = (g.tree ? 256 : 4) << j;   // a tree per thread
             int32_t b = 0;
             std::vector<int32_t> blk;
             for (int32_t q = 0; q < g.n_seg; ++q) {
@@ -616,9 +621,15 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
 void build_point(qaoa_plan_s* P, const InnerHost& in) {
     P->in_point = InPoint{};
     const size_t M = P->hp.cones.size();
-    if (P->hp.n_inst != 1 || M > IN_POINT || in.cones.size() != M || !P->wh_groups.empty() || P->opt.profile ||
+    P->d2_point = false;
+    if (P->hp.n_inst != 1 || M > D2_POINT || in.cones.size() + in.tr.size() != M || !P->wh_groups.empty() || P->opt.profile ||
         P->opt.tune != 0 || P->opt.one_cone_at_a_time)
         return;
+    if (in.cones.empty()) {   // trees, in orbit order
+        P->d2_point = P->in_groups.size() == 1;
+        return;
+    }
+    if (M > IN_POINT) return;
     const size_t rows = static_cast<size_t>(3 + P->hp.p) * (P->hp.cut_max - P->hp.cut_min + 1) * sizeof(float2) +
                         static_cast<size_t>(P->wz + 1) * sizeof(double2);
     const size_t sums = P->hp.p > 2 ? static_cast<size_t>(in_point_waves(true, 0)) * (2 * P->hp.p + 1) * 512 : 0;
@@ -627,15 +638,17 @@ void build_point(qaoa_plan_s* P, const InnerHost& in) {
     auto u16 = [](int64_t x) { return static_cast<uint16_t>(x); };
     for (const auto& g : P->in_groups)
         for (int64_t i = g.first; i < g.first + g.count; ++i) {
-            const ConeIn& c = in.cones[static_cast<size_t>(i)];
-            const int64_t t = i - g.first;   // trees: four of a class to a wave
-            if (!g.tree && c.cfg_off < 0) return;
             if (q.n_part + g.chunks > IN_POINT || q.n + g.chunks > IN_POINT) return;
-            if (g.tree && t % 4 == 0)
-                q.unit[q.n++] = {u16(g.tr + t), 0, 1, u16(q.n_part), static_cast<uint8_t>(c.kin),
-                                 static_cast<uint8_t>(std::min<int64_t>(4, g.count - t))};
+            if (g.tree) {
+                if (i == g.first)
+                    q.unit[q.n++] = {u16(i), 0, 1, u16(q.n_part), 0, static_cast<uint8_t>(g.count)};
+                q.part[q.n_part++] = {1, u16(in.tr[static_cast<size_t>(i)].orbit)};
+                continue;
+            }
+            const ConeIn& c = in.cones[static_cast<size_t>(i)];
+            if (c.cfg_off < 0) return;
             for (int32_t ch = 0; ch < g.chunks; ++ch) {
-                if (!g.tree) q.unit[q.n++] = {u16(i), u16(ch), u16(g.chunks), u16(q.n_part), static_cast<uint8_t>(c.kin), 0};
+                q.unit[q.n++] = {u16(i), u16(ch), u16(g.chunks), u16(q.n_part), static_cast<uint8_t>(c.kin), 0};
                 q.part[q.n_part++] = {u16(g.chunks), u16(c.orbit)};
             }
         }
@@ -953,11 +966,14 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     const size_t o_dlf = has_wd ? place(wd.leaf.size() * sizeof(ZLeaf)) : 0;
     const size_t o_ilf = has_in ? place(in.leaf.size() * sizeof(ZLeaf)) : 0;
     const size_t o_dcf = has_wd ? place(wd.cfg.size() * sizeof(CfgWd)) : 0;
-    const size_t o_itr = has_in ? place(in.tr.size() * sizeof(ConeTr)) : 0;
-    const size_t o_itc = has_in ? place(in.trcfg.size() * sizeof(uint32_t)) : 0;
-    const size_t o_ity = has_in ? place(in.types.size() * sizeof(ZLeaf)) : 0;
+    const bool has_tr = !in.tr.empty();
+    const size_t o_tr = has_tr ? place(in.tr.size() * sizeof(D2Cone)) : 0;
+    const size_t o_tb = has_tr ? place(in.branch.size() * sizeof(int32_t)) : 0;
+    const size_t o_tt2 = has_tr ? place(in.types.size() * sizeof(D2Type)) : 0;
+    const size_t o_tl = has_tr ? place(in.leaf2.size() * sizeof(D2Leaf)) : 0;
     const size_t o_ic = has_in ? place(in.cfg.size() * sizeof(CfgList)) : 0;
-    const size_t o_is = has_in ? place(in.seg.size() * sizeof(int32_t)) : 0;
+    const bool has_seg = !in.seg.empty();
+    const size_t o_is = has_seg ? place(in.seg.size() * sizeof(int32_t)) : 0;
     const size_t copied = arena;
     const size_t o_wo = has_wh ? place(static_cast<size_t>(wh.obs) * sizeof(float)) : 0;
     const size_t o_dta = has_wd ? place(static_cast<size_t>(wd.tab_bytes)) : 0;
@@ -995,6 +1011,12 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
             put(o_wm, wh.mem.data(), wh.mem.size() * sizeof(MemWh));
             put(o_ww, wh.Wg.data(), wh.Wg.size() * sizeof(double));
         }
+        if (has_tr) {
+            put(o_tr, in.tr.data(), in.tr.size() * sizeof(D2Cone));
+            put(o_tb, in.branch.data(), in.branch.size() * sizeof(int32_t));
+            put(o_tt2, in.types.data(), in.types.size() * sizeof(D2Type));
+            put(o_tl, in.leaf2.data(), in.leaf2.size() * sizeof(D2Leaf));
+        }
         if (has_wd) {
             put(o_dco, wd.cones.data(), wd.cones.size() * sizeof(ConeWd));
             put(o_dun, wd.units.data(), wd.units.size() * sizeof(UnitWd));
@@ -1005,13 +1027,10 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
         if (has_in) {
             put(o_in, in.cones.data(), in.cones.size() * sizeof(ConeIn));
             put(o_ig, in.grp.data(), in.grp.size() * sizeof(GrpIn));
-            put(o_itr, in.tr.data(), in.tr.size() * sizeof(ConeTr));
-            put(o_itc, in.trcfg.data(), in.trcfg.size() * sizeof(uint32_t));
-            put(o_ity, in.types.data(), in.types.size() * sizeof(ZLeaf));
             put(o_ilf, in.leaf.data(), in.leaf.size() * sizeof(ZLeaf));
             put(o_ic, in.cfg.data(), in.cfg.size() * sizeof(CfgList));
-            put(o_is, in.seg.data(), in.seg.size() * sizeof(int32_t));
         }
+        if (has_seg) put(o_is, in.seg.data(), in.seg.size() * sizeof(int32_t));
         if (d1) {
             put(o_dc, dc.data(), dc.size() * sizeof(ConeD1));
             put(o_dw, dw.data(), dw.size() * sizeof(double2));
@@ -1048,13 +1067,14 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     P->d_wdtab = has_wd ? base + o_dta : nullptr;
     P->d_in = has_in ? reinterpret_cast<ConeIn*>(base + o_in) : nullptr;
     P->d_ingrp = has_in ? reinterpret_cast<GrpIn*>(base + o_ig) : nullptr;
-    P->d_tr = has_in ? reinterpret_cast<ConeTr*>(base + o_itr) : nullptr;
-    P->d_trcfg = has_in ? reinterpret_cast<uint32_t*>(base + o_itc) : nullptr;
-    P->d_types = has_in ? reinterpret_cast<ZLeaf*>(base + o_ity) : nullptr;
+    P->d_tr = has_tr ? reinterpret_cast<D2Cone*>(base + o_tr) : nullptr;
+    P->d_branch = has_tr ? reinterpret_cast<int32_t*>(base + o_tb) : nullptr;
+    P->d_types = has_tr ? reinterpret_cast<D2Type*>(base + o_tt2) : nullptr;
+    P->d_leaf2 = has_tr ? reinterpret_cast<D2Leaf*>(base + o_tl) : nullptr;
     P->n_types = static_cast<int32_t>(in.types.size());
     P->d_leaf = has_in ? reinterpret_cast<ZLeaf*>(base + o_ilf) : nullptr;
     P->d_incfg = has_in ? reinterpret_cast<CfgList*>(base + o_ic) : nullptr;
-    P->d_inseg = has_in ? reinterpret_cast<int32_t*>(base + o_is) : nullptr;
+    P->d_inseg = has_seg ? reinterpret_cast<int32_t*>(base + o_is) : nullptr;
     P->d_intab = has_in ? base + o_it : nullptr;
     P->d_cut = base + o_cut;
     P->d_tt = base + o_tt;
@@ -1154,10 +1174,6 @@ InArgs inner_args(const qaoa_plan_s* P, const double* gamma, const double* beta,
     a.grp = P->d_ingrp;
     a.leaf = P->d_leaf;
     a.wz = P->wz;
-    a.tr = P->d_tr;
-    a.trcfg = P->d_trcfg;
-    a.types = P->d_types;
-    a.n_types = P->n_types;
     a.tab = P->d_intab;
     a.gamma = gamma;
     a.beta = beta;
@@ -1171,23 +1187,75 @@ InArgs inner_args(const qaoa_plan_s* P, const double* gamma, const double* beta,
     a.g = g;
     return a;
 }
+D2Args depth2_args(const qaoa_plan_s* P, const double* gamma, const double* beta, int64_t gamma_P, double* zz, double* g) {
+    D2Args a{};
+    a.cones = P->d_tr;
+    a.branch = P->d_branch;
+    a.types = P->d_types;
+    a.leaf = P->d_leaf2;
+    a.n_types = P->n_types;
+    a.gamma = gamma;
+    a.beta = beta;
+    a.gamma_P = gamma_P;
+    a.deltas = P->d_inst_delta;
+    a.M = static_cast<int32_t>(P->hp.cones.size());
+    a.zz = zz;
+    a.g = g;
+    return a;
+}
+
+// The trees of a group.
+hipError_t launch_tree_group(const qaoa_plan_s* P, const qaoa_plan_s::InGroup& grp, bool grad, int upw_log2,
+                             int64_t n_points, const double* gamma, const double* beta, int64_t gamma_P, double* zz,
+                             double* g, hipStream_t st) {
+    D2Args a = depth2_args(P, gamma, beta, gamma_P, zz, g);
+    if (P->opt.one_cone_at_a_time) {
+        a.units = a.upw = a.blocks = a.n_seg = a.P = 1;
+        for (int64_t i = 0; i < grp.count; ++i) {
+            a.cones = P->d_tr + grp.first + i;
+            a.inst0 = P->tr_inst[static_cast<size_t>(grp.first + i)];
+            for (int64_t pt = 0; pt < n_points; ++pt) {
+                a.point0 = static_cast<int32_t>(pt);
+                const hipError_t e = launch_depth2(a, grad, st);
+                if (e != hipSuccess) return e;
+            }
+        }
+        return hipSuccess;
+    }
+    a.cones = P->d_tr + grp.first;
+    a.units = static_cast<int32_t>(grp.count);
+    a.upw = 1 << upw_log2;
+    a.blocks = grp.blocks[upw_log2];
+    a.n_seg = grp.n_seg;
+    a.inst0 = P->tr_inst[static_cast<size_t>(grp.first)];
+    a.seg = grp.n_seg > 1 ? P->d_inseg + grp.seg[upw_log2] : nullptr;
+    // a grid holds fewer than 2^32 threads
+    const int64_t slab = std::max<int64_t>(1, (static_cast<int64_t>(UINT32_MAX) / 256) / a.blocks);
+    for (int64_t p0 = 0; p0 < n_points; p0 += slab) {
+        a.point0 = static_cast<int32_t>(p0);
+        a.P = static_cast<int32_t>(std::min(slab, n_points - p0));
+        const hipError_t e = launch_depth2(a, grad, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 }  // namespace
 
 hipError_t launch_inner_group(const qaoa_plan_s* P, const qaoa_plan_s::InGroup& grp, bool grad, int upw_log2,
                               int64_t n_points, const double* gamma, const double* beta, int64_t gamma_P, double* zz,
                               double* g, double* part, size_t part_cap, hipStream_t st) {
+    if (grp.tree) return launch_tree_group(P, grp, grad, upw_log2, n_points, gamma, beta, gamma_P, zz, g, st);
     const HostPlan& hp = P->hp;
     InArgs a = inner_args(P, gamma, beta, gamma_P, zz, g);
     a.cones = P->d_in + grp.first;
     a.signs = grp.signs ? 1 : 0;
-    if (grp.tree) a.tr = P->d_tr + grp.tr;
     a.chunks = grp.chunks;
     a.part = part;
     const int64_t nv = grad ? 2 * hp.p + 1 : 1;
     auto run = [&](int64_t p0, int64_t np, int64_t cones) {
         a.point0 = static_cast<int32_t>(p0);
         a.P = static_cast<int32_t>(np);
-        hipError_t e = grp.tree ? launch_inner_tree(grp.kin, grad, a, st) : launch_inner(grp.kin, grad, a, st);
+        hipError_t e = launch_inner(grp.kin, grad, a, st);
         if (e == hipSuccess && grp.chunks > 1) e = launch_inner_sum(a, static_cast<int32_t>(cones), grad, st);
         return e;
     };
@@ -1198,7 +1266,6 @@ hipError_t launch_inner_group(const qaoa_plan_s* P, const qaoa_plan_s::InGroup& 
         a.blocks = (grp.chunks + 3) / 4;
         for (int64_t i = 0; i < grp.count; ++i) {
             a.cones = P->d_in + grp.first + i;
-            if (grp.tree) a.tr = P->d_tr + grp.tr + i;
             a.inst0 = P->in_inst[static_cast<size_t>(grp.first + i)];
             for (int64_t pt = 0; pt < n_points; ++pt) {
                 const hipError_t e = run(pt, 1, 1);
@@ -1349,6 +1416,13 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
     const int32_t M = static_cast<int32_t>(hp.cones.size());
     const int32_t R = hp.cut_max - hp.cut_min + 1;
     if (P->in_max_k > P->opt.k_lds_max && budget_refuses(P, P->in_max_k, grad, msg)) return QAOA_ENOMEM;
+    if (P->d2_point) {
+        D2Args a = depth2_args(P, gamma, beta, n_points, term_zz, grad ? term_grad : nullptr);
+        a.units = M;
+        a.P = static_cast<int32_t>(n_points);
+        QCHECK(launch_depth2_point(a, P->d_W, energy, dgamma, dbeta, stream));
+        return QAOA_OK;
+    }
     if (P->in_point.n) {
         InArgs a = inner_args(P, gamma, beta, n_points, term_zz, grad ? term_grad : nullptr);
         InPoint q = P->in_point;
@@ -1356,7 +1430,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         q.energy = energy;
         q.dgamma = dgamma;
         q.dbeta = dbeta;
-        QCHECK(launch_inner_point(a, q, grad, n_points, stream));
+        QCHECK(launch_inner_point(a, depth2_args(P, gamma, beta, n_points, nullptr, nullptr), q, grad, n_points, stream));
         return QAOA_OK;
     }
     const size_t npl = static_cast<size_t>(hp.n_inst) * n_points * p;   // (instance, point, layer) rows
@@ -1404,7 +1478,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
     // units per wave: the workgroup's set-up (phase rows) is shared by more units once the waves
     // fill the chip several times over
     auto inner_upw = [&](const qaoa_plan_s::InGroup& grp) {
-        const int64_t units = grp.count * grp.chunks * n_points / (grp.tree ? 4 : 1);
+        const int64_t units = grp.count * grp.chunks * n_points / (grp.tree ? 64 : 1);
         int j = 0;
         while (j < 3 && (units >> (j + 1)) >= (int64_t{1} << 15)) ++j;
         return j;
@@ -1814,9 +1888,11 @@ void release_device(qaoa_plan_s* P) {
     P->cap_part = 0;
     P->d_in = nullptr;
     P->d_ingrp = nullptr;
-    P->d_leaf = P->d_wdleaf = P->d_types = nullptr;
+    P->d_leaf = P->d_wdleaf = nullptr;
     P->d_tr = nullptr;
-    P->d_trcfg = nullptr;
+    P->d_branch = nullptr;
+    P->d_types = nullptr;
+    P->d_leaf2 = nullptr;
     P->d_intab = nullptr;
     P->d_wd = nullptr;
     P->d_wdunit = nullptr;

@@ -10,6 +10,7 @@
 #include "device.hpp"
 #include "hbm_impl.hpp"
 #include "inner.hpp"
+#include "inner_plan.hpp"
 #include "plan.hpp"
 #include "qaoa.h"
 #include "whole.hpp"
@@ -48,8 +49,7 @@ struct qaoa_plan_s {
         int kin, K;         // inner qubits; cone qubits, or 0
         bool wh;            // cones that are members of wh_groups
         bool signs;         // cones with leaves (shell.hpp)
-        bool tree;          // inner_tree.hip; from d_tr + tr on
-        int64_t tr;
+        bool tree;          // closed form (depth2.hip): from d_tr + first on, one unit per cone
         int64_t first, count;
         int32_t chunks;     // units of work per cone
         int32_t n_seg;      // instances
@@ -75,9 +75,12 @@ struct qaoa_plan_s {
     qaoa::ZLeaf* d_wdleaf = nullptr;
     qaoa::ZLeaf* d_leaf = nullptr;       // of the cones in d_in
     int32_t wz = 0;                      // largest coupling of a leaf
-    qaoa::ConeTr* d_tr = nullptr;        // those whose shell is leaves only, their signs and choices of leaves
-    uint32_t* d_trcfg = nullptr;
-    qaoa::ZLeaf* d_types = nullptr;
+    qaoa::D2Cone* d_tr = nullptr;        // depth-2 trees
+    int32_t* d_branch = nullptr;
+    qaoa::D2Type* d_types = nullptr;
+    qaoa::D2Leaf* d_leaf2 = nullptr;
+    std::vector<int32_t> tr_inst;        // instance of each
+    bool d2_point = false;               // all cones are trees, few enough for one launch per call
     int32_t n_types = 0;
     qaoa::CfgWd* d_wdcfg = nullptr;
     uint8_t* d_wdtab = nullptr;
@@ -176,11 +179,19 @@ inline bool depth1_closed(const qaoa_plan_s* P) { return P->hp.p == 1 && P->opt.
 // over, and the kernels for whole cones store half of the state) whose inner state fits the
 // registers of one wave.  Every such cone measured faster there: 14 qubits, p = 2 (6 inner)
 // 93x, 18 qubits (8 inner) 4x, 26 qubits (8 inner) 150x; C_10000(1,2) at one point, 10-11 qubits
-// with as many amplitudes as before, 26.7 -> 16 us for the call.  Real weights and
-// forced layouts (tune >= 2) keep the kernels for whole cones.
+// with as many amplitudes as before, 26.7 -> 16 us for the call.  Real weights (but for
+// depth-2 trees) and forced layouts (tune >= 2) keep the kernels for whole cones.
 inline bool inner_cone(const qaoa_plan_s* P, const Cone& c) {
     const int32_t p = P->hp.p;
-    return p >= 2 && p <= IN_PMAX && !P->hp.realw && P->opt.tune < 2 && c.nd[p - 1] <= IN_KMAX && c.nd[p - 1] < c.k;
+    return p >= 2 && p <= IN_PMAX && P->opt.tune < 2 && c.nd[p - 1] <= IN_KMAX && c.nd[p - 1] < c.k &&
+           (!P->hp.realw || (p == 2 && tree_cone(c, true)));
+}
+
+// Those of them in the closed form of depth2_impl.hpp (a term of a 14-qubit cone: 0.6 ns as states of
+// its 6 inner qubits, 0.03 ns).  Up to 10 inner qubits, as for the states: the tests hold the pass
+// kinds that larger cones launch.
+inline bool closed_tree(const qaoa_plan_s* P, const Cone& c) {
+    return P->hp.p == 2 && inner_cone(P, c) && tree_cone(c, P->hp.realw);
 }
 
 // Cones with more inner qubits, on a workgroup each.  The lines at 26 (p = 2) and 25 cone qubits
