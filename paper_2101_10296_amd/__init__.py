@@ -37,6 +37,26 @@ def _check(st: int):
         raise QaoaError(st, _capi.lib().qaoa_last_error().decode(errors="replace"))
 
 
+_T = None
+
+
+def _torch():
+    """torch, imported at the first evaluation (plans and host queries do without it)."""
+    global _T
+    if _T is None:
+        import torch
+        _T = torch
+    return _T
+
+
+def _stream(t) -> int:
+    """The current stream of the tensor's device, as the C interface takes it (torch's own accessor for
+    the raw handle: 0.2 us, 1.9 us through a Stream object)."""
+    torch = _torch()
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return raw(t.get_device()) if raw is not None else torch.cuda.current_stream(t.device).cuda_stream
+
+
 def _i32(a):
     return np.ascontiguousarray(np.asarray(a, dtype=np.int32))
 
@@ -95,11 +115,12 @@ class Plan:
             _check(L.qaoa_plan_batch(arr, len(_instances), C.byref(o), C.byref(h)))
         self._h = h
         self.p = int(p)
-        inf = self.info()
-        self.n_nodes = int(inf["n_nodes"])
-        self.n_edges = int(inf["n_edges"])
-        self.n_orbits = int(inf["n_orbits"])
-        self.n_instances = int(inf["n_instances"])
+        inf = _capi.PlanInfo()
+        _check(L.qaoa_plan_query(h, C.byref(inf)))
+        self.n_nodes = inf.n_nodes
+        self.n_edges = inf.n_edges
+        self.n_orbits = inf.n_orbits
+        self.n_instances = inf.n_instances
 
     @classmethod
     def batch(cls, instances, p: int, **opts):
@@ -153,9 +174,17 @@ class Plan:
     def _angles(self, gamma, beta):
         """(gamma, beta) as contiguous float64 [N * P, p] with N = n_instances: [P, p] inputs
         are shared by every instance, [N, P, p] inputs give each instance its own points."""
-        import torch
+        torch = _torch()
         if not (isinstance(gamma, torch.Tensor) and isinstance(beta, torch.Tensor)):
             raise TypeError("gamma and beta must be torch tensors on a HIP device")
+        shape = gamma.shape
+        if (self.n_instances == 1 and len(shape) == 2 and shape[1] == self.p and beta.shape == shape
+                and gamma.is_cuda and beta.is_cuda):
+            # the usual call: nothing to reshape, and nothing to convert for contiguous FP64 (5 us less)
+            f64 = torch.float64
+            g = gamma if gamma.dtype is f64 else gamma.detach().to(f64)
+            b = beta if beta.dtype is f64 else beta.detach().to(f64)
+            return (g if g.is_contiguous() else g.contiguous(), b if b.is_contiguous() else b.contiguous(), shape[0])
         if gamma.device.type != "cuda" or beta.device.type != "cuda":
             raise ValueError("gamma and beta must live on the GPU")
         if gamma.shape != beta.shape:
@@ -180,10 +209,10 @@ class Plan:
 
     @staticmethod
     def _out(t, shape, device):
-        import torch
+        torch = _torch()
         if t is None:
             return torch.empty(shape, dtype=torch.float64, device=device)
-        if tuple(t.shape) != tuple(shape) or t.dtype != torch.float64 or not t.is_contiguous() or t.device != device:
+        if t.shape != shape or t.dtype != torch.float64 or not t.is_contiguous() or t.device != device:
             raise ValueError(f"output tensor must be contiguous float64 {tuple(shape)} on {device}")
         return t
 
@@ -194,34 +223,33 @@ class Plan:
         out: optional preallocated E (or (E, zz) with term_zz), e.g. to keep device pointers
         fixed for graph replay."""
         g, b, P = self._angles(gamma, beta)
+        dev = g.device
         o = out if isinstance(out, (tuple, list)) else (out, None)
-        E = self._out(o[0], self._shape(P), g.device)
-        zz = self._out(o[1], (P, max(self.n_orbits, 1)), g.device) if term_zz else None
-        import torch
-        stream = torch.cuda.current_stream(g.device).cuda_stream
+        E = self._out(o[0], self._shape(P), dev)
+        zz = self._out(o[1], (P, max(self.n_orbits, 1)), dev) if term_zz else None
         _check(_capi.lib().qaoa_energy(self._h, P, g.data_ptr(), b.data_ptr(), E.data_ptr(),
-                                       None if zz is None else zz.data_ptr(), stream))
+                                       None if zz is None else zz.data_ptr(), _stream(g)))
         return (E, zz[:, : self.n_orbits]) if term_zz else E
 
     def energy_grad(self, gamma, beta, out=None):
         """(E [P], dE/dgamma [P, p], dE/dbeta [P, p]) as cuda float64 tensors.
 
         out: optional preallocated (E, dgamma, dbeta)."""
-        import torch
         g, b, P = self._angles(gamma, beta)
+        dev = g.device
         o = out if out is not None else (None, None, None)
-        E = self._out(o[0], self._shape(P), g.device)
-        dg = self._out(o[1], self._shape(P, self.p), g.device)
-        db = self._out(o[2], self._shape(P, self.p), g.device)
-        stream = torch.cuda.current_stream(g.device).cuda_stream
+        E = self._out(o[0], self._shape(P), dev)
+        shape = self._shape(P, self.p)
+        dg = self._out(o[1], shape, dev)
+        db = self._out(o[2], shape, dev)
         _check(_capi.lib().qaoa_energy_grad(self._h, P, g.data_ptr(), b.data_ptr(), E.data_ptr(),
-                                            dg.data_ptr(), db.data_ptr(), stream))
+                                            dg.data_ptr(), db.data_ptr(), _stream(g)))
         return E, dg, db
 
     def energy_grad_terms(self, gamma, beta):
         """(E [P], dE/dgamma [P, p], dE/dbeta [P, p], zz [P, M], d zz / d(gamma, beta) [P, 2p, M]):
         the energy gradient together with every orbit term and its own gradient."""
-        import torch
+        torch = _torch()
         g, b, P = self._angles(gamma, beta)
         dev = g.device
         M = max(self.n_orbits, 1)
@@ -230,9 +258,8 @@ class Plan:
         db = torch.empty(self._shape(P, self.p), dtype=torch.float64, device=dev)
         zz = torch.empty((P, M), dtype=torch.float64, device=dev)
         tg = torch.empty((P, 2 * self.p, M), dtype=torch.float64, device=dev)
-        stream = torch.cuda.current_stream(dev).cuda_stream
         _check(_capi.lib().qaoa_energy_grad_terms(self._h, P, g.data_ptr(), b.data_ptr(), E.data_ptr(), dg.data_ptr(),
-                                                  db.data_ptr(), zz.data_ptr(), tg.data_ptr(), stream))
+                                                  db.data_ptr(), zz.data_ptr(), tg.data_ptr(), _stream(g)))
         return E, dg, db, zz[:, : self.n_orbits], tg[:, :, : self.n_orbits]
 
     def close(self):
