@@ -32,6 +32,8 @@ struct D1Args {
     double g_scale;          // k_depth1_point: factor of the stored d zz / d theta (the unit, for radians)
 };
 
+constexpr int D1_POINT = 2048;   // orbits of a plan whose terms and sums are one launch
+
 // Items t = point * n_cones + slot, item0 <= t < n_items.
 hipError_t launch_depth1_terms(const D1Args& a, int64_t item0, int64_t n_items, bool grad, hipStream_t st);
 // One instance, cones[m] of orbit m: terms and weighted sums together.

@@ -1369,7 +1369,7 @@ qaoa_status enqueue_depth1(qaoa_plan_s* P, int64_t n_points, const double* gamma
     const int32_t M = static_cast<int32_t>(hp.cones.size());
     if (P->max_k > P->opt.k_lds_max && budget_refuses(P, P->max_k, grad, msg)) return QAOA_ENOMEM;
     D1Args a{P->d_d1, P->d_d1w, M, gamma, beta, n_points, P->d_inst_delta, n_points, M, term_zz, term_grad, 1.0};
-    if (hp.n_inst == 1 && M <= 2048 && !P->opt.profile && !P->opt.one_cone_at_a_time) {
+    if (hp.n_inst == 1 && M <= D1_POINT && !P->opt.profile && !P->opt.one_cone_at_a_time) {
         a.g_scale = hp.inst_delta[0];   // the caller's per-term gradient is in radians
         QCHECK(launch_depth1_point(a, P->d_W, energy, dgamma, dbeta, stream));
         return QAOA_OK;
