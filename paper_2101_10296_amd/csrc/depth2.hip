@@ -1,13 +1,16 @@
 // Kernels of the depth-2 closed form (depth2_impl.hpp).
 //
-// Bound: FP64 issue, some 400 operations a term with its gradient where the plan has few kinds of
-// branches (unit and small integer weights): the workgroup evaluates each kind's sines and cosines
-// once for its cones.  Real weights, where every branch is its own kind, take some 20 sines and
-// cosines a term instead.  Measured on one MI355X, energy and gradient at p = 2 of random 3-regular
-// graphs: n = 10000, 256 points, 215.6 ms on the kernels for whole cones, 2.32 ms as states of the
-// inner qubits, 0.194 ms with this form (the kernel 112 us: 3.8 million terms, and 154 MB of them
-// written); Gaussian weights, n = 104, 19 points, 390 -> 87 us (most of it the few cones with
-// cycles); a ring at 16384 points 118 -> 51 (states, one launch) -> 6.7 us.
+// Where the plan has few kinds of sides (unit and small integer weights), a workgroup evaluates each
+// kind of branch and of side once, in LDS, and a term is some 130 FP64 operations on two sides and
+// an edge: bound by the writes of the terms (n = 10000, random 3-regular, 256 points, energy and
+// gradient: 154 MB in 36 us, 4.3 TB/s; 112 us where each term multiplied its own branches).
+// Otherwise (real weights: every branch its own kind) a term takes some 20 sines and cosines: bound
+// by FP64 issue.
+//
+// Calls on one MI355X, energy and gradient at p = 2: that graph 215.6 ms on the kernels for whole
+// cones, 2.32 ms as states of the inner qubits, 0.136 ms here (90 us of it the weighted sums and the
+// 65 cones with cycles); Gaussian weights, n = 104, 19 points, 390 -> 87 us (most of it the cones
+// with cycles); a ring at 16384 points 118 -> 51 (states, one launch) -> 6.7 us.
 #include "depth2_impl.hpp"
 
 namespace qaoa {
@@ -17,6 +20,7 @@ namespace {
 template <bool GRAD, bool TABLE>
 __global__ void __launch_bounds__(256) k_depth2(D2Args a) {
     __shared__ D2Val s_v[TABLE ? D2_TABLE : 1];
+    __shared__ D2Side<GRAD> s_s[TABLE ? D2_TABLE : 1];
     __shared__ D2Angles s_a;
     const int tid = threadIdx.x;
     const int64_t point = blockIdx.x / a.blocks + a.point0;
@@ -40,10 +44,17 @@ __global__ void __launch_bounds__(256) k_depth2(D2Args a) {
         if (tid < a.n_types) s_v[tid] = d2_val(a.types[tid], a.leaf, t1, t2);
     __syncthreads();
     const D2Angles an = s_a;
+    if constexpr (TABLE) {
+        if (tid < a.n_sides) {
+            const D2SideDef d = a.sides[tid];
+            s_s[tid] = d2_side<GRAD>(d.n, an, [&](int i) { return s_v[a.branch[d.off + i]]; });
+        }
+        __syncthreads();
+    }
     for (int u = u0 + tid, i = 0; i < a.upw && u < u1; ++i, u += 256) {
         const D2Cone c = a.cones[u];
         double v[5];
-        if constexpr (TABLE) d2_term<GRAD>(s_v[c.edge], c.nu, c.nv, an, [&](int j) { return s_v[a.branch[c.off + j]]; }, v);
+        if constexpr (TABLE) d2_term<GRAD>(s_v[c.edge], s_s[c.u], s_s[c.v], an, v);
         else d2_cone<GRAD>(a, c, t1, t2, an, v);
         a.zz[static_cast<size_t>(point) * a.M + c.orbit] = v[0];
         if constexpr (GRAD) {
@@ -110,7 +121,7 @@ hipError_t launch_depth2(const D2Args& a, bool grad, hipStream_t st) {
     const int64_t blocks = static_cast<int64_t>(a.blocks) * a.P;
     if (blocks <= 0) return hipSuccess;
     const dim3 grid(static_cast<unsigned>(blocks)), block(256);
-    if (a.n_types <= D2_TABLE) {
+    if (a.n_types <= D2_TABLE && a.n_sides <= D2_TABLE) {
         if (grad) hipLaunchKernelGGL((k_depth2<true, true>), grid, block, 0, st, a);
         else hipLaunchKernelGGL((k_depth2<false, true>), grid, block, 0, st, a);
     } else {

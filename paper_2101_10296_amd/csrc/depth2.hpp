@@ -7,7 +7,7 @@
 
 namespace qaoa {
 
-constexpr int D2_TABLE = 32;   // kinds of branches that a workgroup evaluates once for its cones
+constexpr int D2_TABLE = 32;   // kinds of branches, and of sides, that a workgroup evaluates once for its cones
 constexpr int D2_POINT = 256;  // orbits of a plan whose terms and sums are one launch
 
 // A neighbour of u or v (or, without leaves, the edge itself): its coupling and those of its leaves.
@@ -19,19 +19,23 @@ struct D2Leaf {
     double w;                  // m leaves of coupling w (its sign has no part)
     int32_t m, pad_;
 };
+// The neighbours of u or of v: their types in D2Args::branch
+struct D2SideDef {
+    int32_t off, n;
+};
 struct alignas(16) D2Cone {
     int32_t orbit;
     int32_t edge;              // type of the edge's coupling
-    int32_t off;               // types of the neighbours of u, then of v, in D2Args::branch
-    int16_t nu, nv;
+    int32_t u, v;              // sides
 };
 
 struct D2Args {
     const D2Cone* cones;       // of the launch
+    const D2SideDef* sides;
     const int32_t* branch;
     const D2Type* types;
     const D2Leaf* leaf;
-    int32_t n_types;
+    int32_t n_types, n_sides;
     const double* gamma;       // [inst][gamma_P][2]
     const double* beta;
     int64_t gamma_P;

@@ -124,12 +124,11 @@ __device__ __forceinline__ D2Side<GRAD> d2_side(int n, const D2Angles& a, const 
     return s;
 }
 
-// v[0]: <ZZ>; GRAD: v[1..4]: its derivatives in t_1, t_2, beta_1, beta_2.  e: the edge; get(i): neighbour i.
-template <bool GRAD, class Get>
-__device__ __forceinline__ void d2_term(const D2Val& e, int nu, int nv, const D2Angles& a, const Get& get, double (&v)[5]) {
+// v[0]: <ZZ>; GRAD: v[1..4]: its derivatives in t_1, t_2, beta_1, beta_2.  e: the edge; u, w: its sides.
+template <bool GRAD>
+__device__ __forceinline__ void d2_term(const D2Val& e, const D2Side<GRAD>& u, const D2Side<GRAD>& w, const D2Angles& a,
+                                        double (&v)[5]) {
 #pragma clang fp contract(off)
-    const D2Side<GRAD> u = d2_side<GRAD>(nu, a, get);
-    const D2Side<GRAD> w = d2_side<GRAD>(nv, a, [&](int i) { return get(nu + i); });
     const double cb = a.cb, sb = a.sb, C = a.C, S = a.S, CS = C * S, sb2 = sb * sb, cs = cb * sb;
     const double K = u.k + w.k, H = u.H1 + w.H1, Q = fma(u.gr, w.k, w.gr * u.k), R = fma(u.gr, w.H1, w.gr * u.H1);
     const double H2 = u.H2 + w.H2, G = u.gi + w.gi;
@@ -176,7 +175,11 @@ template <bool GRAD>
 __device__ __forceinline__ void d2_cone(const D2Args& a, const D2Cone& c, double t1, double t2, const D2Angles& an,
                                         double (&v)[5]) {
     auto val = [&](int t) { return d2_val(a.types[t], a.leaf, t1, t2); };
-    d2_term<GRAD>(val(c.edge), c.nu, c.nv, an, [&](int i) { return val(a.branch[c.off + i]); }, v);
+    auto side = [&](int q) {
+        const D2SideDef d = a.sides[q];
+        return d2_side<GRAD>(d.n, an, [&](int i) { return val(a.branch[d.off + i]); });
+    };
+    d2_term<GRAD>(val(c.edge), side(c.u), side(c.v), an, v);
 }
 
 }  // namespace qaoa

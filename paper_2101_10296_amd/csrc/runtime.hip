@@ -5,6 +5,7 @@
 #include "inner_plan.hpp"
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -359,6 +360,7 @@ struct InnerHost {
     std::vector<ZLeaf> leaf;
     std::vector<D2Cone> tr;
     std::vector<int32_t> branch;
+    std::vector<D2SideDef> sides;
     std::vector<D2Type> types;
     std::vector<D2Leaf> leaf2;
     int64_t tab_units = 0;   // table bytes / 16
@@ -471,6 +473,37 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         }
         return t;
     };
+    // sides of equal branches are one where all of them have a code (the first 64 kinds)
+    std::vector<std::array<int16_t, 8>> kinds;
+    std::vector<int32_t> kind_side;
+    auto side = [&](int32_t first, int n) {
+        std::array<int16_t, 8> key;
+        key.fill(-1);
+        bool coded = true;
+        for (int i = 0; i < n; ++i) {
+            key[static_cast<size_t>(i)] = shells.branches[static_cast<size_t>(first + i)].code;
+            coded = coded && key[static_cast<size_t>(i)] >= 0;
+        }
+        std::sort(key.begin(), key.begin() + n);
+        size_t k = 0;
+        while (coded && k < kinds.size() && kinds[k] != key) ++k;
+        if (coded && k < kinds.size()) return kind_side[k];
+        const int32_t s = static_cast<int32_t>(in.sides.size());
+        in.sides.push_back({static_cast<int32_t>(in.branch.size()), n});
+        for (int i = 0; i < n; ++i) {
+            ShellBranch b = shells.branches[static_cast<size_t>(first + i)];
+            if (coded) {
+                b.code = key[static_cast<size_t>(i)];
+                b.w = b.code / 343 - 3;
+            }
+            in.branch.push_back(branch_type(b));
+        }
+        if (coded && kinds.size() < 64) {
+            kinds.push_back(key);
+            kind_side.push_back(s);
+        }
+        return s;
+    };
     // a group of in_groups continues where its key does
     auto group = [&](int kin, int kk, bool wh, bool tree, bool signs, int64_t first) -> qaoa_plan_s::InGroup& {
         if (P->in_groups.empty() || P->in_groups.back().kin != kin || P->in_groups.back().K != kk ||
@@ -494,12 +527,11 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         const Cone& c = hp.cones[m];
         const ShellCone& q = sc[i];
         if (q.tree) {
-            D2Cone d{static_cast<int32_t>(m), 0, static_cast<int32_t>(in.branch.size()), q.nu, q.nv};
+            D2Cone d{static_cast<int32_t>(m), 0, side(q.br, q.nu), side(q.br + q.nu, q.nv)};
             ShellBranch edge;   // without leaves
             edge.w = q.w_uv;
             if (!hp.realw && std::abs(q.w_uv) <= 3.0) edge.code = static_cast<int16_t>((static_cast<int>(q.w_uv) + 3) * 343);
             d.edge = branch_type(edge);
-            for (int j = 0; j < q.nu + q.nv; ++j) in.branch.push_back(branch_type(shells.branches[static_cast<size_t>(q.br + j)]));
             qaoa_plan_s::InGroup& g = group(0, by_k ? c.k : 0, is_wh(m), true, false, static_cast<int64_t>(in.tr.size()));
             g.count += 1;
             P->in_max_k = std::max(P->in_max_k, c.k);
@@ -968,6 +1000,7 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     const size_t o_dcf = has_wd ? place(wd.cfg.size() * sizeof(CfgWd)) : 0;
     const bool has_tr = !in.tr.empty();
     const size_t o_tr = has_tr ? place(in.tr.size() * sizeof(D2Cone)) : 0;
+    const size_t o_ts = has_tr ? place(in.sides.size() * sizeof(D2SideDef)) : 0;
     const size_t o_tb = has_tr ? place(in.branch.size() * sizeof(int32_t)) : 0;
     const size_t o_tt2 = has_tr ? place(in.types.size() * sizeof(D2Type)) : 0;
     const size_t o_tl = has_tr ? place(in.leaf2.size() * sizeof(D2Leaf)) : 0;
@@ -1013,6 +1046,7 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
         }
         if (has_tr) {
             put(o_tr, in.tr.data(), in.tr.size() * sizeof(D2Cone));
+            put(o_ts, in.sides.data(), in.sides.size() * sizeof(D2SideDef));
             put(o_tb, in.branch.data(), in.branch.size() * sizeof(int32_t));
             put(o_tt2, in.types.data(), in.types.size() * sizeof(D2Type));
             put(o_tl, in.leaf2.data(), in.leaf2.size() * sizeof(D2Leaf));
@@ -1068,6 +1102,8 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     P->d_in = has_in ? reinterpret_cast<ConeIn*>(base + o_in) : nullptr;
     P->d_ingrp = has_in ? reinterpret_cast<GrpIn*>(base + o_ig) : nullptr;
     P->d_tr = has_tr ? reinterpret_cast<D2Cone*>(base + o_tr) : nullptr;
+    P->d_sides = has_tr ? reinterpret_cast<D2SideDef*>(base + o_ts) : nullptr;
+    P->n_sides = static_cast<int32_t>(in.sides.size());
     P->d_branch = has_tr ? reinterpret_cast<int32_t*>(base + o_tb) : nullptr;
     P->d_types = has_tr ? reinterpret_cast<D2Type*>(base + o_tt2) : nullptr;
     P->d_leaf2 = has_tr ? reinterpret_cast<D2Leaf*>(base + o_tl) : nullptr;
@@ -1190,6 +1226,8 @@ InArgs inner_args(const qaoa_plan_s* P, const double* gamma, const double* beta,
 D2Args depth2_args(const qaoa_plan_s* P, const double* gamma, const double* beta, int64_t gamma_P, double* zz, double* g) {
     D2Args a{};
     a.cones = P->d_tr;
+    a.sides = P->d_sides;
+    a.n_sides = P->n_sides;
     a.branch = P->d_branch;
     a.types = P->d_types;
     a.leaf = P->d_leaf2;
@@ -1480,7 +1518,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
     auto inner_upw = [&](const qaoa_plan_s::InGroup& grp) {
         const int64_t units = grp.count * grp.chunks * n_points / (grp.tree ? 64 : 1);
         int j = 0;
-        while (j < 3 && (units >> (j + 1)) >= (int64_t{1} << 15)) ++j;
+        while (j < 3 && (units >> (j + 1)) >= (int64_t{1} << (grp.tree ? 13 : 15))) ++j;
         return j;
     };
     auto run_inner = [&](const qaoa_plan_s::InGroup& grp, int j) {
@@ -1890,6 +1928,7 @@ void release_device(qaoa_plan_s* P) {
     P->d_ingrp = nullptr;
     P->d_leaf = P->d_wdleaf = nullptr;
     P->d_tr = nullptr;
+    P->d_sides = nullptr;
     P->d_branch = nullptr;
     P->d_types = nullptr;
     P->d_leaf2 = nullptr;

@@ -76,6 +76,8 @@ struct qaoa_plan_s {
     qaoa::ZLeaf* d_leaf = nullptr;       // of the cones in d_in
     int32_t wz = 0;                      // largest coupling of a leaf
     qaoa::D2Cone* d_tr = nullptr;        // depth-2 trees
+    qaoa::D2SideDef* d_sides = nullptr;
+    int32_t n_sides = 0;
     int32_t* d_branch = nullptr;
     qaoa::D2Type* d_types = nullptr;
     qaoa::D2Leaf* d_leaf2 = nullptr;
