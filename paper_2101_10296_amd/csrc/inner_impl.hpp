@@ -375,12 +375,14 @@ __device__ __forceinline__ void in_rows(const InArgs& a, int p, int inst, int po
             dyn[(3 + l) * R + j] = make_float2(x, y);
         }
     }
-    if (a.wz)
-        for (int j = tid; j <= a.wz; j += threads)
+    // on waves of their own, so that the three chains of FP64 sines run side by side
+    const int o1 = threads > 64 ? 64 : 0, o2 = threads > 128 ? 128 : 0;
+    if (a.wz && tid >= o1)
+        for (int j = tid - o1; j <= a.wz; j += threads - o1)
             sincos(a.gamma[ip] * delta * static_cast<double>(j), &ct[j].y, &ct[j].x);
-    if (tid < p) {   // exp(-i beta X) = kappa X^e (1 - i tau X), |tau| <= 1 (see k_tables)
+    if (const int i = tid - o2; i >= 0 && i < p) {   // exp(-i beta X) = kappa X^e (1 - i tau X), |tau| <= 1 (see k_tables)
         double s, c, t, k2;
-        sincos(a.beta[ip + tid], &s, &c);
+        sincos(a.beta[ip + i], &s, &c);
         if (fabs(c) >= fabs(s)) {
             t = s / c;
             k2 = c * c;
@@ -388,9 +390,9 @@ __device__ __forceinline__ void in_rows(const InArgs& a, int p, int inst, int po
             t = -c / s;
             k2 = s * s;
         }
-        sh.t[tid + 1] = static_cast<float>(t);
-        sh.k2[tid + 1] = k2;
-        if (tid == p - 1) {
+        sh.t[i + 1] = static_cast<float>(t);
+        sh.k2[i + 1] = k2;
+        if (i == p - 1) {
             sh.cs[0] = c * c - s * s;
             sh.cs[1] = 2.0 * s * c;
         }
