@@ -106,6 +106,29 @@ struct InPoint {
 hipError_t launch_inner_point(const InArgs& a, const D2Args& d, const InPoint& q, bool grad, int64_t n_points, hipStream_t st);
 
 hipError_t launch_inner(int kin, bool grad, const InArgs& a, hipStream_t st);
+// Several classes in one launch (inner_mix.hip), one unit per wave
+constexpr int IN_CLASSES = 16;
+// Units of a class (over a call's points) that may join: measured faster up to there (16 points of a
+// random 4-regular n = 60 168 -> 143 us, 256 points of the cones with cycles of n = 92, 3-regular, 56 ->
+// 49, 1024 points 158 -> 145, 4096 points 541 -> 532); beyond, set-up shared by several units per
+// wave counts for more.
+constexpr int64_t IN_MIX = 1 << 17;
+struct InMix {
+    struct Class {
+        int32_t kin, signs;
+        int32_t cone0, n_cones;    // from InArgs::cones on
+        int32_t units, chunks;
+        int32_t block0;            // first workgroup of a point
+        int32_t n_seg, inst0;
+        const int32_t* seg;
+        int64_t part0;             // its place in the partial sums
+        int64_t item0;             // first (point, cone, value) of those that launch_inner_mix_sum adds
+    } c[IN_CLASSES];
+    int32_t n, blocks;             // workgroups per point
+    int64_t items;
+};
+hipError_t launch_inner_mix(const InArgs& a, const InMix& m, bool grad, hipStream_t st);
+hipError_t launch_inner_mix_sum(const InArgs& a, const InMix& m, bool grad, hipStream_t st);
 // sums the chunks of every (point, cone) into zz and g
 hipError_t launch_inner_sum(const InArgs& a, int32_t n_cones, bool grad, hipStream_t st);
 // Table of layer l (2..p) of every cone: the cut of the couplings inside the qubits mixed by

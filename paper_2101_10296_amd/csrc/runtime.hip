@@ -1500,6 +1500,44 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
             const size_t one = static_cast<size_t>(grp.count) * grp.chunks * nv;
             part_need = std::max(part_need, std::max(one, std::min<size_t>(one * n_points, size_t{1} << 25)));
         }
+    // classes that share a launch, with room for the sums of all their parts
+    InMix mix{};
+    std::vector<char> mixed(P->in_groups.size(), 0);
+    if (!P->opt.profile && P->opt.tune == 0 && !P->opt.one_cone_at_a_time && n_points <= IN_MIX) {
+        int64_t parts = 0;
+        for (size_t i = 0; i < P->in_groups.size() && mix.n < IN_CLASSES; ++i) {
+            const auto& grp = P->in_groups[i];
+            const int64_t units = grp.count * grp.chunks;
+            if (grp.tree || (grp.wh && use_wh) || units * n_points > IN_MIX ||
+                (grp.chunks > 1 && parts + units * n_points * static_cast<int64_t>(nv) > (int64_t{1} << 25)))
+                continue;
+            InMix::Class& c = mix.c[mix.n++];
+            c.kin = grp.kin;
+            c.signs = grp.signs ? 1 : 0;
+            c.cone0 = static_cast<int32_t>(grp.first);
+            c.n_cones = static_cast<int32_t>(grp.count);
+            c.units = static_cast<int32_t>(units);
+            c.chunks = grp.chunks;
+            c.block0 = mix.blocks;
+            c.n_seg = grp.n_seg;
+            c.inst0 = P->in_inst[static_cast<size_t>(grp.first)];
+            c.seg = grp.n_seg > 1 ? P->d_inseg + grp.seg[0] : nullptr;
+            c.part0 = parts;
+            c.item0 = mix.items;
+            mix.blocks += grp.blocks[0];
+            if (grp.chunks > 1) {
+                parts += units * n_points * static_cast<int64_t>(nv);
+                mix.items += grp.count * n_points * static_cast<int64_t>(nv);
+            }
+            mixed[i] = 1;
+        }
+        if (mix.n < 2) {
+            mix = InMix{};
+            std::fill(mixed.begin(), mixed.end(), char{0});
+        } else {
+            part_need = std::max(part_need, static_cast<size_t>(parts));
+        }
+    }
     const size_t wd_one = static_cast<size_t>(P->wd_all_units) * nv;
     if (wd_one) part_need = std::max(part_need, std::max(wd_one, std::min<size_t>(wd_one * n_points, size_t{1} << 25)));
     if (part_need && (st = grow(P->d_part, P->cap_part, part_need, msg)) != QAOA_OK) return st;
@@ -1524,8 +1562,15 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
     auto run_inner = [&](const qaoa_plan_s::InGroup& grp, int j) {
         return launch_inner_group(P, grp, grad, j, n_points, gamma, beta, n_points, zz, g, P->d_part, P->cap_part, stream);
     };
+    if (mix.n) {
+        InArgs a = inner_args(P, gamma, beta, n_points, zz, g);
+        a.part = P->d_part;
+        a.P = static_cast<int32_t>(n_points);
+        QCHECK(launch_inner_mix(a, mix, grad, stream));
+        QCHECK(launch_inner_mix_sum(a, mix, grad, stream));
+    }
     for (const auto& grp : P->in_groups) {
-        if (grp.wh && use_wh) continue;
+        if ((grp.wh && use_wh) || mixed[static_cast<size_t>(&grp - P->in_groups.data())]) continue;
         if (P->opt.tune == 1 && grp.K <= P->opt.k_lds_max) continue;   // with the other cones of its size, below
         int j = inner_upw(grp);
         if (P->opt.tune == 1) {
