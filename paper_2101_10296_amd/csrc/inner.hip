@@ -39,25 +39,16 @@ k_inner_tables(const ConeIn* __restrict__ cones, const int32_t* __restrict__ ea,
 
 // The chunks of item t = (point, cone, value), in order.
 __device__ __forceinline__ void in_add_parts(const InArgs& a, int64_t t, int32_t n_cones, int32_t nv) {
-            const int v = static_cast<int>(t % nv);
-            const int64_t pc = t / nv;
-            const int32_t c = static_cast<int32_t>(pc % n_cones);
-            const int64_t i = pc / n_cones;
-            const double* src = a.part + (i * a.units + static_cast<int64_t>(c) * a.chunks) * nv + v;
-            double x = 0.0;
-            int ch = 0;
-            for (; ch + 8 <= a.chunks; ch += 8) {   // eight loads in flight, added in order
-                double y[8];
-    #pragma unroll
-                for (int i = 0; i < 8; ++i) y[i] = src[static_cast<size_t>(ch + i) * nv];
-    #pragma unroll
-                for (int i = 0; i < 8; ++i) x += y[i];
-            }
-            for (; ch < a.chunks; ++ch) x += src[static_cast<size_t>(ch) * nv];
-            const int32_t orbit = a.cones[c].orbit;
-            const size_t pt = static_cast<size_t>(i + a.point0);
-            if (v == 0) a.zz[pt * a.M + orbit] = x;
-            else a.g[(pt * 2 * a.p + (v - 1)) * a.M + orbit] = x;
+    const int v = static_cast<int>(t % nv);
+    const int64_t pc = t / nv;
+    const int32_t c = static_cast<int32_t>(pc % n_cones);
+    const int64_t i = pc / n_cones;
+    const double* src = a.part + (i * a.units + static_cast<int64_t>(c) * a.chunks) * nv + v;
+    const double x = in_part_sum(src, a.chunks, nv);
+    const int32_t orbit = a.cones[c].orbit;
+    const size_t pt = static_cast<size_t>(i + a.point0);
+    if (v == 0) a.zz[pt * a.M + orbit] = x;
+    else a.g[(pt * 2 * a.p + (v - 1)) * a.M + orbit] = x;
 }
 
 // One thread per (point, cone, value): the chunks of a cone in order.  Bound by the latency of its loads:

@@ -81,6 +81,22 @@ struct InArgs {
     double* part;              // chunks > 1: [P of the launch][units][values]
 };
 
+// A value of a cone's parts, nv apart, in order.
+__device__ __forceinline__ double in_part_sum(const double* src, int chunks, int nv) {
+    double x = 0.0;
+    int ch = 0;
+    for (; ch + 8 <= chunks; ch += 8) {   // eight loads in flight, added in order
+        double y[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) y[i] = src[static_cast<size_t>(ch + i) * nv];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x += y[i];
+    }
+    for (; ch < chunks; ++ch) x += src[static_cast<size_t>(ch) * nv];
+    return x;
+}
+
+hipError_t launch_inner(int kin, bool grad, const InArgs& a, hipStream_t st);
 // Small plans (inner_point.hip): the units of a point, a wave each, and where their sums go.
 constexpr int IN_POINT = 16;    // units, parts of cones, and orbits, at most
 // waves per workgroup: registers for 4 a SIMD; 2 where a wave holds psi and lambda over more
@@ -105,7 +121,6 @@ struct InPoint {
 // cones of one instance, all with listed configurations; a: cones of the plan, zz and g or null
 hipError_t launch_inner_point(const InArgs& a, const D2Args& d, const InPoint& q, bool grad, int64_t n_points, hipStream_t st);
 
-hipError_t launch_inner(int kin, bool grad, const InArgs& a, hipStream_t st);
 // Several classes in one launch (inner_mix.hip), one unit per wave
 constexpr int IN_CLASSES = 16;
 // Units of a class (over a call's points) that may join: measured faster up to there (16 points of a
@@ -125,10 +140,27 @@ struct InMix {
         int64_t item0;             // first (point, cone, value) of those that launch_inner_mix_sum adds
     } c[IN_CLASSES];
     int32_t n, blocks;             // workgroups per point
+    int32_t all;                   // cones in one unit write partial sums too
     int64_t items;
 };
 hipError_t launch_inner_mix(const InArgs& a, const InMix& m, bool grad, hipStream_t st);
 hipError_t launch_inner_mix_sum(const InArgs& a, const InMix& m, bool grad, hipStream_t st);
+// Plans of few cones with many units: the sums of the parts of k_inner_mix and the weighted sums of the
+// terms in one launch (inner_point.hip)
+struct InPointSum {
+    struct Cone {
+        int64_t part0;             // its class's place in the partial sums
+        int32_t units, unit0;      // of the class per point; the cone's first
+        int32_t chunks, orbit;
+    } c[IN_POINT];
+    int32_t n;
+    const double* W;
+    double* energy;
+    double* dgamma;
+    double* dbeta;
+};
+// a: zz and g or null; n = a.M cones of one instance
+hipError_t launch_inner_point_sum(const InArgs& a, const InPointSum& q, bool grad, hipStream_t st);
 // sums the chunks of every (point, cone) into zz and g
 hipError_t launch_inner_sum(const InArgs& a, int32_t n_cones, bool grad, hipStream_t st);
 // Table of layer l (2..p) of every cone: the cut of the couplings inside the qubits mixed by

@@ -40,7 +40,7 @@ __global__ void __launch_bounds__(256, GRAD && PP == 0 ? 2 : 4) k_inner_mix(InAr
     const int nv = GRAD ? 2 * p + 1 : 1, chunks = c.chunks;
     const int slot = u / chunks, ch = u - slot * chunks;
     const ConeIn& cd = a.cones[c.cone0 + slot];
-    double* out = chunks > 1 ? a.part + c.part0 + (static_cast<size_t>(point - a.point0) * c.units + u) * nv : nullptr;
+    double* out = chunks > 1 || m.all ? a.part + c.part0 + (static_cast<size_t>(point - a.point0) * c.units + u) * nv : nullptr;
     auto put = [&](int code, double x) {
         if (out) out[code] = x;
         else if (code == 0) a.zz[static_cast<size_t>(point) * a.M + cd.orbit] = x;

@@ -17,6 +17,26 @@
 namespace qaoa {
 namespace {
 
+// Value y of the weighted sums: the tree of k_combine over the terms in orbit order (its threads beyond
+// the last orbit hold zeros).
+template <class Q>
+__device__ __forceinline__ void in_point_sums(const InArgs& a, const Q& q, int y, int point, int p, double delta,
+                                              const double (&s_term)[IN_POINT][2 * IN_PMAX + 1]) {
+    double t[IN_POINT];
+#pragma unroll
+    for (int m = 0; m < IN_POINT; ++m) {
+        t[m] = 0.0;
+        if (m < a.M) t[m] = y == 0 ? q.W[m] * (1.0 - s_term[m][y]) * 0.5 : -0.5 * q.W[m] * s_term[m][y];
+    }
+#pragma unroll
+    for (int s = IN_POINT / 2; s > 0; s >>= 1)
+#pragma unroll
+        for (int m = 0; m < s; ++m) t[m] += t[m + s];
+    if (y == 0) q.energy[point] = t[0];
+    else if (y <= p) q.dgamma[static_cast<size_t>(point) * p + (y - 1)] = a.g ? t[0] : delta * t[0];
+    else q.dbeta[static_cast<size_t>(point) * p + (y - 1 - p)] = t[0];
+}
+
 template <bool GRAD, int PP>
 __global__ void __launch_bounds__(64 * in_point_waves(GRAD, PP), GRAD && PP == 0 ? 2 : 4)
 k_inner_point(InArgs a, D2Args d, InPoint q) {
@@ -71,8 +91,7 @@ k_inner_point(InArgs a, D2Args d, InPoint q) {
     }
     __syncthreads();
     if (tid >= nv) return;
-    // thread y: the terms' value y, in orbit order, then the tree of k_combine (whose threads
-    // beyond the last orbit hold zeros)
+    // thread y: the terms' value y
     const int y = tid;
     const double delta = a.deltas[0];
     const double gs = y >= 1 && y <= p && a.g ? delta : 1.0;   // the caller's terms are in radians
@@ -90,27 +109,51 @@ k_inner_point(InArgs a, D2Args d, InPoint q) {
             a.g[(static_cast<size_t>(point) * 2 * p + (y - 1)) * a.M + m] = x;
         }
     }
-    double t[IN_POINT];
-#pragma unroll
-    for (int m = 0; m < IN_POINT; ++m) {
-        t[m] = 0.0;
-        if (m < a.M) t[m] = y == 0 ? q.W[m] * (1.0 - s_term[m][y]) * 0.5 : -0.5 * q.W[m] * s_term[m][y];
+    in_point_sums(a, q, y, point, p, delta, s_term);
+}
+
+// One workgroup per point: a thread per (cone, value) adds the cone's parts as k_inner_sum, then the
+// sums.  Bound by its launch: the 18-qubit cone of a torus, 19 parts, 32 points, the whole call 19.2 us
+// with the parts, the terms and the sums in launches of their own, 17.5 here.
+template <bool GRAD>
+__global__ void __launch_bounds__(320) k_inner_point_sum(InArgs a, InPointSum q) {
+    __shared__ double s_term[IN_POINT][2 * IN_PMAX + 1];
+    const int tid = threadIdx.x, p = a.p, nv = GRAD ? 2 * p + 1 : 1;
+    const int point = blockIdx.x + a.point0;
+    const double delta = a.deltas[0];
+    if (tid < q.n * nv) {
+        const int i = tid / nv, v = tid - i * nv;
+        const InPointSum::Cone& c = q.c[i];
+        const double* src = a.part + c.part0 + (static_cast<size_t>(blockIdx.x) * c.units + c.unit0) * nv + v;
+        double x = in_part_sum(src, c.chunks, nv);
+        if (v >= 1 && v <= p && a.g) x *= delta;   // the caller's terms are in radians
+        s_term[c.orbit][v] = x;
+        if (v == 0) {
+            if (a.zz) a.zz[static_cast<size_t>(point) * a.M + c.orbit] = x;
+        } else if (a.g) {
+            a.g[(static_cast<size_t>(point) * 2 * p + (v - 1)) * a.M + c.orbit] = x;
+        }
     }
-#pragma unroll
-    for (int s = IN_POINT / 2; s > 0; s >>= 1)
-#pragma unroll
-        for (int m = 0; m < s; ++m) t[m] += t[m + s];
-    if (y == 0) q.energy[point] = t[0];
-    else if (y <= p) q.dgamma[static_cast<size_t>(point) * p + (y - 1)] = a.g ? t[0] : delta * t[0];
-    else q.dbeta[static_cast<size_t>(point) * p + (y - 1 - p)] = t[0];
+    __syncthreads();
+    if (tid < nv) in_point_sums(a, q, tid, point, p, delta, s_term);
 }
 
 }  // namespace
 
+hipError_t launch_inner_point_sum(const InArgs& a, const InPointSum& q, bool grad, hipStream_t st) {
+    if (q.n < 1 || q.n > IN_POINT || a.M != q.n || a.p < 2 || a.p > IN_PMAX) return hipErrorInvalidValue;
+    if (a.P <= 0) return hipSuccess;
+    const dim3 grid(static_cast<unsigned>(a.P)), block(320);
+    if (grad) hipLaunchKernelGGL(k_inner_point_sum<true>, grid, block, 0, st, a, q);
+    else hipLaunchKernelGGL(k_inner_point_sum<false>, grid, block, 0, st, a, q);
+    return hipGetLastError();
+}
+
 hipError_t launch_inner_point(const InArgs& a0, const D2Args& d, const InPoint& q, bool grad, int64_t n_points, hipStream_t st) {
     if (q.n < 1 || q.n > IN_POINT || q.n_part > IN_POINT || a0.M > IN_POINT || a0.p < 2 || a0.p > IN_PMAX) return hipErrorInvalidValue;
     const bool sums = a0.p > 2 && grad;
-    const int waves = std::min<int>(q.n, in_point_waves(grad, a0.p == 2 ? 2 : 0));
+    // three waves at least where points leave compute units idle: the set-up's chains (in_rows) side by side
+    const int waves = std::max(n_points <= 256 ? 3 : 1, std::min<int>(q.n, in_point_waves(grad, a0.p == 2 ? 2 : 0)));
     size_t lds = in_rows_bytes(a0);
     if (sums) lds += 8 + static_cast<size_t>(waves) * (2 * a0.p + 1) * 64 * sizeof(double);
     // a grid holds fewer than 2^32 threads

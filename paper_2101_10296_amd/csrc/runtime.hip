@@ -652,6 +652,7 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
 // 778 us and 51, 101, 145, 379).
 void build_point(qaoa_plan_s* P, const InnerHost& in) {
     P->in_point = InPoint{};
+    P->in_parts = InPointSum{};
     const size_t M = P->hp.cones.size();
     P->d2_point = false;
     if (P->hp.n_inst != 1 || M > D2_POINT || in.cones.size() + in.tr.size() != M || !P->wh_groups.empty() || P->opt.profile ||
@@ -665,12 +666,25 @@ void build_point(qaoa_plan_s* P, const InnerHost& in) {
     const size_t rows = static_cast<size_t>(3 + P->hp.p) * (P->hp.cut_max - P->hp.cut_min + 1) * sizeof(float2) +
                         static_cast<size_t>(P->wz + 1) * sizeof(double2);
     const size_t sums = P->hp.p > 2 ? static_cast<size_t>(in_point_waves(true, 0)) * (2 * P->hp.p + 1) * 512 : 0;
-    if (rows + sums > IN_POINT_LDS) return;
+    // too many units for a workgroup per point: units first, then all sums
+    auto parts = [&]() {
+        InPointSum& s = P->in_parts;
+        if (!in.tr.empty()) return;
+        for (const auto& g : P->in_groups)
+            for (int64_t i = 0; i < g.count; ++i) {
+                InPointSum::Cone& c = s.c[s.n++];
+                c.units = static_cast<int32_t>(g.count * g.chunks);
+                c.unit0 = static_cast<int32_t>(i * g.chunks);
+                c.chunks = g.chunks;
+                c.orbit = in.cones[static_cast<size_t>(g.first + i)].orbit;
+            }
+    };
+    if (rows + sums > IN_POINT_LDS) return parts();
     InPoint q{};
     auto u16 = [](int64_t x) { return static_cast<uint16_t>(x); };
     for (const auto& g : P->in_groups)
         for (int64_t i = g.first; i < g.first + g.count; ++i) {
-            if (q.n_part + g.chunks > IN_POINT || q.n + g.chunks > IN_POINT) return;
+            if (q.n_part + g.chunks > IN_POINT || q.n + g.chunks > IN_POINT) return parts();
             if (g.tree) {
                 if (i == g.first)
                     q.unit[q.n++] = {u16(i), 0, 1, u16(q.n_part), 0, static_cast<uint8_t>(g.count)};
@@ -678,7 +692,7 @@ void build_point(qaoa_plan_s* P, const InnerHost& in) {
                 continue;
             }
             const ConeIn& c = in.cones[static_cast<size_t>(i)];
-            if (c.cfg_off < 0) return;
+            if (c.cfg_off < 0) return parts();
             for (int32_t ch = 0; ch < g.chunks; ++ch) {
                 q.unit[q.n++] = {u16(i), u16(ch), u16(g.chunks), u16(q.n_part), static_cast<uint8_t>(c.kin), 0};
                 q.part[q.n_part++] = {u16(g.chunks), u16(c.orbit)};
@@ -1438,6 +1452,23 @@ qaoa_status enqueue_depth1(qaoa_plan_s* P, int64_t n_points, const double* gamma
     return finish_sums(P, n_points, a.zz, a.g, energy, dgamma, dbeta, term_grad != nullptr, P->d_W, tm, stream, msg);
 }
 
+// The next class of a shared launch.
+InMix::Class& mix_class(const qaoa_plan_s* P, const qaoa_plan_s::InGroup& grp, InMix& mix) {
+    InMix::Class& c = mix.c[mix.n++];
+    c.kin = grp.kin;
+    c.signs = grp.signs ? 1 : 0;
+    c.cone0 = static_cast<int32_t>(grp.first);
+    c.n_cones = static_cast<int32_t>(grp.count);
+    c.units = static_cast<int32_t>(grp.count * grp.chunks);
+    c.chunks = grp.chunks;
+    c.block0 = mix.blocks;
+    c.n_seg = grp.n_seg;
+    c.inst0 = P->in_inst[static_cast<size_t>(grp.first)];
+    c.seg = grp.n_seg > 1 ? P->d_inseg + grp.seg[0] : nullptr;
+    mix.blocks += grp.blocks[0];
+    return c;
+}
+
 // The launch sequence of one energy call.  With fixed_batches the HBM groups reuse the
 // batch sizes of the previous call (and so allocate nothing): used while capturing.
 qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const double* beta, double* energy,
@@ -1470,6 +1501,33 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         q.dbeta = dbeta;
         QCHECK(launch_inner_point(a, depth2_args(P, gamma, beta, n_points, nullptr, nullptr), q, grad, n_points, stream));
         return QAOA_OK;
+    }
+    if (P->in_parts.n && n_points <= IN_MIX) {
+        // few cones: their classes in one launch, then all sums
+        const int64_t nvals = grad ? 2 * p + 1 : 1;
+        InMix mix{};
+        InPointSum q = P->in_parts;
+        int64_t parts = 0, units = 0, cone = 0;
+        mix.all = 1;
+        for (const auto& grp : P->in_groups) {
+            units = std::max(units, grp.count * grp.chunks * n_points);
+            mix_class(P, grp, mix).part0 = parts;
+            for (int64_t c = 0; c < grp.count; ++c) q.c[cone++].part0 = parts;
+            parts += grp.count * grp.chunks * n_points * nvals;
+        }
+        if (units <= IN_MIX && parts <= (int64_t{1} << 25)) {
+            if ((st = grow(P->d_part, P->cap_part, static_cast<size_t>(parts), msg)) != QAOA_OK) return st;
+            InArgs a = inner_args(P, gamma, beta, n_points, term_zz, grad ? term_grad : nullptr);
+            a.part = P->d_part;
+            a.P = static_cast<int32_t>(n_points);
+            QCHECK(launch_inner_mix(a, mix, grad, stream));
+            q.W = P->d_W;
+            q.energy = energy;
+            q.dgamma = dgamma;
+            q.dbeta = dbeta;
+            QCHECK(launch_inner_point_sum(a, q, grad, stream));
+            return QAOA_OK;
+        }
     }
     const size_t npl = static_cast<size_t>(hp.n_inst) * n_points * p;   // (instance, point, layer) rows
     const bool use_wh = whole_used(P, grad && term_grad);
@@ -1511,20 +1569,9 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
             if (grp.tree || (grp.wh && use_wh) || units * n_points > IN_MIX ||
                 (grp.chunks > 1 && parts + units * n_points * static_cast<int64_t>(nv) > (int64_t{1} << 25)))
                 continue;
-            InMix::Class& c = mix.c[mix.n++];
-            c.kin = grp.kin;
-            c.signs = grp.signs ? 1 : 0;
-            c.cone0 = static_cast<int32_t>(grp.first);
-            c.n_cones = static_cast<int32_t>(grp.count);
-            c.units = static_cast<int32_t>(units);
-            c.chunks = grp.chunks;
-            c.block0 = mix.blocks;
-            c.n_seg = grp.n_seg;
-            c.inst0 = P->in_inst[static_cast<size_t>(grp.first)];
-            c.seg = grp.n_seg > 1 ? P->d_inseg + grp.seg[0] : nullptr;
+            InMix::Class& c = mix_class(P, grp, mix);
             c.part0 = parts;
             c.item0 = mix.items;
-            mix.blocks += grp.blocks[0];
             if (grp.chunks > 1) {
                 parts += units * n_points * static_cast<int64_t>(nv);
                 mix.items += grp.count * n_points * static_cast<int64_t>(nv);

@@ -58,6 +58,7 @@ struct qaoa_plan_s {
     };
     std::vector<InGroup> in_groups;
     std::vector<int32_t> in_inst;       // instance of each cone in d_in
+    qaoa::InPointSum in_parts{};        // few cones in more units than that (n > 0): their parts' places
     qaoa::InPoint in_point{};           // its units where the plan is small enough (n > 0)
     int32_t in_max_k = 0;               // largest of them and of the wide ones (cone qubits)
     // large cones with 11 to 14 inner qubits: units of work by inner qubits (and k: profile)
