@@ -22,57 +22,10 @@ sys.path.insert(0, ROOT)
 
 import numpy as np  # noqa: E402
 
-PEAK_FP32_TFLOPS = 157.3
 PEAK_HBM_GBS = 8000.0
-
-# HBM traffic of the device-memory pass kernels over their algorithmic bytes, from
-# rocprofv3 FETCH_SIZE and WRITE_SIZE runs of `bench.py --hbm-only --hbm-points 1 --copy-gib 4`
-# (counters scaled by a 4 GiB device copy; summary in profiles/).  Valid only for the kernel
-# sources (and build flags) it was measured on: reported as null once they change.
-HBM_TRAFFIC = {"sources_sha256": "fe95b2630654ddb90d6e5b9a8a14cbcbf6f76c4f49b29aeb2756a23dd7c1b9b1",
-               "counted_over_algorithmic": 1.031,
-               # the program with every cone-size class reading stored forward states
-               # (checkpoint_mode 2, --checkpoint-mode 2 in the counter runs)
-               "counted_over_algorithmic_ckpt": 1.035}
-
-
-# Same for the 14-qubit workgroup-resident adjoint kernel: counted bytes per (cone, point)
-# item (cut tables and phase rows read, five FP64 results written).
-FUSED_TRAFFIC = {"sources_sha256": "a95bec3c946b07d2ac2745d366d5cc15b30f434ca46562838f583d13fd3ba120",
-                 "bytes_per_item": 297.8}
-
-
-def sources_sha256(files) -> str:
-    import hashlib
-    h = hashlib.sha256()
-    for f in files:
-        with open(os.path.join(ROOT, f), "rb") as fh:
-            h.update(fh.read())
-    return h.hexdigest()
-
-
-def hbm_sources_sha256() -> str:
-    return sources_sha256(("paper_2101_10296_amd/csrc/hbm_impl.hpp", "paper_2101_10296_amd/csrc/hbm.hip",
-                           "paper_2101_10296_amd/csrc/fused_impl.hpp", "paper_2101_10296_amd/build.py"))
-
-
-def fused_sources_sha256() -> str:
-    return sources_sha256(("paper_2101_10296_amd/csrc/fused_impl.hpp", "paper_2101_10296_amd/csrc/fused_k14.hip",
-                           "paper_2101_10296_amd/build.py"))
-
-
-def flops_model_8d(k: int, p: int) -> float:
-    """Algorithmic FP32 flops of one forward + adjoint cone evaluation by the hot-path
-    model: forward 2^k [p (6 + 3 k_int) + 6k (p - 1) + 12 + 3] (phase complex multiply and
-    cut count, full mixers of layers 1..p-1, the last two-qubit mixer, the expectation);
-    adjoint 3 x forward + 2^k p (8k + 8) (the inner products with sum_j X_j and C).
-    Counted on the stored half of the state (2^(k-1) amplitudes: cones of k >= 3 qubits are
-    invariant under flipping every qubit) with k_int = 0: cut values come from a table,
-    not a popcount.
-    """
-    n = float(1 << (k - 1 if k >= 3 else k))
-    fwd = p * 6 + 6 * k * (p - 1) + 12 + 3
-    return n * (3 * fwd + p * (8 * k + 8))
+# cones of the 20-30-qubit workload that run as passes over device memory: larger ones run on their
+# inner qubits (11-14 of them, on workgroups), and so do its 20-qubit ones (at most 10, on waves)
+PASS_K = (22, 24)
 
 
 def hbm_bytes_model_8d(k: int, p: int) -> float:
@@ -80,29 +33,6 @@ def hbm_bytes_model_8d(k: int, p: int) -> float:
     memory: 48 p bytes per stored amplitude (forward state stored once per layer, 16 p;
     backward reads and writes psi and lambda once per layer, 32 p)."""
     return 48.0 * p * float(1 << (k - 1))
-
-
-def flops_fwd_adj(k: int, p: int) -> float:
-    """Algorithmic FP32 flops of one forward + adjoint cone evaluation (k qubits, depth p).
-
-    Mixer: 6 flop per amplitude per qubit (c*a - i*s*b); phase: 6 (complex multiply);
-    <Z0 Z1>: 4; Im<lambda|X_j|psi>: 4 per amplitude per qubit; Im<lambda|C|psi>: 5.
-    Forward: D_1|+> (2), p-1 full layers (6k + 6), last two-qubit mixer (12), zz (4).
-    Adjoint (p >= 2): beta_p inner products (8), undo of the last mixer on lambda (12; psi
-    before D_p is kept), p gamma inner products (5), D_p undone on lambda (6) and the other
-    p-2 phases on two states (12), p-1 full layers undone on two states with their inner
-    products (16k; the last stage of layer 1 leaves psi alone, which is not counted).
-    p = 1: beta_1 (8), the last mixer undone on two states (24), gamma_1 (5).
-    Per stored amplitude: cones of k >= 3 qubits keep only the half of the state with
-    qubit k-1 = 0 (the state is invariant under flipping every qubit), 2^(k-1) amplitudes.
-    """
-    n = float(1 << (k - 1 if k >= 3 else k))
-    fwd = 2 + (p - 1) * (6 * k + 6) + 12 + 4
-    if p == 1:
-        adj = 8 + 24 + 5
-    else:
-        adj = 8 + 12 + 5 * p + 6 + 12 * (p - 2) + 16 * k * (p - 1)
-    return n * (fwd + adj)
 
 
 def hbm_groups(kh: int) -> int:
@@ -221,12 +151,13 @@ def oracle_baseline(graphs, ga, be, budget_s: float):
 
 def hbm_measure(Q, torch, W, points: int, ckpt: int = 0) -> dict:
     """Large cones: random 3-regular n=200 at p=3 (300 cones of 20-30 qubits), energy and
-    gradient at the first `points` angle points, through the device-memory pass kernels.
-    The plan is built and evaluated once (device tables, state buffers), then timed on a
-    second evaluation, as in a training loop.
+    gradient at the first `points` angle points.  The plan is built and evaluated once (device
+    tables, state buffers), then timed on a second evaluation, as in a training loop.
 
-    achieved = algorithmic state bytes (hbm_bytes_per_item x items, summed over cone sizes)
-    over the HIP-event time of those kernel groups (passes, zero fill and tile reductions).
+    The cones of 22 to 24 qubits go through the device-memory pass kernels: achieved = their
+    algorithmic state bytes (hbm_bytes_per_item x items, summed over cone sizes) over the
+    HIP-event time of those kernel groups (passes, zero fill and tile reductions).  The others
+    keep their states in LDS or registers (ms_by_k shows all).
     """
     (g, p), = W.workload("c5ii")[0]
     _, ga, be = W.workload("c5ii")
@@ -243,9 +174,11 @@ def hbm_measure(Q, torch, W, points: int, ckpt: int = 0) -> dict:
     wall = time.perf_counter() - t0
     info = pl.info()
     stored = info["checkpointed_classes"] > 0
-    byts, b8d, ms, by_k = 0.0, 0.0, 0.0, {}
+    byts, b8d, ms, by_k, ms_by_k = 0.0, 0.0, 0.0, {}, {}
     for k, items, t in pl.kernel_times():
-        if k > 14:
+        if k > 0:
+            ms_by_k[k] = round(t, 3)
+        if PASS_K[0] <= k <= PASS_K[1]:
             b = hbm_bytes_per_item(k, p, True, bool((info["checkpointed_k_mask"] >> k) & 1)) * items
             byts += b
             b8d += hbm_bytes_model_8d(k, p) * items
@@ -253,20 +186,17 @@ def hbm_measure(Q, torch, W, points: int, ckpt: int = 0) -> dict:
             by_k[k] = round(b / (t * 1e-3) / 1e9, 1)
     pl.close()
     gbs = byts / (ms * 1e-3) / 1e9
-    traffic = None   # counted HBM bytes of the timed evaluation, if the counters are current
-    all_stored = info["checkpointed_classes"] == len(by_k)
-    if hbm_sources_sha256() == HBM_TRAFFIC["sources_sha256"] and (all_stored or not stored):
-        traffic = round(byts * HBM_TRAFFIC["counted_over_algorithmic_ckpt" if stored else "counted_over_algorithmic"])
     return {"workload": f"random 3-regular n=200 (seed 502), p=3, {points} point(s), energy+gradient, "
-                        "300 cones of 20-30 qubits in device memory",
+                        "300 cones of 20-30 qubits, 18 of them (22-24 qubits) in device memory",
             "adjoint": ("forward states read from stored checkpoints (checkpoint_mode %d, %d of %d cone-size "
                         "classes)" % (ckpt, info["checkpointed_classes"], len(by_k))) if stored
                        else "forward states recovered by inverse layers (checkpoint_mode 0)",
             "evals_per_s": round(points / wall, 4), "wall_s": round(wall, 3),
             "first_call_s_incl_plan_and_alloc": round(first, 3),
-            "kernel_ms": round(ms, 2), "algorithmic_GB": round(byts / 1e9, 2),
+            "kernel_ms": round(sum(ms_by_k.values()), 2), "ms_by_k": ms_by_k, "pass_kernel_ms": round(ms, 2),
+            "algorithmic_GB": round(byts / 1e9, 2),
             "roofline": {"bound": "hbm", "achieved": round(gbs, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                         "frac": round(gbs / PEAK_HBM_GBS, 4), "traffic": traffic},
+                         "frac": round(gbs / PEAK_HBM_GBS, 4), "traffic": None},
             "achieved_GBps_by_k": by_k,
             "one_sweep_per_layer_model": {"GB": round(b8d / 1e9, 2),
                                           "GBps": round(b8d / (ms * 1e-3) / 1e9, 1),
@@ -279,8 +209,7 @@ def config4_measure(Q, torch, W) -> dict:
     per depth over all graphs of that depth (each reduced by its own generators), so one
     call per depth evaluates every graph, with all cones of one size in one launch.  Plans
     are built once and reused (a training step over the 48 graphs).  busy = summed HIP-event
-    kernel time over the wall time of the step; the device-memory classes of at least 18
-    qubits at p = 2 are reported with their algorithmic bytes over their kernel time."""
+    kernel time over the wall time of the step."""
     graphs, ga, be = W.workload("c4")
     plans = []
     t0 = time.perf_counter()
@@ -294,7 +223,7 @@ def config4_measure(Q, torch, W) -> dict:
         pl.energy_grad(gt, bt)
     torch.cuda.synchronize()
     reps = 5
-    kern_ms, hbm_b, hbm_ms, hist, launches = 0.0, 0.0, 0.0, {}, 0
+    kern_ms, hist = 0.0, {}
     t0 = time.perf_counter()
     for _ in range(reps):
         for pl, gt, bt, p, _ in plans:
@@ -303,9 +232,6 @@ def config4_measure(Q, torch, W) -> dict:
         for pl, gt, bt, p, _ in plans:
             for k, items, ms in pl.kernel_times():
                 kern_ms += ms
-                if k >= 18 and p >= 2:
-                    hbm_b += hbm_bytes_per_item(k, p, True) * items
-                    hbm_ms += ms
                 if k >= 2:
                     hist[k] = hist.get(k, 0) + items // reps
     wall = (time.perf_counter() - t0) / reps
@@ -319,9 +245,7 @@ def config4_measure(Q, torch, W) -> dict:
             "evals_per_s": round(evals / wall, 1), "ms_per_step": round(wall * 1e3, 3),
             "calls_per_step": len(plans), "orbits": n_orb, "plan_s": round(plan_s, 3),
             "gpu_busy_frac": round(kern_ms / reps / (wall * 1e3), 4),
-            "items_by_k": {str(k): v for k, v in sorted(hist.items())},
-            "hbm_k_ge_18_p2": {"GB": round(hbm_b / reps / 1e9, 3), "kernel_ms": round(hbm_ms / reps, 3),
-                               "achieved_GBps": round(hbm_b / (hbm_ms * 1e-3) / 1e9, 1) if hbm_ms else None}}
+            "items_by_k": {str(k): v for k, v in sorted(hist.items())}}
 
 
 def tuner_measure(Q, torch, W, gt, bt, graphs, reps: int = 3) -> dict:
@@ -350,7 +274,7 @@ def tuner_measure(Q, torch, W, gt, bt, graphs, reps: int = 3) -> dict:
 
 def config5i_measure(Q, torch, W) -> dict:
     """Hypercube Q_12 at p = 1: one orbit, one 24-qubit cone; energy and gradient at 8 points
-    (the p = 1 pass keeps no state: its roofline is the vector ALU)."""
+    (depth 1 in closed form: bound by its launches)."""
     (g, p), = W.workload("c5i")[0]
     _, ga, be = W.workload("c5i")
     gt = torch.tensor(ga, dtype=torch.float64, device="cuda")
@@ -578,22 +502,16 @@ def main():
     evals = len(graphs) * P
     value = evals / (dt / a.steps)
 
-    # dominant kernel: the cone-size group with the largest total time
+    # the cone-size group with the most items: the 14-qubit cones of the 3-regular graph, all trees
+    # (2 + 4 + 8 different qubits), in closed form.  A term is <ZZ> and 2p derivatives, written once
     (norb, kdom), (ms_dom, items_dom, pdom) = max(((k, v) for k, v in kernel_ms.items() if k[1] >= 2),
-                                                  key=lambda kv: kv[1][0])
-    flop = flops_model_8d(kdom, pdom) * items_dom
-    achieved = flop / (ms_dom * 1e-3) / 1e12
-    executed = flops_fwd_adj(kdom, pdom) * items_dom / (ms_dom * 1e-3) / 1e12
-    traffic = None   # counted HBM bytes per launch, if the counters are current for this kernel
-    if kdom == 14 and fused_sources_sha256() == FUSED_TRAFFIC["sources_sha256"]:
-        traffic = round(FUSED_TRAFFIC["bytes_per_item"] * items_dom / a.steps)
-    roofline = {"bound": "alu", "achieved": round(achieved, 3), "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
-                "frac": round(achieved / PEAK_FP32_TFLOPS, 4), "traffic": traffic,
-                "kernel": f"k_fused<K={kdom},grad>", "avg_launch_ms": round(ms_dom / a.steps, 4),
-                "items_per_launch": items_dom // a.steps,
-                "flop_per_item": flops_model_8d(kdom, pdom),
-                "executed_model": {"flop_per_item": flops_fwd_adj(kdom, pdom), "TFLOPs": round(executed, 3),
-                                   "frac": round(executed / PEAK_FP32_TFLOPS, 4)}}
+                                                  key=lambda kv: kv[1][1])
+    per_item = 8 * (1 + 2 * pdom)
+    gbs = per_item * items_dom / (ms_dom * 1e-3) / 1e9
+    roofline = {"bound": "hbm", "achieved": round(gbs, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
+                "frac": round(gbs / PEAK_HBM_GBS, 4), "traffic": None,
+                "kernel": f"k_depth2<grad> (k={kdom})", "avg_launch_ms": round(ms_dom / a.steps, 4),
+                "items_per_launch": items_dom // a.steps, "bytes_per_item": per_item}
 
     extra = {}
     if not a.no_plain:

@@ -88,7 +88,10 @@ typedef struct {
     int32_t max_cone_qubits;      /* 0 = 30 */
     int32_t k_lds_max;            /* cones with k <= this run entirely inside one workgroup,
                                      larger ones as passes over tiles held in device memory
-                                     (0 = default; only 14 is accepted) */
+                                     (0 = default; only 14 is accepted).  Terms in closed form
+                                     (p = 1, trees at p = 2) and cones evaluated on the qubits
+                                     that are mixed need no such states, whatever k; a budget
+                                     that does not hold them is refused all the same */
     int32_t checkpoint_mode;      /* adjoint of cones held in device memory (p >= 2):
                                      0 = uncompute: the forward state is recovered by inverse
                                          layers, two live states per item (default);
@@ -102,7 +105,8 @@ typedef struct {
                                          states without fewer items per batch, or with a batch
                                          that still gives every pass 2^15 workgroups; else
                                          uncompute */
-    int32_t one_cone_at_a_time;   /* 1 = plain GPU path: one launch per (cone, point) */
+    int32_t one_cone_at_a_time;   /* 1 = plain GPU path: one launch per (cone, point); cones that share
+                                     one state: one per (state, point) */
     int32_t profile;              /* 1 = record HIP events around every kernel group of each
                                      energy call (read with qaoa_plan_kernel_times) */
     int32_t graph;                /* 1 = replay: the first call with a given (n_points, gradient
@@ -114,7 +118,8 @@ typedef struct {
     int32_t tune;                 /* 1 = run-time tuning: the first call that needs a kernel class
                                      times its layout choices on the device (workgroup-resident
                                      cones: register bits per LDS stage and workgroup size;
-                                     cones in device memory: tiles per workgroup) and keeps the
+                                     cones in device memory: tiles per workgroup; those evaluated
+                                     on their inner qubits: units per wave) and keeps the
                                      fastest for the rest of the process, per (device
                                      architecture, class, k, p, gradient, real weights);
                                      qaoa_tuning_report lists the choices.  0 = fixed defaults;
@@ -258,8 +263,8 @@ qaoa_status qaoa_energy_grad_noalloc(qaoa_plan_t plan, int64_t n_points, const d
                                      double* dbeta, qaoa_stream_t stream);
 
 /* Diagnostics for plans built with opts.profile = 1: per kernel group of the last energy
- * call (one group per cone size k, plus the table and combine kernels, reported with
- * k = -1 and k = -2), the cone size, the number of (cone, point) items and the elapsed
+ * call (one or more groups per cone size k, plus the table kernel, where one runs, and the
+ * combine kernel, reported with k = -1 and k = -2), the cone size, the number of (cone, point) items and the elapsed
  * milliseconds between HIP events recorded on the call's stream around the group.
  * Blocks until those events have completed.  *n_out = number of groups (at most cap
  * are written).  EINVAL if the plan was not built with profiling or has not run. */
