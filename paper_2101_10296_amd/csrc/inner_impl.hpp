@@ -127,6 +127,25 @@ __device__ __forceinline__ double wave_sum8(double (&v)[8], int lane) {
     return x;
 }
 
+// Two sums over the wave at once: a in the even lanes, b in the odd ones.
+__device__ __forceinline__ double wave_sum2(double a, double b, int lane) {
+    auto dpp = [](auto C, double x) {
+        constexpr int c = decltype(C)::value;
+        const long long v = __double_as_longlong(x);
+        const float lo = dppf<c>(__int_as_float(static_cast<int>(v))), hi = dppf<c>(__int_as_float(static_cast<int>(v >> 32)));
+        return __longlong_as_double((static_cast<long long>(__float_as_int(hi)) << 32) |
+                                    static_cast<long long>(static_cast<unsigned>(__float_as_int(lo))));
+    };
+    const bool up = (lane & 1) != 0;
+    double x = (up ? b : a) + dpp(std::integral_constant<int, 0xB1>{}, up ? a : b);   // lane xor 1
+    x += dpp(std::integral_constant<int, 0x4E>{}, x);                                 // xor 2
+    x += dpp(std::integral_constant<int, 0x124>{}, x);                                // row rotated by 4, 8
+    x += dpp(std::integral_constant<int, 0x128>{}, x);
+    x += __shfl_xor(x, 16, 64);
+    x += __shfl_xor(x, 32, 64);
+    return x;
+}
+
 // Exchange lane bit 4 (W32: 5) with register bit B (an involution).
 template <bool W32, int B, int A>
 __device__ __forceinline__ void lane_reg_swap(float2 (&v)[A]) {

@@ -411,18 +411,26 @@ __global__ void __launch_bounds__((Wz<K>::WG)) k_whole(WhArgs a) {
     if constexpr (GRAD) {
         double* g = a.g + static_cast<size_t>(point) * 2 * p * a.M;
         // entry j of dE/d(gamma, beta) through column rep: -2 dE (the sums weigh it by one)
-        auto put = [&](int j, double x) {
+        // (two entries at once: a wave's sum is six dependent steps of FP64 and lane moves)
+        auto put = [&](int j0, double x0, int j1, double x1) {
             if constexpr (NWV >= 1) {
-                x = wave_sum(x);
+                const int lane = tid & 63, j = lane ? j1 : j0;
+                const double x = wave_sum2(x0, x1, lane);
                 if constexpr (NWV > 1) {
-                    if ((tid & 63) == 0) dsum[j * NWV + (tid >> 6)] = x;
+                    if (lane < 2) dsum[j * NWV + (tid >> 6)] = x;
                 } else {
-                    if (tau == 0 && valid) g[static_cast<size_t>(j) * a.M + gd.rep] = x;
+                    if (lane < 2 && valid) g[static_cast<size_t>(j) * a.M + gd.rep] = x;
                 }
             } else {
 #pragma unroll
-                for (int o = 1; o < Z::TPI; o <<= 1) x += __shfl_xor(x, o, 64);
-                if (tau == 0 && valid) g[static_cast<size_t>(j) * a.M + gd.rep] = x;
+                for (int o = 1; o < Z::TPI; o <<= 1) {
+                    x0 += __shfl_xor(x0, o, 64);
+                    x1 += __shfl_xor(x1, o, 64);
+                }
+                if (tau == 0 && valid) {
+                    g[static_cast<size_t>(j0) * a.M + gd.rep] = x0;
+                    g[static_cast<size_t>(j1) * a.M + gd.rep] = x1;
+                }
             }
         };
         if (valid) {
@@ -458,7 +466,6 @@ __global__ void __launch_bounds__((Wz<K>::WG)) k_whole(WhArgs a) {
             b += w * static_cast<double>(wxsum<Z, T>(f, lam, sg));
             wmix<Z, T>(f, -t, sg);
             wmix<Z, T>(lam, -t, sg);
-            put(p + l, sc * b);
             // gamma of the layer; both states carry 1 / mu, which the undone phase takes back
             const float mu = ml[l].y;
             float ga = 0.f;
@@ -476,7 +483,7 @@ __global__ void __launch_bounds__((Wz<K>::WG)) k_whole(WhArgs a) {
                     lam[r] = cmulc(lam[r], d);
                 }
             }
-            put(l, sc * static_cast<double>(mu) * mu * static_cast<double>(ga));
+            put(p + l, sc * b, l, sc * static_cast<double>(mu) * mu * static_cast<double>(ga));
         };
         int q = p - 1;
         while (q >= 1) {
