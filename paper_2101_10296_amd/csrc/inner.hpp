@@ -103,6 +103,11 @@ constexpr int IN_POINT = 16;    // units, parts of cones, and orbits, at most
 // layers, with its sums in LDS (at most 8 x 19 x 512 bytes)
 constexpr int in_point_waves(bool grad, int pp) { return grad && pp == 0 ? 8 : 16; }
 constexpr size_t IN_POINT_LDS = 60 << 10;        // phase rows and sums of the gradient at most
+// A point of more than four units takes several compute units instead (InPointSum, in two launches) while
+// all of a call's units leave half of the chip's 4096 wave slots free: C_1000(1,2,3) at p = 2, 14
+// units, energy and gradient at 1, 16, 64, 256 points 42.4, 43.4, 44.9, 51.4 us on a workgroup per
+// point, 24.2, 25.3, 28.0, 52.3 spread.
+constexpr int64_t IN_SPREAD = 1 << 11;
 struct InPoint {
     struct Unit {              // in class order, a cone's parts together
         uint16_t cone, chunk, chunks, part;

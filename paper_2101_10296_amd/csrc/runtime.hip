@@ -699,6 +699,7 @@ void build_point(qaoa_plan_s* P, const InnerHost& in) {
             }
         }
     P->in_point = q;
+    if (q.n > 4) parts();   // for few points
 }
 
 struct WideHost {
@@ -1492,7 +1493,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         QCHECK(launch_depth2_point(a, P->d_W, energy, dgamma, dbeta, stream));
         return QAOA_OK;
     }
-    if (P->in_point.n) {
+    if (P->in_point.n && !(P->in_parts.n && n_points * P->in_point.n <= IN_SPREAD)) {
         InArgs a = inner_args(P, gamma, beta, n_points, term_zz, grad ? term_grad : nullptr);
         InPoint q = P->in_point;
         q.W = P->d_W;
