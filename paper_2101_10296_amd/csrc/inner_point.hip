@@ -10,7 +10,8 @@
 //
 // Bound: the serial chain of one unit (phase rows, descriptors and tables through L2, then about
 // 2000 instructions of one wave).  Energy and gradient of C_10000(1,2) at p = 2 (inner states of
-// 6 and 7 qubits, one unit each), one point: 18.8 us a call in three launches, 13.6 here.
+// 6 and 7 qubits, one unit each), one point: 18.8 us a call in three launches, 13.6 in one (now 9.7,
+// with the set-up on three waves and less host time around the call).
 #include "depth2_impl.hpp"
 #include "inner_impl.hpp"
 

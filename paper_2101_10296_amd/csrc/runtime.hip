@@ -648,8 +648,8 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
 // line at any number of points: a class's launch gives a point's few units a workgroup of their
 // own too, and leaves its other waves idle (energy and gradient of C_10000(1,2) at p = 2, 1, 256,
 // 2048 and 16384 points: 18.8, 17.9, 36, 191 us in separate launches, 13.6, 13.3, 22, 109 here;
-// rings at p = 2 .. 5, 1 point: 16, 16, 19, 42 us and 13, 13, 18, 41; 16384 points: 118, 218, 309,
-// 778 us and 51, 101, 145, 379).
+// rings at p = 3 .. 5, 1 point: 16, 19, 42 us and 13, 18, 41; 16384 points: 218, 309, 778 us and 101,
+// 145, 379).
 void build_point(qaoa_plan_s* P, const InnerHost& in) {
     P->in_point = InPoint{};
     P->in_parts = InPointSum{};

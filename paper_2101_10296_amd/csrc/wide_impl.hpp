@@ -12,7 +12,7 @@
 // choices of signs, 21 up to the cone's symmetries, of 2^14 amplitudes that never leave the compute
 // unit, in place of seven sweeps over 2^29 amplitudes in device memory.  90 terms of 19 to 30
 // qubits, energy and gradient: 257 -> 20.5 ms with listed configurations of the leaves, 8.9 with
-// lists up to any symmetry, 7.5 with signs (5.5 of it in the passes of cones of up to 24 qubits).
+// lists up to any symmetry, 7.0 with signs (5.5 of it in the passes of cones of up to 24 qubits).
 // Bound: vector instruction issue (about 200 per amplitude with the gradient) at one to two
 // workgroups per CU (LDS).
 #pragma once
