@@ -644,8 +644,8 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
 // The units of a plan whose calls are one launch (inner_point.hip): one instance, all cones on their
 // inner qubits with listed configurations, and at most 16 units and orbits.  Up to there one
 // compute unit holds a point's waves at once; the 18-qubit cone of a torus, 19 units of two rounds
-// each, would run them one after the other where the separate launches spread them over five.  No
-// line at any number of points: a class's launch gives a point's few units a workgroup of their
+// each, would run them one after the other where the separate launches spread them over five.  Beyond
+// four units few points are spread as well (IN_SPREAD); else there is no line at any number of points: a class's launch gives a point's few units a workgroup of their
 // own too, and leaves its other waves idle (energy and gradient of C_10000(1,2) at p = 2, 1, 256,
 // 2048 and 16384 points: 18.8, 17.9, 36, 191 us in separate launches, 13.6, 13.3, 22, 109 here;
 // rings at p = 3 .. 5, 1 point: 16, 19, 42 us and 13, 18, 41; 16384 points: 218, 309, 778 us and 101,

@@ -1,8 +1,8 @@
 """Shell qubits next to one inner qubit, averaged as a dephasing (GPU).
 
 Against the FP64 oracle and the kernels for whole cones (tune = 2), at the tolerances of
-test_gpu_parity.py: cones of 4 to 6 inner qubits whose shell is leaves only (a row of a wave
-each) with every number of leaves, equal and unequal ones, no symmetry (16 signs: two
+test_gpu_parity.py: cones whose shell is leaves only (at depth 2 trees, in closed form, or
+with coupled neighbours) with every number of leaves, equal and unequal ones, no symmetry (16 signs: two
 rounds), u and v swapped, coupled neighbours, couplings of either sign, none of which is
 1, and just beyond the limits (couplings above 3, seven leaves, a shared leaf: groups or the
 general kernel); larger inner states with leaves at depths 2 to 4; an inner qubit with five
