@@ -28,7 +28,7 @@ struct ConeIn {
     int32_t cfg_off;           // listed configurations, or -1: decoded where they are used
     uint32_t n_cfg;            // listed entries: a whole number of rounds (weight 0 beyond the last)
     uint32_t zmask;            // inner qubits with leaves
-    int32_t z_off;             // their leaves: 16 entries from here
+    int32_t z_off;             // their leaves: 16 entries from here (zmask 0: none stand there)
     int32_t pad0_;
     double shell_norm;         // 2^-(qubits of the groups)
     int16_t base[IN_PMAX + 1]; // [l], l = 2..p: phase row index of table value 0 of layer l; [1] = [2]

@@ -534,7 +534,7 @@ __device__ __forceinline__ void in_unit(const InArgs& a, const ConeIn& cd, uint3
     double Wd = 0.0;                                  // gamma_1 through the weights
     if constexpr (SIGNS) {
         __builtin_amdgcn_wave_barrier();              // the last unit's weights are read
-        if (lane < 16) zfac[lane] = z_factor(a.leaf[cd.z_off + lane], ct);
+        z_factors(zmask, a.leaf, cd.z_off, ct, lane, zfac);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }

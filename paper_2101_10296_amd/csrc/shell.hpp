@@ -22,7 +22,7 @@ struct alignas(16) ZLeaf {
 };
 
 // f and df of one inner qubit; ct[j]: cosine and sine of j t.
-__device__ __forceinline__ double2 z_factor(const ZLeaf& q, const double2* ct) {
+__host__ __device__ __forceinline__ double2 z_factor(const ZLeaf& q, const double2* ct) {
     double f = 1.0, df = 0.0;
     for (int i = 0; i < ZL_W && q.m[i]; ++i) {
         const double2 c = ct[q.w[i]];
@@ -34,8 +34,15 @@ __device__ __forceinline__ double2 z_factor(const ZLeaf& q, const double2* ct) {
     return make_double2(f, df);
 }
 
+// fac[lane] of the inner qubits in zmask, a lane each.  The others have no factor, and where zmask is 0
+// no record stands at z_off: neither is read.
+__host__ __device__ __forceinline__ void z_factors(uint32_t zmask, const ZLeaf* leaf, int32_t z_off, const double2* ct, int lane,
+                                                   double2* fac) {
+    if (lane < 16 && ((zmask >> lane) & 1u)) fac[lane] = z_factor(leaf[z_off + lane], ct);
+}
+
 // Weight w of a configuration with the signs z of the qubits zmask, and its derivative.
-__device__ __forceinline__ double z_weight(uint32_t zmask, uint32_t z, const double2* fac, double& w) {
+__host__ __device__ __forceinline__ double z_weight(uint32_t zmask, uint32_t z, const double2* fac, double& w) {
     double dw = 0.0;
     for (; zmask; zmask &= zmask - 1) {
         const int a = __builtin_ctz(zmask);

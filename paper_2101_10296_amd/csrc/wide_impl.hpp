@@ -182,7 +182,7 @@ __global__ void __launch_bounds__((Uz<KIN>::W), Uz<KIN>::W > 512 ? 4 : 3) k_wide
     }
     __syncthreads();
     // the unit's configurations and their weights (the first wave)
-    if (tid < 16 && cd.zmask) s_z[tid] = z_factor(a.leaf[cd.z_off + tid], ct);
+    z_factors(cd.zmask, a.leaf, cd.z_off, ct, tid, s_z);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     if (tid < WD_CFG) {
