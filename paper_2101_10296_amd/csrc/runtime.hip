@@ -720,6 +720,7 @@ void build_wide(qaoa_plan_s* P, std::vector<int64_t>& ord, std::vector<int32_t>&
     P->wd_groups.clear();
     P->wd_units.clear();
     P->wd_all_units = 0;
+    P->wd_rows = 1;
     if (ord.empty()) return;
     const bool by_k = P->opt.profile != 0;
     std::stable_sort(ord.begin(), ord.end(), [&](int64_t a, int64_t b) {
@@ -747,7 +748,10 @@ void build_wide(qaoa_plan_s* P, std::vector<int64_t>& ord, std::vector<int32_t>&
         d.inst = c.inst;
         d.kin = q.kin;
         d.nc = q.nc;
-        layer_cuts(c, shells, q, p, hp.cut_min, d.mixed, d.base, d.mid);
+        d.cut_min = c.cut_min;
+        d.n_rows = c.cut_max - c.cut_min + 1;
+        P->wd_rows = std::max(P->wd_rows, d.n_rows);
+        layer_cuts(c, shells, q, p, c.cut_min, d.mixed, d.base, d.mid);
         d.shell_norm = std::ldexp(1.0, -(c.k - q.kin - q.n_leaf));
         d.cfg_off = -1;
         d.zmask = q.zmask;
@@ -1142,7 +1146,7 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
                                 P->d_ew, P->d_tt, nullptr));
         if (has_wd)
             QCHECK(launch_wide_tables(P->d_wd, static_cast<int64_t>(wd.cones.size()), P->d_ea, P->d_eb, P->d_ew, hp.p,
-                                      hp.cut_min, P->d_wdtab, nullptr));
+                                      P->d_wdtab, nullptr));
         if (has_in)
             QCHECK(launch_inner_tables(P->d_in, static_cast<int64_t>(in.cones.size()), P->d_ea, P->d_eb, P->d_ew, hp.p,
                                        hp.cut_min, P->d_intab, nullptr));
@@ -1646,8 +1650,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         a.gamma_P = n_points;
         a.deltas = P->d_inst_delta;
         a.p = p;
-        a.R = R;
-        a.cut_min = hp.cut_min;
+        a.R = P->wd_rows;
         a.M = M;
         a.all_units = static_cast<int32_t>(P->wd_all_units);
         a.part = P->d_part;

@@ -70,6 +70,7 @@ struct qaoa_plan_s {
     std::vector<WdGroup> wd_groups;
     std::vector<std::pair<int32_t, int32_t>> wd_units;   // (first unit, units) of each cone
     int64_t wd_all_units = 0;
+    int32_t wd_rows = 1;                // phases per row of the largest cut range
     qaoa::ConeWd* d_wd = nullptr;
     qaoa::UnitWd* d_wdunit = nullptr;
     qaoa::GrpWd* d_wdgrp = nullptr;

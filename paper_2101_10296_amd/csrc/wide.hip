@@ -18,12 +18,12 @@ namespace {
 
 __global__ void __launch_bounds__(256)
 k_wide_tables(const ConeWd* __restrict__ cones, const int32_t* __restrict__ ea, const int32_t* __restrict__ eb,
-              const int32_t* __restrict__ ew, int32_t p, int32_t cut_min, uint8_t* __restrict__ tab) {
+              const int32_t* __restrict__ ew, int32_t p, uint8_t* __restrict__ tab) {
     const ConeWd& cd = cones[blockIdx.x];
     const uint32_t n = 1u << cd.kin;
     const int l = 2 + blockIdx.y;
     uint8_t* out = tab + cd.tab_off + static_cast<size_t>(l - 2) * n;
-    const int m = cd.mixed[l - 1], cmin = cd.base[l] + cut_min;
+    const int m = cd.mixed[l - 1], cmin = cd.base[l] + cd.cut_min;
     for (uint32_t x = blockIdx.z * 256 + threadIdx.x; x < n; x += gridDim.z * 256) {
         int32_t c = 0;
         for (int32_t e = 0; e < cd.n_edges; ++e) {
@@ -70,10 +70,10 @@ hipError_t launch_wide_sum(const WdArgs& a, int32_t n_cones, bool grad, hipStrea
 }
 
 hipError_t launch_wide_tables(const ConeWd* cones, int64_t n_cones, const int32_t* ea, const int32_t* eb,
-                              const int32_t* ew, int32_t p, int32_t cut_min, uint8_t* tab, hipStream_t st) {
+                              const int32_t* ew, int32_t p, uint8_t* tab, hipStream_t st) {
     if (n_cones <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_wide_tables, dim3(static_cast<unsigned>(n_cones), static_cast<unsigned>(p - 1), n_cones < 64 ? 8 : 1), dim3(256), 0,
-                       st, cones, ea, eb, ew, p, cut_min, tab);
+                       st, cones, ea, eb, ew, p, tab);
     return hipGetLastError();
 }
 

@@ -16,6 +16,7 @@ constexpr int WD_CONE2 = 26;    // cone qubits from which this form is used: p =
 constexpr int WD_CONE3 = 25;    // p = 3
 constexpr int WD_NEXT = 8;      // inner qubits that layers 2 and up mix at most
 constexpr int WD_CFG = 8;       // configurations per unit of work
+constexpr int WD_ROWS = 256;    // phases per row: a cone's cut values span at most 255 units
 
 struct ConeWd {
     int32_t orbit, inst;
@@ -28,6 +29,7 @@ struct ConeWd {
     int32_t first_unit, n_units;
     int32_t edge_off, n_edges;
     int32_t kin;
+    int32_t cut_min, n_rows;    // of the cone: cut value of row index 0, phases per row
     int64_t tab_off;            // bytes: tables of layers 2 .. p, 2^kin each
     double shell_norm;
     int16_t base[4];
@@ -67,7 +69,8 @@ struct WdArgs {
     const double* beta;
     int64_t gamma_P;
     const double* deltas;
-    int32_t p, R, cut_min;
+    int32_t p;
+    int32_t R;                  // phases per row in LDS: the largest n_rows of the plan's cones
     int32_t P, point0;          // points of the launch
     int32_t M;
     int32_t n_units;            // of the launch
@@ -82,6 +85,6 @@ hipError_t launch_wide(int kin, bool grad, const WdArgs& a, hipStream_t st);
 // sums the units of n_cones cones into zz and g
 hipError_t launch_wide_sum(const WdArgs& a, int32_t n_cones, bool grad, hipStream_t st);
 hipError_t launch_wide_tables(const ConeWd* cones, int64_t n_cones, const int32_t* ea, const int32_t* eb,
-                              const int32_t* ew, int32_t p, int32_t cut_min, uint8_t* tab, hipStream_t st);
+                              const int32_t* ew, int32_t p, uint8_t* tab, hipStream_t st);
 
 }  // namespace qaoa

@@ -147,10 +147,11 @@ __global__ void __launch_bounds__((Uz<KIN>::W), Uz<KIN>::W > 512 ? 4 : 3) k_wide
     const ConeWd& cd = a.cones[unit.cone];
     const size_t ip = (static_cast<size_t>(cd.inst) * a.gamma_P + point) * PP;
     const double delta = a.deltas[cd.inst];
-    for (int i = tid; i < PP * R; i += Z::W) {
-        const int l = i / R, j = i - l * R;
+    const int n_rows = cd.n_rows;
+    for (int i = tid; i < PP * n_rows; i += Z::W) {
+        const int l = i / n_rows, j = i - l * n_rows;
         double s, c;
-        sincos(a.gamma[ip + l] * delta * static_cast<double>(a.cut_min + j), &s, &c);
+        sincos(a.gamma[ip + l] * delta * static_cast<double>(cd.cut_min + j), &s, &c);
         const float x = static_cast<float>(c), y = static_cast<float>(-s);
         if (l == 0) {   // times 1, i, -1, -i
             dyn[j] = make_float2(x, y);
@@ -435,6 +436,12 @@ template <int KIN>
 hipError_t launch_wide_k(bool grad, const WdArgs& a, hipStream_t st) {
     const int64_t blocks = static_cast<int64_t>(a.n_units) * a.P;
     if (blocks <= 0) return hipSuccess;
+    // rows of the cone's own cut values: with those of the whole plan (up to 511 phases where cones have
+    // couplings of opposite signs) 14 inner qubits would not fit the 160 KiB
+    static_assert(Uz<KIN>::NPAD * sizeof(float2) + WD_CFG * sizeof(CfgWd) + Uz<KIN>::W + 512 +
+                          ((3 + WD_PMAX) * WD_ROWS + 2 * WD_ROWS) * sizeof(float2) <= 160 * 1024,
+                  "state, configurations, sums (a double per eight threads), phase rows, cosines");
+    if (a.R > WD_ROWS || a.wz >= WD_ROWS) return hipErrorInvalidValue;
     const size_t lds = (static_cast<size_t>(3 + a.p) * a.R + 2 * (a.wz + 1)) * sizeof(float2);
     const dim3 grid(static_cast<unsigned>(blocks)), block(Uz<KIN>::W);
     if (a.p == 2) {

@@ -79,3 +79,29 @@ def test_random_regular_p3(Q):
     for j, x in enumerate((g, h)):
         own = Q.Plan(x.n, x.edges, p=3).energy(dev(gb[j]), dev(bb[j]))
         assert (Eb[j] - own).abs().max().item() <= 1e-6 * x.m
+
+
+def test_rows_of_opposite_signs(Q):
+    # 30 qubits at p = 3, 14 of them inner: the 3-regular tree around an edge with couplings 8 and 9, and
+    # with -8 and -9, in one plan.  Its phases span 509 cut values, a cone's 255: rows of the plan's
+    # range would not fit beside the state
+    e, outer, n = [(0, 1)], [0, 1], 2
+    for _ in range(3):
+        outer = [(a, b) for i, a in enumerate(outer) for b in (n + 2 * i, n + 2 * i + 1)]
+        e, n, outer = e + outer, n + len(outer), [b for _, b in outer]
+    w = np.full(len(e), 9.0)
+    w[:7] = 8.0
+    assert n == 30 and w.sum() == 254
+    ga, be = W.draw_angles(1, 3, 930)
+    two = Q.Plan.batch([(n, e, w), (n, e, -w)], 3)
+    info = two.info()
+    assert info["max_k"] == 30 and info["cut_max"] - info["cut_min"] == 508
+    out = two.energy_grad(dev(ga), dev(be))
+    for j, x in enumerate((w, -w)):
+        own = Q.Plan(n, e, p=3, weights=x)
+        assert own.cone(0)[0] == 30
+        ref = own.energy_grad(dev(ga), dev(be))
+        _same([y[j] for y in out], ref, 254.0)
+        assert (out[0][j] - ref[0]).abs().max().item() <= 1e-10 * 254
+    passes = Q.Plan(n, e, p=3, weights=w, tune=2, mem_budget_bytes=64 << 30)
+    _same([y[0] for y in out], passes.energy_grad(dev(ga), dev(be)), 254.0)
