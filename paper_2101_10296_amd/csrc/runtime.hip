@@ -709,6 +709,7 @@ struct WideHost {
     std::vector<CfgWd> cfg;
     std::vector<ZLeaf> leaf;
     int64_t tab_bytes = 0;
+    bool too_many = false;   // units: more than 32-bit integers index
 };
 
 // Fills P->wd_groups and the descriptors for the orbits in ord (wide.hpp); their edges are appended.
@@ -720,6 +721,7 @@ void build_wide(qaoa_plan_s* P, std::vector<int64_t>& ord, std::vector<int32_t>&
     P->wd_groups.clear();
     P->wd_units.clear();
     P->wd_all_units = 0;
+    P->wd_most_units = 0;
     P->wd_rows = 1;
     if (ord.empty()) return;
     const bool by_k = P->opt.profile != 0;
@@ -791,13 +793,17 @@ void build_wide(qaoa_plan_s* P, std::vector<int64_t>& ord, std::vector<int32_t>&
         d.n_edges = q.n_edges;
         const int kk = by_k ? c.k : 0;
         if (P->wd_groups.empty() || P->wd_groups.back().kin != q.kin || P->wd_groups.back().K != kk)
-            P->wd_groups.push_back({q.kin, kk, static_cast<int64_t>(w.units.size()), 0, 0});
+            P->wd_groups.push_back({q.kin, kk, static_cast<int64_t>(w.units.size()), 0});
         d.first_unit = static_cast<int32_t>(w.units.size());
         for (uint32_t c0 = 0; c0 < d.n_cfg; c0 += WD_CFG)
             w.units.push_back({static_cast<int32_t>(i), c0, std::min<uint32_t>(d.n_cfg, c0 + WD_CFG)});
+        if (w.units.size() > static_cast<size_t>(INT32_MAX)) {
+            w.too_many = true;
+            return;
+        }
         d.n_units = static_cast<int32_t>(w.units.size()) - d.first_unit;
+        P->wd_most_units = std::max<int64_t>(P->wd_most_units, d.n_units);
         P->wd_groups.back().count += d.n_units;
-        P->wd_groups.back().cones += 1;
         P->wd_units.emplace_back(d.first_unit, d.n_units);
         P->in_max_k = std::max(P->in_max_k, c.k);
         w.cones.push_back(d);
@@ -900,6 +906,10 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     build_point(P, in);
     WideHost wd;
     build_wide(P, wdord, ea, eb, ew, wd);
+    if (wd.too_many) {
+        msg = "the plan's cones take more than 2^31 - 1 units of work; descriptors index them with 32-bit integers";
+        return QAOA_EINVAL;
+    }
     // depth-1 cones: the couplings of the edge's two ends
     std::vector<ConeD1> dc(d1ord.size());
     std::vector<double2> dw;
@@ -1474,6 +1484,82 @@ InMix::Class& mix_class(const qaoa_plan_s* P, const qaoa_plan_s::InGroup& grp, I
     return c;
 }
 
+// The cones on 11 to 14 inner qubits, as many of them per launch as the partial sums' room and the grid
+// (fewer than 2^32 threads, 1024 per unit) hold, for as many points.  A cone's units and their order
+// are its own: its sums do not depend on the split.
+qaoa_status enqueue_wide(qaoa_plan_s* P, bool grad, int64_t n_points, const double* gamma, const double* beta, double* zz,
+                         double* g, GroupTimer& tm, hipStream_t stream, std::string& msg) {
+    const HostPlan& hp = P->hp;
+    WdArgs a{};
+    a.cones = P->d_wd;
+    a.grp = P->d_wdgrp;
+    a.leaf = P->d_wdleaf;
+    a.wz = P->wz;
+    a.cfg = P->d_wdcfg;
+    a.tab = P->d_wdtab;
+    a.gamma = gamma;
+    a.beta = beta;
+    a.gamma_P = n_points;
+    a.deltas = P->d_inst_delta;
+    a.p = hp.p;
+    a.R = P->wd_rows;
+    a.M = static_cast<int32_t>(hp.cones.size());
+    a.part = P->d_part;
+    a.zz = zz;
+    a.g = g;
+    const int64_t nv = grad ? 2 * hp.p + 1 : 1;
+    const int64_t room = static_cast<int64_t>(P->cap_part) / nv;
+    constexpr int64_t GRID = static_cast<int64_t>(UINT32_MAX) / 1024;
+    const size_t n_cones = P->wd_units.size();
+    for (size_t c0 = 0, c1; c0 < n_cones; c0 = c1) {
+        const int64_t u0 = P->wd_units[c0].first;
+        int64_t u1 = u0;
+        for (c1 = c0; c1 < n_cones; ++c1) {
+            const int64_t end = u1 + P->wd_units[c1].second;
+            if (c1 > c0 && end - u0 > std::min(room, GRID)) break;
+            u1 = end;
+        }
+        a.cone0 = static_cast<int32_t>(c0);
+        a.sum_unit0 = static_cast<int32_t>(u0);
+        a.all_units = static_cast<int32_t>(u1 - u0);
+        // (a sum takes a workgroup of 256 threads per cone, which has one unit at least)
+        const int64_t slab = std::max<int64_t>(1, std::min(room, GRID) / (u1 - u0));
+        for (int64_t p0 = 0; p0 < n_points; p0 += slab) {
+            const int32_t pc = static_cast<int32_t>(std::min(slab, n_points - p0));
+            for (const auto& grp : P->wd_groups) {
+                const int64_t first = std::max(grp.first, u0), last = std::min(grp.first + grp.count, u1);
+                if (first >= last) continue;
+                auto launch = [&](int64_t f, int64_t count, int64_t i0, int64_t np) {
+                    a.units = P->d_wdunit + f;
+                    a.unit0 = static_cast<int32_t>(f - u0);
+                    a.n_units = static_cast<int32_t>(count);
+                    a.point0 = static_cast<int32_t>(p0 + i0);
+                    a.P = static_cast<int32_t>(np);
+                    a.part = P->d_part + static_cast<size_t>(i0) * a.all_units * nv;
+                    return launch_wide(grp.kin, grad, a, stream);
+                };
+                int64_t cones = 0;
+                for (size_t c = c0; c < c1; ++c) cones += P->wd_units[c].first >= first && P->wd_units[c].first < last;
+                QCHECK(tm.begin(grp.K, cones * pc));
+                if (P->opt.one_cone_at_a_time) {
+                    for (int64_t i = 0; i < pc; ++i)
+                        for (size_t c = c0; c < c1; ++c)
+                            if (P->wd_units[c].first >= first && P->wd_units[c].first < last)
+                                QCHECK(launch(P->wd_units[c].first, P->wd_units[c].second, i, 1));
+                } else {
+                    QCHECK(launch(first, last - first, 0, pc));
+                }
+                QCHECK(tm.end());
+            }
+            a.point0 = static_cast<int32_t>(p0);
+            a.P = pc;
+            a.part = P->d_part;
+            QCHECK(launch_wide_sum(a, static_cast<int32_t>(c1 - c0), grad, stream));
+        }
+    }
+    return QAOA_OK;
+}
+
 // The launch sequence of one energy call.  With fixed_batches the HBM groups reuse the
 // batch sizes of the previous call (and so allocate nothing): used while capturing.
 qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const double* beta, double* energy,
@@ -1590,8 +1676,10 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
             part_need = std::max(part_need, static_cast<size_t>(parts));
         }
     }
-    const size_t wd_one = static_cast<size_t>(P->wd_all_units) * nv;
-    if (wd_one) part_need = std::max(part_need, std::max(wd_one, std::min<size_t>(wd_one * n_points, size_t{1} << 25)));
+    if (!P->wd_units.empty()) {   // a cone's at least
+        const size_t all = static_cast<size_t>(P->wd_all_units) * nv * static_cast<size_t>(n_points);
+        part_need = std::max({part_need, static_cast<size_t>(P->wd_most_units) * nv, std::min(all, size_t{1} << 25)});
+    }
     if (part_need && (st = grow(P->d_part, P->cap_part, part_need, msg)) != QAOA_OK) return st;
     GroupTimer tm(P, stream);
     if (tables) {
@@ -1637,59 +1725,9 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         QCHECK(run_inner(grp, j));
         QCHECK(tm.end());
     }
-    if (!P->wd_groups.empty()) {
-        WdArgs a{};
-        a.cones = P->d_wd;
-        a.grp = P->d_wdgrp;
-        a.leaf = P->d_wdleaf;
-        a.wz = P->wz;
-        a.cfg = P->d_wdcfg;
-        a.tab = P->d_wdtab;
-        a.gamma = gamma;
-        a.beta = beta;
-        a.gamma_P = n_points;
-        a.deltas = P->d_inst_delta;
-        a.p = p;
-        a.R = P->wd_rows;
-        a.M = M;
-        a.all_units = static_cast<int32_t>(P->wd_all_units);
-        a.part = P->d_part;
-        a.zz = zz;
-        a.g = g;
-        const int32_t n_cones = static_cast<int32_t>(P->wd_units.size());
-        // points per launch: the partial sums' room, and fewer than 2^32 threads
-        const int64_t slab = std::max<int64_t>(
-            1, std::min<int64_t>(static_cast<int64_t>(P->cap_part / wd_one),
-                                 (static_cast<int64_t>(UINT32_MAX) / 1024) / std::max<int64_t>(P->wd_all_units, n_cones)));
-        for (int64_t p0 = 0; p0 < n_points; p0 += slab) {
-            a.point0 = static_cast<int32_t>(p0);
-            a.P = static_cast<int32_t>(std::min(slab, n_points - p0));
-            for (const auto& grp : P->wd_groups) {
-                auto launch = [&](int64_t first, int64_t count) {
-                    a.units = P->d_wdunit + first;
-                    a.unit0 = static_cast<int32_t>(first);
-                    a.n_units = static_cast<int32_t>(count);
-                    return launch_wide(grp.kin, grad, a, stream);
-                };
-                QCHECK(tm.begin(grp.K, grp.cones * a.P));
-                if (P->opt.one_cone_at_a_time) {
-                    const WdArgs all = a;
-                    for (int64_t i = 0; i < all.P; ++i)
-                        for (const auto& u : P->wd_units)
-                            if (u.first >= grp.first && u.first < grp.first + grp.count) {
-                                a.point0 = all.point0 + static_cast<int32_t>(i);
-                                a.P = 1;
-                                a.part = all.part + static_cast<size_t>(i) * wd_one;
-                                QCHECK(launch(u.first, u.second));
-                            }
-                    a = all;
-                } else {
-                    QCHECK(launch(grp.first, grp.count));
-                }
-                QCHECK(tm.end());
-            }
-            QCHECK(launch_wide_sum(a, n_cones, grad, stream));
-        }
+    if (!P->wd_units.empty()) {
+        st = enqueue_wide(P, grad, n_points, gamma, beta, zz, g, tm, stream, msg);
+        if (st != QAOA_OK) return st;
     }
     if (use_wh)
         for (const auto& grp : P->wh_groups) {

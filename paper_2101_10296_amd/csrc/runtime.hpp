@@ -65,11 +65,10 @@ struct qaoa_plan_s {
     struct WdGroup {
         int kin, K;
         int64_t first, count;   // units
-        int64_t cones;
     };
     std::vector<WdGroup> wd_groups;
     std::vector<std::pair<int32_t, int32_t>> wd_units;   // (first unit, units) of each cone
-    int64_t wd_all_units = 0;
+    int64_t wd_all_units = 0, wd_most_units = 0;   // of the plan, of one cone
     int32_t wd_rows = 1;                // phases per row of the largest cut range
     qaoa::ConeWd* d_wd = nullptr;
     qaoa::UnitWd* d_wdunit = nullptr;

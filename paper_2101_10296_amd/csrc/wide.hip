@@ -40,11 +40,11 @@ __global__ void __launch_bounds__(256) k_wide_sum(WdArgs a, int32_t n_cones, int
     const int64_t b = blockIdx.x;
     const int32_t c = static_cast<int32_t>(b % n_cones);
     const int64_t pt = b / n_cones;
-    const ConeWd& cd = a.cones[c];
+    const ConeWd& cd = a.cones[a.cone0 + c];
     const int v = threadIdx.x & 7, q = threadIdx.x >> 3;   // at most 7 values
     double x = 0.0;
     if (v < nv) {
-        const double* src = a.part + (pt * a.all_units + cd.first_unit) * nv + v;
+        const double* src = a.part + (pt * a.all_units + (cd.first_unit - a.sum_unit0)) * nv + v;
         for (int u = q; u < cd.n_units; u += 32) x += src[static_cast<size_t>(u) * nv];
     }
     sh[threadIdx.x] = x;

@@ -75,14 +75,15 @@ struct WdArgs {
     int32_t M;
     int32_t n_units;            // of the launch
     int32_t unit0;              // its first unit's place in the partial sums
-    int32_t all_units;          // units of the plan (a point's row of partial sums)
+    int32_t all_units;          // units of a point's row of partial sums
+    int32_t cone0, sum_unit0;   // first cone of that row, and its first unit
     double* part;               // [P][all_units][values]
     double* zz;                 // [..][M], rows from point 0 of the call
     double* g;
 };
 
 hipError_t launch_wide(int kin, bool grad, const WdArgs& a, hipStream_t st);
-// sums the units of n_cones cones into zz and g
+// sums the units of the n_cones cones from cone0 on into zz and g
 hipError_t launch_wide_sum(const WdArgs& a, int32_t n_cones, bool grad, hipStream_t st);
 hipError_t launch_wide_tables(const ConeWd* cones, int64_t n_cones, const int32_t* ea, const int32_t* eb,
                               const int32_t* ew, int32_t p, uint8_t* tab, hipStream_t st);

@@ -105,3 +105,21 @@ def test_rows_of_opposite_signs(Q):
         assert (out[0][j] - ref[0]).abs().max().item() <= 1e-10 * 254
     passes = Q.Plan(n, e, p=3, weights=w, tune=2, mem_budget_bytes=64 << 30)
     _same([y[0] for y in out], passes.energy_grad(dev(ga), dev(be)), 254.0)
+
+
+def test_more_units_than_a_grid_holds(Q):
+    # 14 inner qubits, 16 shell qubits next to two of them each, 16 different pairs: 2^15 configurations in
+    # 4096 units of 1024 threads.  1026 such cones exceed the 2^32 threads of a grid
+    e, n = [(0, 1)] + [(0, 2 + i) for i in range(6)] + [(1, 8 + i) for i in range(6)], 14
+    for lo in (2, 8):
+        for a, b in [(a, b) for a in range(6) for b in range(a + 1, 6)][::2]:
+            e += [(lo + a, n), (lo + b, n)]
+            n += 1
+    one = Q.Plan(n, e, p=2, reduce=False)
+    assert n == 30 and one.cone(0)[0] == 30 and 1026 * 4096 * 1024 > 2 ** 32
+    ga, be = W.draw_angles(1, 2, 940)
+    E, zz = one.energy(dev(ga), dev(be), term_zz=True)
+    many = Q.Plan.batch([(n, e)] * 1026, 2, reduce=False)
+    Em, zm = many.energy(dev(ga), dev(be), term_zz=True)
+    assert torch.equal(zm.reshape(1026, -1)[:, 0], zz[0, 0].expand(1026))
+    assert (Em - E).abs().max().item() <= 1e-6 * len(e)
