@@ -1348,10 +1348,26 @@ hipError_t launch_inner_group(const qaoa_plan_s* P, const qaoa_plan_s::InGroup& 
     a.inst0 = P->in_inst[static_cast<size_t>(grp.first)];
     a.seg = grp.n_seg > 1 ? P->d_inseg + grp.seg[upw_log2] : nullptr;
     // points per launch: a grid holds fewer than 2^32 threads, and the partial sums their room
-    int64_t slab = std::max<int64_t>(1, (static_cast<int64_t>(UINT32_MAX) / 256) / a.blocks);
-    if (grp.chunks > 1) slab = std::min(slab, static_cast<int64_t>(part_cap) / (a.units * nv));
-    for (int64_t p0 = 0; p0 < n_points; p0 += slab) {
-        const hipError_t e = run(p0, std::min(slab, n_points - p0), grp.count);
+    auto slabs = [&](int64_t cones) {
+        int64_t slab = std::max<int64_t>(1, (static_cast<int64_t>(UINT32_MAX) / 256) / a.blocks);
+        if (grp.chunks > 1) slab = std::min(slab, static_cast<int64_t>(part_cap) / (a.units * nv));
+        for (int64_t p0 = 0; p0 < n_points; p0 += slab) {
+            const hipError_t e = run(p0, std::min(slab, n_points - p0), cones);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    };
+    const int64_t room = grp.chunks > 1 ? static_cast<int64_t>(part_cap) / (grp.chunks * nv) : grp.count;   // cones
+    if (room >= grp.count) return slabs(grp.count);
+    // the sums of a point's cones exceed a small memory budget: runs of cones of one instance (same bits)
+    a.n_seg = 1;
+    for (int64_t i = 0, j; i < grp.count; i = j) {
+        a.inst0 = P->in_inst[static_cast<size_t>(grp.first + i)];
+        for (j = i + 1; j < grp.count && j - i < room && P->in_inst[static_cast<size_t>(grp.first + j)] == a.inst0; ++j) {}
+        a.cones = P->d_in + grp.first + i;
+        a.units = static_cast<int32_t>((j - i) * grp.chunks);
+        a.blocks = (a.units + 4 * a.upw - 1) / (4 * a.upw);
+        const hipError_t e = slabs(j - i);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -1420,6 +1436,19 @@ qaoa_status finish_sums(qaoa_plan_s* P, int64_t n_points, double* zz, double* g,
                           dgamma, dbeta, stream));
     QCHECK(tm.end());
     return QAOA_OK;
+}
+
+// Values of partial sums that a call holds at most: 2^25, and where a memory budget is set, what it leaves
+// beside one item of the largest class in device memory.  (A single cone's parts are always held:
+// less than its state would take.)
+size_t part_limit(const qaoa_plan_s* P) {
+    constexpr size_t MOST = size_t{1} << 25;
+    if (P->opt.mem_budget_bytes == 0) return MOST;
+    const size_t budget = static_cast<size_t>(P->opt.mem_budget_bytes);
+    size_t item = 0;
+    for (const auto& grp : P->hbm_groups)
+        item = std::max(item, hbm_item_bytes(grp.K, P->hp.p, true, P->hp.p >= 2 && P->opt.checkpoint_mode == 1));
+    return std::min(MOST, (budget > item ? budget - item : 0) / sizeof(double));
 }
 
 // First cone of a size class that the kernel for whole cones runs.
@@ -1606,7 +1635,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
             for (int64_t c = 0; c < grp.count; ++c) q.c[cone++].part0 = parts;
             parts += grp.count * grp.chunks * n_points * nvals;
         }
-        if (units <= IN_MIX && parts <= (int64_t{1} << 25)) {
+        if (units <= IN_MIX && parts <= static_cast<int64_t>(part_limit(P))) {
             if ((st = grow(P->d_part, P->cap_part, static_cast<size_t>(parts), msg)) != QAOA_OK) return st;
             InArgs a = inner_args(P, gamma, beta, n_points, term_zz, grad ? term_grad : nullptr);
             a.part = P->d_part;
@@ -1641,13 +1670,14 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         if ((st = grow(P->d_g, P->cap_g, static_cast<size_t>(n_points) * 2 * p * M, msg)) != QAOA_OK) return st;
         g = P->d_g;
     }
-    // partial sums of cones in several units: a point's at least, 2^25 values at most
+    // partial sums of cones in several units: a cone's at least
     size_t part_need = 0;
+    const size_t part_most = part_limit(P);
     const size_t nv = grad ? 2 * static_cast<size_t>(p) + 1 : 1;
     for (const auto& grp : P->in_groups)
         if (grp.chunks > 1) {
-            const size_t one = static_cast<size_t>(grp.count) * grp.chunks * nv;
-            part_need = std::max(part_need, std::max(one, std::min<size_t>(one * n_points, size_t{1} << 25)));
+            const size_t one = static_cast<size_t>(grp.chunks) * nv;
+            part_need = std::max(part_need, std::max(one, std::min(one * grp.count * n_points, part_most)));
         }
     // classes that share a launch, with room for the sums of all their parts
     InMix mix{};
@@ -1658,7 +1688,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
             const auto& grp = P->in_groups[i];
             const int64_t units = grp.count * grp.chunks;
             if (grp.tree || (grp.wh && use_wh) || units * n_points > IN_MIX ||
-                (grp.chunks > 1 && parts + units * n_points * static_cast<int64_t>(nv) > (int64_t{1} << 25)))
+                (grp.chunks > 1 && parts + units * n_points * static_cast<int64_t>(nv) > static_cast<int64_t>(part_most)))
                 continue;
             InMix::Class& c = mix_class(P, grp, mix);
             c.part0 = parts;
@@ -1678,7 +1708,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
     }
     if (!P->wd_units.empty()) {   // a cone's at least
         const size_t all = static_cast<size_t>(P->wd_all_units) * nv * static_cast<size_t>(n_points);
-        part_need = std::max({part_need, static_cast<size_t>(P->wd_most_units) * nv, std::min(all, size_t{1} << 25)});
+        part_need = std::max({part_need, static_cast<size_t>(P->wd_most_units) * nv, std::min(all, part_most)});
     }
     if (part_need && (st = grow(P->d_part, P->cap_part, part_need, msg)) != QAOA_OK) return st;
     GroupTimer tm(P, stream);
@@ -1806,6 +1836,9 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
             QCHECK(hipMemGetInfo(&fr, &tot));
             const size_t held = P->cap_phi * sizeof(float2) + P->cap_lam * sizeof(float2) + P->cap_gpart * sizeof(double);
             budget = static_cast<size_t>(0.85 * static_cast<double>(fr + held));
+        } else if (!fixed_batches) {   // less the partial sums of other cones, down to one item (part_limit)
+            const size_t item = P->opt.checkpoint_mode == 1 ? per_ck : per_unc, parts = P->cap_part * sizeof(double);
+            if (budget > item) budget = budget - item > parts ? budget - parts : item;
         }
         // tiles (group 0: tile pairs) per workgroup: up to 8 while the class keeps >= 4096
         // workgroups (16 per CU); fixed per class, so an item's sums run in the same order
