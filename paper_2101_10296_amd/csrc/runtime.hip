@@ -251,7 +251,7 @@ struct WholeHost {
     std::vector<MemWh> mem;
     std::vector<int64_t> rep;    // representative orbit of each group
     std::vector<double> Wg;
-    int64_t obs = 0;             // floats of the observable tables
+    int64_t obs = 0;             // entries of the observable tables
 };
 
 void build_whole(qaoa_plan_s* P, WholeHost& w) {
@@ -330,6 +330,11 @@ void build_whole(qaoa_plan_s* P, WholeHost& w) {
         g.cut_range = range;
         g.mid = static_cast<float>(0.5 * (range - 1));
         g.c0 = static_cast<float>(0.5 * (c.cf_min + c.cf_max));
+        double most = 0.0;
+        for (size_t q = static_cast<size_t>(g.mem_off); q < w.mem.size(); ++q) most = std::max(most, std::fabs(w.mem[q].W));
+        const int unit = most > 0.0 ? std::ilogb(most) : 0;
+        g.scale = std::ldexp(1.0, unit);
+        for (size_t q = static_cast<size_t>(g.mem_off); q < w.mem.size(); ++q) w.mem[q].W = std::ldexp(w.mem[q].W, -unit);
         g.v_off = w.obs;
         w.obs += int64_t{1} << (c.k - 1);
         if (P->wh_groups.empty() || P->wh_groups.back().K != c.k)
@@ -1037,7 +1042,7 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     const bool has_seg = !in.seg.empty();
     const size_t o_is = has_seg ? place(in.seg.size() * sizeof(int32_t)) : 0;
     const size_t copied = arena;
-    const size_t o_wo = has_wh ? place(static_cast<size_t>(wh.obs) * sizeof(float)) : 0;
+    const size_t o_wo = has_wh ? place(static_cast<size_t>(wh.obs) * sizeof(double)) : 0;
     const size_t o_dta = has_wd ? place(static_cast<size_t>(wd.tab_bytes)) : 0;
     const size_t o_it = has_in ? place(static_cast<size_t>(in.tab_units) * 16) : 0;
     const size_t o_cut = place(static_cast<size_t>(std::max<int64_t>(cut_bytes, 16)));
@@ -1121,7 +1126,7 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     P->d_wh = has_wh ? reinterpret_cast<GroupWh*>(base + o_wg) : nullptr;
     P->d_whmem = has_wh ? reinterpret_cast<MemWh*>(base + o_wm) : nullptr;
     P->d_Wg = has_wh ? reinterpret_cast<double*>(base + o_ww) : nullptr;
-    P->d_whobs = has_wh ? reinterpret_cast<float*>(base + o_wo) : nullptr;
+    P->d_whobs = has_wh ? reinterpret_cast<double*>(base + o_wo) : nullptr;
     P->d_wd = has_wd ? reinterpret_cast<ConeWd*>(base + o_dco) : nullptr;
     P->d_wdunit = has_wd ? reinterpret_cast<UnitWd*>(base + o_dun) : nullptr;
     P->d_wdgrp = has_wd ? reinterpret_cast<GrpWd*>(base + o_dgr) : nullptr;

@@ -105,7 +105,7 @@ struct qaoa_plan_s {
     std::vector<WhGroup> wh_groups;
     qaoa::GroupWh* d_wh = nullptr;
     qaoa::MemWh* d_whmem = nullptr;
-    float* d_whobs = nullptr;
+    double* d_whobs = nullptr;
     double* d_Wg = nullptr;             // orbit weights of the gradient sums: 1 at a group's column
     // HBM-resident cones, grouped by k
     struct HGroup {

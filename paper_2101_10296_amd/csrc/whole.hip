@@ -18,7 +18,7 @@ bool fits(int p, int rowcap, bool realw) {
 }
 
 __global__ void __launch_bounds__(256)
-k_whole_obs(const GroupWh* __restrict__ groups, const MemWh* __restrict__ mem, uint32_t n, float* __restrict__ obs) {
+k_whole_obs(const GroupWh* __restrict__ groups, const MemWh* __restrict__ mem, uint32_t n, double* __restrict__ obs) {
     const GroupWh& g = groups[blockIdx.x];
     for (uint32_t x = threadIdx.x; x < n; x += 256) {
         double v = 0.0;
@@ -26,7 +26,7 @@ k_whole_obs(const GroupWh* __restrict__ groups, const MemWh* __restrict__ mem, u
             const MemWh& e = mem[g.mem_off + m];
             v += (((x >> e.u) ^ (x >> e.v)) & 1u) ? 0.5 * e.W : -0.5 * e.W;
         }
-        obs[g.v_off + x] = static_cast<float>(v);
+        obs[g.v_off + x] = v;
     }
 }
 }  // namespace
@@ -47,7 +47,7 @@ bool whole_fits(int K, int p, int rowcap, bool realw) {
     }
 }
 
-hipError_t launch_whole_obs(const GroupWh* groups, int64_t n_groups, const MemWh* mem, int K, float* obs, hipStream_t st) {
+hipError_t launch_whole_obs(const GroupWh* groups, int64_t n_groups, const MemWh* mem, int K, double* obs, hipStream_t st) {
     if (n_groups <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_whole_obs, dim3(static_cast<unsigned>(n_groups)), dim3(256), 0, st, groups, mem,
                        1u << (K - 1), obs);

@@ -16,7 +16,8 @@ struct GroupWh {
     int32_t rep;                // column that carries the group's gradient
     int32_t mem_off, n_mem;     // members
     int64_t cut_off;            // cut table of the representative cone (bytes; real weights: floats)
-    int64_t v_off;              // observable table (floats)
+    int64_t v_off;              // observable table (doubles)
+    double scale;               // its unit: the largest power of two up to the members' largest weight
     int32_t cut_row;            // phase row index of table value 0: cut_min of the cone - cut_min of the plan
     int32_t cut_range;          // phases of the cone
     float mid;                  // centre of the cut values, relative to table value 0
@@ -27,14 +28,14 @@ struct MemWh {
     int32_t orbit;
     int32_t u, v;               // the term's qubits in the representative's order
     int32_t pad_;
-    double W;                   // orbit weight
+    double W;                   // orbit weight in the group's unit
 };
 
 struct WhArgs {
     const GroupWh* groups;      // of one cone size
     const MemWh* mem;
     const uint8_t* cut;
-    const float* obs;
+    const double* obs;
     const double* gamma;        // [inst][gamma_P][p]
     const double* beta;
     int64_t gamma_P;
@@ -51,7 +52,8 @@ struct WhArgs {
 hipError_t launch_whole(int K, bool grad, const WhArgs& a, hipStream_t st);
 // whether the phase rows of a depth-p circuit fit the kernel's LDS
 bool whole_fits(int K, int p, int rowcap, bool realw);
-// V(x) - sum W / 2 with V(x) = sum over the members of W [x_u != x_v], x with qubit K - 1 = 0
-hipError_t launch_whole_obs(const GroupWh* groups, int64_t n_groups, const MemWh* mem, int K, float* obs, hipStream_t st);
+// V(x) - sum W / 2 with V(x) = sum over the members of W [x_u != x_v], x with qubit K - 1 = 0, in the
+// group's unit (weights of any size then stay in range where the product with psi is rounded to FP32)
+hipError_t launch_whole_obs(const GroupWh* groups, int64_t n_groups, const MemWh* mem, int K, double* obs, hipStream_t st);
 
 }  // namespace qaoa

@@ -442,14 +442,14 @@ __global__ void __launch_bounds__((Wz<K>::WG)) k_whole(WhArgs a) {
         }
         float2 lam[A];
         {
-            const float* V = a.obs + gd.v_off + y0;
+            const double* V = a.obs + gd.v_off + y0;
 #pragma unroll
             for (int r = 0; r < A; ++r) {
-                const float v = V[wreg<Z, 0>(r)];
-                lam[r] = make_float2(v * f[r].x, v * f[r].y);
+                const double v = V[wreg<Z, 0>(r)];
+                lam[r] = make_float2(static_cast<float>(v * f[r].x), static_cast<float>(v * f[r].y));
             }
         }
-        const double sc = -2.0 * 2.0 * hs;   // d<V> = 2 Im <lambda| . |psi>
+        const double sc = -2.0 * 2.0 * hs, unit = gd.scale;   // d<V> = 2 Im <lambda| . |psi>
         // undo layer l, which ended in layout END
         auto unlayer = [&](auto END, int l) {
             constexpr int F = decltype(END)::value, T = 1 - F;
@@ -483,7 +483,7 @@ __global__ void __launch_bounds__((Wz<K>::WG)) k_whole(WhArgs a) {
                     lam[r] = cmulc(lam[r], d);
                 }
             }
-            put(p + l, sc * b, l, sc * static_cast<double>(mu) * mu * static_cast<double>(ga));
+            put(p + l, sc * b * unit, l, sc * static_cast<double>(mu) * mu * static_cast<double>(ga) * unit);
         };
         int q = p - 1;
         while (q >= 1) {

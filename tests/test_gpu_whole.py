@@ -101,3 +101,19 @@ def test_rows_beyond_lds(Q):
     w = np.full(g.m, 9.0)
     ga, be = W.draw_angles(1, 120, 870)
     check_energy(Q, g, 120, ga, be, reduce=False, weights=w, grad=False)
+
+
+@pytest.mark.parametrize("n", [6, 9, 12, 14])
+def test_weights_of_any_size(Q, n):
+    # weights times 2^e at angles over 2^e: the same circuit, so the results times 2^e (energies, dE/dbeta)
+    # and 2^2e (dE/dgamma), bit for bit; products of two weights leave the range of FP32
+    g = _ring_with_chords(n, 20 + n)
+    w = np.random.default_rng(n).normal(size=g.m)
+    p = n // 2 + 1
+    ga, be = W.draw_angles(3, p, 880 + n)
+    E, dg, db = Q.Plan(g.n, g.edges, p=p, weights=w, reduce=False).energy_grad(dev(ga), dev(be))
+    assert torch.isfinite(dg).all() and torch.isfinite(db).all()
+    for e in (70, 100):
+        s = 2.0 ** e
+        E1, dg1, db1 = Q.Plan(g.n, g.edges, p=p, weights=w * s, reduce=False).energy_grad(dev(ga / s), dev(be))
+        assert torch.equal(E1, E * s) and torch.equal(db1, db * s) and torch.equal(dg1, dg * s * s)
