@@ -259,9 +259,10 @@ __device__ __forceinline__ void in_mix(float2 (&v)[A], float t, int m, const flo
     });
 }
 
-// Im <l| sum_(j < m) X_j |f>, this lane's share.
+// Im <l| sum_(j < m) X_j |f>, this lane's share: FP32 over the register qubits and over those of the row
+// (four each, as the stages of fused_impl.hpp), FP64 beyond.
 template <int KIN, bool FULL, int A>
-__device__ __forceinline__ float in_xsum(float2 (&f)[A], float2 (&l)[A], int m, const float (&sg)[4]) {
+__device__ __forceinline__ double in_xsum(float2 (&f)[A], float2 (&l)[A], int m, const float (&sg)[4]) {
     using Z = Iz<KIN>;
     float acc = 0.f;
     auto reg_bit = [&](int i) {
@@ -279,6 +280,8 @@ __device__ __forceinline__ float in_xsum(float2 (&f)[A], float2 (&l)[A], int m, 
 #pragma unroll
     for (int i = 0; i < Z::RB; ++i)
         if (FULL || i < 2 || i < m) reg_bit(i);
+    double sum = static_cast<double>(acc);
+    acc = 0.f;
     static_for<0, Z::ROW>([&](auto I) {
         constexpr int i = decltype(I)::value;
         if (FULL || 4 + i < m) {
@@ -288,6 +291,8 @@ __device__ __forceinline__ float in_xsum(float2 (&f)[A], float2 (&l)[A], int m, 
             acc = fmaf(sg[i], a0 + a1, acc);
         }
     });
+    if constexpr (Z::ROW > 0) sum += static_cast<double>(acc);
+    acc = 0.f;
     static_for<4, Z::LB>([&](auto I) {
         constexpr int i = decltype(I)::value;
         if (FULL || 4 + i < m) {
@@ -299,7 +304,8 @@ __device__ __forceinline__ float in_xsum(float2 (&f)[A], float2 (&l)[A], int m, 
             __builtin_amdgcn_sched_barrier(0);
         }
     });
-    return acc;
+    if constexpr (Z::LB > 4) sum += static_cast<double>(acc);
+    return sum;
 }
 
 // The lane's table bytes of one layer (A of them, in register order).
@@ -617,14 +623,13 @@ __device__ __forceinline__ void in_unit(const InArgs& a, const ConeIn& cd, uint3
         if constexpr (GRAD) {
             if constexpr (SIGNS) Wd = fma(dwt, zv + 2.0 * s_cs[0] * s_cs[1] * iv + s_cs[1] * s_cs[1] * dv, Wd);
             Gp = fma(wt, static_cast<double>(gp), Gp);
-            float b1 = 0.f;
             if constexpr (PP == 0) {
                 for (int ly = p - 1; ly >= 2; --ly) {
                     const int m = cd.mixed[ly];
                     const double k2 = kpow(ly);
                     const float s = static_cast<float>(sqrt(k2));
-                    const float b = in_xsum<KIN, false>(f, l, m, sg);
-                    lsum[(p + ly) * 64 + lane] = fma(wt, static_cast<double>(b), lsum[(p + ly) * 64 + lane]);
+                    const double b = in_xsum<KIN, false>(f, l, m, sg);
+                    lsum[(p + ly) * 64 + lane] = fma(wt, b, lsum[(p + ly) * 64 + lane]);
                     in_mix<KIN, false>(f, -s_t[ly], m, sg);
                     in_mix<KIN, false>(l, -s_t[ly], m, sg);
                     Tab<A> X;
@@ -645,8 +650,7 @@ __device__ __forceinline__ void in_unit(const InArgs& a, const ConeIn& cd, uint3
                     lsum[ly * 64 + lane] = fma(wt * k2, static_cast<double>(ga), lsum[ly * 64 + lane]);
                 }
             }
-            b1 = in_xsum<KIN, true>(f, l, KIN, sg);
-            B1 = fma(wt, static_cast<double>(b1), B1);
+            B1 = fma(wt, in_xsum<KIN, true>(f, l, KIN, sg), B1);
             in_mix<KIN, true>(l, -s_t[1], KIN, sg);
             float g1 = 0.f;
             T.opaque();

@@ -125,9 +125,10 @@ __device__ __forceinline__ void wmix(float2 (&v)[A], float t, const float (&sg)[
     });
 }
 
-// Im <l| sum X_j |f> over the qubits that layout LAY mixes.
+// Im <l| sum X_j |f> over the qubits that layout LAY mixes: FP32 over those in registers and over those of
+// the row, FP64 beyond.
 template <class Z, int LAY, int A>
-__device__ __forceinline__ float wxsum(float2 (&f)[A], float2 (&l)[A], const float (&sg)[4]) {
+__device__ __forceinline__ double wxsum(float2 (&f)[A], float2 (&l)[A], const float (&sg)[4]) {
     float acc = 0.f;
 #pragma unroll
     for (int i = 0; i < (LAY == 0 ? Z::RB : Z::NR); ++i) {
@@ -144,6 +145,8 @@ __device__ __forceinline__ float wxsum(float2 (&f)[A], float2 (&l)[A], const flo
         acc += a0 - a1;
         __builtin_amdgcn_sched_barrier(0);
     }
+    const double sum = static_cast<double>(acc);
+    acc = 0.f;
     static_for<0, (LAY == 0 ? Z::ROW : Z::NQ)>([&](auto I) {
         constexpr int i = decltype(I)::value;
         float a0 = 0.f, a1 = 0.f;
@@ -151,7 +154,7 @@ __device__ __forceinline__ float wxsum(float2 (&f)[A], float2 (&l)[A], const flo
         for (int r = 0; r < A; r += 4) row_dot4<i>(a0, a1, f, l, r);
         acc = fmaf(sg[i], a0 + a1, acc);
     });
-    return acc;
+    return sum + static_cast<double>(acc);
 }
 
 // c b with c = i^-E.
@@ -455,7 +458,7 @@ __global__ void __launch_bounds__((Wz<K>::WG)) k_whole(WhArgs a) {
             constexpr int F = decltype(END)::value, T = 1 - F;
             const float t = ml[l].x;
             const double k2 = mk[l];
-            double b = static_cast<double>(wxsum<Z, F>(f, lam, sg));
+            double b = wxsum<Z, F>(f, lam, sg);
             wmix<Z, F>(f, -t, sg);
             wmix<Z, F>(lam, -t, sg);
             double w = 1.0;   // every undone qubit scales the inner products by 1 / |kappa|^2
@@ -463,7 +466,7 @@ __global__ void __launch_bounds__((Wz<K>::WG)) k_whole(WhArgs a) {
             for (int e = 0; e < (F == 0 ? Z::RB + Z::ROW : Z::NR + Z::NQ); ++e) w *= k2;
             b += w * static_cast<double>(wunpose2<Z, F, T>(f, lam, xb, xb2, F ? o1 : o0, T ? o1 : o0, t, sT));
             w *= k2;
-            b += w * static_cast<double>(wxsum<Z, T>(f, lam, sg));
+            b += w * wxsum<Z, T>(f, lam, sg);
             wmix<Z, T>(f, -t, sg);
             wmix<Z, T>(lam, -t, sg);
             // gamma of the layer; both states carry 1 / mu, which the undone phase takes back

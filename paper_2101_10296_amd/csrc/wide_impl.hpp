@@ -107,13 +107,16 @@ __device__ __forceinline__ float rdot_bit(int i, const float2 (&f)[A], const flo
     return a0 + a1;
 }
 
-// Im <l| sum X_j |f> over the first m <= 8 qubits in L0.
+// Im <l| sum X_j |f> over the first m <= 8 qubits in L0: over those in registers, and over those of the row
+// (FP32 over four qubits each; the two are added in FP64).
 template <int A>
-__device__ __forceinline__ float pxsum(const float2 (&f)[A], const float2 (&l)[A], int m, const float (&sg)[4]) {
+__device__ __forceinline__ float2 pxsum(const float2 (&f)[A], const float2 (&l)[A], int m, const float (&sg)[4]) {
     float acc = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
         if (i < 2 || i < m) acc += rdot_bit(i, f, l);
+    const float regs = acc;
+    acc = 0.f;
     static_for<0, 4>([&](auto I) {
         constexpr int i = decltype(I)::value;
         if (4 + i < m) {
@@ -123,7 +126,7 @@ __device__ __forceinline__ float pxsum(const float2 (&f)[A], const float2 (&l)[A
             acc = fmaf(sg[i], a0 + a1, acc);
         }
     });
-    return acc;
+    return make_float2(regs, acc);
 }
 
 template <int KIN, bool GRAD, int PP>
@@ -352,7 +355,8 @@ __global__ void __launch_bounds__((Uz<KIN>::W), Uz<KIN>::W > 512 ? 4 : 3) k_wide
                 const int m = cd.mixed[2];
                 const double k2 = kpow(2);
                 const float s = static_cast<float>(sqrt(k2));
-                B2 = fma(wt, static_cast<double>(pxsum(f, lam, m, sg)), B2);
+                const float2 b2 = pxsum(f, lam, m, sg);
+                B2 = fma(wt, static_cast<double>(b2.x) + static_cast<double>(b2.y), B2);
                 pmix(f, -s_t[2], m, sg);
                 pmix(lam, -s_t[2], m, sg);
                 T[0].opaque();
@@ -372,7 +376,8 @@ __global__ void __launch_bounds__((Uz<KIN>::W), Uz<KIN>::W > 512 ? 4 : 3) k_wide
                 G2 = fma(wt * k2, static_cast<double>(ga), G2);
             }
             // layer 1: the terms of qubits 0-7 behind it; then lambda alone is undone
-            B1 = fma(wt, static_cast<double>(pxsum(f, lam, 8, sg)), B1);
+            const float2 b1 = pxsum(f, lam, 8, sg);
+            B1 = fma(wt, static_cast<double>(b1.x) + static_cast<double>(b1.y), B1);
             wmix<Z, 0>(lam, -t1, sg);
             wtrans<Z, 0, 1>(lam, xb, o0, o1);
             wmix<Z, 1>(lam, -t1, sg);
@@ -391,6 +396,8 @@ __global__ void __launch_bounds__((Uz<KIN>::W), Uz<KIN>::W > 512 ? 4 : 3) k_wide
             float bu = 0.f;
 #pragma unroll
             for (int i = 0; i < Z::NR; ++i) bu += rdot_bit(i, f, lam);
+            const float bur = bu;
+            bu = 0.f;
             static_for<0, Z::NQ>([&](auto I) {
                 constexpr int i = decltype(I)::value;
                 float a0 = 0.f, a1 = 0.f;
@@ -398,7 +405,7 @@ __global__ void __launch_bounds__((Uz<KIN>::W), Uz<KIN>::W > 512 ? 4 : 3) k_wide
                 for (int r = 0; r < A; r += 4) row_dot4<i>(a0, a1, f, lam, r);
                 bu = fmaf(sg[i], a0 + a1, bu);
             });
-            B1u = fma(wt, static_cast<double>(bu), B1u);
+            B1u = fma(wt, static_cast<double>(bur) + static_cast<double>(bu), B1u);
         }
     }
     // psi is at its true norm times 2^(kin/2) behind layer 1; the undone layer scales lambda by 1 / mu_1
