@@ -1728,14 +1728,14 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
     const std::string arch = P->opt.tune == 1 ? device_arch(P->device) : std::string();
     // units per wave: the workgroup's set-up (phase rows) is shared by more units once the waves
     // fill the chip several times over
-    auto inner_upw = [&](const qaoa_plan_s::InGroup& grp) {
-        const int64_t units = grp.count * grp.chunks * n_points / (grp.tree ? 64 : 1);
+    auto inner_upw = [&](const qaoa_plan_s::InGroup& grp, int64_t points) {
+        const int64_t units = grp.count * grp.chunks * points / (grp.tree ? 64 : 1);
         int j = 0;
         while (j < 3 && (units >> (j + 1)) >= (int64_t{1} << (grp.tree ? 13 : 15))) ++j;
         return j;
     };
-    auto run_inner = [&](const qaoa_plan_s::InGroup& grp, int j) {
-        return launch_inner_group(P, grp, grad, j, n_points, gamma, beta, n_points, zz, g, P->d_part, P->cap_part, stream);
+    auto run_inner = [&](const qaoa_plan_s::InGroup& grp, int j, int64_t points) {   // the call's first points
+        return launch_inner_group(P, grp, grad, j, points, gamma, beta, n_points, zz, g, P->d_part, P->cap_part, stream);
     };
     if (mix.n) {
         InArgs a = inner_args(P, gamma, beta, n_points, zz, g);
@@ -1747,17 +1747,17 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
     for (const auto& grp : P->in_groups) {
         if ((grp.wh && use_wh) || mixed[static_cast<size_t>(&grp - P->in_groups.data())]) continue;
         if (P->opt.tune == 1 && grp.K <= P->opt.k_lds_max) continue;   // with the other cones of its size, below
-        int j = inner_upw(grp);
+        int j = inner_upw(grp, n_points);
         if (P->opt.tune == 1) {
             const TuneKey key{arch, 2, grp.K, p, grad ? 1 : 0, 0};
             int upw = 1 << j;
             if (!tune_lookup(key, upw) && !fixed_batches)
                 QCHECK(tune_pick(key, {1, 2, 4, 8}, grp.count * n_points, stream,
-                                 [&](int v) { return run_inner(grp, __builtin_ctz(static_cast<unsigned>(v))); }, upw));
+                                 [&](int v) { return run_inner(grp, __builtin_ctz(static_cast<unsigned>(v)), n_points); }, upw));
             j = __builtin_ctz(static_cast<unsigned>(std::min(upw, 8)));
         }
         QCHECK(tm.begin(grp.K, grp.count * n_points));
-        QCHECK(run_inner(grp, j));
+        QCHECK(run_inner(grp, j, n_points));
         QCHECK(tm.end());
     }
     if (!P->wd_units.empty()) {
@@ -1770,14 +1770,16 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
             QCHECK(launch_whole_group(P, grp, grad, n_points, gamma, beta, n_points, zz, g, stream));
             QCHECK(tm.end());
         }
-    // all cones of one size in layout v; the default (0) takes the cones with a shell on their inner
-    // qubits (tune = 1 plans hold them in both forms)
+    // the first n items of one cone size in layout v; the default (0) takes the cones with a shell, which
+    // come first, on their inner qubits (tune = 1 plans hold them in both forms): of n items all of these
+    // cones at the first points, where the other layouts take the first cones at all points
     auto run_size = [&](const qaoa_plan_s::Group& grp, int v, int64_t n) {
         int64_t done = lds_from(grp, use_wh) * n_points;
         if (v == 0 && grp.n_in > 0) {
+            const int64_t points = std::min(n_points, n / grp.n_in);
             for (const auto& ig : P->in_groups)
                 if (ig.K == grp.K) {
-                    const hipError_t e = run_inner(ig, inner_upw(ig));
+                    const hipError_t e = run_inner(ig, inner_upw(ig, points), points);
                     if (e != hipSuccess) return e;
                 }
             done = grp.n_in * n_points;
@@ -1798,7 +1800,8 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
                     variant = 0;
                 } else {
                     // timed on up to 2^16 items of this call (their results are written again below)
-                    const int64_t ns = std::min<int64_t>(items, int64_t{1} << 16);
+                    int64_t ns = std::min<int64_t>(items, int64_t{1} << 16);
+                    if (grp.n_in * n_points > ns) ns = std::max<int64_t>(1, ns / grp.n_in) * grp.n_in;   // whole points
                     QCHECK(tune_pick(key, cand, ns, stream, [&](int v) {
                         return run_size(grp, v, ns);
                     }, variant));

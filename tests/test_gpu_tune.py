@@ -77,3 +77,20 @@ def test_tuned_plans_match_defaults(Q):
         choice = int(ln.split("choice=")[1].split()[0])
         times = dict(kv.split("=") for kv in ln.split("ms:")[1].split())
         assert str(choice) in times and all(float(t) > 0 for t in times.values())
+
+
+def test_candidates_run_the_same_items(Q):
+    # 2.56 million items a size, of which some 60 000 are timed: also of the layout that takes the cones on
+    # their inner qubits, whose time is then a small part of the whole class's
+    g = W.circulant(10000, (1, 2))
+    ga, be = W.draw_angles(256, 2, 140)
+    plain = Q.Plan(g.n, g.edges, p=2, profile=True)
+    plain.energy(dev(ga), dev(be))
+    plain.energy(dev(ga), dev(be))
+    whole = {k: ms for k, items, ms in plain.kernel_times() if k > 0}
+    assert sorted(whole) == [10, 11]
+    Q.Plan(g.n, g.edges, p=2, tune=True).energy(dev(ga), dev(be))
+    for k, ms in whole.items():
+        ln, = [ln for ln in Q.tuning_report().splitlines() if "workgroup-variant k=%d p=2 grad=0" % k in ln]
+        assert 30000 <= int(ln.split("items=")[1].split()[0]) <= 1 << 16
+        assert float(ln.split(" 0=")[1].split()[0]) <= 0.25 * ms
