@@ -121,7 +121,8 @@ typedef struct {
                                      cones in device memory: tiles per workgroup; those evaluated
                                      on their inner qubits: units per wave) and keeps the
                                      fastest for the rest of the process, per (device
-                                     architecture, class, k, p, gradient, real weights);
+                                     architecture, class, k, p, gradient, real weights, and which
+                                     inner forms the class's cones have);
                                      qaoa_tuning_report lists the choices.  0 = fixed defaults;
                                      2, 3, 4, 5 = workgroup layout 0 (default), 1 (one register
                                      bit fewer per stage), 2 (workgroups of >= 256 threads),
@@ -288,8 +289,8 @@ qaoa_status qaoa_find_generators(const qaoa_problem* pr, int32_t max_generators,
                                  int32_t* generators, int32_t* n_found, int32_t* complete);
 
 /* The run-time tuner's choices so far in this process (plans built with opts.tune = 1), one
- * line per kernel class: device architecture, class, k, p, gradient, real weights, the
- * chosen layout and the milliseconds measured for every candidate.  Writes at most cap - 1
+ * line per kernel class: device architecture, class, k, p, gradient, real weights, the inner
+ * forms of its cones where it has any ("form="), the chosen layout and the milliseconds measured for every candidate.  Writes at most cap - 1
  * characters and a terminating zero into buf (caller-owned host memory, may be NULL when
  * cap is 0); *len = the length of the whole report.  The tuner serves the batching and
  * scheduling of the light-cone evaluations (Sec. 2.3 terms are independent work items).

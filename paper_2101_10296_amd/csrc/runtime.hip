@@ -20,15 +20,18 @@ namespace {
 // ---- run-time tuner (plans built with opts.tune = 1).  Layout choices of a kernel class
 // are timed once per process on the first call that needs them (HIP events on the call's
 // stream) and the fastest is kept, keyed by (device architecture, what, k, p, gradient,
-// real weights).  what = 0: register bits per LDS stage / workgroup size of the
+// real weights, form).  form: which of the size's cones run on their inner qubits, and how many
+// those are (empty: none): their time says nothing about cones in another form.  what = 0: register bits per LDS stage / workgroup size of the
 // workgroup-resident kernel (fused_variants); what = 1: tiles per workgroup of the
 // device-memory passes; what = 2: units per wave of cones above k_lds_max qubits that run on
 // their inner qubits (reported under the name of 1: such a unit stands where a tile stood).
 struct TuneKey {
     std::string arch;
     int what, k, p, grad, realw;
+    std::string form;
     bool operator<(const TuneKey& o) const {
-        return std::tie(arch, what, k, p, grad, realw) < std::tie(o.arch, o.what, o.k, o.p, o.grad, o.realw);
+        return std::tie(arch, what, k, p, grad, realw, form) <
+               std::tie(o.arch, o.what, o.k, o.p, o.grad, o.realw, o.form);
     }
 };
 struct TuneRec {
@@ -1501,6 +1504,11 @@ qaoa_status enqueue_depth1(qaoa_plan_s* P, int64_t n_points, const double* gamma
     return finish_sums(P, n_points, a.zz, a.g, energy, dgamma, dbeta, term_grad != nullptr, P->d_W, tm, stream, msg);
 }
 
+// A class's form in the tuner's keys: "tree", or inner qubits ("z": with leaves).
+std::string inner_form(const qaoa_plan_s::InGroup& grp) {
+    return grp.tree ? "tree" : std::to_string(grp.kin) + (grp.signs ? "z" : "");
+}
+
 // The next class of a shared launch.
 InMix::Class& mix_class(const qaoa_plan_s* P, const qaoa_plan_s::InGroup& grp, InMix& mix) {
     InMix::Class& c = mix.c[mix.n++];
@@ -1749,7 +1757,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         if (P->opt.tune == 1 && grp.K <= P->opt.k_lds_max) continue;   // with the other cones of its size, below
         int j = inner_upw(grp, n_points);
         if (P->opt.tune == 1) {
-            const TuneKey key{arch, 2, grp.K, p, grad ? 1 : 0, 0};
+            const TuneKey key{arch, 2, grp.K, p, grad ? 1 : 0, 0, inner_form(grp)};
             int upw = 1 << j;
             if (!tune_lookup(key, upw) && !fixed_batches)
                 QCHECK(tune_pick(key, {1, 2, 4, 8}, grp.count * n_points, stream,
@@ -1793,7 +1801,11 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         if (lds_from(grp, use_wh) >= grp.count) continue;
         int variant = P->opt.tune >= 2 ? P->opt.tune - 2 : 0;   // tune 2, 3, 4: a fixed layout variant
         if (P->opt.tune == 1 && !P->opt.one_cone_at_a_time) {
-            const TuneKey key{arch, 0, grp.K, p, grad ? 1 : 0, hp.realw ? 1 : 0};
+            std::string form;   // of the size's cones: those on their inner qubits, "+" others
+            for (const auto& ig : P->in_groups)
+                if (ig.K == grp.K) form += (form.empty() ? "" : ",") + inner_form(ig);
+            if (!form.empty() && grp.n_in < grp.count) form += "+";
+            const TuneKey key{arch, 0, grp.K, p, grad ? 1 : 0, hp.realw ? 1 : 0, form};
             if (!tune_lookup(key, variant)) {
                 const std::vector<int> cand = fused_variants(grp.K, grad);
                 if (cand.size() <= 1 || fixed_batches) {
@@ -1853,7 +1865,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         // whatever the batching
         int tpw = 1;
         while (tpw < 8 && 2 * tpw <= tiles / 2 && items * tiles / (2 * tpw) >= 4096) tpw *= 2;
-        const TuneKey tkey{arch, 1, k, p, grad ? 1 : 0, 0};
+        const TuneKey tkey{arch, 1, k, p, grad ? 1 : 0, 0, ""};
         bool tune_tpw = false;
         if (P->opt.tune == 1) {
             int c = 0;
@@ -2047,9 +2059,11 @@ std::string tuning_report() {
     for (const auto& kv : g_tune) {
         const TuneKey& key = kv.first;
         const TuneRec& r = kv.second;
-        std::snprintf(line, sizeof(line), "%s %s k=%d p=%d grad=%d realw=%d items=%lld choice=%d ms:",
-                      key.arch.c_str(), key.what == 0 ? "workgroup-variant" : "passes-tiles-per-workgroup", key.k,
-                      key.p, key.grad, key.realw, static_cast<long long>(r.items), r.choice);
+        std::snprintf(line, sizeof(line), "%s %s k=%d p=%d grad=%d realw=%d", key.arch.c_str(),
+                      key.what == 0 ? "workgroup-variant" : "passes-tiles-per-workgroup", key.k, key.p, key.grad, key.realw);
+        out += line;
+        if (!key.form.empty()) out += " form=" + key.form;
+        std::snprintf(line, sizeof(line), " items=%lld choice=%d ms:", static_cast<long long>(r.items), r.choice);
         out += line;
         for (const auto& cm : r.ms) {
             std::snprintf(line, sizeof(line), " %d=%.4f", cm.first, cm.second);

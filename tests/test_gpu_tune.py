@@ -94,3 +94,18 @@ def test_candidates_run_the_same_items(Q):
         ln, = [ln for ln in Q.tuning_report().splitlines() if "workgroup-variant k=%d p=2 grad=0" % k in ln]
         assert 30000 <= int(ln.split("items=")[1].split()[0]) <= 1 << 16
         assert float(ln.split(" 0=")[1].split()[0]) <= 0.25 * ms
+
+
+def test_choices_are_kept_per_form(Q):
+    # 10 qubits at p = 2 and energies alone: whole-graph cones, cones on 6 inner qubits, and trees, a record each
+    ga, be = W.draw_angles(4, 2, 141)
+    ring = np.array([(i, j) for i in range(10) for j in range(i + 1, 10) if j - i in (1, 2, 3, 5)], np.int32)
+    tree = np.array([(0, 1)] + [(i // 4, 2 + i) for i in range(8)], np.int32)
+    for n, e in ((10, ring), (40, W.circulant(40, (1, 2)).edges), (10, tree)):
+        pl = Q.Plan(n, e, p=2, reduce=False, tune=True)
+        assert pl.info()["k_hist"][10] > 0
+        E = pl.energy(dev(ga), dev(be))
+        assert (E - Q.Plan(n, e, p=2, reduce=False).energy(dev(ga), dev(be))).abs().max().item() <= ZZ_TOL * len(e) / 2
+    forms = {ln.partition(" form=")[2].partition(" ")[0] for ln in Q.tuning_report().splitlines()
+             if "workgroup-variant k=10 p=2 grad=0" in ln}
+    assert len(forms) >= 3, forms
