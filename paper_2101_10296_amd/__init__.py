@@ -160,11 +160,12 @@ class Plan:
     def kernel_times(self):
         """[(k, items, ms)] per kernel group of the last call (plans built with profile=True);
         k = -1 is the angle-table kernel, k = -2 the orbit-weighted combination."""
-        cap = 64
+        n = C.c_int32()
+        _check(_capi.lib().qaoa_plan_kernel_times(self._h, 0, None, None, None, C.byref(n)))
+        cap = n.value   # one group per number of qubits and form of its cones
         ks = np.zeros(cap, np.int32)
         it = np.zeros(cap, np.int64)
         ms = np.zeros(cap, np.float64)
-        n = C.c_int32()
         _check(_capi.lib().qaoa_plan_kernel_times(self._h, cap, ks.ctypes.data_as(C.POINTER(C.c_int32)),
                                                   it.ctypes.data_as(C.POINTER(C.c_int64)),
                                                   ms.ctypes.data_as(C.POINTER(C.c_double)), C.byref(n)))

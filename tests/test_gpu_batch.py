@@ -102,3 +102,29 @@ def test_batch_shared_points_terms_and_autograd(Q):
     (Et * wts).sum().backward()
     torch.testing.assert_close(gt.grad, (wts[:, :, None] * dg).sum(0))
     torch.testing.assert_close(bt.grad, (wts[:, :, None] * db).sum(0))
+
+
+def test_kernel_times_of_many_classes(Q):
+    # sparse random graphs of up to six neighbours a node: cones of some hundred sizes, inner qubits and
+    # forms, a timed group each; every (orbit, point) is in one of them
+    inst = []
+    for seed in range(40):
+        rng = np.random.default_rng(seed)
+        e, deg = set(), np.zeros(80, int)
+        while len(e) < 100:
+            a, b = sorted(int(x) for x in rng.choice(80, 2, replace=False))
+            if deg[a] < 6 and deg[b] < 6 and (a, b) not in e:
+                e.add((a, b))
+                deg[a] += 1
+                deg[b] += 1
+        try:
+            Q.Plan(80, sorted(e), p=2)
+        except Q.QaoaError:   # a cone of more than 30 qubits
+            continue
+        inst.append((80, sorted(e)))
+    ga, be = W.draw_angles(2, 2, 150)
+    pl = Q.Plan.batch(inst, 2, profile=True)
+    pl.energy_grad(dev(ga), dev(be))
+    times = pl.kernel_times()
+    assert len(times) > 64 and all(ms > 0 for _, _, ms in times)
+    assert sum(items for k, items, _ in times if k > 0) == 2 * pl.n_orbits
