@@ -1017,9 +1017,10 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     const size_t o_ewd = hp.realw ? place(std::max<size_t>(ewd.size(), 1) * sizeof(double)) : 0;
     const size_t o_dc = d1 ? place(dc.size() * sizeof(ConeD1)) : 0;
     const size_t o_dw = d1 ? place(dw.size() * sizeof(double2)) : 0;
-    for (size_t i = 0; i < wh.groups.size(); ++i) {   // their cut tables
-        const auto at = std::find_if(cd.begin(), cd.end(), [&](const ConeDev& d) { return d.orbit == wh.rep[i]; });
-        wh.groups[i].cut_off = at->cut_off;
+    if (!wh.groups.empty()) {   // their representatives' cut tables
+        std::vector<int64_t> cut_of(static_cast<size_t>(Mall), 0);
+        for (const ConeDev& d : cd) cut_of[static_cast<size_t>(d.orbit)] = d.cut_off;
+        for (GroupWh& g : wh.groups) g.cut_off = cut_of[static_cast<size_t>(g.rep)];
     }
     const bool has_wh = !wh.groups.empty();
     const size_t o_wg = has_wh ? place(wh.groups.size() * sizeof(GroupWh)) : 0;
