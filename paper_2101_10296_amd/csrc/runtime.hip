@@ -332,7 +332,6 @@ void build_whole(qaoa_plan_s* P, WholeHost& w) {
         g.cut_row = hp.realw ? 0 : c.cut_min - hp.cut_min;
         g.cut_range = range;
         g.mid = static_cast<float>(0.5 * (range - 1));
-        g.c0 = static_cast<float>(0.5 * (c.cf_min + c.cf_max));
         double most = 0.0;
         for (size_t q = static_cast<size_t>(g.mem_off); q < w.mem.size(); ++q) most = std::max(most, std::fabs(w.mem[q].W));
         const int unit = most > 0.0 ? std::ilogb(most) : 0;

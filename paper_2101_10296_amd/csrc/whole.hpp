@@ -21,7 +21,6 @@ struct GroupWh {
     int32_t cut_row;            // phase row index of table value 0: cut_min of the cone - cut_min of the plan
     int32_t cut_range;          // phases of the cone
     float mid;                  // centre of the cut values, relative to table value 0
-    float c0;                   // real weights: centre subtracted in the cut table
 };
 
 struct MemWh {

@@ -469,7 +469,9 @@ __global__ void __launch_bounds__((Wz<K>::WG)) k_whole(WhArgs a) {
             b += w * wxsum<Z, T>(f, lam, sg);
             wmix<Z, T>(f, -t, sg);
             wmix<Z, T>(lam, -t, sg);
-            // gamma of the layer; both states carry 1 / mu, which the undone phase takes back
+            // gamma of the layer, from cut values less a constant (integers: their centre; real ones: the
+            // table's): Im <lambda|psi> = Im <psi|V|psi> = 0 at every layer, V being real.  Both states
+            // carry 1 / mu, which the undone phase takes back
             const float mu = ml[l].y;
             float ga = 0.f;
 #pragma unroll
