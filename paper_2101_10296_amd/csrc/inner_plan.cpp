@@ -1,13 +1,14 @@
 // Host planning of cones evaluated on their inner qubits (inner_plan.hpp).
 #include "inner_plan.hpp"
 
+#include "pool.hpp"
+
 #include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <new>
-#include <system_error>
 #include <thread>
 
 namespace qaoa {
@@ -517,16 +518,12 @@ void ShellPlanner::add(const std::vector<const Cone*>& cones, std::vector<ShellC
             no_mem = true;
         }
     };
-    std::vector<std::thread> pool;
+    Pool pool;
     size_t started = 1;
-    try {
-        for (; started < nt; ++started) pool.emplace_back(work, started);
-    } catch (const std::system_error&) {
-        // no more threads: the remaining ranges run here
-    }
-    for (size_t t = started; t < nt; ++t) work(t);
+    while (started < nt && pool.start(work, started)) ++started;
+    for (size_t t = started; t < nt; ++t) work(t);   // no more threads: the remaining ranges run here
     work(0);
-    for (auto& t : pool) t.join();
+    pool.join();
     if (no_mem) throw std::bad_alloc();
     for (size_t t = 0; t < nt; ++t) {   // shapes and couplings of the parts, in order
         const int64_t e0 = static_cast<int64_t>(ea.size());
@@ -570,14 +567,10 @@ void ShellPlanner::list() {
     };
     // (a thread takes some 30 us to start)
     const size_t nt = std::min<size_t>({8, std::max(1u, std::thread::hardware_concurrency()), todo.size() / 64 + 1});
-    std::vector<std::thread> pool;
-    try {
-        for (size_t t = 1; t < nt; ++t) pool.emplace_back(work);
-    } catch (const std::system_error&) {
-        // no more threads: the rest runs here
-    }
+    Pool pool;
+    for (size_t t = 1; t < nt && pool.start(work); ++t) {}   // what they do not take runs here
     work();
-    for (auto& t : pool) t.join();
+    pool.join();
     if (no_mem) throw std::bad_alloc();
 }
 

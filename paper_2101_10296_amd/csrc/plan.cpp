@@ -12,12 +12,13 @@
 //    by (distance, node id); every edge induced on the ball is a cone edge
 #include "plan.hpp"
 
+#include "pool.hpp"
+
 #include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
 #include <numeric>
-#include <system_error>
 #include <thread>
 
 namespace qaoa {
@@ -340,19 +341,12 @@ void build_host_plan(int32_t n, int64_t m, const int32_t* eu, const int32_t* ev,
     if (nt == 1) {
         extract(0);
     } else {
-        std::vector<std::thread> pool;
+        Pool pool;
         int64_t started = 1;
-        try {
-            for (int64_t t = 1; t < nt; ++t) {
-                pool.emplace_back(extract, t);
-                started = t + 1;
-            }
-        } catch (const std::system_error&) {
-            // no more threads: the remaining ranges run here
-        }
-        for (int64_t t = started; t < nt; ++t) extract(t);
+        while (started < nt && pool.start(extract, started)) ++started;
+        for (int64_t t = started; t < nt; ++t) extract(t);   // no more threads: the remaining ranges run here
         extract(0);
-        for (auto& th : pool) th.join();
+        pool.join();
     }
     for (int64_t t = 0; t < nt; ++t)
         if (no_mem[t]) throw std::bad_alloc();
