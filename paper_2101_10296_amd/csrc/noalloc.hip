@@ -104,6 +104,7 @@ qaoa_status run_energy_grad_noalloc(qaoa_plan_s* P, int64_t n_points, const doub
             return QAOA_EHIP;                                          \
         }                                                              \
     } while (0)
+    const Shared sh = shared_states(P, true, false, n_points);   // as qaoa_energy_grad
     for (int64_t i0 = 0; i0 < n_points; i0 += chunk) {
         const int64_t pc = std::min<int64_t>(chunk, n_points - i0);
         if (depth1_closed(P)) {
@@ -127,18 +128,17 @@ qaoa_status run_energy_grad_noalloc(qaoa_plan_s* P, int64_t n_points, const doub
         const EvalArgs ea{static_cast<int32_t>(pc), p, M, R, phase, mix, gamma + static_cast<size_t>(i0) * p,
                           static_cast<int32_t>(n_points), hp.realw ? 1 : 0, zz, g};
         for (const auto& grp : P->in_groups)
-            if (P->opt.tune != 1 && !(grp.wh && whole_used(P, false)))   // a tuned plan holds these cones in lds_groups too
+            if (P->opt.tune != 1 && !sh.of(grp.wh))   // a tuned plan holds these cones in lds_groups too
                 NCHECK(launch_inner_group(P, grp, true, 0, pc, gamma + static_cast<size_t>(i0) * p,
                                           beta + static_cast<size_t>(i0) * p, n_points, zz, g, nullptr, 0, stream));
-        const bool wh = whole_used(P, false);
         for (const auto& grp : P->lds_groups)   // default layout: no tuning runs here
-            NCHECK(launch_fused(grp.K, true, 0, P->d_cones + grp.first, (wh ? grp.n_wh : grp.n_skip) * pc, grp.count * pc, P->d_cut,
+            NCHECK(launch_fused(grp.K, true, 0, P->d_cones + grp.first, (sh.of(wh_class(grp.K)) ? grp.n_wh : grp.n_skip) * pc, grp.count * pc, P->d_cut,
                                 grp.rowcap, ea, stream));
         for (const auto& grp : P->wh_groups)
-            if (wh)
+            if (sh.of(wh_class(grp.K)))
                 NCHECK(launch_whole_group(P, grp, true, pc, gamma + static_cast<size_t>(i0) * p,
                                           beta + static_cast<size_t>(i0) * p, n_points, zz, g, stream));
-        NCHECK(launch_combine(P->d_W, wh ? P->d_Wg : P->d_W, zz, g, M, p, P->d_inst_orbit, P->d_inst_delta, ni, pc, n_points, i0, energy,
+        NCHECK(launch_combine(P->d_W, sh.Wg, zz, g, M, p, P->d_inst_orbit, P->d_inst_delta, ni, pc, n_points, i0, energy,
                               dgamma, dbeta, stream));
     }
 #undef NCHECK

@@ -252,8 +252,7 @@ struct WholeHost {
     std::vector<char> member;    // per orbit; empty: none
     std::vector<GroupWh> groups;
     std::vector<MemWh> mem;
-    std::vector<int64_t> rep;    // representative orbit of each group
-    std::vector<double> Wg;
+    std::vector<double> Wg;      // see qaoa_plan_s::d_Wg
     int64_t obs = 0;             // entries of the observable tables
 };
 
@@ -345,17 +344,23 @@ void build_whole(qaoa_plan_s* P, WholeHost& w) {
         cls.count += 1;
         cls.members += g.n_mem;
         cls.rowcap = std::max(cls.rowcap, range);
-        w.rep.push_back(rep);
         w.groups.push_back(g);
     }
     if (w.groups.empty()) return;
     w.member.assign(hp.cones.size(), 0);
-    w.Wg = hp.W;
-    for (const MemWh& e : w.mem) {
-        w.member[static_cast<size_t>(e.orbit)] = 1;
-        w.Wg[static_cast<size_t>(e.orbit)] = 0.0;
+    for (const MemWh& e : w.mem) w.member[static_cast<size_t>(e.orbit)] = 1;
+    for (int sel = 0; sel < (P->wh_groups.back().K > 12 ? 4 : 1); ++sel) {
+        w.Wg.insert(w.Wg.end(), hp.W.begin(), hp.W.end());
+        double* Wg = w.Wg.data() + static_cast<size_t>(sel) * hp.W.size();
+        for (const auto& cls : P->wh_groups) {
+            if (cls.K > 12 && !((sel >> (cls.K - 13)) & 1)) continue;
+            for (int64_t i = cls.first; i < cls.first + cls.count; ++i) {
+                const GroupWh& g = w.groups[static_cast<size_t>(i)];
+                for (int32_t m = g.mem_off; m < g.mem_off + g.n_mem; ++m) Wg[w.mem[static_cast<size_t>(m)].orbit] = 0.0;
+                Wg[g.rep] = 1.0;
+            }
+        }
     }
-    for (int64_t r : w.rep) w.Wg[static_cast<size_t>(r)] = 1.0;
 }
 
 // Descriptors of the cones evaluated on their inner qubits (inner.hpp).
@@ -429,7 +434,9 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
     P->in_max_k = 0;   // build_wide adds its own
     P->wz = 0;
     if (ord.empty()) return;
-    auto is_wh = [&](int64_t m) { return !member.empty() && member[static_cast<size_t>(m)] != 0; };
+    auto wh_of = [&](int64_t m) {
+        return !member.empty() && member[static_cast<size_t>(m)] != 0 ? wh_class(hp.cones[static_cast<size_t>(m)].k) : 0;
+    };
     in.cones.reserve(ord.size());
     ShellPlanner shells(p, p == 2, hp.realw);
     std::vector<ShellCone> sc;
@@ -442,7 +449,8 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         for (size_t i = 0; i < by.size(); ++i) {
             const ShellCone& q = raw[i];
             const uint32_t k = by_k ? static_cast<uint32_t>(list_of[i]->k) : 0u;
-            by[i] = {static_cast<uint32_t>(q.kin) << 9 | k << 3 | (is_wh(ord[i]) ? 4u : 0u) | (q.tree ? 2u : 0u) | (q.zmask ? 1u : 0u),
+            by[i] = {static_cast<uint32_t>(q.kin) << 12 | k << 6 | static_cast<uint32_t>(wh_of(ord[i])) << 2 | (q.tree ? 2u : 0u) |
+                         (q.zmask ? 1u : 0u),
                      static_cast<int32_t>(i)};
         }
         std::sort(by.begin(), by.end());
@@ -512,7 +520,7 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         return s;
     };
     // a group of in_groups continues where its key does
-    auto group = [&](int kin, int kk, bool wh, bool tree, bool signs, int64_t first) -> qaoa_plan_s::InGroup& {
+    auto group = [&](int kin, int kk, int wh, bool tree, bool signs, int64_t first) -> qaoa_plan_s::InGroup& {
         if (P->in_groups.empty() || P->in_groups.back().kin != kin || P->in_groups.back().K != kk ||
             P->in_groups.back().wh != wh || P->in_groups.back().tree != tree || P->in_groups.back().signs != signs) {
             qaoa_plan_s::InGroup g{};
@@ -539,7 +547,7 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
             edge.w = q.w_uv;
             if (!hp.realw && std::abs(q.w_uv) <= 3.0) edge.code = static_cast<int16_t>((static_cast<int>(q.w_uv) + 3) * 343);
             d.edge = branch_type(edge);
-            qaoa_plan_s::InGroup& g = group(0, by_k ? c.k : 0, is_wh(m), true, false, static_cast<int64_t>(in.tr.size()));
+            qaoa_plan_s::InGroup& g = group(0, by_k ? c.k : 0, wh_of(m), true, false, static_cast<int64_t>(in.tr.size()));
             g.count += 1;
             P->in_max_k = std::max(P->in_max_k, c.k);
             P->tr_inst.push_back(c.inst);
@@ -594,7 +602,7 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         d.edge_off = static_cast<int32_t>(edge0 + q.edge);
         d.n_edges = q.n_edges;
         const int kk = by_k ? c.k : 0;
-        group(q.kin, kk, is_wh(m), false, q.zmask != 0, static_cast<int64_t>(in.cones.size())).count += 1;
+        group(q.kin, kk, wh_of(m), false, q.zmask != 0, static_cast<int64_t>(in.cones.size())).count += 1;
         P->in_max_k = std::max(P->in_max_k, c.k);
         P->in_inst.push_back(c.inst);
         in.cones.push_back(d);
@@ -1206,6 +1214,31 @@ struct GroupTimer {
 
 }  // namespace
 
+// The gradient of a shared state of 14 qubits spills (about 1 KB a thread), and a point of its group
+// occupies a compute unit for as long as several members' own states do: c times as long.  It is taken
+// where the members would fill the chip c times as often.  Measured (us, energy and gradient of
+// three members, shared and on their own): p = 2, 1, 256 and 4096 points 38 and 18, 61 and 49, 840 and
+// 693; p = 5 78 and 51, 148 and 153, 2051 and 2318; real weights, p = 2, 49 and 30, 77 and 113.  13
+// qubits at p = 2: 20 and 15 while the members fill it once, 20 and 28 when twice.  Up to 12
+// qubits, and for energies alone, it is never behind (12 qubits, p = 2: 13 and 14, 1 point; 101 and 275).
+Shared shared_states(const qaoa_plan_s* P, bool grad, bool terms_read, int64_t n_points) {
+    Shared s;
+    s.Wg = P->d_W;
+    if (P->wh_groups.empty() || terms_read) return s;
+    auto fills = [&](int64_t n) { return (n * n_points + 255) / 256; };
+    int sel = 0;
+    for (const auto& cls : P->wh_groups) {
+        int64_t c = 1;
+        if (grad && cls.K == 14) c = P->hp.realw ? 2 : P->hp.p <= 3 ? 4 : 3;
+        if (grad && cls.K == 13 && P->hp.p == 2) c = 2;
+        if (fills(cls.members) < c * fills(cls.count)) continue;
+        s.on[wh_class(cls.K) - 12] = true;
+        if (cls.K > 12) sel |= 1 << (cls.K - 13);
+    }
+    s.Wg = P->d_Wg + static_cast<size_t>(sel) * P->hp.W.size();
+    return s;
+}
+
 hipError_t launch_whole_group(const qaoa_plan_s* P, const qaoa_plan_s::WhGroup& grp, bool grad, int64_t n_points,
                               const double* gamma, const double* beta, int64_t gamma_P, double* zz, double* g,
                               hipStream_t st) {
@@ -1460,7 +1493,7 @@ size_t part_limit(const qaoa_plan_s* P) {
 }
 
 // First cone of a size class that the kernel for whole cones runs.
-int64_t lds_from(const qaoa_plan_s::Group& grp, bool use_wh) { return use_wh ? grp.n_wh : grp.n_skip; }
+int64_t lds_from(const qaoa_plan_s::Group& grp, const Shared& sh) { return sh.of(wh_class(grp.K)) ? grp.n_wh : grp.n_skip; }
 
 // The launches of a depth-1 call.  One instance of few orbits: terms and weighted sums in one
 // launch (2048 orbits are eight per thread of the point's workgroup; larger plans fill the chip
@@ -1663,10 +1696,10 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         }
     }
     const size_t npl = static_cast<size_t>(hp.n_inst) * n_points * p;   // (instance, point, layer) rows
-    const bool use_wh = whole_used(P, grad && term_grad);
+    const Shared sh = shared_states(P, grad, grad && term_grad, n_points);
     // phase and mixer tables, for the kernels that read them
     bool tables = !P->hbm_groups.empty();
-    for (const auto& grp : P->lds_groups) tables = tables || lds_from(grp, use_wh) < grp.count;
+    for (const auto& grp : P->lds_groups) tables = tables || lds_from(grp, sh) < grp.count;
     if (tables) {
         if ((st = grow(P->d_phase, P->cap_phase, npl * R, msg)) != QAOA_OK) return st;
         if ((st = grow(P->d_mix, P->cap_mix, npl, msg)) != QAOA_OK) return st;
@@ -1700,7 +1733,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         for (size_t i = 0; i < P->in_groups.size() && mix.n < IN_CLASSES; ++i) {
             const auto& grp = P->in_groups[i];
             const int64_t units = grp.count * grp.chunks;
-            if (grp.tree || (grp.wh && use_wh) || units * n_points > IN_MIX ||
+            if (grp.tree || sh.of(grp.wh) || units * n_points > IN_MIX ||
                 (grp.chunks > 1 && parts + units * n_points * static_cast<int64_t>(nv) > static_cast<int64_t>(part_most)))
                 continue;
             InMix::Class& c = mix_class(P, grp, mix);
@@ -1753,7 +1786,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         QCHECK(launch_inner_mix_sum(a, mix, grad, stream));
     }
     for (const auto& grp : P->in_groups) {
-        if ((grp.wh && use_wh) || mixed[static_cast<size_t>(&grp - P->in_groups.data())]) continue;
+        if (sh.of(grp.wh) || mixed[static_cast<size_t>(&grp - P->in_groups.data())]) continue;
         if (P->opt.tune == 1 && grp.K <= P->opt.k_lds_max) continue;   // with the other cones of its size, below
         int j = inner_upw(grp, n_points);
         if (P->opt.tune == 1) {
@@ -1772,17 +1805,17 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         st = enqueue_wide(P, grad, n_points, gamma, beta, zz, g, tm, stream, msg);
         if (st != QAOA_OK) return st;
     }
-    if (use_wh)
-        for (const auto& grp : P->wh_groups) {
-            QCHECK(tm.begin(grp.K, grp.members * n_points));
-            QCHECK(launch_whole_group(P, grp, grad, n_points, gamma, beta, n_points, zz, g, stream));
-            QCHECK(tm.end());
-        }
+    for (const auto& grp : P->wh_groups) {
+        if (!sh.of(wh_class(grp.K))) continue;
+        QCHECK(tm.begin(grp.K, grp.members * n_points));
+        QCHECK(launch_whole_group(P, grp, grad, n_points, gamma, beta, n_points, zz, g, stream));
+        QCHECK(tm.end());
+    }
     // the first n items of one cone size in layout v; the default (0) takes the cones with a shell, which
     // come first, on their inner qubits (tune = 1 plans hold them in both forms): of n items all of these
     // cones at the first points, where the other layouts take the first cones at all points
     auto run_size = [&](const qaoa_plan_s::Group& grp, int v, int64_t n) {
-        int64_t done = lds_from(grp, use_wh) * n_points;
+        int64_t done = lds_from(grp, sh) * n_points;
         if (v == 0 && grp.n_in > 0) {
             const int64_t points = std::min(n_points, n / grp.n_in);
             for (const auto& ig : P->in_groups)
@@ -1798,7 +1831,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
     for (const auto& grp : P->lds_groups) {
         const ConeDev* cones = P->d_cones + grp.first;
         const int64_t items = grp.count * n_points;
-        if (lds_from(grp, use_wh) >= grp.count) continue;
+        if (lds_from(grp, sh) >= grp.count) continue;
         int variant = P->opt.tune >= 2 ? P->opt.tune - 2 : 0;   // tune 2, 3, 4: a fixed layout variant
         if (P->opt.tune == 1 && !P->opt.one_cone_at_a_time) {
             std::string form;   // of the size's cones: those on their inner qubits, "+" others
@@ -1820,9 +1853,9 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
                 }
             }
         }
-        QCHECK(tm.begin(grp.K, items - lds_from(grp, use_wh) * n_points));
+        QCHECK(tm.begin(grp.K, items - lds_from(grp, sh) * n_points));
         if (P->opt.one_cone_at_a_time) {
-            for (int64_t it = lds_from(grp, use_wh) * n_points; it < items; ++it)
+            for (int64_t it = lds_from(grp, sh) * n_points; it < items; ++it)
                 QCHECK(launch_fused(grp.K, grad, 0, cones, it, it + 1, P->d_cut, grp.rowcap, ea, stream));
         } else {
             QCHECK(run_size(grp, variant, items));
@@ -1983,8 +2016,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         }
         QCHECK(tm.end());
     }
-    return finish_sums(P, n_points, zz, g, energy, dgamma, dbeta, grad && term_grad, use_wh ? P->d_Wg : P->d_W, tm, stream,
-                       msg);
+    return finish_sums(P, n_points, zz, g, energy, dgamma, dbeta, grad && term_grad, sh.Wg, tm, stream, msg);
 }
 
 void drop_graph(qaoa_plan_s* P) {

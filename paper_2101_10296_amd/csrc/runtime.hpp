@@ -47,7 +47,7 @@ struct qaoa_plan_s {
     // launches are timed per cone size: profile, tune = 1)
     struct InGroup {
         int kin, K;         // inner qubits; cone qubits, or 0
-        bool wh;            // cones that are members of wh_groups
+        int wh;             // cones that are members of wh_groups: wh_class of their size; else 0
         bool signs;         // cones with leaves (shell.hpp)
         bool tree;          // closed form (depth2.hip): from d_tr + first on, one unit per cone
         int64_t first, count;
@@ -106,7 +106,9 @@ struct qaoa_plan_s {
     qaoa::GroupWh* d_wh = nullptr;
     qaoa::MemWh* d_whmem = nullptr;
     double* d_whobs = nullptr;
-    double* d_Wg = nullptr;             // orbit weights of the gradient sums: 1 at a group's column
+    // orbit weights of the gradient sums, for every choice of classes that share their states (bit 0: 13
+    // qubits, bit 1: 14; up to 12 always): 1 at a sharing group's column, 0 at its other members
+    double* d_Wg = nullptr;
     // HBM-resident cones, grouped by k
     struct HGroup {
         int K;
@@ -209,10 +211,16 @@ inline bool wide_cone(const qaoa_plan_s* P, const Cone& c) {
            c.nd[p - 1] <= WD_KMAX && c.nd[p - 2] <= WD_NEXT && c.nd[p - 1] < c.k;
 }
 
-// Whether a call may evaluate the groups of wh_groups on their shared state.
-inline bool whole_used(const qaoa_plan_s* P, bool terms_read) {
-    return !P->wh_groups.empty() && !terms_read;
-}
+// Sizes of shared states with a line of their own.
+inline int wh_class(int K) { return K <= 12 ? 12 : K; }
+
+// Which groups of wh_groups a call evaluates on their shared state.
+struct Shared {
+    bool on[3] = {};         // wh_class 12, 13, 14
+    const double* Wg;        // weights of the gradient sums
+    bool of(int cls) const { return cls != 0 && on[cls - 12]; }   // cls: wh_class, or 0
+};
+Shared shared_states(const qaoa_plan_s* P, bool grad, bool terms_read, int64_t n_points);
 hipError_t launch_whole_group(const qaoa_plan_s* P, const qaoa_plan_s::WhGroup& grp, bool grad, int64_t n_points,
                               const double* gamma, const double* beta, int64_t gamma_P, double* zz, double* g,
                               hipStream_t st);

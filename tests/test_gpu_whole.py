@@ -139,3 +139,24 @@ def test_first_call_of_many_groups_is_linear(Q):
 
     first(100)
     assert first(20000) <= 8 * first(5000)   # 5.4 measured; 13.6 with a search of all cones for each group
+
+
+@pytest.mark.parametrize("few", [False, True])
+def test_own_or_shared_by_size_and_items(Q, few):
+    # 12, 13 and 14 qubits in one plan: which sizes share their states in a gradient call depends on members
+    # and points (13: two fills of the chip, 14 at p = 2: four); the sums against the terms' own forms
+    gs = [W.circulant(n, (1, 2, 3)) for n in (12, 13, 14)]
+    gens = [None, gs[1].gens() if few else None, None]   # few: three members of 13 qubits
+    pl = Q.Plan.batch([(g.n, g.edges, None, x) for g, x in zip(gs, gens)], 2)
+    for P in (1, 8, 32):
+        ga, be = W.draw_angles(P, 2, 960 + P)
+        E, dg, db = pl.energy_grad(dev(ga), dev(be))
+        E2, dg2, db2, zz, tg = pl.energy_grad_terms(dev(ga), dev(be))
+        for j, g in enumerate(gs):
+            assert (E[j] - E2[j]).abs().max().item() <= ZZ_TOL * g.m / 2
+            scale = max(dg2[j].abs().max().item(), db2[j].abs().max().item(), 1e-3 * g.m)
+            assert max((dg[j] - dg2[j]).abs().max().item(), (db[j] - db2[j]).abs().max().item()) <= 1e-4 * scale
+        own = [Q.Plan(g.n, g.edges, p=2, generators=x, tune=2).energy_grad(dev(ga), dev(be)) for g, x in zip(gs, gens)]
+        for j, (g, o) in enumerate(zip(gs, own)):
+            scale = max(o[1].abs().max().item(), o[2].abs().max().item(), 1e-3 * g.m)
+            assert max((dg[j] - o[1]).abs().max().item(), (db[j] - o[2]).abs().max().item()) <= 1e-4 * scale
