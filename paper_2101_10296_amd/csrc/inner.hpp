@@ -126,6 +126,13 @@ struct InPoint {
 // cones of one instance, all with listed configurations; a: cones of the plan, zz and g or null
 hipError_t launch_inner_point(const InArgs& a, const D2Args& d, const InPoint& q, bool grad, int64_t n_points, hipStream_t st);
 
+// Workgroups (four units of a class) of a call's small cones, 10 qubits at most, from which these run
+// whole, near the crossings for graphs of 9 to 16 nodes.  us per call, inner and whole: 12 nodes with 15
+// orbits, p = 2 (6 workgroups a point; with the gradient 5) 1024 points 32 and 44, 64 and 61; 2048
+// points 56 and 47, 117 and 71; a path of 13 nodes, p = 3 (4) 1024 points 31 and 37, 95 and 59; 2048
+// points 58 and 38, 187 and 64; p = 5 (3) 1024 points 76 and 94, 251 and 210; 4096 points 292 and 175,
+// 992 and 532.
+constexpr int64_t in_small(int p, bool grad) { return p == 2 ? (grad ? 13 << 9 : 12 << 10) : (grad ? 4 << 10 : 11 << 9); }
 // Several classes in one launch (inner_mix.hip), one unit per wave
 constexpr int IN_CLASSES = 16;
 // Units of a class (over a call's points) that may join: measured faster up to there (16 points of a

@@ -104,7 +104,8 @@ qaoa_status run_energy_grad_noalloc(qaoa_plan_s* P, int64_t n_points, const doub
             return QAOA_EHIP;                                          \
         }                                                              \
     } while (0)
-    const Shared sh = shared_states(P, true, false, n_points);   // as qaoa_energy_grad
+    const Forms forms = choose_forms(P, true, false, n_points);   // as qaoa_energy_grad
+    const Shared& sh = forms.sh;
     for (int64_t i0 = 0; i0 < n_points; i0 += chunk) {
         const int64_t pc = std::min<int64_t>(chunk, n_points - i0);
         if (depth1_closed(P)) {
@@ -127,13 +128,17 @@ qaoa_status run_energy_grad_noalloc(qaoa_plan_s* P, int64_t n_points, const doub
         // instance's block of n_points
         const EvalArgs ea{static_cast<int32_t>(pc), p, M, R, phase, mix, gamma + static_cast<size_t>(i0) * p,
                           static_cast<int32_t>(n_points), hp.realw ? 1 : 0, zz, g};
-        for (const auto& grp : P->in_groups)
+        for (const auto& grp : *forms.in)
             if (P->opt.tune != 1 && !sh.of(grp.wh))   // a tuned plan holds these cones in lds_groups too
                 NCHECK(launch_inner_group(P, grp, true, 0, pc, gamma + static_cast<size_t>(i0) * p,
                                           beta + static_cast<size_t>(i0) * p, n_points, zz, g, nullptr, 0, stream));
-        for (const auto& grp : P->lds_groups)   // default layout: no tuning runs here
-            NCHECK(launch_fused(grp.K, true, 0, P->d_cones + grp.first, (sh.of(wh_class(grp.K)) ? grp.n_wh : grp.n_skip) * pc, grp.count * pc, P->d_cut,
-                                grp.rowcap, ea, stream));
+        for (const auto& grp : P->lds_groups) {   // default layout: no tuning runs here
+            int64_t span[2][2];
+            const int n_runs = forms.runs(grp, span);
+            for (int r = 0; r < n_runs; ++r)
+                NCHECK(launch_fused(grp.K, true, 0, P->d_cones + grp.first, span[r][0] * pc, span[r][1] * pc, P->d_cut,
+                                    grp.rowcap, ea, stream));
+        }
         for (const auto& grp : P->wh_groups)
             if (sh.of(wh_class(grp.K)))
                 NCHECK(launch_whole_group(P, grp, true, pc, gamma + static_cast<size_t>(i0) * p,

@@ -376,7 +376,15 @@ struct InnerHost {
     std::vector<D2Type> types;
     std::vector<D2Leaf> leaf2;
     int64_t tab_units = 0;   // table bytes / 16
+    std::vector<char> band;  // in_band of every orbit
 };
+
+// Configurations that a wave runs at once, and the rounds of them that a cone takes.
+uint32_t shell_at_once(const ShellCone& q) { return 64u >> std::max(0, q.kin - 4); }
+uint32_t shell_rounds(const ShellPlanner& sp, const ShellCone& q) {
+    const std::vector<ShellCfg>* list = sp.configurations(q.shape);
+    return ((list ? static_cast<uint32_t>(list->size()) : q.runs()) + shell_at_once(q) - 1) / shell_at_once(q);
+}
 
 // Mixed prefixes and cut ranges of every layer: base = phase row index of the smallest cut value of the
 // couplings inside the qubits mixed by layer l - 1, mid = centre of the layer's cut values in
@@ -429,10 +437,15 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
     const int32_t p = hp.p;
     const bool by_k = P->opt.profile || P->opt.tune == 1;
     P->in_groups.clear();
+    P->in_bands.clear();
+    for (auto& list : P->in_rest) list.clear();
+    P->in_serial.clear();
+    P->n_in_cones = 0;
     P->in_inst.clear();
     P->tr_inst.clear();
     P->in_max_k = 0;   // build_wide adds its own
     P->wz = 0;
+    in.band.assign(hp.cones.size(), 0);
     if (ord.empty()) return;
     auto wh_of = [&](int64_t m) {
         return !member.empty() && member[static_cast<size_t>(m)] != 0 ? wh_class(hp.cones[static_cast<size_t>(m)].k) : 0;
@@ -445,12 +458,25 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         for (size_t i = 0; i < ord.size(); ++i) list_of[i] = &hp.cones[static_cast<size_t>(ord[i])];
         std::vector<ShellCone> raw;
         shells.add(list_of, raw);
+        shells.list();
         std::vector<std::pair<uint32_t, int32_t>> by(ord.size());   // class, place in ord
         for (size_t i = 0; i < by.size(); ++i) {
             const ShellCone& q = raw[i];
-            const uint32_t k = by_k ? static_cast<uint32_t>(list_of[i]->k) : 0u;
-            by[i] = {static_cast<uint32_t>(q.kin) << 12 | k << 6 | static_cast<uint32_t>(wh_of(ord[i])) << 2 | (q.tree ? 2u : 0u) |
-                         (q.zmask ? 1u : 0u),
+            const Cone& c = *list_of[i];
+            const uint32_t k = by_k ? static_cast<uint32_t>(c.k) : 0u, wh = static_cast<uint32_t>(wh_of(ord[i]));
+            const uint32_t rounds = q.tree ? 0u : shell_rounds(shells, q);
+            const int band = in_band(P, c, q.tree, rounds);
+            in.band[static_cast<size_t>(ord[i])] = static_cast<char>(band);
+            if (band) {
+                auto& all = P->in_bands;
+                auto at = std::find_if(all.begin(), all.end(), [&](const qaoa_plan_s::Band& b) {
+                    return b.K == c.k && b.wh == static_cast<int>(wh);
+                });
+                if (at == all.end()) at = all.insert(all.end(), {band, static_cast<int>(wh), c.k, 0, 0});
+                at->count += 1;
+                at->rounds = std::max(at->rounds, static_cast<int32_t>(rounds));
+            }
+            by[i] = {static_cast<uint32_t>(q.kin) << 12 | k << 6 | wh << 2 | (q.tree ? 2u : 0u) | (q.zmask ? 1u : 0u),
                      static_cast<int32_t>(i)};
         }
         std::sort(by.begin(), by.end());
@@ -462,7 +488,6 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         }
         ord.swap(sorted);
     }
-    shells.list();
     const int64_t edge0 = static_cast<int64_t>(ea.size());
     ea.insert(ea.end(), shells.ea.begin(), shells.ea.end());
     eb.insert(eb.end(), shells.eb.begin(), shells.eb.end());
@@ -520,22 +545,13 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         return s;
     };
     // a group of in_groups continues where its key does
-    auto group = [&](int kin, int kk, int wh, bool tree, bool signs, int64_t first) -> qaoa_plan_s::InGroup& {
-        if (P->in_groups.empty() || P->in_groups.back().kin != kin || P->in_groups.back().K != kk ||
-            P->in_groups.back().wh != wh || P->in_groups.back().tree != tree || P->in_groups.back().signs != signs) {
-            qaoa_plan_s::InGroup g{};
-            g.kin = kin;
-            g.K = kk;
-            g.wh = wh;
-            g.tree = tree;
-            g.signs = signs;
-            g.first = first;
-            P->in_groups.push_back(g);
-        }
+    auto group = [&](const qaoa_plan_s::InGroup& want) -> qaoa_plan_s::InGroup& {
+        auto key = [](const qaoa_plan_s::InGroup& g) { return std::tie(g.kin, g.K, g.wh, g.tree, g.signs); };
+        if (P->in_groups.empty() || key(P->in_groups.back()) != key(want)) P->in_groups.push_back(want);
         return P->in_groups.back();
     };
     std::vector<int32_t> listed_at;   // first entry of each shape's list, -1: not placed yet
-    std::vector<uint32_t> rounds;
+    std::vector<uint32_t> rounds;     // of in.cones
     rounds.reserve(ord.size());
     for (size_t i = 0; i < ord.size(); ++i) {
         const int64_t m = ord[i];
@@ -547,14 +563,18 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
             edge.w = q.w_uv;
             if (!hp.realw && std::abs(q.w_uv) <= 3.0) edge.code = static_cast<int16_t>((static_cast<int>(q.w_uv) + 3) * 343);
             d.edge = branch_type(edge);
-            qaoa_plan_s::InGroup& g = group(0, by_k ? c.k : 0, wh_of(m), true, false, static_cast<int64_t>(in.tr.size()));
-            g.count += 1;
+            qaoa_plan_s::InGroup want{};
+            want.K = by_k ? c.k : 0;
+            want.wh = wh_of(m);
+            want.tree = true;
+            want.first = static_cast<int64_t>(in.tr.size());
+            group(want).count += 1;
             P->in_max_k = std::max(P->in_max_k, c.k);
             P->tr_inst.push_back(c.inst);
             in.tr.push_back(d);
             continue;
         }
-        const uint32_t cpw = 64u >> std::max(0, q.kin - 4);
+        const uint32_t cpw = shell_at_once(q);
         ConeIn d{};
         d.orbit = static_cast<int32_t>(m);
         d.inst = c.inst;
@@ -601,31 +621,20 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         in.tab_units += (p - 1) * std::max<int64_t>(1, (int64_t{1} << q.kin) / 16);
         d.edge_off = static_cast<int32_t>(edge0 + q.edge);
         d.n_edges = q.n_edges;
-        const int kk = by_k ? c.k : 0;
-        group(q.kin, kk, wh_of(m), false, q.zmask != 0, static_cast<int64_t>(in.cones.size())).count += 1;
+        qaoa_plan_s::InGroup want{};
+        want.kin = q.kin;
+        want.K = by_k ? c.k : 0;
+        want.wh = wh_of(m);
+        want.signs = q.zmask != 0;
+        want.first = static_cast<int64_t>(in.cones.size());
+        group(want).count += 1;
         P->in_max_k = std::max(P->in_max_k, c.k);
         P->in_inst.push_back(c.inst);
         in.cones.push_back(d);
     }
-    for (auto& g : P->in_groups) {
-        // Units of work: a cone's rounds in parts of 8, of 2 where that leaves a point with fewer than
-        // 1024 units (latency: the 18-qubit cone of a torus at 32 points 42 -> 24 us), at most 2^15
-        // of them.  Set by the plan alone, so that a term's sum is the same whatever the number of
-        // points.  Classes of cones that fit the allocation-free call (k_lds_max qubits: 16
-        // rounds at most) stay whole, as parts need room for their sums.
-        uint32_t most = 1;
-        int32_t max_k = 0;
-        for (int64_t i = g.first; i < g.first + g.count && !g.tree; ++i) {
-            most = std::max(most, rounds[static_cast<size_t>(i)]);
-            max_k = std::max(max_k, hp.cones[static_cast<size_t>(in.cones[static_cast<size_t>(i)].orbit)].k);
-        }
-        int64_t ch = 1;
-        if (max_k > P->opt.k_lds_max) {
-            ch = (most + IN_ROUNDS - 1) / IN_ROUNDS;
-            if (ch * g.count < 1024) ch = std::min<int64_t>((most + 1) / 2, std::max<int64_t>(ch, 1024 / g.count));
-        }
-        ch = std::min(ch, std::max<int64_t>(1, (int64_t{1} << 15) / g.count));
-        g.chunks = static_cast<int32_t>(ch);
+    // workgroups and segments of a class whose units are set
+    auto place = [&](qaoa_plan_s::InGroup& g) {
+        const int64_t ch = g.chunks;
         std::vector<int32_t> unit{0}, inst;   // segments of one instance
         for (int64_t i = 0; i < g.count; ++i) {
             const int32_t j = (g.tree ? P->tr_inst : P->in_inst)[static_cast<size_t>(g.first + i)];
@@ -653,6 +662,75 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
                 in.seg.insert(in.seg.end(), inst.begin(), inst.end());
             }
         }
+    };
+    for (auto& g : P->in_groups) {
+        // Units of work: a cone's rounds in parts of 8, of 2 where that leaves a point with fewer than
+        // 1024 units (latency: the 18-qubit cone of a torus at 32 points 42 -> 24 us), at most 2^15
+        // of them.  Set by the plan alone, so that a term's sum is the same whatever the number of
+        // points.  Classes of cones that fit the allocation-free call (k_lds_max qubits: 16
+        // rounds at most) stay whole, as parts need room for their sums.
+        uint32_t most = 1;
+        int32_t max_k = 0;
+        for (int64_t i = g.first; i < g.first + g.count && !g.tree; ++i) {
+            most = std::max(most, rounds[static_cast<size_t>(i)]);
+            max_k = std::max(max_k, hp.cones[static_cast<size_t>(in.cones[static_cast<size_t>(i)].orbit)].k);
+        }
+        int64_t ch = 1;
+        if (max_k > P->opt.k_lds_max) {
+            ch = (most + IN_ROUNDS - 1) / IN_ROUNDS;
+            if (ch * g.count < 1024) ch = std::min<int64_t>((most + 1) / 2, std::max<int64_t>(ch, 1024 / g.count));
+        }
+        ch = std::min(ch, std::max<int64_t>(1, (int64_t{1} << 15) / g.count));
+        g.chunks = static_cast<int32_t>(ch);
+        place(g);
+        for (int64_t i = g.first; i < g.first + g.count && !g.tree; ++i)
+            if (in.band[static_cast<size_t>(in.cones[static_cast<size_t>(i)].orbit)] != 3)
+                g.rounds = std::max(g.rounds, static_cast<int32_t>((rounds[static_cast<size_t>(i)] + ch - 1) / ch));
+        for (int j = 0; j < 2 && !g.tree; ++j) {
+            int32_t n = 0;   // of the instance
+            for (int64_t i = g.first; i < g.first + g.count; ++i) {
+                const size_t at = static_cast<size_t>(i);
+                if (i > g.first && P->in_inst[at] != P->in_inst[at - 1]) n = 0;
+                const int band = in.band[static_cast<size_t>(in.cones[at].orbit)];
+                if (band >= 1 && band <= j + 1 && n++ % 4 == 0) g.small[j] += 1;
+            }
+        }
+    }
+    P->n_in_cones = static_cast<int64_t>(in.cones.size());
+    for (const auto& b : P->in_bands)
+        if (b.band == 3 && std::find(P->in_serial.begin(), P->in_serial.end(), b.K) == P->in_serial.end())
+            P->in_serial.push_back(b.K);
+    auto most = [&](int K) {
+        int32_t n = 0;
+        for (const auto& b : P->in_bands) n = std::max(n, b.K == K ? b.rounds : 0);
+        return n;
+    };
+    std::sort(P->in_serial.begin(), P->in_serial.end(), [&](int x, int y) { return std::make_pair(-most(x), x) < std::make_pair(-most(y), y); });
+    for (int rest = 0; rest < 2 + static_cast<int>(P->in_serial.size()) && !P->in_bands.empty(); ++rest) {
+        uint32_t sizes = rest == 0 ? (1u << 10) - 1 : rest == 1 ? (1u << 11) - 1 : 0;   // that leave
+        for (int j = 0; j < rest - 1; ++j) sizes |= 1u << P->in_serial[static_cast<size_t>(j)];
+        for (const auto& all : P->in_groups) {
+            auto stays = [&](int64_t i) {
+                if (all.tree) return true;
+                const size_t m = static_cast<size_t>(in.cones[static_cast<size_t>(i)].orbit);
+                return in.band[m] == 0 || !((sizes >> hp.cones[m].k) & 1u);
+            };
+            qaoa_plan_s::InGroup g = all;
+            g.count = 0;
+            for (int64_t i = all.first; i < all.first + all.count; ++i) g.count += stays(i);
+            if (g.count == 0) continue;
+            if (g.count < all.count) {   // its units are those of the whole class, and so a term's sum
+                g.first = static_cast<int64_t>(in.cones.size());
+                for (int64_t i = all.first; i < all.first + all.count; ++i)
+                    if (stays(i)) {
+                        const ConeIn copy = in.cones[static_cast<size_t>(i)];
+                        in.cones.push_back(copy);
+                        P->in_inst.push_back(P->in_inst[static_cast<size_t>(i)]);
+                    }
+                place(g);
+            }
+            P->in_rest[rest].push_back(g);
+        }
     }
 }
 
@@ -670,7 +748,7 @@ void build_point(qaoa_plan_s* P, const InnerHost& in) {
     P->in_parts = InPointSum{};
     const size_t M = P->hp.cones.size();
     P->d2_point = false;
-    if (P->hp.n_inst != 1 || M > D2_POINT || in.cones.size() + in.tr.size() != M || !P->wh_groups.empty() || P->opt.profile ||
+    if (P->hp.n_inst != 1 || M > D2_POINT || static_cast<size_t>(P->n_in_cones) + in.tr.size() != M || !P->wh_groups.empty() || P->opt.profile ||
         P->opt.tune != 0 || P->opt.one_cone_at_a_time)
         return;
     if (in.cones.empty()) {   // trees, in orbit order
@@ -852,6 +930,12 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     build_whole(P, wh);
     auto member = [&](int64_t m) { return !wh.member.empty() && wh.member[static_cast<size_t>(m)]; };
     std::vector<int64_t> d1ord, inord, wdord;
+    for (int64_t m = 0; m < Mall && !d1; ++m)
+        if (!wide_cone(P, hp.cones[m]) && inner_cone(P, hp.cones[m])) inord.push_back(m);
+    std::vector<int32_t> ea, eb, ew;
+    InnerHost in;
+    build_inner(P, inord, wh.member, ea, eb, ew, in);
+    build_point(P, in);
     for (int64_t m = 0; m < Mall; ++m) {
         const bool small = hp.cones[m].k <= P->opt.k_lds_max;
         const bool inner = !d1 && inner_cone(P, hp.cones[m]);
@@ -859,22 +943,23 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
             wdord.push_back(m);
             continue;
         }
-        if (inner) inord.push_back(m);
         // (the tuner compares both kernels; a group's state reads its representative's cut table)
-        if (inner && !(P->opt.tune == 1 && small) && !member(m)) continue;
+        if (inner && !(P->opt.tune == 1 && small) && !member(m) && in.band[static_cast<size_t>(m)] == 0) continue;
         (d1 ? d1ord : small ? ord : hord).push_back(m);
     }
+    auto part_of = [&](int64_t m) {   // Group::n_part; tune = 1: cones in both forms first
+        const bool inner = inner_cone(P, hp.cones[static_cast<size_t>(m)]), both = in.band[static_cast<size_t>(m)] != 0;
+        if (P->opt.tune == 1) return inner ? 3 : 4;
+        return member(m) ? (both ? 1 : inner ? 0 : 2) : both ? 3 : 4;
+    };
     std::stable_sort(ord.begin(), ord.end(), [&](int64_t a, int64_t b) {
         const Cone &x = hp.cones[a], &y = hp.cones[b];
-        if (x.k != y.k) return x.k < y.k;
-        if (member(a) != member(b)) return member(a) != 0;
-        return inner_cone(P, x) > inner_cone(P, y);
+        return x.k != y.k ? x.k < y.k : part_of(a) < part_of(b);
     });
     std::stable_sort(hord.begin(), hord.end(), [&](int64_t a, int64_t b) { return hp.cones[a].k < hp.cones[b].k; });
     const int64_t M = static_cast<int64_t>(ord.size());
     std::vector<ConeDev> cd(M);
-    std::vector<int32_t> ea, eb, ew;
-    std::vector<double> ewd;   // real weights (plans with real weights only)
+    std::vector<double> ewd(hp.realw ? ea.size() : 0, 0.0);   // real weights (plans with real weights only)
     int64_t cut_bytes = 0;
     P->lds_groups.clear();
     for (int64_t s = 0; s < M; ++s) {
@@ -908,17 +993,10 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
         ew.insert(ew.end(), c.ew.begin(), c.ew.end());
         if (P->lds_groups.empty() || P->lds_groups.back().K != c.k) P->lds_groups.push_back({c.k, s, 0, 1});
         P->lds_groups.back().count += 1;
-        if (member(ord[s])) {
-            P->lds_groups.back().n_wh += 1;
-            if (inner_cone(P, c)) P->lds_groups.back().n_skip += 1;
-        } else if (inner_cone(P, c)) {
-            P->lds_groups.back().n_in += 1;
-        }
+        P->lds_groups.back().n_part[part_of(ord[s])] += 1;
+        if (P->opt.tune == 1 && inner_cone(P, c)) P->lds_groups.back().n_in += 1;
         P->lds_groups.back().rowcap = std::max(P->lds_groups.back().rowcap, d.cut_range);
     }
-    InnerHost in;
-    build_inner(P, inord, wh.member, ea, eb, ew, in);
-    build_point(P, in);
     WideHost wd;
     build_wide(P, wdord, ea, eb, ew, wd);
     if (wd.too_many) {
@@ -1174,7 +1252,7 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
             QCHECK(launch_wide_tables(P->d_wd, static_cast<int64_t>(wd.cones.size()), P->d_ea, P->d_eb, P->d_ew, hp.p,
                                       P->d_wdtab, nullptr));
         if (has_in)
-            QCHECK(launch_inner_tables(P->d_in, static_cast<int64_t>(in.cones.size()), P->d_ea, P->d_eb, P->d_ew, hp.p,
+            QCHECK(launch_inner_tables(P->d_in, P->n_in_cones, P->d_ea, P->d_eb, P->d_ew, hp.p,
                                        hp.cut_min, P->d_intab, nullptr));
     }
     for (const auto& g : P->wh_groups)
@@ -1216,11 +1294,13 @@ struct GroupTimer {
 
 // The gradient of a shared state of 14 qubits spills (about 1 KB a thread), and a point of its group
 // occupies a compute unit for as long as several members' own states do: c times as long.  It is taken
-// where the members would fill the chip c times as often.  Measured (us, energy and gradient of
-// three members, shared and on their own): p = 2, 1, 256 and 4096 points 38 and 18, 61 and 49, 840 and
-// 693; p = 5 78 and 51, 148 and 153, 2051 and 2318; real weights, p = 2, 49 and 30, 77 and 113.  13
-// qubits at p = 2: 20 and 15 while the members fill it once, 20 and 28 when twice.  Up to 12
-// qubits, and for energies alone, it is never behind (12 qubits, p = 2: 13 and 14, 1 point; 101 and 275).
+// where the members would fill the chip c times as often.  Measured (us, energy and gradient, one
+// shared state a point against filling the chip once, twice and three times with members): p = 2, up to
+// 64, 128 and 256 points 43, 54 and 61 against 22, 36 and 50; p = 3 65, 82 and 95 against 33, 59 and
+// 87; p = 5 100, 128 and 148 against 55, 104 and 153; p = 8 141, 188 and 212 against 88, 173 and
+// 255; real weights, p = 2, 58, 70 and 77 against 35, 73 and 113.  13 qubits at p = 2: 20 against 18 and 28.
+// Up to 12 qubits, and for energies alone, a shared state is never behind (12 qubits, p = 2, three members: 13
+// and 14, 1 point; 101 and 275, 4096).
 Shared shared_states(const qaoa_plan_s* P, bool grad, bool terms_read, int64_t n_points) {
     Shared s;
     s.Wg = P->d_W;
@@ -1229,7 +1309,9 @@ Shared shared_states(const qaoa_plan_s* P, bool grad, bool terms_read, int64_t n
     int sel = 0;
     for (const auto& cls : P->wh_groups) {
         int64_t c = 1;
-        if (grad && cls.K == 14) c = P->hp.realw ? 2 : P->hp.p <= 3 ? 4 : 3;
+        const int64_t states = cls.count * n_points;
+        if (grad && cls.K == 14)
+            c = P->hp.realw || (P->hp.p > 2 && states <= 64) ? 2 : P->hp.p > 3 || states <= (P->hp.p == 2 ? 64 : 128) ? 3 : 4;
         if (grad && cls.K == 13 && P->hp.p == 2) c = 2;
         if (fills(cls.members) < c * fills(cls.count)) continue;
         s.on[wh_class(cls.K) - 12] = true;
@@ -1237,6 +1319,99 @@ Shared shared_states(const qaoa_plan_s* P, bool grad, bool terms_read, int64_t n
     }
     s.Wg = P->d_Wg + static_cast<size_t>(sel) * P->hp.W.size();
     return s;
+}
+
+int Forms::runs(const qaoa_plan_s::Group& g, int64_t (&r)[2][2]) const {
+    const bool s = sh.of(wh_class(g.K)), w = ((whole >> g.K) & 1u) != 0;
+    const bool on[5] = {false, !s && w, !s, w, true};
+    int n = 0;
+    int64_t at = 0;
+    for (int i = 0; i < 5; ++i) {
+        const int64_t end = at + g.n_part[i];
+        if (on[i] && end > at) {
+            if (n > 0 && r[n - 1][1] == at) {
+                r[n - 1][1] = end;
+            } else {
+                r[n][0] = at;
+                r[n++][1] = end;
+            }
+        }
+        at = end;
+    }
+    return n;
+}
+
+// Bands 1 and 2: a unit of a cone on its inner qubits takes a wave, however few amplitudes it has, where
+// the kernel for whole cones holds many small cones in one; but a call's units share one launch, and
+// whole cones take one per size.  So few units run on their inner qubits, many whole (in_small).
+// Measured (ns an item where they fill the chip, inner and whole): p = 2, energies, 8, 9 and 10 qubits
+// 1.5 and 0.4, 1.2 and 0.45, 1.0 and 0.7, 11 qubits 1.7 and 1.5; with the gradient 3.1 and 0.7, 2.7
+// and 2.1, 2.2 and 4.2; p = 3, 8 to 11 qubits, gradient 7.5 and 1.2, 7.8 and 2.0, 8.9 and 4.4, 9.4
+// and 11.6.
+// Where they are the lesser part of the inner classes' workgroups, they hide behind the others.  Plans of
+// up to four units have no idle waves: theirs of 10 qubits stay (a ring at p = 4, 8192 points: 78 us
+// inner, 111 whole).
+// Band 3: a wave takes a cone's rounds in series, where whole cones have a workgroup each, as many items as
+// compute units.  Inner classes share a launch, as long as the cone of most rounds; whole cones take a
+// launch a size, none more where cones of that size run whole anyway.  So the sizes of most rounds
+// leave as long as that shortens the sum.  The estimates (us) are lines through measured latencies:
+// p = 3, gradient, 12, 13 and 14 qubits in 2, 4 and 6 rounds 24, 42 and 60 inner, 21, 23 and 30 whole;
+// energies 12, 18 and 25, and 11, 13 and 15.  Beyond 256 items the inner form is never behind (28
+// cones of 14 qubits, 32 points: 64 and 112).
+Forms choose_forms(const qaoa_plan_s* P, bool grad, bool terms_read, int64_t n_points) {
+    Forms f;
+    f.sh = shared_states(P, grad, terms_read, n_points);
+    f.in = &P->in_groups;
+    if (P->opt.tune != 0) {   // a layout is asked for, or chosen by timing
+        f.whole = ~0u;   // (cones of tune = 1 that have both forms)
+        return f;
+    }
+    if (P->in_bands.empty()) return f;
+    const bool ten = !(grad && P->hp.p == 2) && !(P->in_point.n > 0 && P->in_point.n <= 4);   // 10 qubits as well
+    int64_t few = 0, blocks = 0;
+    int32_t others = 0;   // rounds at most, outside band 3
+    for (const auto& g : P->in_groups) {
+        if (f.sh.of(g.wh) || g.tree) continue;
+        others = std::max(others, g.rounds);
+        few += g.small[ten ? 1 : 0];
+        blocks += g.blocks[0];
+    }
+    if (few * n_points >= in_small(P->hp.p, grad) && 2 * few >= blocks) {
+        f.whole = ten ? (1u << 11) - 1 : (1u << 10) - 1;
+        f.in = &P->in_rest[ten ? 1 : 0];
+        return f;
+    }
+    const size_t n = P->in_serial.size();
+    if (n == 0) return f;
+    const double layers = P->hp.p - 1, round = layers * (grad ? (P->hp.p == 2 ? 3.4 : 4.4) : 1.65);
+    int64_t span[2][2];
+    uint32_t runs = 0;   // sizes with a launch of whole cones
+    for (const auto& g : P->lds_groups)
+        if (f.runs(g, span) > 0) runs |= 1u << g.K;
+    double moved = runs || !P->hbm_groups.empty() ? 0.0 : 3.5;   // phase rows
+    double best = 0.0;
+    uint32_t sizes = 0;
+    for (size_t j = 0; j <= n; ++j) {   // the first j sizes whole
+        int32_t left = others;
+        for (const auto& b : P->in_bands)
+            if (b.band == 3 && !f.sh.of(b.wh) && !((sizes >> b.K) & 1u)) left = std::max(left, b.rounds);
+        const double t = (j ? moved : 0.0) + (left ? 6.0 + left * round : 0.0);
+        if (j == 0 || t < best) {
+            best = t;
+            f.whole = sizes;
+            f.in = j ? &P->in_rest[1 + j] : &P->in_groups;
+        }
+        if (j == n) break;
+        const int K = P->in_serial[j];
+        int64_t items = 0;
+        for (const auto& b : P->in_bands)
+            if (b.K == K && !f.sh.of(b.wh)) items += b.count * n_points;
+        if (items > 256) break;
+        if (items && !((runs >> K) & 1u))
+            moved += grad ? 8.0 + layers * (K < 14 ? 0.5 * K + 1.0 : 10.5) : 5.5 + layers * (0.65 * K - 4.6);
+        sizes |= 1u << K;
+    }
+    return f;
 }
 
 hipError_t launch_whole_group(const qaoa_plan_s* P, const qaoa_plan_s::WhGroup& grp, bool grad, int64_t n_points,
@@ -1492,8 +1667,6 @@ size_t part_limit(const qaoa_plan_s* P) {
     return std::min(MOST, (budget > item ? budget - item : 0) / sizeof(double));
 }
 
-// First cone of a size class that the kernel for whole cones runs.
-int64_t lds_from(const qaoa_plan_s::Group& grp, const Shared& sh) { return sh.of(wh_class(grp.K)) ? grp.n_wh : grp.n_skip; }
 
 // The launches of a depth-1 call.  One instance of few orbits: terms and weighted sums in one
 // launch (2048 orbits are eight per thread of the point's workgroup; larger plans fill the chip
@@ -1658,7 +1831,12 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         QCHECK(launch_depth2_point(a, P->d_W, energy, dgamma, dbeta, stream));
         return QAOA_OK;
     }
-    if (P->in_point.n && !(P->in_parts.n && n_points * P->in_point.n <= IN_SPREAD)) {
+    const Forms forms = choose_forms(P, grad, grad && term_grad, n_points);
+    // (p = 2: a point's workgroup waits for the slowest of many units, spilled to 128 registers; beyond what
+    // the chip holds at once their classes share a launch instead: a 12-node graph of 15 orbits, energy and
+    // gradient at 512 and 1024 points 55 -> 35, 106 -> 56 us; deeper, both are bound by the same sums in LDS)
+    const bool crowd = p == 2 && P->in_point.n > 4 && P->in_point.n * n_points > 4096;
+    if (!forms.whole && P->in_point.n && !crowd && !(P->in_parts.n && n_points * P->in_point.n <= IN_SPREAD)) {
         InArgs a = inner_args(P, gamma, beta, n_points, term_zz, grad ? term_grad : nullptr);
         InPoint q = P->in_point;
         q.W = P->d_W;
@@ -1668,7 +1846,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         QCHECK(launch_inner_point(a, depth2_args(P, gamma, beta, n_points, nullptr, nullptr), q, grad, n_points, stream));
         return QAOA_OK;
     }
-    if (P->in_parts.n && n_points <= IN_MIX) {
+    if (!forms.whole && P->in_parts.n && n_points <= IN_MIX) {
         // few cones: their classes in one launch, then all sums
         const int64_t nvals = grad ? 2 * p + 1 : 1;
         InMix mix{};
@@ -1696,10 +1874,11 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         }
     }
     const size_t npl = static_cast<size_t>(hp.n_inst) * n_points * p;   // (instance, point, layer) rows
-    const Shared sh = shared_states(P, grad, grad && term_grad, n_points);
+    const Shared& sh = forms.sh;
+    int64_t span[2][2];   // a size's runs of cones on the kernel for whole cones
     // phase and mixer tables, for the kernels that read them
     bool tables = !P->hbm_groups.empty();
-    for (const auto& grp : P->lds_groups) tables = tables || lds_from(grp, sh) < grp.count;
+    for (const auto& grp : P->lds_groups) tables = tables || forms.runs(grp, span) > 0;
     if (tables) {
         if ((st = grow(P->d_phase, P->cap_phase, npl * R, msg)) != QAOA_OK) return st;
         if ((st = grow(P->d_mix, P->cap_mix, npl, msg)) != QAOA_OK) return st;
@@ -1720,18 +1899,19 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
     size_t part_need = 0;
     const size_t part_most = part_limit(P);
     const size_t nv = grad ? 2 * static_cast<size_t>(p) + 1 : 1;
-    for (const auto& grp : P->in_groups)
+    const std::vector<qaoa_plan_s::InGroup>& classes = *forms.in;
+    for (const auto& grp : classes)
         if (grp.chunks > 1) {
             const size_t one = static_cast<size_t>(grp.chunks) * nv;
             part_need = std::max(part_need, std::max(one, std::min(one * grp.count * n_points, part_most)));
         }
     // classes that share a launch, with room for the sums of all their parts
     InMix mix{};
-    std::vector<char> mixed(P->in_groups.size(), 0);
+    std::vector<char> mixed(classes.size(), 0);
     if (!P->opt.profile && P->opt.tune == 0 && !P->opt.one_cone_at_a_time && n_points <= IN_MIX) {
         int64_t parts = 0;
-        for (size_t i = 0; i < P->in_groups.size() && mix.n < IN_CLASSES; ++i) {
-            const auto& grp = P->in_groups[i];
+        for (size_t i = 0; i < classes.size() && mix.n < IN_CLASSES; ++i) {
+            const auto& grp = classes[i];
             const int64_t units = grp.count * grp.chunks;
             if (grp.tree || sh.of(grp.wh) || units * n_points > IN_MIX ||
                 (grp.chunks > 1 && parts + units * n_points * static_cast<int64_t>(nv) > static_cast<int64_t>(part_most)))
@@ -1785,8 +1965,8 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         QCHECK(launch_inner_mix(a, mix, grad, stream));
         QCHECK(launch_inner_mix_sum(a, mix, grad, stream));
     }
-    for (const auto& grp : P->in_groups) {
-        if (sh.of(grp.wh) || mixed[static_cast<size_t>(&grp - P->in_groups.data())]) continue;
+    for (const auto& grp : classes) {
+        if (sh.of(grp.wh) || mixed[static_cast<size_t>(&grp - classes.data())]) continue;
         if (P->opt.tune == 1 && grp.K <= P->opt.k_lds_max) continue;   // with the other cones of its size, below
         int j = inner_upw(grp, n_points);
         if (P->opt.tune == 1) {
@@ -1815,7 +1995,7 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
     // come first, on their inner qubits (tune = 1 plans hold them in both forms): of n items all of these
     // cones at the first points, where the other layouts take the first cones at all points
     auto run_size = [&](const qaoa_plan_s::Group& grp, int v, int64_t n) {
-        int64_t done = lds_from(grp, sh) * n_points;
+        int64_t done = 0;
         if (v == 0 && grp.n_in > 0) {
             const int64_t points = std::min(n_points, n / grp.n_in);
             for (const auto& ig : P->in_groups)
@@ -1831,7 +2011,8 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
     for (const auto& grp : P->lds_groups) {
         const ConeDev* cones = P->d_cones + grp.first;
         const int64_t items = grp.count * n_points;
-        if (lds_from(grp, sh) >= grp.count) continue;
+        const int n_runs = forms.runs(grp, span);
+        if (n_runs == 0) continue;
         int variant = P->opt.tune >= 2 ? P->opt.tune - 2 : 0;   // tune 2, 3, 4: a fixed layout variant
         if (P->opt.tune == 1 && !P->opt.one_cone_at_a_time) {
             std::string form;   // of the size's cones: those on their inner qubits, "+" others
@@ -1853,12 +2034,19 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
                 }
             }
         }
-        QCHECK(tm.begin(grp.K, items - lds_from(grp, sh) * n_points));
+        int64_t n_run = 0;
+        for (int r = 0; r < n_runs; ++r) n_run += span[r][1] - span[r][0];
+        QCHECK(tm.begin(grp.K, n_run * n_points));
         if (P->opt.one_cone_at_a_time) {
-            for (int64_t it = lds_from(grp, sh) * n_points; it < items; ++it)
-                QCHECK(launch_fused(grp.K, grad, 0, cones, it, it + 1, P->d_cut, grp.rowcap, ea, stream));
-        } else {
+            for (int r = 0; r < n_runs; ++r)
+                for (int64_t it = span[r][0] * n_points; it < span[r][1] * n_points; ++it)
+                    QCHECK(launch_fused(grp.K, grad, 0, cones, it, it + 1, P->d_cut, grp.rowcap, ea, stream));
+        } else if (P->opt.tune == 1) {
             QCHECK(run_size(grp, variant, items));
+        } else {
+            for (int r = 0; r < n_runs; ++r)
+                QCHECK(launch_fused(grp.K, grad, variant, cones, span[r][0] * n_points, span[r][1] * n_points, P->d_cut,
+                                    grp.rowcap, ea, stream));
         }
         QCHECK(tm.end());
     }

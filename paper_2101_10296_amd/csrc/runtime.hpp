@@ -30,9 +30,10 @@ struct qaoa_plan_s {
         int64_t first;  // first slot in d_cones
         int64_t count;  // cones in this group
         int32_t rowcap; // largest cut range of the group's cones
-        int64_t n_skip = 0; // the first n_skip cones are members of wh_groups with a form of their own in
-                            // in_groups: here for their group's cut table only
-        int64_t n_wh = 0;   // the first n_wh cones are members of wh_groups
+        // in this order: members of wh_groups that have an inner form only (here for their group's cut
+        // table), members with an inner form and this one (in_band), members with this one alone, others
+        // in both forms, others in this one
+        int64_t n_part[5] = {0, 0, 0, 0, 0};
         int64_t n_in = 0;   // tune = 1 (no wh_groups): the first n_in cones are also in in_groups
     };
     std::vector<Group> lds_groups;      // workgroup-resident cones, grouped by K
@@ -52,11 +53,25 @@ struct qaoa_plan_s {
         bool tree;          // closed form (depth2.hip): from d_tr + first on, one unit per cone
         int64_t first, count;
         int32_t chunks;     // units of work per cone
+        int32_t rounds;     // of configurations of a unit at most (cones outside band 3)
+        int32_t small[2];   // workgroups per point that its cones of band 1, of bands 1 and 2 would take alone
         int32_t n_seg;      // instances
         int64_t seg[4];     // n_seg > 1: offset of the segment tables for 1, 2, 4, 8 units per wave
         int32_t blocks[4];  // workgroups per point
     };
     std::vector<InGroup> in_groups;
+    // the same classes without the cones of band 1, of bands 1 and 2, of the first one to four sizes of
+    // band 3 in in_serial (Forms); classes that hold none of them as above, the others with copies of
+    // their descriptors behind the originals
+    std::vector<InGroup> in_rest[6];
+    std::vector<int> in_serial;         // sizes in band 3, those of most rounds first
+    struct Band {           // cones of one size in bands
+        int band, wh, K;    // wh: as InGroup
+        int64_t count;
+        int32_t rounds;     // of one cone at most
+    };
+    std::vector<Band> in_bands;
+    int64_t n_in_cones = 0;             // descriptors in d_in without the copies
     std::vector<int32_t> in_inst;       // instance of each cone in d_in
     qaoa::InPointSum in_parts{};        // few cones in more units than that (n > 0): their parts' places
     qaoa::InPoint in_point{};           // its units where the plan is small enough (n > 0)
@@ -221,6 +236,24 @@ struct Shared {
     bool of(int cls) const { return cls != 0 && on[cls - 12]; }   // cls: wh_class, or 0
 };
 Shared shared_states(const qaoa_plan_s* P, bool grad, bool terms_read, int64_t n_points);
+
+// Cones of up to k_lds_max qubits with an inner form that is not always the faster one (no trees, which
+// are in closed form): 1 up to 9 qubits, 2 of 10, 3 of 11 to 14 that take several rounds of
+// configurations; 0: always the inner form.  A call chooses one form for each band (whole_forms).
+inline int in_band(const qaoa_plan_s* P, const Cone& c, bool tree, uint32_t rounds) {
+    if (P->opt.tune != 0 || tree || c.k > P->opt.k_lds_max) return 0;
+    return c.k <= 9 ? 1 : c.k == 10 ? 2 : rounds >= 2 ? 3 : 0;
+}
+
+// What a call runs in which form.
+struct Forms {
+    Shared sh;
+    uint32_t whole = 0;      // sizes whose cones in bands run on the kernel for whole cones: a bit each
+    const std::vector<qaoa_plan_s::InGroup>* in = nullptr;   // classes on their inner qubits, but for those that share
+    // runs [begin, end) of a size's cones on the kernel for whole cones: at most two
+    int runs(const qaoa_plan_s::Group& g, int64_t (&r)[2][2]) const;
+};
+Forms choose_forms(const qaoa_plan_s* P, bool grad, bool terms_read, int64_t n_points);
 hipError_t launch_whole_group(const qaoa_plan_s* P, const qaoa_plan_s::WhGroup& grp, bool grad, int64_t n_points,
                               const double* gamma, const double* beta, int64_t gamma_P, double* zz, double* g,
                               hipStream_t st);
