@@ -795,6 +795,9 @@ void build_point(qaoa_plan_s* P, const InnerHost& in) {
     if (q.n > 4) parts();   // for few points
 }
 
+// Plans whose cones of 10 qubits never run whole (choose_forms).
+bool ten_stay(const qaoa_plan_s* P) { return P->in_point.n > 0 && P->in_point.n <= 4; }
+
 struct WideHost {
     std::vector<ConeWd> cones;
     std::vector<UnitWd> units;
@@ -936,6 +939,9 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     InnerHost in;
     build_inner(P, inord, wh.member, ea, eb, ew, in);
     build_point(P, in);
+    if (ten_stay(P))   // no need of their other form
+        for (int64_t m : inord)
+            if (hp.cones[static_cast<size_t>(m)].k == 10) in.band[static_cast<size_t>(m)] = 0;
     for (int64_t m = 0; m < Mall; ++m) {
         const bool small = hp.cones[m].k <= P->opt.k_lds_max;
         const bool inner = !d1 && inner_cone(P, hp.cones[m]);
@@ -1367,7 +1373,7 @@ Forms choose_forms(const qaoa_plan_s* P, bool grad, bool terms_read, int64_t n_p
         return f;
     }
     if (P->in_bands.empty()) return f;
-    const bool ten = !(grad && P->hp.p == 2) && !(P->in_point.n > 0 && P->in_point.n <= 4);   // 10 qubits as well
+    const bool ten = !(grad && P->hp.p == 2) && !ten_stay(P);   // 10 qubits as well
     int64_t few = 0, blocks = 0;
     int32_t others = 0;   // rounds at most, outside band 3
     for (const auto& g : P->in_groups) {
