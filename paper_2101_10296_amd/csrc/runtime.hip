@@ -710,8 +710,11 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
         uint32_t sizes = rest == 0 ? (1u << 10) - 1 : rest == 1 ? (1u << 11) - 1 : 0;   // that leave
         for (int j = 0; j < rest - 1; ++j) sizes |= 1u << P->in_serial[static_cast<size_t>(j)];
         for (const auto& all : P->in_groups) {
+            if (all.tree) {
+                P->in_rest[rest].push_back(all);
+                continue;
+            }
             auto stays = [&](int64_t i) {
-                if (all.tree) return true;
                 const size_t m = static_cast<size_t>(in.cones[static_cast<size_t>(i)].orbit);
                 return in.band[m] == 0 || !((sizes >> hp.cones[m].k) & 1u);
             };
@@ -933,8 +936,12 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
     build_whole(P, wh);
     auto member = [&](int64_t m) { return !wh.member.empty() && wh.member[static_cast<size_t>(m)]; };
     std::vector<int64_t> d1ord, inord, wdord;
+    std::vector<char> inner_of(static_cast<size_t>(Mall), 0);
     for (int64_t m = 0; m < Mall && !d1; ++m)
-        if (!wide_cone(P, hp.cones[m]) && inner_cone(P, hp.cones[m])) inord.push_back(m);
+        if (!wide_cone(P, hp.cones[m]) && inner_cone(P, hp.cones[m])) {
+            inner_of[static_cast<size_t>(m)] = 1;
+            inord.push_back(m);
+        }
     std::vector<int32_t> ea, eb, ew;
     InnerHost in;
     build_inner(P, inord, wh.member, ea, eb, ew, in);
@@ -943,9 +950,8 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
         for (int64_t m : inord)
             if (hp.cones[static_cast<size_t>(m)].k == 10) in.band[static_cast<size_t>(m)] = 0;
     for (int64_t m = 0; m < Mall; ++m) {
-        const bool small = hp.cones[m].k <= P->opt.k_lds_max;
-        const bool inner = !d1 && inner_cone(P, hp.cones[m]);
-        if (!d1 && wide_cone(P, hp.cones[m])) {
+        const bool small = hp.cones[m].k <= P->opt.k_lds_max, inner = inner_of[static_cast<size_t>(m)] != 0;
+        if (!d1 && !inner && wide_cone(P, hp.cones[m])) {
             wdord.push_back(m);
             continue;
         }
@@ -954,7 +960,7 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
         (d1 ? d1ord : small ? ord : hord).push_back(m);
     }
     auto part_of = [&](int64_t m) {   // Group::n_part; tune = 1: cones in both forms first
-        const bool inner = inner_cone(P, hp.cones[static_cast<size_t>(m)]), both = in.band[static_cast<size_t>(m)] != 0;
+        const bool inner = inner_of[static_cast<size_t>(m)] != 0, both = in.band[static_cast<size_t>(m)] != 0;
         if (P->opt.tune == 1) return inner ? 3 : 4;
         return member(m) ? (both ? 1 : inner ? 0 : 2) : both ? 3 : 4;
     };
@@ -1000,7 +1006,7 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
         if (P->lds_groups.empty() || P->lds_groups.back().K != c.k) P->lds_groups.push_back({c.k, s, 0, 1});
         P->lds_groups.back().count += 1;
         P->lds_groups.back().n_part[part_of(ord[s])] += 1;
-        if (P->opt.tune == 1 && inner_cone(P, c)) P->lds_groups.back().n_in += 1;
+        if (P->opt.tune == 1 && inner_of[static_cast<size_t>(ord[s])]) P->lds_groups.back().n_in += 1;
         P->lds_groups.back().rowcap = std::max(P->lds_groups.back().rowcap, d.cut_range);
     }
     WideHost wd;
