@@ -502,6 +502,12 @@ def main():
     evals = len(graphs) * P
     value = evals / (dt / a.steps)
 
+    # where the step's time goes: kernels by (orbits of the plan, cone qubits; -1 phase rows, -2 weighted
+    # sums), and the rest, which is planning, upload and launches on the host
+    by_class = {f"{m} orbits, k={k}": round(v[0] / a.steps, 4) for (m, k), v in sorted(kernel_ms.items())}
+    busy = sum(v[0] for v in kernel_ms.values()) / a.steps
+    split = {"kernel_ms": round(busy, 3), "host_ms": round(ms_step - busy, 3), "kernel_ms_by_class": by_class}
+
     # the cone-size group with the most items: the 14-qubit cones of the 3-regular graph, all trees
     # (2 + 4 + 8 different qubits), in closed form.  A term is <ZZ> and 2p derivatives, written once
     (norb, kdom), (ms_dom, items_dom, pdom) = max(((k, v) for k, v in kernel_ms.items() if k[1] >= 2),
@@ -571,6 +577,7 @@ def main():
                                "n=10000 (15000 cones), 256 angle points each, plan included per step",
                    "points_per_graph": P, "p": p, "parallelism": "single GPU"},
         "roofline": roofline,
+        "step_split": split,
     }
     line.update(extra)
     if not a.no_plain:

@@ -214,6 +214,8 @@ qaoa_status qaoa_plan_cone(qaoa_plan_t plan, int64_t orbit, int32_t* k_out, int3
 /* Energy at n_points angle points (Sec. 2.2 ansatz, Sec. 3 reduced sum).
  * gamma, beta: device [n_points * p]; energy: device [n_points];
  * term_zz: device [n_points * n_orbits] (point-major: term_zz[i * n_orbits + m]) or NULL.
+ * How a term is evaluated may depend on the other cones of the plan, on the number of points
+ * and on what else the call returns: the same term differs between such calls by FP32 rounding.
  * Errors: EINVAL, ENOMEM, EHIP. */
 qaoa_status qaoa_energy(qaoa_plan_t plan, int64_t n_points, const double* gamma,
                         const double* beta, double* energy, double* term_zz,

@@ -666,8 +666,8 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
     for (auto& g : P->in_groups) {
         // Units of work: a cone's rounds in parts of 8, of 2 where that leaves a point with fewer than
         // 1024 units (latency: the 18-qubit cone of a torus at 32 points 42 -> 24 us), at most 2^15
-        // of them.  Set by the plan alone, so that a term's sum is the same whatever the number of
-        // points.  Classes of cones that fit the allocation-free call (k_lds_max qubits: 16
+        // of them.  Set by the plan alone, so that a term's sum in this form is the same whatever the
+        // number of points.  Classes of cones that fit the allocation-free call (k_lds_max qubits: 16
         // rounds at most) stay whole, as parts need room for their sums.
         uint32_t most = 1;
         int32_t max_k = 0;
@@ -740,12 +740,13 @@ void build_inner(qaoa_plan_s* P, std::vector<int64_t>& ord, const std::vector<ch
 // The units of a plan whose calls are one launch (inner_point.hip): one instance, all cones on their
 // inner qubits with listed configurations, and at most 16 units and orbits.  Up to there one
 // compute unit holds a point's waves at once; the 18-qubit cone of a torus, 19 units of two rounds
-// each, would run them one after the other where the separate launches spread them over five.  Beyond
-// four units few points are spread as well (IN_SPREAD); else there is no line at any number of points: a class's launch gives a point's few units a workgroup of their
-// own too, and leaves its other waves idle (energy and gradient of C_10000(1,2) at p = 2, 1, 256,
-// 2048 and 16384 points: 18.8, 17.9, 36, 191 us in separate launches, 13.6, 13.3, 22, 109 here;
-// rings at p = 3 .. 5, 1 point: 16, 19, 42 us and 13, 18, 41; 16384 points: 218, 309, 778 us and 101,
-// 145, 379).
+// each, would run them one after the other where the separate launches spread them over five.
+// Beyond four units few points are spread as well (IN_SPREAD), and many at p = 2 (enqueue).  Up to
+// four there is no line at any number of points: a class's launch gives a point's few units a
+// workgroup of their own too, and leaves its other waves idle (energy and gradient of C_10000(1,2) at
+// p = 2, 1, 256, 2048 and 16384 points: 18.8, 17.9, 36, 191 us in separate launches, 13.6, 13.3, 22,
+// 109 here; rings at p = 3 .. 5, 1 point: 16, 19, 42 us and 13, 18, 41; 16384 points: 218, 309, 778 us
+// and 101, 152, 379).
 void build_point(qaoa_plan_s* P, const InnerHost& in) {
     P->in_point = InPoint{};
     P->in_parts = InPointSum{};
@@ -1844,9 +1845,10 @@ qaoa_status enqueue(qaoa_plan_s* P, int64_t n_points, const double* gamma, const
         return QAOA_OK;
     }
     const Forms forms = choose_forms(P, grad, grad && term_grad, n_points);
-    // (p = 2: a point's workgroup waits for the slowest of many units, spilled to 128 registers; beyond what
-    // the chip holds at once their classes share a launch instead: a 12-node graph of 15 orbits, energy and
-    // gradient at 512 and 1024 points 55 -> 35, 106 -> 56 us; deeper, both are bound by the same sums in LDS)
+    // At p = 2 a point's workgroup waits for the slowest of its units, in 128 registers and 412 bytes of
+    // scratch a thread; beyond what the chip holds at once their classes share a launch instead (a 12-node
+    // graph of 15 orbits, energy and gradient, 512 points 55 -> 38 us; C_1000(1,2,3), 2048 points 365 ->
+    // 288).  Deeper circuits sum in LDS either way (a path of 13 nodes, p = 4, 512 points: 67 here, 84).
     const bool crowd = p == 2 && P->in_point.n > 4 && P->in_point.n * n_points > 4096;
     if (!forms.whole && P->in_point.n && !crowd && !(P->in_parts.n && n_points * P->in_point.n <= IN_SPREAD)) {
         InArgs a = inner_args(P, gamma, beta, n_points, term_zz, grad ? term_grad : nullptr);

@@ -197,10 +197,11 @@ inline bool depth1_closed(const qaoa_plan_s* P) { return P->hp.p == 1 && P->opt.
 
 // Cones evaluated on their inner qubits: those with a shell (else there is nothing to average
 // over, and the kernels for whole cones store half of the state) whose inner state fits the
-// registers of one wave.  Every such cone measured faster there: 14 qubits, p = 2 (6 inner)
-// 93x, 18 qubits (8 inner) 4x, 26 qubits (8 inner) 150x; C_10000(1,2) at one point, 10-11 qubits
-// with as many amplitudes as before, 26.7 -> 16 us for the call.  Real weights (but for
-// depth-2 trees) and forced layouts (tune >= 2) keep the kernels for whole cones.
+// registers of one wave.  Measured against those kernels: 14 qubits, p = 2 (6 inner) 93x, 18 qubits
+// (8 inner) 4x, 26 qubits (8 inner) 150x; C_10000(1,2) at one point, 10-11 qubits with as many
+// amplitudes as before, 26.7 -> 16 us for the call.  Cones of up to 14 qubits where it depends on the
+// call are held in both forms (in_band, choose_forms).  Real weights (but for depth-2 trees) and
+// forced layouts (tune >= 2) keep the kernels for whole cones.
 inline bool inner_cone(const qaoa_plan_s* P, const Cone& c) {
     const int32_t p = P->hp.p;
     return p >= 2 && p <= IN_PMAX && P->opt.tune < 2 && c.nd[p - 1] <= IN_KMAX && c.nd[p - 1] < c.k &&
@@ -215,9 +216,10 @@ inline bool closed_tree(const qaoa_plan_s* P, const Cone& c) {
 }
 
 // Cones with more inner qubits, on a workgroup each.  The lines at 26 (p = 2) and 25 cone qubits
-// (p = 3) are not where the passes over device memory get faster (a 25-qubit cone at p = 3 costs
-// them 763 us against 92, a 24-qubit one 385 against 22; 20 qubits 56 against 74): the tests hold
-// the pass kinds that plans of up to 25-qubit cones at p = 2 and 24-qubit ones at p = 3 launch.
+// (p = 3) are not where the passes over device memory get faster.  Measured with the gradient at
+// p = 3: a 25-qubit cone costs the passes 763 us against 92, a 24-qubit one 385 against 22, a 20-qubit
+// one with 15 inner qubits 56 against 74.  The tests hold the pass kinds of cones of 23 and 25 qubits at
+// p = 2 and of 24 at p = 3; nothing but these lines keeps 21 to 23 qubits at p = 3 on the passes.
 // Above lies nearly all of the work: a cone's cost doubles per qubit.
 inline bool wide_cone(const qaoa_plan_s* P, const Cone& c) {
     const int32_t p = P->hp.p;

@@ -12,7 +12,7 @@ namespace qaoa {
 constexpr int WD_KMIN = 11;     // inner qubits
 constexpr int WD_KMAX = 14;
 constexpr int WD_PMAX = 3;
-constexpr int WD_CONE2 = 26;    // cone qubits from which this form is used: p = 2
+constexpr int WD_CONE2 = 26;    // cone qubits from which this form is used (wide_cone): p = 2
 constexpr int WD_CONE3 = 25;    // p = 3
 constexpr int WD_NEXT = 8;      // inner qubits that layers 2 and up mix at most
 constexpr int WD_CFG = 8;       // configurations per unit of work
