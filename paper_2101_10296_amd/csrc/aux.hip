@@ -1,6 +1,9 @@
 // Small kernels around the light-cone kernels: per-call angle tables, per-plan cut
 // tables, and the orbit-weighted combination of term values into E and dE.
+#include <algorithm>
+
 #include "device.hpp"
+#include "inner.hpp"
 
 namespace qaoa {
 
@@ -40,22 +43,68 @@ __global__ void k_tables(const double* __restrict__ gamma, const double* __restr
     }
 }
 
-// Cut table of cone c: table[x] = C(x) - cut_min for every basis state x of its k qubits,
-// C(x) = sum over cone edges (a, b) of w_ab [x_a != x_b]  (MaxCut cost, Sec. 2.4).
-__global__ void k_cut_tables(const ConeDev* __restrict__ cones, const int32_t* __restrict__ ea,
-                             const int32_t* __restrict__ eb, const int32_t* __restrict__ ew,
-                             uint8_t* __restrict__ tables) {
-    const ConeDev cd = cones[blockIdx.x];
+// Tables of a new plan (integer weights), which its first call waits for.  One launch for both kinds, as cones
+// in two forms have both.  A first call at p = 2 on a 20-node graph, 81 us with the inner tables alone: 22
+// more for cut tables on a workgroup of 256 threads a cone with each edge read from memory, 6 more in
+// parts with edges in LDS, 1 more in the same launch.
+constexpr int CUT_EDGES = 14 * 13 / 2;   // different pairs of a workgroup-resident cone's qubits
+
+// Cut table of a cone: table[x] = C(x) - cut_min for every basis state x of its k qubits,
+// C(x) = sum over cone edges (a, b) of w_ab [x_a != x_b]  (MaxCut cost, Sec. 2.4).  Bound by latency where
+// cones are few: a lane's four entries read each edge once, from LDS (k >= 2: entries come in fours),
+// and few cones are spread in parts of 256 entries.
+__device__ __forceinline__ void cut_table(const ConeDev& cd, uint32_t part, uint32_t parts, const PlanTabs& a) {
+    __shared__ int32_t edge[CUT_EDGES];   // ends and weight, which a table of bytes bounds by 255
     const uint32_t N = 1u << cd.k;
-    uint8_t* out = tables + cd.cut_off;
-    for (uint32_t x = threadIdx.x; x < N; x += blockDim.x) {
+    if (part * 256u >= N) return;
+    const int32_t n = cd.n_edges < CUT_EDGES ? cd.n_edges : CUT_EDGES;
+    for (int32_t e = threadIdx.x; e < n; e += 64)
+        edge[e] = a.ea[cd.edge_off + e] | a.eb[cd.edge_off + e] << 8 | a.ew[cd.edge_off + e] * 65536;
+    __syncthreads();
+    uint8_t* out = a.cut + cd.cut_off;
+    for (uint32_t x = part * 256u + threadIdx.x * 4u; x < N; x += parts * 256u) {
+        int32_t c[4] = {-cd.cut_min, -cd.cut_min, -cd.cut_min, -cd.cut_min};
+#pragma unroll 4
+        for (int32_t e = 0; e < n; ++e) {
+            const int32_t q = edge[e], i = q & 255, j = (q >> 8) & 255, w = q >> 16;
+#pragma unroll
+            for (uint32_t y = 0; y < 4; ++y) c[y] += w * static_cast<int32_t>((((x + y) >> i) ^ ((x + y) >> j)) & 1u);
+        }
+        uint32_t v = 0;
+#pragma unroll
+        for (int y = 0; y < 4; ++y) v |= static_cast<uint32_t>(static_cast<uint8_t>(c[y])) << (8 * y);
+        *reinterpret_cast<uint32_t*>(out + x) = v;   // cut_off: a multiple of 16
+    }
+}
+
+// Table of layer l of a cone on its inner qubits: the cut of the couplings inside the qubits mixed by layer
+// l - 1, minus its smallest value.  In parts where the cones alone leave the chip idle (one workgroup
+// took 60 us for the four tables of a ring's 10 inner qubits).
+__device__ __forceinline__ void inner_table(const ConeIn& cd, int l, uint32_t part, uint32_t parts, const PlanTabs& a) {
+    const uint32_t n = 1u << cd.kin, ts = n < 16u ? 16u : n;
+    uint8_t* out = a.tab + static_cast<size_t>(cd.tab_off) * 16 + static_cast<size_t>(l - 2) * ts;
+    const int m = cd.mixed[l - 1], cmin = cd.base[l] + a.cut_min;
+    for (uint32_t x = part * 64u + threadIdx.x; x < ts; x += parts * 64u) {
         int32_t c = 0;
         for (int32_t e = 0; e < cd.n_edges; ++e) {
-            const int32_t a = ea[cd.edge_off + e], b = eb[cd.edge_off + e];
-            c += ew[cd.edge_off + e] * static_cast<int32_t>(((x >> a) ^ (x >> b)) & 1u);
+            const int32_t i = a.ea[cd.edge_off + e], j = a.eb[cd.edge_off + e];
+            if (j < m) c += a.ew[cd.edge_off + e] * static_cast<int32_t>(((x >> i) ^ (x >> j)) & 1u);
         }
-        out[x] = static_cast<uint8_t>(c - cd.cut_min);
+        out[x] = static_cast<uint8_t>(x < n ? c - cmin : 0);
     }
+}
+
+// cut_parts workgroups for each of n_cones cones, then in_parts for each layer 2 .. p of n_in inner ones
+__global__ void __launch_bounds__(64) k_plan_tables(PlanTabs a) {
+    uint32_t b = blockIdx.x;
+    const uint32_t cuts = static_cast<uint32_t>(a.n_cones) * a.cut_parts;
+    if (b < cuts) {
+        cut_table(a.cones[b / a.cut_parts], b % a.cut_parts, a.cut_parts, a);
+        return;
+    }
+    b -= cuts;
+    const uint32_t t = b / a.in_parts, layers = static_cast<uint32_t>(a.p - 1);
+    inner_table(a.in[t / layers], 2 + static_cast<int>(t % layers), b % a.in_parts, a.in_parts, a);
 }
 
 // Real-weight cut table of cone c over the stored half (qubit k-1 = 0 for k >= 3):
@@ -178,13 +227,21 @@ hipError_t launch_tables(const double* gamma, const double* beta, int64_t n_pl, 
     return hipGetLastError();
 }
 
-hipError_t launch_cut_tables(const ConeDev* cones, int64_t n_cones, const int32_t* ea, const int32_t* eb,
-                             const int32_t* ew, uint8_t* tables, hipStream_t st) {
-    // one block per cone; a grid holds fewer than 2^32 threads
-    constexpr int64_t CH = static_cast<int64_t>(UINT32_MAX) / 256;
-    for (int64_t c0 = 0; c0 < n_cones; c0 += CH) {
-        const unsigned nx = static_cast<unsigned>(n_cones - c0 < CH ? n_cones - c0 : CH);
-        hipLaunchKernelGGL(k_cut_tables, dim3(nx), dim3(256), 0, st, cones + c0, ea, eb, ew, tables);
+hipError_t launch_plan_tables(PlanTabs a, int32_t max_k, hipStream_t st) {
+    // a workgroup per cone (and layer), more where that leaves the chip idle; a grid holds fewer than 2^32 threads
+    const int64_t parts = max_k > 8 ? int64_t{1} << (max_k - 8) : 1, few = 16384 / std::max<int64_t>(a.n_cones, 1);
+    a.cut_parts = static_cast<uint32_t>(std::clamp<int64_t>(few, 1, parts));
+    a.in_parts = a.n_in < 64 ? 8 : 1;
+    const int64_t layers = std::max(a.p - 1, 1), most = (int64_t{UINT32_MAX} / 64 - 16384) / (2 * layers);
+    const int64_t n_cones = a.n_cones, n_in = a.n_in;
+    for (int64_t c0 = 0; c0 < std::max(n_cones, n_in); c0 += most) {
+        PlanTabs q = a;
+        q.cones += std::min(c0, n_cones);
+        q.in += std::min(c0, n_in);
+        q.n_cones = std::clamp<int64_t>(n_cones - c0, 0, most);
+        q.n_in = std::clamp<int64_t>(n_in - c0, 0, most);
+        const int64_t blocks = q.n_cones * q.cut_parts + q.n_in * layers * q.in_parts;
+        hipLaunchKernelGGL(k_plan_tables, dim3(static_cast<unsigned>(blocks)), dim3(64), 0, st, q);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

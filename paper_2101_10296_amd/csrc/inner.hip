@@ -16,27 +16,6 @@ hipError_t launch_inner(int kin, bool grad, const InArgs& a, hipStream_t st) {
 
 namespace {
 
-// A workgroup per cone, layer and part of the table: parts where the cones alone leave the chip idle (one
-// workgroup took 60 us for the four tables of a ring's 10 inner qubits, on a new plan's first call).
-__global__ void __launch_bounds__(64)
-k_inner_tables(const ConeIn* __restrict__ cones, const int32_t* __restrict__ ea, const int32_t* __restrict__ eb,
-               const int32_t* __restrict__ ew, int32_t p, int32_t cut_min, uint8_t* __restrict__ tab) {
-    const ConeIn& cd = cones[blockIdx.x];
-    const uint32_t n = 1u << cd.kin, ts = n < 16u ? 16u : n;
-    uint8_t* out = tab + static_cast<size_t>(cd.tab_off) * 16;
-    const int l = 2 + blockIdx.y;
-    out += static_cast<size_t>(blockIdx.y) * ts;
-    const int m = cd.mixed[l - 1], cmin = cd.base[l] + cut_min;
-    for (uint32_t x = blockIdx.z * 64 + threadIdx.x; x < ts; x += gridDim.z * 64) {
-        int32_t c = 0;
-        for (int32_t e = 0; e < cd.n_edges; ++e) {
-            const int32_t i = ea[cd.edge_off + e], j = eb[cd.edge_off + e];
-            if (j < m) c += ew[cd.edge_off + e] * static_cast<int32_t>(((x >> i) ^ (x >> j)) & 1u);
-        }
-        out[x] = static_cast<uint8_t>(x < n ? c - cmin : 0);
-    }
-}
-
 // The chunks of item t = (point, cone, value), in order.
 __device__ __forceinline__ void in_add_parts(const InArgs& a, int64_t t, int32_t n_cones, int32_t nv) {
     const int v = static_cast<int>(t % nv);
@@ -95,19 +74,6 @@ hipError_t launch_inner_sum(const InArgs& a, int32_t n_cones, bool grad, hipStre
     hipLaunchKernelGGL(k_inner_sum, dim3(static_cast<unsigned>(blocks < 65536 ? blocks : 65536)), dim3(256), 0, st, a,
                        n_cones, nv);
     return hipGetLastError();
-}
-
-hipError_t launch_inner_tables(const ConeIn* cones, int64_t n_cones, const int32_t* ea, const int32_t* eb,
-                               const int32_t* ew, int32_t p, int32_t cut_min, uint8_t* tab, hipStream_t st) {
-    // a grid holds fewer than 2^32 threads
-    constexpr int64_t CH = static_cast<int64_t>(UINT32_MAX) / (64 * IN_PMAX);
-    for (int64_t c0 = 0; c0 < n_cones; c0 += CH) {
-        const unsigned nx = static_cast<unsigned>(n_cones - c0 < CH ? n_cones - c0 : CH);
-        hipLaunchKernelGGL(k_inner_tables, dim3(nx, p - 1, nx < 64 ? 8 : 1), dim3(64), 0, st, cones + c0, ea, eb, ew, p, cut_min, tab);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
 }
 
 }  // namespace qaoa

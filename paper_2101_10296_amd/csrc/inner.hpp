@@ -175,9 +175,22 @@ struct InPointSum {
 hipError_t launch_inner_point_sum(const InArgs& a, const InPointSum& q, bool grad, hipStream_t st);
 // sums the chunks of every (point, cone) into zz and g
 hipError_t launch_inner_sum(const InArgs& a, int32_t n_cones, bool grad, hipStream_t st);
-// Table of layer l (2..p) of every cone: the cut of the couplings inside the qubits mixed by
-// layer l - 1, minus its smallest value, a byte per inner basis state.
-hipError_t launch_inner_tables(const ConeIn* cones, int64_t n_cones, const int32_t* ea, const int32_t* eb,
-                               const int32_t* ew, int32_t p, int32_t cut_min, uint8_t* tab, hipStream_t st);
+// Tables of a new plan: of whole cones (cut: a byte per basis state) and of cones on their inner qubits
+// (tab: a byte per inner basis state and layer 2 .. p).
+struct ConeDev;
+struct PlanTabs {
+    const ConeDev* cones;
+    const ConeIn* in;
+    const int32_t* ea;
+    const int32_t* eb;
+    const int32_t* ew;
+    uint8_t* cut;
+    uint8_t* tab;
+    int64_t n_cones, n_in;
+    int32_t p;
+    int32_t cut_min;               // of the plan
+    uint32_t cut_parts, in_parts;  // set by the launcher
+};
+hipError_t launch_plan_tables(PlanTabs a, int32_t max_k, hipStream_t st);   // max_k: qubits of the largest of cones
 
 }  // namespace qaoa

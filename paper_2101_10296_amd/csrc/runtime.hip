@@ -1258,15 +1258,14 @@ qaoa_status ensure_device(qaoa_plan_s* P, std::string& msg) {
         QCHECK(launch_tt_tables_real(P->d_hcones, static_cast<int64_t>(hc.size()), max_groups, P->d_ea, P->d_eb,
                                      P->d_ewd, reinterpret_cast<float*>(P->d_tt), nullptr));
     } else {
-        QCHECK(launch_cut_tables(P->d_cones, M, P->d_ea, P->d_eb, P->d_ew, P->d_cut, nullptr));
+        const PlanTabs tabs = {P->d_cones, P->d_in, P->d_ea, P->d_eb, P->d_ew, P->d_cut, P->d_intab, M, has_in ? P->n_in_cones : 0,
+                               hp.p, hp.cut_min, 0, 0};
+        QCHECK(launch_plan_tables(tabs, M ? cd.back().k : 0, nullptr));
         QCHECK(launch_tt_tables(P->d_hcones, static_cast<int64_t>(hc.size()), max_groups, P->d_ea, P->d_eb,
                                 P->d_ew, P->d_tt, nullptr));
         if (has_wd)
             QCHECK(launch_wide_tables(P->d_wd, static_cast<int64_t>(wd.cones.size()), P->d_ea, P->d_eb, P->d_ew, hp.p,
                                       P->d_wdtab, nullptr));
-        if (has_in)
-            QCHECK(launch_inner_tables(P->d_in, P->n_in_cones, P->d_ea, P->d_eb, P->d_ew, hp.p,
-                                       hp.cut_min, P->d_intab, nullptr));
     }
     for (const auto& g : P->wh_groups)
         QCHECK(launch_whole_obs(P->d_wh + g.first, g.count, P->d_whmem, g.K, P->d_whobs, nullptr));

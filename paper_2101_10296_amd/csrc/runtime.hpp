@@ -284,8 +284,6 @@ hipError_t launch_fused(int K, bool grad, int variant, const ConeDev* cones, int
 std::vector<int> fused_variants(int K, bool grad);
 hipError_t launch_tables(const double* gamma, const double* beta, int64_t n_pl, int32_t R, int32_t cmin,
                          const double* deltas, int64_t pl_per_inst, float2* phase, float2* mix, hipStream_t st);
-hipError_t launch_cut_tables(const ConeDev* cones, int64_t n_cones, const int32_t* ea, const int32_t* eb,
-                             const int32_t* ew, uint8_t* tables, hipStream_t st);
 hipError_t launch_cut_tables_real(const ConeDev* cones, int64_t n_cones, const int32_t* ea, const int32_t* eb,
                                   const double* ew, float* tables, hipStream_t st);
 hipError_t launch_pass(int kind, const PassArgs& pa, hipStream_t st);

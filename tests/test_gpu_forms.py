@@ -123,3 +123,23 @@ def test_allocation_free_call_in_the_same_form(Q):
         torch.cuda.synchronize()
         for x, y in zip(got, want):
             assert (x - y).abs().max().item() <= 1e-12 * g.m
+
+
+# Whole cones' cut tables are made in parts of 256 entries, fewer to a cone where cones are many: cones of 2 p + 2
+# qubits of a small ring and of thousands (workgroups that make a table alone), the same bits.
+@pytest.mark.parametrize("p,n", [(2, 300), (3, 700), (4, 5000), (6, 300), (6, 17000)])
+def test_tables_of_few_and_many_cones(Q, p, n):
+    ga, be = W.draw_angles(2, p, n + p)
+    terms = []
+    for m in (4 * p + 8, n):
+        g = W.circulant(m, (1,))
+        pl = Q.Plan(g.n, g.edges, p=p, reduce=False, tune=2)
+        zz = pl.energy(dev(ga), dev(be), term_zz=True)[1]
+        edges = np.array(sorted(tuple(e) for e in np.sort(np.asarray(g.edges), 1)))
+        inside = (edges[:, 1] == edges[:, 0] + 1) & (edges[:, 0] >= p) & (edges[:, 1] < m - p)   # numbered alike
+        terms.append(zz[:, torch.as_tensor(np.flatnonzero(inside), device=zz.device)])
+    few, many = terms
+    assert few.shape[1] == 2 * p + 7 and many.shape[1] == n - 2 * p - 1
+    assert torch.equal(few[:, :1].expand_as(few), few) and torch.equal(few[:, :1].expand_as(many), many)
+    g = W.circulant(4 * p + 8, (1,))
+    check_energy(Q, g, p, ga, be, reduce=True, plan_kw=dict(tune=2))
